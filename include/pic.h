@@ -51,8 +51,9 @@ extern "C" {
 /* arithmetic forms */
 #define PIC_FP64  0  /* FP64 positions (cell units), velocities, fields and deposit */
 #define PIC_FP32R 1  /* int32 cell + FP32 offset, FP32 velocity and field, int64
-                        fixed-point deposit (2^-32 e), FP32 Poisson solve with FP64
-                        residual refinement */
+                        fixed-point deposit (2^-32 e), Poisson solve held to an FP64
+                        residual (one FP64 solve, or FP32 sweeps with FP64 residual
+                        refinement: max_refine 1, refine_tol 0) */
 
 /* pic_fields selection bits */
 #define PIC_PHI       1u  /* double [nodes]                     V        */
@@ -100,7 +101,9 @@ typedef struct pic_config {
   int32_t pp_cutoff_cells;
   int32_t md_subcycles;
   int32_t precision;           /* PIC_FP64 or PIC_FP32R */
-  int32_t max_refine;          /* FP32R: most residual-refinement sweeps per solve (1..16) */
+  int32_t max_refine;          /* FP32R: most residual-refinement sweeps per solve (1..16);
+                                  with 2 or more and a refine_tol above 0 one FP64 solve
+                                  takes their place and counts as one sweep */
   int32_t sort_interval;       /* steps between re-binnings of the electrons (0: never; see pic_tuning) */
   double dx, dt;
   double n0;

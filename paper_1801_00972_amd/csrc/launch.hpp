@@ -67,14 +67,16 @@ void launch_lists_f32r(const PartF32R P[2], const PartF32R D[2], const float* E,
 void launch_species_lists_f32r(const PartF32R P[2], const PartF32R D[2], const float* E,
                                long long* rho, const MdTables& md, const SpeciesStep S[2],
                                const WorkLists L[2], int do_mcc, int sp, hipStream_t st);
-// The fields of a step in one launch: phi (from the refined solve's psi,
-// lifted with the electrode voltages, when psi is given; otherwise phi is read
-// as stored), E = -grad phi into E (FP64 double2 pairs or FP32 float4), the
-// MD cells' corrected node fields, and zero_next (nn 8-byte words, may be
-// null) cleared for the next deposit.
+// The fields of a step in one launch: phi (the solve's psi lifted with the
+// electrode voltages), E = -grad phi into E (FP64 double2 pairs or FP32
+// float4), the MD cells' corrected node fields, zero_next (nn 8-byte words,
+// may be null) cleared for the next deposit and, with b, the sums of the
+// squared residual b - A psi and of b^2 per block of field_out_sums(nn) blocks.
+inline long field_out_sums(long nn) { return (nn + 255) / 256; }
 void launch_field_out(const double* psi, double* phi, void* E, int e_f64,
-                      unsigned long long* zero_next, const MdTables& md, int nx, int ny, int nz,
-                      double dx, RfDrive rf, hipStream_t st);
+                      unsigned long long* zero_next, const double* b, double* partials,
+                      const MdTables& md, int nx, int ny, int nz, double dx, RfDrive rf,
+                      hipStream_t st);
 void launch_init_f64(const PartF64& P, int n, int ppc, int nx, int ny, int sp, uint32_t k0,
                      uint32_t k1, double vth, hipStream_t st);
 void launch_init_f32r(const PartF32R& P, int n, int ppc, int nx, int ny, int sp, uint32_t k0,
@@ -163,22 +165,81 @@ void launch_field_energy(const void* E, int e_f64, long nxy, int nz, double* out
 void launch_advance_step(uint32_t* step, int32_t* cnt0, int32_t* cnt1, hipStream_t st);
 
 // mesh
-void launch_solve_f64(const FftPlanHost& P, int nx, int ny, int nz, const double* b, void* work,
-                      const void* tw_x, const void* tw_y, const void* inv, double* phi, RfDrive rf,
-                      hipStream_t st);
-void launch_solve_refined(const FftPlanHost& P, int nx, int ny, int nz, const double* b,
-                          double* psi, double* r, void* work32, const void* tw_x32,
-                          const void* tw_y32, const void* inv, RfDrive rf, int sweeps,
-                          double tol, double* norms, int* ctl, hipStream_t st,
-                          bool have_r0 = false);
-// one grain's share of the FP32R right-hand side: interior node `node` (the
-// index into b), grain g, the fixed-point part of its charge quantum at that
-// corner; a replica's table is sorted by node, then by grain and corner
+// one grain's share of the right-hand side: interior node `node` (the index
+// into b), grain g, its cloud-in-cell weight there (w, the FP64 form) and the
+// fixed-point part of its charge quantum (part, FP32R); a replica's table is
+// sorted by node, then by grain and corner
 struct GrainShare {
   long long part;
+  double w;
   int node;
   int g;
 };
+// The FP64 Poisson solve on the half spectrum (spectral.hip).  A line of
+// length N: its radices, and per stage the multiplier that divides by the
+// product of the earlier radices (see div_by).
+constexpr int kFftStages = 8;
+constexpr int kRowThreads = 1024;  // threads of a block that takes whole planes
+struct FftLine {
+  int N, nst;
+  int radix[kFftStages];
+  unsigned mul_s[kFftStages];
+};
+// hx = nx / 2 + 1 independent columns, npair row pairs, ldx the row stride of
+// the packed rows in LDS (odd), buf elements per LDS buffer; full: a block
+// takes a whole plane, else `pairs` row pairs (chunks of them a plane) and, in
+// a kernel of their own, `cols` columns (col_chunks of them)
+struct SpectralPlan {
+  FftLine fx, fy;
+  int K, hx, npair, ldx, buf, full;
+  int pairs, chunks, cols, col_chunks;
+  unsigned mul_nx, mul_hx, mul_pairs, mul_last, mul_cols, mul_cols_last;
+};
+// false if a side has a prime factor above 5
+bool spectral_plan(int nx, int ny, int nz, SpectralPlan* p);
+int spectral_setup();  // once per device before the first solve; 0 on success
+// what the right-hand side is formed from: the unit charge of one grain, the
+// FP64 accumulator, or the fixed-point one
+enum { kRhsUnit = 0, kRhsRho64 = 1, kRhsFixed = 2 };
+struct SpectralArgs {
+  const double2 *tw_x, *tw_y;
+  const double* rho64;
+  const long long* rhofx;
+  double scale;
+  const GrainShare* tab;
+  const int* tab_start;  // [blocks of the rows kernel + 1] first entry of each; null without grains
+  int unit;
+  const unsigned long long* counts;
+  int ng;
+  double we;
+  double* Q;
+  double* psi;  // the result, interior planes
+  double* b;    // kRhsFixed: the right-hand side, stored
+};
+// The refinement's record (FP32R; ctl null: none): norms[0..1] ||r||^2 and
+// ||b||^2 of the residual a solve ended with, ctl[0] whether it met the
+// tolerance, ctl[1] sweeps, ctl[2] solves that did not, ctl[3] set while the
+// last solve's sums (`partials`, nb pairs, from the field kernel) are still to
+// be added up: the next solve does so on its way, or launch_final_test.
+struct RefineState {
+  const double* partials;
+  int nb;
+  double* norms;
+  int* ctl;
+  double tol2;
+};
+void launch_spectral_solve(const SpectralPlan& p, const SpectralArgs& a, int in, double2* work,
+                           const double* inv, const RefineState& rs, hipStream_t st,
+                           hipEvent_t first_done = nullptr, int* rc = nullptr);
+void launch_final_test(const RefineState& rs, hipStream_t st);
+// tridiagonal factors of `cols` columns from sin^2 tables (pi m / nx, pi n / ny)
+void launch_factors(const double* sx2, const double* sy2, int cols, int ny, int K, double* inv,
+                    hipStream_t st);
+void launch_solve_refined(const FftPlanHost& P, int nx, int ny, int nz, const double* b,
+                          double* psi, double* r, void* work32, const void* tw_x32,
+                          const void* tw_y32, const void* inv, int sweeps,
+                          double tol, double* norms, int* ctl, hipStream_t st,
+                          bool have_r0 = false);
 // the FP32R right-hand side (fixed-point rho and the grains' shares, tab)
 // and the first residual with its norm partials (partials = norms + 2 of the
 // refined solve, which then runs with have_r0); also freezes Q_g
@@ -206,32 +267,22 @@ struct RhsArgs {
 // that record fails.
 int launch_rhs_solve_refined(const RhsArgs& a, const FftPlanHost& P, int nx, int ny, int nz,
                              double* b, double* psi, double* r, void* work32,
-                             const void* tw_x32, const void* tw_y32, const void* inv, RfDrive rf,
+                             const void* tw_x32, const void* tw_y32, const void* inv,
                              int sweeps, double tol, double* norms, int* ctl, hipStream_t st,
                              bool defer_final, hipEvent_t first_done);
 // the residual after the last of `sweeps` refinement sweeps and its stopping
 // test (norms, ctl as launch_solve_refined); psi and b unchanged since the solve
 void launch_refine_final(int nx, int ny, int nz, const double* b, const double* psi, double* r,
                          int sweeps, double tol, double* norms, int* ctl, hipStream_t st);
-void launch_rhs_f64(const double* rho, double scale, double* b, int nx, int ny, int nz,
-                    hipStream_t st);
-void launch_grain_rhs(const unsigned long long* counts, const double* gpos, int ng, int nx, int ny,
-                      int nz, double we, double* Q, double* b, double scale, int mode,
-                      long long Qp, hipStream_t st);
-void launch_unit_rhs(const double* gpos, int g, int nx, int ny, int nz, double scale, double* b,
-                     hipStream_t st);
-void launch_extract_cube(const double* E, const int* gcell, int g, int c, int nx, int ny, double* U,
-                         hipStream_t st);
-// phi of the unit-charge solve on grain g's MD cube into Uphi[g][(2c+2)^3]
-void launch_extract_cube_phi(const double* phi, const int* gcell, int g, int c, int nx, int ny,
-                             double* Uphi, hipStream_t st);
+// field and potential of the unit-charge solve (interior potential psi, both
+// electrodes at 0) on grain g's MD cube: U[g][3][(2c+2)^3], Uphi[g][(2c+2)^3]
+void launch_extract_cube(const double* psi, const int* gcell, int g, int c, int nx, int ny, int nz,
+                         double dx, double* U, double* Uphi, hipStream_t st);
 // the potential on the fine grid's nodes (stored, or added to the rf-phase
 // bin of the step when avg.step is set); Uphi may be null without grains
 void launch_fine_phi(const double* phi, const MdTables& md, const double* Uphi, const FineBox& fb,
                      int nx, int ny, int nz, double dx, double radius, double* out,
                      const AvgBins& avg, hipStream_t st);
-void launch_efield_f64(const double* phi, double* E, int nx, int ny, int nz, double dx,
-                       hipStream_t st);
 void launch_e_out(const double* E64, const float* E32, double* out, long nn, hipStream_t st);
 void launch_rho_total(const double* acc64, const long long* accfx, double* tot64, long long* totfx,
                       const unsigned long long* counts, const double* gpos, int ng, int nx, int ny,

@@ -147,23 +147,21 @@ struct FftGeom {
   int L;             // lines per block
   int lines_per_plane;
   long elem_stride, line_stride, plane_stride;  // in elements of the work array
-  long real_plane_offset;  // added to the real array offset (phi: one wall plane)
 };
 
 enum { IN_COMPLEX = 0, IN_REAL = 1 };
-enum { OUT_COMPLEX = 0, OUT_REAL_LIFT = 1, OUT_REAL_ACCUM = 2, OUT_REAL_STORE = 3 };
+enum { OUT_COMPLEX = 0, OUT_REAL_ACCUM = 2 };
 
 template <typename T, int IN, int OUT>
 __global__ __launch_bounds__(256) void fft_lines_kernel(FftGeom g, const cplx<T>* __restrict__ tw,
                                                         int forward, cplx<T>* __restrict__ work,
                                                         const double* __restrict__ rin,
                                                         double in_scale, double* __restrict__ rout,
-                                                        double out_scale, RfDrive rf, int nz,
+                                                        double out_scale,
                                                         const int* __restrict__ skip) {
   using C = cplx<T>;
   extern __shared__ unsigned char smem_raw[];
   if (skip && *skip) return;  // a refinement sweep after convergence
-  const double V = OUT == OUT_REAL_LIFT ? rf_voltage(rf) : 0.0;
   C* buf0 = reinterpret_cast<C*>(smem_raw);
   C* buf1 = buf0 + g.L * g.N;
   const int N = g.N, L = g.L;
@@ -197,12 +195,6 @@ __global__ __launch_bounds__(256) void fft_lines_kernel(FftGeom g, const cplx<T>
     const C v = src[l * N + e];
     if (OUT == OUT_COMPLEX) {
       work[off] = v;
-    } else if (OUT == OUT_REAL_LIFT) {
-      // interior plane k = plane + 1 of phi
-      rout[off + g.real_plane_offset] =
-          (double)v.x * out_scale + V * (double)(plane + 1) / (double)nz;
-    } else if (OUT == OUT_REAL_STORE) {
-      rout[off] = (double)v.x * out_scale;
     } else {
       rout[off] += (double)v.x * out_scale;
     }
@@ -228,7 +220,7 @@ __global__ __launch_bounds__(kPlaneThreads) void fft_plane_kernel(Fft2Geom g, co
                                                         int forward, cplx<T>* __restrict__ work,
                                                         const double* __restrict__ rin,
                                                         double in_scale, double* __restrict__ rout,
-                                                        double out_scale, RfDrive rf, int nz,
+                                                        double out_scale,
                                                         const int* __restrict__ skip) {
   using C = cplx<T>;
   extern __shared__ unsigned char smem_raw[];
@@ -259,16 +251,10 @@ __global__ __launch_bounds__(kPlaneThreads) void fft_plane_kernel(Fft2Geom g, co
     C* other = res == b0 ? b1 : b0;
     res = fft_stages(res, other, nx, ny, nx, 1, g.fx, g.nfx, tw_x, false);
   }
-  const double V = OUT == OUT_REAL_LIFT ? rf_voltage(rf) : 0.0;
   for (int i = threadIdx.x; i < np; i += blockDim.x) {
     const C v = res[i];
     if (OUT == OUT_COMPLEX) {
       work[pbase + i] = v;
-    } else if (OUT == OUT_REAL_LIFT) {
-      // interior plane k = plane + 1 of phi
-      rout[pbase + np + i] = (double)v.x * out_scale + V * (double)(plane + 1) / (double)nz;
-    } else if (OUT == OUT_REAL_STORE) {
-      rout[pbase + i] = (double)v.x * out_scale;
     } else {
       rout[pbase + i] += (double)v.x * out_scale;
     }
@@ -556,14 +542,7 @@ __global__ void thomas_kernel(cplx<T>* __restrict__ d, const TC* __restrict__ in
   }
 }
 
-// ---------------------------------------------------------------- RHS
-// b (interior planes) = scale * rho (all nodes); FP64 form rho in units of w e
-__global__ void rhs_f64_kernel(const double* __restrict__ rho, double scale, double* __restrict__ b,
-                               long plane, long n_int) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n_int) b[i] = scale * rho[i + plane];
-}
-
+// ---------------------------------------------------------------- grains
 // CIC nodes and weights of a grain (its position is at least one cell inside)
 __device__ __forceinline__ void grain_nodes(const double* gpos, int g, int nx, int ny, long n[8],
                                             double w[8], float off[3], int cell[3]) {
@@ -605,102 +584,11 @@ __device__ __forceinline__ void grain_split(long long Q, double fx, double fy, d
   }
 }
 
-// Grain charges at the start of the step: Q_g = (C_i - C_e) w e is frozen for
-// the step's MD kernel, and the grains' CIC charge is added to the RHS.
-// mode 0: FP64 (b += scale_w * net * W); mode 1: FP32R (b += scale_fixed * net * part)
-__global__ void grain_rhs_kernel(const unsigned long long* __restrict__ counts, const double* gpos,
-                                 int ng, int nx, int ny, int nz, double we, double* __restrict__ Q,
-                                 double* __restrict__ b, double scale, int mode, long long Qp) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const long plane = (long)nx * ny;
-  for (int g = 0; g < ng; ++g) {
-    const long long net = (long long)counts[2 * g + 1] - (long long)counts[2 * g + 0];
-    Q[g] = (double)net * we;
-    if (!b || net == 0) continue;
-    long n[8];
-    double w[8];
-    float off[3];
-    int cell[3];
-    grain_nodes(gpos, g, nx, ny, n, w, off, cell);
-    long long part[8];
-    if (mode == 1) {
-      const double X = gpos[3 * g], Y = gpos[3 * g + 1], Z = gpos[3 * g + 2];
-      grain_split(Qp, X - floor(X), Y - floor(Y), Z - floor(Z), part);
-    }
-    for (int t = 0; t < 8; ++t) {
-      const long k = n[t] / plane;
-      if (k < 1 || k > nz - 1) continue;
-      const double add = mode == 1 ? scale * (double)(net * part[t]) : scale * (double)net * w[t];
-      b[n[t] - plane] += add;
-    }
-  }
-}
-
-// The same in parallel for up to kGrainPairs / 8 grains: thread p takes
-// corner t = p % 8 of grain g = p / 8; the first (grain, corner) pair of each
-// node adds, in (grain, corner) order, every contribution to that node, so the
-// sums are those of the serial loop above, bit for bit.
-constexpr int kGrainPairs = 2048;
-__global__ __launch_bounds__(256) void grain_rhs_par_kernel(
-    const unsigned long long* __restrict__ counts, const double* gpos, int ng, int nx, int ny,
-    int nz, double we, double* __restrict__ Q, double* __restrict__ b, double scale, int mode,
-    long long Qp) {
-  __shared__ long s_node[kGrainPairs];
-  __shared__ double s_add[kGrainPairs];
-  const long plane = (long)nx * ny;
-  const int npair = 8 * ng;
-  for (int p = threadIdx.x; p < npair; p += blockDim.x) {
-    const int g = p >> 3, t = p & 7;
-    const long long net = (long long)counts[2 * g + 1] - (long long)counts[2 * g + 0];
-    if (t == 0) Q[g] = (double)net * we;
-    long n[8];
-    double w[8];
-    float off[3];
-    int cell[3];
-    grain_nodes(gpos, g, nx, ny, n, w, off, cell);
-    long long part[8];
-    if (mode == 1) {
-      const double X = gpos[3 * g], Y = gpos[3 * g + 1], Z = gpos[3 * g + 2];
-      grain_split(Qp, X - floor(X), Y - floor(Y), Z - floor(Z), part);
-    }
-    const long k = n[t] / plane;
-    const bool in = b && net != 0 && k >= 1 && k <= nz - 1;
-    s_node[p] = in ? n[t] : -1;
-    s_add[p] = mode == 1 ? scale * (double)(net * part[t]) : scale * (double)net * w[t];
-  }
-  __syncthreads();
-  for (int p = threadIdx.x; p < npair; p += blockDim.x) {
-    const long node = s_node[p];
-    if (node < 0) continue;
-    bool first = true;
-    for (int q = 0; q < p && first; ++q) first = s_node[q] != node;
-    if (!first) continue;
-    double v = b[node - plane];
-    for (int q = p; q < npair; ++q)
-      if (s_node[q] == node) v += s_add[q];
-    b[node - plane] = v;
-  }
-}
-
-// unit (1 C) charge of grain g on the RHS, for its unit field
-__global__ void unit_rhs_kernel(const double* gpos, int g, int nx, int ny, int nz, double scale,
-                                double* __restrict__ b) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const long plane = (long)nx * ny;
-  long n[8];
-  double w[8];
-  float off[3];
-  int cell[3];
-  grain_nodes(gpos, g, nx, ny, n, w, off, cell);
-  for (int t = 0; t < 8; ++t) {
-    const long k = n[t] / plane;
-    if (k >= 1 && k <= nz - 1) b[n[t] - plane] += scale * w[t];
-  }
-}
-
-// copy grain g's field (interleaved double pairs) on its cube into U[g][3][side^3]
-__global__ void extract_cube_kernel(const double2* __restrict__ E, const int* gcell, int g, int c,
-                                    int nx, int ny, double* __restrict__ U) {
+// the field and the potential of grain g's unit-charge solve (psi, both
+// electrodes at 0) on its cube: U[g][3][side^3] and Uphi[g][side^3]
+__global__ void extract_cube_kernel(const double* __restrict__ psi, const int* gcell, int g, int c,
+                                    int nx, int ny, int nz, double dx, double* __restrict__ U,
+                                    double* __restrict__ Uphi) {
   const int side = 2 * c + 2;
   const long cube = (long)side * side * side;
   const long l = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -710,12 +598,13 @@ __global__ void extract_cube_kernel(const double2* __restrict__ E, const int* gc
   const int k = gcell[3 * g + 2] - c + cz;
   i = ((i % nx) + nx) % nx;
   j = ((j % ny) + ny) % ny;
-  const long n = i + (long)nx * (j + (long)ny * k);
-  const double2 a = E[2 * n], bz = E[2 * n + 1];
+  double ex, ey, ez;
+  node_field(psi, nx, ny, nz, dx, 0.0, i, j, k, ex, ey, ez);
   double* Ug = U + (long)g * 3 * cube;
-  Ug[l] = a.x;
-  Ug[cube + l] = a.y;
-  Ug[2 * cube + l] = bz.x;
+  Ug[l] = ex;
+  Ug[cube + l] = ey;
+  Ug[2 * cube + l] = ez;
+  Uphi[(long)g * cube + l] = phi_node(psi, (long)nx * ny, i + (long)nx * j, k, nz, 0.0);
 }
 
 // ---------------------------------------------------------------- refinement
@@ -878,37 +767,6 @@ __global__ __launch_bounds__(1024) void norm_reduce_kernel(const double* __restr
   }
 }
 
-__global__ void walls_kernel(double* __restrict__ phi, long plane, int nz, RfDrive rf) {
-  const double V = rf_voltage(rf);
-  const long n = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= plane) return;
-  phi[n] = 0.0;
-  phi[(long)nz * plane + n] = V;
-}
-
-// ---------------------------------------------------------------- field
-// E = -grad phi from a stored phi (field readouts; the step's fields come
-// from field_out_kernel).  Stored interleaved per node: FP64 as two double
-// pairs (Ex,Ey),(Ez,0); FP32 as one float4 (Ex,Ey,Ez,0).
-template <typename OutT>
-__global__ void efield_kernel(const double* __restrict__ phi, OutT* __restrict__ E, int nx, int ny,
-                              int nz, double dx) {
-  const long plane = (long)nx * ny;
-  // grid: x over the plane's nodes, y over the planes
-  const int pn = (int)(blockIdx.x * blockDim.x + threadIdx.x), k = (int)blockIdx.y;
-  if (pn >= plane) return;
-  const long n = (long)k * plane + pn;
-  const int y = pn / nx, x = pn - y * nx;
-  double ex, ey, ez;
-  node_field<false>(phi, nx, ny, nz, dx, 0.0, x, y, k, ex, ey, ez);
-  if constexpr (std::is_same<OutT, double2>::value) {
-    E[2 * n] = make_double2(ex, ey);
-    E[2 * n + 1] = make_double2(ez, 0.0);
-  } else {
-    E[n] = make_float4((float)ex, (float)ey, (float)ez, 0.0f);
-  }
-}
-
 // ---------------------------------------------------------------- readouts
 __global__ void e_out_kernel(const double2* __restrict__ E2, const float4* __restrict__ E4,
                              double* __restrict__ out, long nn) {
@@ -991,21 +849,6 @@ __global__ void avg_out_kernel(const double* __restrict__ acc, int b0, int b1, l
     c += cnt[b];
   }
   out[u] = c ? s / (double)c * (u < n_plain ? 1.0 : wv) : 0.0;
-}
-
-// phi of the unit-charge solve on grain g's MD cube: Uphi[g][side^3]
-__global__ void extract_cube_phi_kernel(const double* __restrict__ phi, const int* gcell, int g,
-                                        int c, int nx, int ny, double* __restrict__ Uphi) {
-  const int side = 2 * c + 2;
-  const long cube = (long)side * side * side;
-  const long l = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= cube) return;
-  const int cx = (int)(l % side), cy = (int)((l / side) % side), cz = (int)(l / (side * side));
-  int i = gcell[3 * g] - c + cx, j = gcell[3 * g + 1] - c + cy;
-  const int k = gcell[3 * g + 2] - c + cz;
-  i = ((i % nx) + nx) % nx;
-  j = ((j % ny) + ny) % ny;
-  Uphi[(long)g * cube + l] = phi[i + (long)nx * (j + (long)ny * k)];
 }
 
 // The potential on the nodes of the fine grid: the mesh potential with the
@@ -1114,14 +957,13 @@ static FftGeom make_geom(const FftPlanHost& P, bool along_x, int nx, int ny, lon
   g.elem_stride = along_x ? 1 : nx;
   g.line_stride = along_x ? nx : 1;
   g.plane_stride = plane;
-  g.real_plane_offset = plane;
   return g;
 }
 
 template <typename T>
 static void fft_launch(const FftGeom& g, int planes, const void* tw, int forward, int in_mode,
                        int out_mode, void* work, const double* rin, double in_scale, double* rout,
-                       double out_scale, RfDrive rf, int nz, hipStream_t st,
+                       double out_scale, hipStream_t st,
                        const int* skip = nullptr) {
   using C = cplx<T>;
   const int blocks = planes * (g.lines_per_plane / g.L);
@@ -1130,19 +972,13 @@ static void fft_launch(const FftGeom& g, int planes, const void* tw, int forward
   C* w = (C*)work;
   if (in_mode == IN_REAL && out_mode == OUT_COMPLEX)
     hipLaunchKernelGGL((fft_lines_kernel<T, IN_REAL, OUT_COMPLEX>), dim3(blocks), dim3(256), lds, st,
-                       g, t, forward, w, rin, in_scale, rout, out_scale, rf, nz, skip);
+                       g, t, forward, w, rin, in_scale, rout, out_scale, skip);
   else if (in_mode == IN_COMPLEX && out_mode == OUT_COMPLEX)
     hipLaunchKernelGGL((fft_lines_kernel<T, IN_COMPLEX, OUT_COMPLEX>), dim3(blocks), dim3(256), lds,
-                       st, g, t, forward, w, rin, in_scale, rout, out_scale, rf, nz, skip);
-  else if (out_mode == OUT_REAL_LIFT)
-    hipLaunchKernelGGL((fft_lines_kernel<T, IN_COMPLEX, OUT_REAL_LIFT>), dim3(blocks), dim3(256), lds,
-                       st, g, t, forward, w, rin, in_scale, rout, out_scale, rf, nz, skip);
-  else if (out_mode == OUT_REAL_STORE)
-    hipLaunchKernelGGL((fft_lines_kernel<T, IN_COMPLEX, OUT_REAL_STORE>), dim3(blocks), dim3(256),
-                       lds, st, g, t, forward, w, rin, in_scale, rout, out_scale, rf, nz, skip);
+                       st, g, t, forward, w, rin, in_scale, rout, out_scale, skip);
   else
     hipLaunchKernelGGL((fft_lines_kernel<T, IN_COMPLEX, OUT_REAL_ACCUM>), dim3(blocks), dim3(256),
-                       lds, st, g, t, forward, w, rin, in_scale, rout, out_scale, rf, nz, skip);
+                       lds, st, g, t, forward, w, rin, in_scale, rout, out_scale, skip);
 }
 
 // 2-D plane transforms when two plane buffers fit in 64 KB of LDS
@@ -1151,7 +987,7 @@ constexpr size_t kPlaneLds = 65536;
 template <typename T>
 static void fft_plane_launch(const FftPlanHost& P, int nx, int ny, int planes, const void* tw_x,
                              const void* tw_y, int forward, int in_mode, int out_mode, void* work,
-                             const double* rin, double* rout, double out_scale, RfDrive rf, int nz,
+                             const double* rin, double* rout, double out_scale,
                              hipStream_t st, const int* skip = nullptr) {
   using C = cplx<T>;
   Fft2Geom g{};
@@ -1169,16 +1005,10 @@ static void fft_plane_launch(const FftPlanHost& P, int nx, int ny, int planes, c
   C* w = (C*)work;
   if (in_mode == IN_REAL)
     hipLaunchKernelGGL((fft_plane_kernel<T, IN_REAL, OUT_COMPLEX>), dim3(planes), dim3(kPlaneThreads), lds, st,
-                       g, tx, ty, forward, w, rin, 1.0, rout, out_scale, rf, nz, skip);
-  else if (out_mode == OUT_REAL_LIFT)
-    hipLaunchKernelGGL((fft_plane_kernel<T, IN_COMPLEX, OUT_REAL_LIFT>), dim3(planes),
-                       dim3(kPlaneThreads), lds, st, g, tx, ty, forward, w, rin, 1.0, rout, out_scale, rf, nz, skip);
-  else if (out_mode == OUT_REAL_STORE)
-    hipLaunchKernelGGL((fft_plane_kernel<T, IN_COMPLEX, OUT_REAL_STORE>), dim3(planes),
-                       dim3(kPlaneThreads), lds, st, g, tx, ty, forward, w, rin, 1.0, rout, out_scale, rf, nz, skip);
+                       g, tx, ty, forward, w, rin, 1.0, rout, out_scale, skip);
   else
     hipLaunchKernelGGL((fft_plane_kernel<T, IN_COMPLEX, OUT_REAL_ACCUM>), dim3(planes),
-                       dim3(kPlaneThreads), lds, st, g, tx, ty, forward, w, rin, 1.0, rout, out_scale, rf, nz, skip);
+                       dim3(kPlaneThreads), lds, st, g, tx, ty, forward, w, rin, 1.0, rout, out_scale, skip);
 }
 
 // the tridiagonal solves of every mode: work in T, the factorisation inv and
@@ -1200,40 +1030,31 @@ static void tridiag_launch(void* work, const void* inv, int K, long modes, hipSt
                        (const double*)inv, K, modes, skip);
 }
 
-// one FFT + tridiagonal + inverse FFT solve of A psi = b (T = double or float);
-// out_mode OUT_REAL_LIFT writes phi (with the lift), OUT_REAL_ACCUM adds to psi
+// one FFT + tridiagonal + inverse FFT solve of A psi = b, added to psi
 template <typename T>
 static void solve_once(const FftPlanHost& P, int nx, int ny, int nz, const double* b, void* work,
-                       const void* tw_x, const void* tw_y, const void* inv, int out_mode,
-                       double* out, RfDrive rf, hipStream_t st, const int* skip = nullptr) {
+                       const void* tw_x, const void* tw_y, const void* inv,
+                       double* out, hipStream_t st, const int* skip = nullptr) {
   const long plane = (long)nx * ny;
   const int K = nz - 1;
   if (2 * sizeof(cplx<T>) * (size_t)plane <= kPlaneLds) {
     fft_plane_launch<T>(P, nx, ny, K, tw_x, tw_y, 1, IN_REAL, OUT_COMPLEX, work, b, nullptr, 0.0,
-                        rf, nz, st, skip);
+                        st, skip);
     tridiag_launch<T>(work, inv, K, plane, st, skip);
-    fft_plane_launch<T>(P, nx, ny, K, tw_x, tw_y, 0, IN_COMPLEX, out_mode, work, nullptr, out,
-                        1.0 / (double)plane, rf, nz, st, skip);
+    fft_plane_launch<T>(P, nx, ny, K, tw_x, tw_y, 0, IN_COMPLEX, OUT_REAL_ACCUM, work, nullptr, out,
+                        1.0 / (double)plane, st, skip);
     return;
   }
   const FftGeom gx = make_geom(P, true, nx, ny, plane);
   const FftGeom gy = make_geom(P, false, nx, ny, plane);
-  fft_launch<T>(gx, K, tw_x, 1, IN_REAL, OUT_COMPLEX, work, b, 1.0, nullptr, 0.0, rf, nz, st, skip);
-  fft_launch<T>(gy, K, tw_y, 1, IN_COMPLEX, OUT_COMPLEX, work, nullptr, 0.0, nullptr, 0.0, rf, nz,
+  fft_launch<T>(gx, K, tw_x, 1, IN_REAL, OUT_COMPLEX, work, b, 1.0, nullptr, 0.0, st, skip);
+  fft_launch<T>(gy, K, tw_y, 1, IN_COMPLEX, OUT_COMPLEX, work, nullptr, 0.0, nullptr, 0.0,
                 st, skip);
   tridiag_launch<T>(work, inv, K, plane, st, skip);
-  fft_launch<T>(gy, K, tw_y, 0, IN_COMPLEX, OUT_COMPLEX, work, nullptr, 0.0, nullptr, 0.0, rf, nz,
+  fft_launch<T>(gy, K, tw_y, 0, IN_COMPLEX, OUT_COMPLEX, work, nullptr, 0.0, nullptr, 0.0,
                 st, skip);
-  fft_launch<T>(gx, K, tw_x, 0, IN_COMPLEX, out_mode, work, nullptr, 0.0, out,
-                1.0 / (double)plane, rf, nz, st, skip);
-}
-
-void launch_solve_f64(const FftPlanHost& P, int nx, int ny, int nz, const double* b, void* work,
-                      const void* tw_x, const void* tw_y, const void* inv, double* phi, RfDrive rf,
-                      hipStream_t st) {
-  solve_once<double>(P, nx, ny, nz, b, work, tw_x, tw_y, inv, OUT_REAL_LIFT, phi, rf, st);
-  hipLaunchKernelGGL(walls_kernel, dim3(nb256((long)nx * ny)), dim3(256), 0, st, phi,
-                     (long)nx * ny, nz, rf);
+  fft_launch<T>(gx, K, tw_x, 0, IN_COMPLEX, OUT_REAL_ACCUM, work, nullptr, 0.0, out,
+                1.0 / (double)plane, st, skip);
 }
 
 // FP32 solves refined in FP64, starting from the psi the previous solve left
@@ -1250,7 +1071,7 @@ void launch_solve_f64(const FftPlanHost& P, int nx, int ny, int nz, const double
 // interior plane; ctl as in norm_reduce_kernel.
 void launch_solve_refined(const FftPlanHost& P, int nx, int ny, int nz, const double* b,
                           double* psi, double* r, void* work32, const void* tw_x32,
-                          const void* tw_y32, const void* inv, RfDrive rf, int sweeps,
+                          const void* tw_y32, const void* inv, int sweeps,
                           double tol, double* norms, int* ctl, hipStream_t st, bool have_r0) {
   const long plane = (long)nx * ny;
   const int nb = (int)(nb256(plane) * (nz - 1));
@@ -1260,8 +1081,7 @@ void launch_solve_refined(const FftPlanHost& P, int nx, int ny, int nz, const do
   hipLaunchKernelGGL(norm_reduce_kernel, dim3(1), dim3(1024), 0, st, norms + 2, nb, norms, ctl,
                      tol * tol, 0, 0);
   for (int it = 1; it <= sweeps; ++it) {
-    solve_once<float>(P, nx, ny, nz, r, work32, tw_x32, tw_y32, inv, OUT_REAL_ACCUM, psi, rf, st,
-                      ctl);
+    solve_once<float>(P, nx, ny, nz, r, work32, tw_x32, tw_y32, inv, psi, st, ctl);
     hipLaunchKernelGGL(residual_kernel<true>, dim3(nb256(plane), nz - 1), dim3(256), 0, st, psi,
                        b, r, nx, ny, nz - 1, norms + 2, ctl);
     hipLaunchKernelGGL(norm_reduce_kernel, dim3(1), dim3(1024), 0, st, norms + 2, nb, norms, ctl,
@@ -1293,7 +1113,7 @@ void launch_refine_final(int nx, int ny, int nz, const double* b, const double* 
 // that reads rho and the grains' counts); -1 if that record fails.
 int launch_rhs_solve_refined(const RhsArgs& a, const FftPlanHost& P, int nx, int ny, int nz,
                              double* b, double* psi, double* r, void* work32,
-                             const void* tw_x32, const void* tw_y32, const void* inv, RfDrive rf,
+                             const void* tw_x32, const void* tw_y32, const void* inv,
                              int sweeps, double tol, double* norms, int* ctl, hipStream_t st,
                              bool defer_final, hipEvent_t first_done) {
   using C = cplx<float>;
@@ -1303,7 +1123,7 @@ int launch_rhs_solve_refined(const RhsArgs& a, const FftPlanHost& P, int nx, int
     launch_rhs_residual(a.rho, a.scale, a.tab, a.ntab, a.counts, a.ng, a.we, a.Q, b, psi, r, nx,
                         ny, nz, norms + 2, st);
     if (first_done && hipEventRecord(first_done, st) != hipSuccess) return -1;
-    launch_solve_refined(P, nx, ny, nz, b, psi, r, work32, tw_x32, tw_y32, inv, rf, sweeps, tol,
+    launch_solve_refined(P, nx, ny, nz, b, psi, r, work32, tw_x32, tw_y32, inv, sweeps, tol,
                          norms, ctl, st, true);
     return 0;
   }
@@ -1328,7 +1148,7 @@ int launch_rhs_solve_refined(const RhsArgs& a, const FftPlanHost& P, int nx, int
   for (int it = 1; it <= sweeps; ++it) {
     tridiag_launch<float>(work32, inv, K, plane, st, ctl);
     fft_plane_launch<float>(P, nx, ny, K, tw_x32, tw_y32, 0, IN_COMPLEX, OUT_REAL_ACCUM, work32,
-                            nullptr, psi, 1.0 / (double)plane, rf, nz, st, ctl);
+                            nullptr, psi, 1.0 / (double)plane, st, ctl);
     if (it < sweeps) {
       hipLaunchKernelGGL((residual_fft_kernel<float, false>), dim3(K), dim3(kPlaneThreads), lds,
                          st, g, tx, ty, w, psi, b, a, norms + 2, ctl);
@@ -1356,41 +1176,11 @@ void launch_refine_final(int nx, int ny, int nz, const double* b, const double* 
                      tol * tol, sweeps, 1);
 }
 
-void launch_rhs_f64(const double* rho, double scale, double* b, int nx, int ny, int nz,
-                    hipStream_t st) {
-  const long plane = (long)nx * ny, n_int = plane * (nz - 1);
-  hipLaunchKernelGGL(rhs_f64_kernel, dim3(nb256(n_int)), dim3(256), 0, st, rho, scale, b, plane,
-                     n_int);
-}
-
-void launch_grain_rhs(const unsigned long long* counts, const double* gpos, int ng, int nx, int ny,
-                      int nz, double we, double* Q, double* b, double scale, int mode,
-                      long long Qp, hipStream_t st) {
-  if (ng <= 0) return;
-  if (8 * ng <= kGrainPairs)
-    hipLaunchKernelGGL(grain_rhs_par_kernel, dim3(1), dim3(256), 0, st, counts, gpos, ng, nx, ny,
-                       nz, we, Q, b, scale, mode, Qp);
-  else
-    hipLaunchKernelGGL(grain_rhs_kernel, dim3(1), dim3(64), 0, st, counts, gpos, ng, nx, ny, nz,
-                       we, Q, b, scale, mode, Qp);
-}
-
-void launch_unit_rhs(const double* gpos, int g, int nx, int ny, int nz, double scale, double* b,
-                     hipStream_t st) {
-  hipLaunchKernelGGL(unit_rhs_kernel, dim3(1), dim3(64), 0, st, gpos, g, nx, ny, nz, scale, b);
-}
-
-void launch_extract_cube(const double* E, const int* gcell, int g, int c, int nx, int ny, double* U,
-                         hipStream_t st) {
+void launch_extract_cube(const double* psi, const int* gcell, int g, int c, int nx, int ny, int nz,
+                         double dx, double* U, double* Uphi, hipStream_t st) {
   const long side = 2 * c + 2, cube = side * side * side;
-  hipLaunchKernelGGL(extract_cube_kernel, dim3(nb256(cube)), dim3(256), 0, st, (const double2*)E,
-                     gcell, g, c, nx, ny, U);
-}
-
-void launch_efield_f64(const double* phi, double* E, int nx, int ny, int nz, double dx,
-                       hipStream_t st) {
-  hipLaunchKernelGGL(efield_kernel<double2>, dim3(nb256((long)nx * ny), nz + 1), dim3(256), 0, st,
-                     phi, (double2*)E, nx, ny, nz, dx);
+  hipLaunchKernelGGL(extract_cube_kernel, dim3(nb256(cube)), dim3(256), 0, st, psi, gcell, g, c, nx,
+                     ny, nz, dx, U, Uphi);
 }
 
 void launch_e_out(const double* E64, const float* E32, double* out, long nn, hipStream_t st) {
@@ -1423,13 +1213,6 @@ void launch_avg_out(const double* acc, int b0, int b1, long stride, long total, 
   if (total <= 0) return;
   hipLaunchKernelGGL(avg_out_kernel, dim3(nb256(total)), dim3(256), 0, st, acc, b0, b1, stride,
                      total, n_plain, cnt, wv, out);
-}
-
-void launch_extract_cube_phi(const double* phi, const int* gcell, int g, int c, int nx, int ny,
-                             double* Uphi, hipStream_t st) {
-  const long side = 2 * c + 2, cube = side * side * side;
-  hipLaunchKernelGGL(extract_cube_phi_kernel, dim3(nb256(cube)), dim3(256), 0, st, phi, gcell, g, c,
-                     nx, ny, Uphi);
 }
 
 void launch_fine_phi(const double* phi, const MdTables& md, const double* Uphi, const FineBox& fb,

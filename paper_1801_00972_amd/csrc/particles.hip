@@ -297,36 +297,81 @@ __device__ __forceinline__ void md_corner(const MdTables& md, int nx, int ny, ui
 
 // The fields of a step in one launch.  Blocks [0, nbm): one thread per (MD box
 // cell in a cube, corner) forms the corrected node field; E at the node is
-// formed from phi and rounded to the storage type first, so it is what a read
+// formed from psi and rounded to the storage type first, so it is what a read
 // of E returns (these blocks come first: their dependent table loads then
 // overlap the node blocks' streaming).  Blocks from nbm on: one thread per
-// node writes phi (kLift: from the refined solve's interior potential psi and
-// the electrode voltages; otherwise phi is the stored src), E = -grad phi in
-// the storage type, and clears the next step's charge accumulator.
-template <typename ET, bool kLift>
-__global__ __launch_bounds__(256) void field_out_kernel(const double* __restrict__ src,
+// node writes phi (psi, the solve's interior potential, and the electrodes'
+// lift) and E = -grad phi in the storage type, and clears the next step's
+// charge accumulator.  With b (FP32R) the block's sums of (b - A psi)^2 and b^2
+// over its interior nodes go to partials: the six neighbours are at hand, so
+// the residual costs one more read per node and no pass of its own.
+template <typename ET>
+__global__ __launch_bounds__(256) void field_out_kernel(const double* __restrict__ psi,
                                                         double* __restrict__ phi,
                                                         ET* __restrict__ E,
                                                         unsigned long long* __restrict__ zero_next,
+                                                        const double* __restrict__ b,
+                                                        double* __restrict__ partials,
                                                         MdTables md, int nx, int ny, int nz,
                                                         double dx, RfDrive rf, int nbm) {
-  const double V = kLift ? rf_voltage(rf) : 0.0;
+  const double V = rf_voltage(rf);
   if ((int)blockIdx.x >= nbm) {
+    __shared__ double s_r[4], s_b[4];
     const int plane = nx * ny;
     const int n = ((int)blockIdx.x - nbm) * (int)blockDim.x + (int)threadIdx.x;
-    if (n >= plane * (nz + 1)) return;
-    const int k = n / plane, pn = n - k * plane;
-    const int y = pn / nx, x = pn - y * nx;
-    if (kLift) phi[n] = phi_node<true>(src, plane, pn, k, nz, V);
-    double ex, ey, ez;
-    node_field<kLift>(src, nx, ny, nz, dx, V, x, y, k, ex, ey, ez);
-    if constexpr (std::is_same<ET, double2>::value) {
-      E[2 * (long)n] = make_double2(ex, ey);
-      E[2 * (long)n + 1] = make_double2(ez, 0.0);
-    } else {
-      E[n] = make_float4((float)ex, (float)ey, (float)ez, 0.0f);
+    double rr = 0.0, bb = 0.0;
+    if (n < plane * (nz + 1)) {
+      const int k = n / plane, pn = n - k * plane;
+      const int y = pn / nx, x = pn - y * nx;
+      if (zero_next) zero_next[n] = 0ull;
+      const int row = y * nx;
+      const int xp = row + (x + 1 == nx ? 0 : x + 1), xm = row + (x == 0 ? nx - 1 : x - 1);
+      const int yp = (y + 1 == ny ? 0 : y + 1) * nx + x, ym = (y == 0 ? ny - 1 : y - 1) * nx + x;
+      const bool in = k > 0 && k < nz;
+      const double* p0 = psi + (long)(k - 1) * plane;
+      const double qc = in ? p0[pn] : 0.0;
+      const double qxp = in ? p0[xp] : 0.0, qxm = in ? p0[xm] : 0.0;
+      const double qyp = in ? p0[yp] : 0.0, qym = in ? p0[ym] : 0.0;
+      const double qzp = k + 1 < nz ? p0[plane + pn] : 0.0, qzm = k > 1 ? p0[pn - plane] : 0.0;
+      // the lifted potential at height q: psi + V q / nz, 0 and V on the electrodes
+      auto lift = [&](double q, int h) { return h == 0 ? 0.0 : (h == nz ? V : q + V * (double)h / (double)nz); };
+      const double c = lift(qc, k);
+      phi[n] = c;
+      const double ex = -(lift(qxp, k) - lift(qxm, k)) / (2.0 * dx);
+      const double ey = -(lift(qyp, k) - lift(qym, k)) / (2.0 * dx);
+      double ez;
+      if (k == 0) ez = -(lift(qzp, 1) - c) / dx;
+      else if (k == nz) ez = -(c - lift(qzm, nz - 1)) / dx;
+      else ez = -(lift(qzp, k + 1) - lift(qzm, k - 1)) / (2.0 * dx);
+      if constexpr (std::is_same<ET, double2>::value) {
+        E[2 * (long)n] = make_double2(ex, ey);
+        E[2 * (long)n + 1] = make_double2(ez, 0.0);
+      } else {
+        E[n] = make_float4((float)ex, (float)ey, (float)ez, 0.0f);
+      }
+      if (b && in) {
+        const double bi = b[n - plane];
+        const double r = bi - (qxp + qxm + qyp + qym + qzp + qzm - 6.0 * qc);
+        rr = r * r;
+        bb = bi * bi;
+      }
     }
-    if (zero_next) zero_next[n] = 0ull;
+    if (!b) return;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      rr += __shfl_xor(rr, off, 64);
+      bb += __shfl_xor(bb, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+      s_r[threadIdx.x >> 6] = rr;
+      s_b[threadIdx.x >> 6] = bb;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const long blk = (long)blockIdx.x - nbm;
+      partials[2 * blk] = s_r[0] + s_r[1] + s_r[2] + s_r[3];
+      partials[2 * blk + 1] = s_b[0] + s_b[1] + s_b[2] + s_b[3];
+    }
     return;
   }
   const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -336,13 +381,13 @@ __global__ __launch_bounds__(256) void field_out_kernel(const double* __restrict
   const int t = (int)(gid & 7);
   const uint32_t cl = md.cell_list[bi];
   if ((cl & 255u) == 0u) return;
-  const int a = (int)(bi % md.bsx), b = (int)((bi / md.bsx) % md.bsy);
+  const int a = (int)(bi % md.bsx), bb = (int)((bi / md.bsx) % md.bsy);
   const int c = (int)(bi / ((long)md.bsx * md.bsy));
-  const int i0 = (md.bx0 + a) % nx, j0 = (md.by0 + b) % ny, k0 = md.bz0 + c;
+  const int i0 = (md.bx0 + a) % nx, j0 = (md.by0 + bb) % ny, k0 = md.bz0 + c;
   const int ta = t & 1, tb = (t >> 1) & 1, tc = t >> 2;
   const int in = i0 + ta == nx ? 0 : i0 + ta, jn = j0 + tb == ny ? 0 : j0 + tb;
   double En[3];
-  node_field<kLift>(src, nx, ny, nz, dx, V, in, jn, k0 + tc, En[0], En[1], En[2]);
+  node_field(psi, nx, ny, nz, dx, V, in, jn, k0 + tc, En[0], En[1], En[2]);
   if constexpr (!std::is_same<ET, double2>::value) {
 #pragma unroll
     for (int q = 0; q < 3; ++q) En[q] = (double)(float)En[q];
@@ -2814,27 +2859,18 @@ void launch_push_batch_f32r(const PushDescF32* descs, const int32_t* start, int 
 constexpr int kMdBlocks = kMdTallyRows;
 
 void launch_field_out(const double* psi, double* phi, void* E, int e_f64,
-                      unsigned long long* zero_next, const MdTables& md, int nx, int ny, int nz,
-                      double dx, RfDrive rf, hipStream_t st) {
+                      unsigned long long* zero_next, const double* b, double* partials,
+                      const MdTables& md, int nx, int ny, int nz, double dx, RfDrive rf,
+                      hipStream_t st) {
   const long nn = (long)nx * ny * (nz + 1);
-  const int nbe = nblk(nn, 256);
+  const int nbe = (int)field_out_sums(nn);
   const int nbm = md.n_grains > 0 ? nblk(8L * md.bsx * md.bsy * md.bsz, 256) : 0;
-  const double* src = psi ? psi : phi;
-  if (e_f64) {
-    if (psi)
-      hipLaunchKernelGGL((field_out_kernel<double2, true>), dim3(nbe + nbm), dim3(256), 0, st, src,
-                         phi, (double2*)E, zero_next, md, nx, ny, nz, dx, rf, nbm);
-    else
-      hipLaunchKernelGGL((field_out_kernel<double2, false>), dim3(nbe + nbm), dim3(256), 0, st,
-                         src, phi, (double2*)E, zero_next, md, nx, ny, nz, dx, rf, nbm);
-  } else {
-    if (psi)
-      hipLaunchKernelGGL((field_out_kernel<float4, true>), dim3(nbe + nbm), dim3(256), 0, st, src,
-                         phi, (float4*)E, zero_next, md, nx, ny, nz, dx, rf, nbm);
-    else
-      hipLaunchKernelGGL((field_out_kernel<float4, false>), dim3(nbe + nbm), dim3(256), 0, st, src,
-                         phi, (float4*)E, zero_next, md, nx, ny, nz, dx, rf, nbm);
-  }
+  if (e_f64)
+    hipLaunchKernelGGL(field_out_kernel<double2>, dim3(nbe + nbm), dim3(256), 0, st, psi, phi,
+                       (double2*)E, zero_next, b, partials, md, nx, ny, nz, dx, rf, nbm);
+  else
+    hipLaunchKernelGGL(field_out_kernel<float4>, dim3(nbe + nbm), dim3(256), 0, st, psi, phi,
+                       (float4*)E, zero_next, b, partials, md, nx, ny, nz, dx, rf, nbm);
 }
 
 void launch_collide_f64(const PartF64& P, const SpeciesStep& S, const WorkLists& L,

@@ -69,18 +69,29 @@ struct Replica {
   // mesh
   void* rho[2]{};      // accumulators: double (units w e) or int64 (2^-32 e)
   int rho_cur = 0;
-  double* b = nullptr;
+  double* b = nullptr;     // FP32R: the right-hand side
   double* phi = nullptr;
   void* E = nullptr;   // double pairs (FP64) or float4 (FP32R)
-  double* psi = nullptr;
+  double* psi = nullptr;   // phi without the electrodes' lift, interior planes
+  // the FP64 solve on the half spectrum: plan, work array, roots of unity,
+  // tridiagonal factors
+  SpectralPlan plan{};
+  double2* work = nullptr;
+  double2* tw_x = nullptr;
+  double2* tw_y = nullptr;
+  double* inv = nullptr;
+  // FP32R contexts whose refinement takes FP32 sweeps (fp32_sweeps): residual,
+  // FP32 work array and roots, factors of the full spectrum
+  bool sweeps32 = false;
   double* r = nullptr;
-  void* work = nullptr;
-  void* tw_x = nullptr;
-  void* tw_y = nullptr;
-  void* inv = nullptr;
+  float2* work32 = nullptr;
+  float* tw_x32 = nullptr;
+  float* tw_y32 = nullptr;
+  double* inv_full = nullptr;
   FftPlanHost fft{};
   double* norms = nullptr;
-  int* refine_ctl = nullptr;  // FP32R refinement: [0] converged, [1] sweeps, [2] unconverged solves
+  int* refine_ctl = nullptr;  // FP32R refinement: see RefineState
+  bool final_pending = false;  // the last solve's residual sums are still to be added up
   double* tot64 = nullptr;
   long long* totfx = nullptr;
   double* eout = nullptr;
@@ -108,8 +119,9 @@ struct Replica {
   // near-grain tables
   MdTables md{};
   double* d_Q = nullptr;
-  GrainShare* d_gtab = nullptr;  // FP32R: the grains' right-hand-side shares (sorted)
+  GrainShare* d_gtab = nullptr;  // the grains' right-hand-side shares (sorted)
   int n_gtab = 0;
+  int* d_gtab_start = nullptr;  // first share of each block of the solve's rows kernel
   // grain counts; event tallies live per chunk in lists[sp].tally
   unsigned long long* d_gc = nullptr;
   int64_t wall_base[2][2]{};  // electrode counts handed over by pic_set_state
@@ -414,11 +426,11 @@ int validate(const pic_config& c, std::string& why) {
   return PIC_OK;
 }
 
-// The FP32R grains' shares of the right-hand side: for each grain its 8 CIC
-// nodes (those on interior planes) and the exact fixed-point split of one
-// macro charge Qp at its offsets, the split the particle deposit makes, sorted
-// by node and then by (grain, corner), the order in which the separate grain
-// kernel adds them.  Each step adds scale (net_g part) at the node.
+// The grains' shares of the right-hand side: for each grain its 8 CIC nodes
+// (those on interior planes), their weights and the exact fixed-point split of
+// one macro charge Qp at its offsets, the split the particle deposit makes,
+// sorted by node and then by (grain, corner).  Each step adds scale (net_g w),
+// FP32R scale (net_g part), at the node.
 std::vector<GrainShare> grain_shares(const Replica& R) {
   struct Key {
     long node;
@@ -452,7 +464,9 @@ std::vector<GrainShare> grain_shares(const Replica& R) {
       const long n = ii[a] + (long)R.nx * (jj[b] + (long)R.ny * (k0 + c));
       const long k = n / plane;
       if (k < 1 || k > R.nz - 1) continue;
-      v.push_back(Key{n - plane, 8 * g + t, GrainShare{part[t], (int)(n - plane), g}});
+      const double fx = X - i0, fy = Y - j0, fz = Z - k0;
+      const double w = (a ? fx : 1.0 - fx) * (b ? fy : 1.0 - fy) * (c ? fz : 1.0 - fz);
+      v.push_back(Key{n - plane, 8 * g + t, GrainShare{part[t], w, (int)(n - plane), g}});
     }
   }
   std::sort(v.begin(), v.end(), [](const Key& x, const Key& y) {
@@ -537,53 +551,71 @@ int setup_md(pic_ctx* ctx, Replica& R) {
   md.gpos = d_gpos;
   md.gcell = d_gcell;
   md.U = d_U;
-  if (R.prec != PIC_FP64) {
-    const std::vector<GrainShare> tab = grain_shares(R);
-    R.n_gtab = (int)tab.size();
-    TRY(dalloc(ctx, R, &R.d_gtab, std::max<size_t>(tab.size(), 1)));
-    if (!tab.empty())
-      HIPCHK(ctx, hipMemcpy(R.d_gtab, tab.data(), tab.size() * sizeof(GrainShare),
-                            hipMemcpyHostToDevice));
+  const std::vector<GrainShare> tab = grain_shares(R);
+  R.n_gtab = (int)tab.size();
+  TRY(dalloc(ctx, R, &R.d_gtab, std::max<size_t>(tab.size(), 1)));
+  if (!tab.empty())
+    HIPCHK(ctx, hipMemcpy(R.d_gtab, tab.data(), tab.size() * sizeof(GrainShare),
+                          hipMemcpyHostToDevice));
+  const SpectralPlan& pl = R.plan;
+  std::vector<int> first((size_t)pl.K * pl.chunks + 1, 0);
+  size_t e = 0;
+  for (size_t b = 0; b < first.size(); ++b) {
+    const long plane = (long)(b / pl.chunks), row = std::min(2L * pl.pairs * (long)(b % pl.chunks), (long)R.ny);
+    while (e < tab.size() && tab[e].node < plane * R.nxy + row * R.nx) ++e;
+    first[b] = (int)e;
   }
+  TRY(dalloc(ctx, R, &R.d_gtab_start, first.size()));
+  HIPCHK(ctx, hipMemcpy(R.d_gtab_start, first.data(), first.size() * sizeof(int),
+                        hipMemcpyHostToDevice));
   return PIC_OK;
 }
 
-// FFT twiddles in T and the tridiagonal factors in double (the tridiagonal
-// solves run in double in both forms)
+// roots of unity exp(2 pi i t / N) in T
 template <typename T>
-int setup_solver_tables(pic_ctx* ctx, Replica& R, void** tw_x, void** tw_y, void** inv) {
-  auto twiddles = [&](int N, void** out) -> int {
-    std::vector<T> h(2 * N);
-    for (int t = 0; t < N; ++t) {
-      const double a = 2.0 * kPi * (double)t / (double)N;
-      h[2 * t] = (T)std::cos(a);
-      h[2 * t + 1] = (T)std::sin(a);
-    }
-    T* d;
-    TRY(dalloc(ctx, R, &d, 2 * N));
-    HIPCHK(ctx, hipMemcpy(d, h.data(), 2 * N * sizeof(T), hipMemcpyHostToDevice));
-    *out = d;
-    return PIC_OK;
-  };
-  TRY(twiddles(R.nx, tw_x));
-  TRY(twiddles(R.ny, tw_y));
-  const int K = R.nz - 1;
-  std::vector<double> h((size_t)K * R.nxy);
-  for (long mn = 0; mn < R.nxy; ++mn) {
-    const int m = (int)(mn % R.nx), n = (int)(mn / R.nx);
-    const double sx = std::sin(kPi * m / R.nx), sy = std::sin(kPi * n / R.ny);
-    const double diag = -(2.0 + 4.0 * (sx * sx + sy * sy));
-    double cprev = 0.0;
-    for (int k = 0; k < K; ++k) {
-      const double f = 1.0 / (diag - cprev);
-      h[(size_t)k * R.nxy + mn] = f;
-      cprev = f;
-    }
+int setup_roots(pic_ctx* ctx, Replica& R, int N, T** out) {
+  std::vector<T> h(2 * (size_t)N);
+  for (int t = 0; t < N; ++t) {
+    const double a = 2.0 * kPi * (double)t / (double)N;
+    h[2 * t] = (T)std::cos(a);
+    h[2 * t + 1] = (T)std::sin(a);
   }
-  double* d;
-  TRY(dalloc(ctx, R, &d, h.size()));
-  HIPCHK(ctx, hipMemcpy(d, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice));
-  *inv = d;
+  TRY(dalloc(ctx, R, out, 2 * (size_t)N));
+  HIPCHK(ctx, hipMemcpy(*out, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
+  return PIC_OK;
+}
+
+// the solver's tables: roots of unity and the tridiagonal factors (formed on
+// the device), of the half spectrum and, for FP32 sweeps, of the full one
+int setup_solver(pic_ctx* ctx, Replica& R) {
+  if (!spectral_plan(R.nx, R.ny, R.nz, &R.plan))
+    return fail(ctx, PIC_EINVAL, "FFT length not supported");
+  const int K = R.nz - 1;
+  const long modes = (long)R.plan.hx * R.ny;
+  TRY(dalloc(ctx, R, &R.work, (size_t)K * modes));
+  double *tx, *ty;
+  TRY(setup_roots<double>(ctx, R, R.nx, &tx));
+  TRY(setup_roots<double>(ctx, R, R.ny, &ty));
+  R.tw_x = (double2*)tx;
+  R.tw_y = (double2*)ty;
+  std::vector<double> s2((size_t)R.nx + R.ny);
+  for (int m = 0; m < R.nx; ++m) s2[m] = std::pow(std::sin(kPi * m / R.nx), 2);
+  for (int n = 0; n < R.ny; ++n) s2[R.nx + n] = std::pow(std::sin(kPi * n / R.ny), 2);
+  double* d_s2;
+  TRY(dalloc(ctx, R, &d_s2, s2.size()));
+  HIPCHK(ctx, hipMemcpy(d_s2, s2.data(), s2.size() * 8, hipMemcpyHostToDevice));
+  TRY(dalloc(ctx, R, &R.inv, (size_t)K * modes));
+  launch_factors(d_s2, d_s2 + R.nx, R.plan.hx, R.ny, K, R.inv, ctx->stream);
+  R.sweeps32 = R.prec == PIC_FP32R && !(R.cfg.max_refine >= 2 && R.cfg.refine_tol > 0);
+  if (R.sweeps32) {
+    TRY(dalloc(ctx, R, &R.work32, R.n_int));
+    TRY(dalloc(ctx, R, &R.r, R.n_int));
+    TRY(setup_roots<float>(ctx, R, R.nx, &R.tw_x32));
+    TRY(setup_roots<float>(ctx, R, R.ny, &R.tw_y32));
+    TRY(dalloc(ctx, R, &R.inv_full, R.n_int));
+    launch_factors(d_s2, d_s2 + R.nx, R.nx, R.ny, K, R.inv_full, ctx->stream);
+  }
+  CHECK_LAUNCH(ctx);
   return PIC_OK;
 }
 
@@ -722,6 +754,11 @@ int deposit_current(pic_ctx* ctx, Replica& R) {
   return PIC_OK;
 }
 
+RefineState refine_state(const Replica& R) {
+  return RefineState{R.norms + 2, (int)field_out_sums(R.nn), R.norms, R.refine_ctl,
+                     R.cfg.refine_tol * R.cfg.refine_tol};
+}
+
 // phi_k and E_k from rho_k, the grains' charges and V(t_k); also freezes Q_g.
 // zero_next: the same launch clears the other charge accumulator for the
 // step's deposit of rho_{k+1}
@@ -738,26 +775,63 @@ int solve_fields(pic_ctx* ctx, Replica& R, bool zero_next = false,
   const double vol = c.dx * c.dx * c.dx;
   unsigned long long* next =
       zero_next ? (unsigned long long*)R.rho[1 - R.rho_cur] : nullptr;  // 8-byte words, 0 = 0.0
-  if (R.prec == PIC_FP64) {
-    const double scale = -c.dx * c.dx / kEps0 * (R.we / vol);
-    launch_rhs_f64((const double*)R.rho[R.rho_cur], scale, R.b, R.nx, R.ny, R.nz, st);
-    launch_grain_rhs(R.d_gc, R.md.gpos, c.n_grains, R.nx, R.ny, R.nz, R.we, R.d_Q, R.b, scale, 0,
-                     R.Qp, st);
-    launch_solve_f64(R.fft, R.nx, R.ny, R.nz, R.b, R.work, R.tw_x, R.tw_y, R.inv, R.phi, rf, st);
-    launch_field_out(nullptr, R.phi, R.E, 1, next, R.md, R.nx, R.ny, R.nz, c.dx, rf, st);
+  if (!R.sweeps32) {
+    // One FP64 solve on the half spectrum.  FP32R: in place of up to max_refine
+    // FP32 sweeps (two of those cost the same passes over the mesh, twice the
+    // launches, and leave a larger residual; a single one, max_refine = 1, or
+    // a tolerance of 0, which asks for every sweep, keeps them).  Solved from
+    // the right-hand side, not from a residual against the last potential:
+    // the result then depends on the charge alone, and a correction's error is
+    // that of the residual's rounding times the condition of the lowest mode
+    // (4x6x1025 cells: 3e-12 of phi, against 2e-15).  The sums of the residual
+    // it ends with are added up by the next solve, or on request (flush_final).
+    const bool f64 = R.prec == PIC_FP64;
+    SpectralArgs a{};
+    a.tw_x = R.tw_x;
+    a.tw_y = R.tw_y;
+    a.rho64 = (const double*)R.rho[R.rho_cur];
+    a.rhofx = (const long long*)R.rho[R.rho_cur];
+    a.scale = -c.dx * c.dx / kEps0 * ((f64 ? R.we : kCharge / 4294967296.0) / vol);
+    a.tab = R.d_gtab;
+    a.tab_start = R.d_gtab_start;
+    a.counts = R.d_gc;
+    a.ng = c.n_grains;
+    a.we = R.we;
+    a.Q = R.d_Q;
+    a.psi = R.psi;
+    a.b = R.b;
+    int rc = 0;
+    launch_spectral_solve(R.plan, a, f64 ? kRhsRho64 : kRhsFixed, R.work, R.inv,
+                          f64 ? RefineState{} : refine_state(R), st, first_done, &rc);
+    if (rc != 0) return fail(ctx, PIC_EDEVICE, "event record in the field solve failed");
+    if (final_pending) *final_pending = false;
+    R.final_pending = !f64;
   } else {
     const double scale = -c.dx * c.dx / kEps0 * (kCharge / 4294967296.0 / vol);
     const RhsArgs ra{(const long long*)R.rho[R.rho_cur], scale, R.d_gtab, R.n_gtab, R.d_gc,
                      c.n_grains, R.we, R.d_Q};
     const int deferred = launch_rhs_solve_refined(
-        ra, R.fft, R.nx, R.ny, R.nz, R.b, R.psi, R.r, R.work, R.tw_x, R.tw_y, R.inv, rf,
+        ra, R.fft, R.nx, R.ny, R.nz, R.b, R.psi, R.r, R.work32, R.tw_x32, R.tw_y32, R.inv_full,
         c.max_refine, c.refine_tol, R.norms, R.refine_ctl, st, final_pending != nullptr,
         first_done);
     if (deferred < 0) return fail(ctx, PIC_EDEVICE, "event record in the field solve failed");
     if (final_pending) *final_pending = deferred != 0;
-    launch_field_out(R.psi, R.phi, R.E, 0, next, R.md, R.nx, R.ny, R.nz, c.dx, rf, st);
   }
+  const bool sums = R.prec != PIC_FP64 && !R.sweeps32;
+  launch_field_out(R.psi, R.phi, R.E, R.prec == PIC_FP64, next, sums ? R.b : nullptr, R.norms + 2, R.md,
+                   R.nx, R.ny, R.nz, c.dx, rf, st);
   CHECK_LAUNCH(ctx);
+  return PIC_OK;
+}
+
+// adds up the residual the last FP32R solve ended with and records its test, if
+// no later solve has
+int flush_final(pic_ctx* ctx, Replica& R) {
+  if (!R.final_pending) return PIC_OK;
+  launch_final_test(refine_state(R), ctx->stream);
+  CHECK_LAUNCH(ctx);
+  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  R.final_pending = false;
   return PIC_OK;
 }
 
@@ -1245,6 +1319,7 @@ int build_batch(pic_ctx* ctx) {
 void advance_host(Replica& R, int sorts) {
   R.rho_cur = 1 - R.rho_cur;
   R.step += 1;
+  if (R.prec == PIC_FP32R && !R.sweeps32) R.final_pending = true;
   for (int sp = 0; sp < 2; ++sp)
     if (sorts & (1 << sp)) R.cur[sp] = 1 - R.cur[sp];
 }
@@ -1414,28 +1489,20 @@ int unit_fields(pic_ctx* ctx, Replica& R) {
   const int ng = c.n_grains;
   if (ng == 0) return PIC_OK;
   hipStream_t st = ctx->stream;
-  // FP64 solver resources for the unit-charge solves (the FP32R form uses them only here)
-  void *tw_x = R.tw_x, *tw_y = R.tw_y, *inv = R.inv, *work = R.work;
-  double* E = (double*)R.E;
-  if (R.prec != PIC_FP64) {
-    TRY(setup_solver_tables<double>(ctx, R, &tw_x, &tw_y, &inv));
-    double2* w2;
-    TRY(dalloc(ctx, R, &w2, R.n_int));
-    work = w2;
-    TRY(dalloc(ctx, R, &E, 2 * 2 * R.nn));
-  }
-  const double scale = -c.dx * c.dx / kEps0 / (c.dx * c.dx * c.dx);
+  SpectralArgs a{};
+  a.tw_x = R.tw_x;
+  a.tw_y = R.tw_y;
+  a.scale = -c.dx * c.dx / kEps0 / (c.dx * c.dx * c.dx);
+  a.tab = R.d_gtab;
+  a.tab_start = R.d_gtab_start;
+  a.psi = R.psi;
   const long side = 2L * c.pp_cutoff_cells + 2;
   TRY(dalloc(ctx, R, &R.Uphi, (size_t)ng * side * side * side));
   for (int g = 0; g < ng; ++g) {
-    launch_zero_f64(R.b, R.n_int, st);
-    launch_unit_rhs(R.md.gpos, g, R.nx, R.ny, R.nz, scale, R.b, st);
-    launch_solve_f64(R.fft, R.nx, R.ny, R.nz, R.b, work, tw_x, tw_y, inv, R.phi,
-                     RfDrive{0.0, 0.0, 0.0, 0.0, R.d_step}, st);
-    launch_extract_cube_phi(R.phi, R.md.gcell, g, c.pp_cutoff_cells, R.nx, R.ny, R.Uphi, st);
-    launch_efield_f64(R.phi, E, R.nx, R.ny, R.nz, c.dx, st);
-    launch_extract_cube(E, R.md.gcell, g, c.pp_cutoff_cells, R.nx, R.ny,
-                        const_cast<double*>(R.md.U), st);
+    a.unit = g;
+    launch_spectral_solve(R.plan, a, kRhsUnit, R.work, R.inv, RefineState{}, st);
+    launch_extract_cube(R.psi, R.md.gcell, g, c.pp_cutoff_cells, R.nx, R.ny, R.nz, c.dx,
+                        const_cast<double*>(R.md.U), R.Uphi, st);
   }
   CHECK_LAUNCH(ctx);
   HIPCHK(ctx, hipStreamSynchronize(st));
@@ -1578,10 +1645,6 @@ int init_replica(pic_ctx* ctx, Replica& R, const pic_config& cin) {
     double* E;
     TRY(dalloc(ctx, R, &E, 4 * R.nn));
     R.E = E;
-    double2* w;
-    TRY(dalloc(ctx, R, &w, R.n_int));
-    R.work = w;
-    TRY(setup_solver_tables<double>(ctx, R, &R.tw_x, &R.tw_y, &R.inv));
   } else {
     long long *r0, *r1;
     TRY(dalloc(ctx, R, &r0, R.nn));
@@ -1591,18 +1654,14 @@ int init_replica(pic_ctx* ctx, Replica& R, const pic_config& cin) {
     float* E;
     TRY(dalloc(ctx, R, &E, 4 * R.nn));
     R.E = E;
-    float2* w;
-    TRY(dalloc(ctx, R, &w, R.n_int));
-    R.work = w;
-    TRY(setup_solver_tables<float>(ctx, R, &R.tw_x, &R.tw_y, &R.inv));
-    TRY(dalloc(ctx, R, &R.psi, R.n_int));
-    launch_zero_f64(R.psi, R.n_int, st);  // the first solve starts from psi = 0
-    TRY(dalloc(ctx, R, &R.r, R.n_int));
+    TRY(dalloc(ctx, R, &R.b, R.n_int));
+    launch_zero_f64(R.b, R.n_int, st);
   }
-  TRY(dalloc(ctx, R, &R.b, R.n_int));
+  TRY(setup_solver(ctx, R));
+  TRY(dalloc(ctx, R, &R.psi, R.n_int));
   TRY(dalloc(ctx, R, &R.phi, R.nn));
   // two sums and a partial pair per residual block (blocks of 256 nodes per plane)
-  TRY(dalloc(ctx, R, &R.norms, 2 + 2 * ((R.nxy + 255) / 256) * (R.nz - 1)));
+  TRY(dalloc(ctx, R, &R.norms, 2 + 2 * std::max(((R.nxy + 255) / 256) * (R.nz - 1), field_out_sums(R.nn))));
   TRY(dalloc(ctx, R, &R.d_gc, 2 * std::max(c.n_grains, 1)));
   const long nkey = sort_keys(R.ngrid);
   TRY(dalloc(ctx, R, &R.d_hist, nkey));
@@ -1628,6 +1687,7 @@ int init_replica(pic_ctx* ctx, Replica& R, const pic_config& cin) {
   }
   TRY(setup_md(ctx, R));
   TRY(unit_fields(ctx, R));
+  launch_zero_f64(R.psi, R.n_int, st);  // the first FP32R solve starts from psi = 0
 
   // load: ppc particles per cell, Maxwellian, Philox keyed by the seed
   const uint32_t k0 = (uint32_t)(c.seed & 0xffffffffu), k1 = (uint32_t)(c.seed >> 32);
@@ -1878,6 +1938,7 @@ int pic_init(const pic_config* cfgs, int n_replicas, void* hip_stream, pic_ctx**
   std::unique_ptr<pic_ctx> ctx(new (std::nothrow) pic_ctx());
   if (!ctx) return fail(nullptr, PIC_ENOMEM, "host allocation failed");
   ctx->stream = (hipStream_t)hip_stream;
+  if (spectral_setup() != 0) return fail(nullptr, PIC_EDEVICE, "kernel attributes could not be set");
   for (int r = 0; r < n_replicas; ++r) {
     std::unique_ptr<Replica> R(new (std::nothrow) Replica());
     if (!R) return fail(nullptr, PIC_ENOMEM, "host allocation failed");
@@ -2391,6 +2452,7 @@ int pic_save(pic_ctx* ctx, const char* path) {
       if (R.coul.count)
         HIPCHK(ctx, hipMemcpy(&n_coul, R.coul.count, 8, hipMemcpyDeviceToHost));
       int ctl[4] = {0, 0, 0, 0};
+      TRY(flush_final(ctx, R));
       HIPCHK(ctx, hipMemcpy(ctl, R.refine_ctl, sizeof(ctl), hipMemcpyDeviceToHost));
       ok = ok && put(out.f, &n_coul, 1) && put(out.f, &ctl[2], 1);
       // ionisation: the next ids, the pairs made, the ones dropped
@@ -2518,6 +2580,7 @@ int pic_load(pic_ctx* ctx, const char* path) {
     }
     if (R.coul.count) HIPCHK(ctx, hipMemcpy(R.coul.count, &S.n_coul, 8, hipMemcpyHostToDevice));
     const int ctl[4] = {0, 0, S.unconverged, 0};
+    R.final_pending = false;
     HIPCHK(ctx, hipMemcpy(R.refine_ctl, ctl, sizeof(ctl), hipMemcpyHostToDevice));
     if (!S.psi.empty())
       HIPCHK(ctx, hipMemcpy(R.psi, S.psi.data(), S.psi.size() * 8, hipMemcpyHostToDevice));
@@ -2536,6 +2599,7 @@ int pic_get_counters(pic_ctx* ctx, int replica, pic_counters* out) {
   Replica* R = get_rep(ctx, replica);
   if (!R || !out) return fail(ctx, PIC_EINVAL, "bad replica or out");
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  TRY(flush_final(ctx, *R));
   double norms[2] = {0, 0};
   int ctl[4] = {0, 0, 0, 0};
   HIPCHK(ctx, hipMemcpy(norms, R->norms, sizeof(norms), hipMemcpyDeviceToHost));
