@@ -437,10 +437,11 @@ int pic_derived(pic_ctx* ctx, int replica, double out[7]);
  *                      beyond it take the global-memory path); initially 2
  *   ion_tile_margin    the same for the ions; initially 1
  *   batch_push         1: the pushes of every replica and species run as one
- *                      persistent launch (all replicas FP32R only); initially
- *                      1 for an FP32R ensemble, else 0
- *   batch_blocks       the persistent grid, a multiple of 8 (the XCD count);
- *                      initially 4 per compute unit
+ *                      launch (all replicas FP32R only); initially 1 for an FP32R
+ *                      ensemble, else 0
+ *   batch_blocks       a multiple of 8 (the XCD count), initially 4 per compute
+ *                      unit; without effect (it was the grid of a persistent
+ *                      push, which a block per work item is faster than)
  *   use_graphs         1: a step is the replay of a captured HIP graph; 0:
  *                      direct launches; initially 1
  */
@@ -485,7 +486,7 @@ int pic_autotune(pic_ctx* ctx, int trial_steps, pic_tuning* tried, double* ms_pe
  * context's stream; pic_profile_read synchronises and returns the summed
  * elapsed time (ms) and the number of launches measured since enabling.
  *   PIC_PROF_PUSH   the streaming gather / push / electrode / candidate / deposit
- *                   kernel (one launch per species and step)
+ *                   kernel (one launch of both species per step)
  *   PIC_PROF_FIELD  the whole field stage of a step (RHS, Poisson, E)
  *   PIC_PROF_SORT   the periodic cell sort of both species
  *   PIC_PROF_LISTS  the listed particles of one species: sub-cycled near-grain

@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 #include "pic_types.hpp"
 
 namespace pic {
@@ -29,63 +31,50 @@ int tile_grid(int nx, int ny, int nz, int extra);
 // blocks of the MD kernel; each owns a tally row after the ngrid tile rows
 constexpr int kMdTallyRows = 4096;
 long sort_keys(int ngrid);                  // ints of sort workspace (tile counts and cursors)
-// the streaming kernel of one species (gather, push, walls, candidate test, deposit)
-void launch_push_f64(const PartF64& P, const double* E, double* rho, const MdTables& md,
-                     const SpeciesStep& S, const WorkLists& L, hipStream_t st);
-void launch_push_f32r(const PartF32R& P, const float* E, long long* rho, const MdTables& md,
-                      const SpeciesStep& S, const WorkLists& L, hipStream_t st);
-// the push of every (replica, species) of an FP32R ensemble in one persistent launch;
-// start[d] is the first work item (tile) of descriptor d, start[ndesc] the total;
-// queue: 8 ints of device scratch, cleared by the launcher (items dealt per XCD)
-void launch_push_batch_f32r(const PushDescF32* descs, const int32_t* start, int ndesc, int grid,
-                            int* queue, hipStream_t st);
-// the collisions of one species' push candidates (right after its push)
-void launch_collide_f64(const PartF64& P, const SpeciesStep& S, const WorkLists& L,
-                        hipStream_t st);
-void launch_collide_f32r(const PartF32R& P, const SpeciesStep& S, const WorkLists& L,
-                         hipStream_t st);
-// the listed particles of both species of an FP64 replica, after both
-// pushes: outliers and sub-cycled MD motion (each with its collision and
-// deposit); each kernel covers both species in one launch
-void launch_lists_f64(const PartF64 P[2], const double* E, double* rho, const MdTables& md,
-                      const SpeciesStep S[2], unsigned long long* gc, const WorkLists L[2],
-                      int do_mcc, hipStream_t st);
-// FP32R MD particles: their list (before the push, md_scan_kernel), their
-// sub-cycled motion from P into the other record buffers D (beside the push),
-// then, with the outliers, their states copied back into P and their
-// collisions (after the push): of both species (sp_only -1) or of one
-void launch_md_scan_f32r(const PartF32R P[2], const WorkLists L[2], const MdTables& md,
-                         const SpeciesStep S[2], int nx, int ny, int nz, hipStream_t st);
-void launch_md_move_f32r(const PartF32R P[2], const PartF32R D[2], const float* E,
-                         long long* rho, const MdTables& md, const SpeciesStep S[2],
-                         unsigned long long* gc, const WorkLists L[2], hipStream_t st);
-void launch_lists_f32r(const PartF32R P[2], const PartF32R D[2], const float* E, long long* rho,
-                       const MdTables& md, const SpeciesStep S[2], const WorkLists L[2],
-                       int do_mcc, int sp_only, hipStream_t st);
-// all of that for species sp in one launch, its collision candidates included
-// (in place of launch_collide_f32r and launch_lists_f32r for that species)
-void launch_species_lists_f32r(const PartF32R P[2], const PartF32R D[2], const float* E,
-                               long long* rho, const MdTables& md, const SpeciesStep S[2],
-                               const WorkLists L[2], int do_mcc, int sp, hipStream_t st);
+// the streaming kernel (gather, push, walls, candidate test, deposit) of both
+// species (descs[0], descs[1] in device memory, L either one's lists); without
+// `move` the deposit alone, of the current positions (arrays freshly sorted)
+void launch_push(const PushDescF64* descs, const WorkLists& L, bool move, hipStream_t st);
+void launch_push(const PushDescF32* descs, const WorkLists& L, bool move, hipStream_t st);
+// the push of every (replica, species) of an FP32R ensemble in one launch;
+// start[d] is the first work item (push block) of descriptor d, start[ndesc] =
+// items the total
+void launch_push_batch_f32r(const PushDescF32* descs, const int32_t* start, int ndesc, int items,
+                            hipStream_t st);
+// the MD particles' sub-cycled motion from P into the other record buffers D
+// (beside the push), both species
+void launch_md_move(const PartF64 P[2], const PartF64 D[2], const void* E, void* rho,
+                    const MdTables& md, const SpeciesStep S[2], unsigned long long* gc,
+                    const WorkLists L[2], hipStream_t st);
+void launch_md_move(const PartF32R P[2], const PartF32R D[2], const void* E, void* rho,
+                    const MdTables& md, const SpeciesStep S[2], unsigned long long* gc,
+                    const WorkLists L[2], hipStream_t st);
+// the push blocks (first tiles) whose window of `margin` cells meets the MD
+// cubes' bounding box
+std::vector<int32_t> near_blocks(const WorkLists& L, const MdTables& md, int nx, int ny, int nz,
+                                 int margin, bool f64);
+// everything after the push (descs as in launch_push): the collision candidates
+// it had no room for, the outliers, the MD particles' states back from D with
+// their collisions, and the next step's MD lists
+void launch_lists(const PushDescF64* descs, const PartF64 D[2], bool grains, const WorkLists L[2],
+                  int do_mcc, hipStream_t st);
+void launch_lists(const PushDescF32* descs, const PartF32R D[2], bool grains, const WorkLists L[2],
+                  int do_mcc, hipStream_t st);
 // The fields of a step in one launch: phi (the solve's psi lifted with the
 // electrode voltages), E = -grad phi into E (FP64 double2 pairs or FP32
 // float4), the MD cells' corrected node fields, zero_next (nn 8-byte words,
-// may be null) cleared for the next deposit and, with b, the sums of the
+// may be null) cleared for the next deposit, with it the counts of the lists
+// L[].md_next, and, with b, the sums of the
 // squared residual b - A psi and of b^2 per block of field_out_sums(nn) blocks.
 inline long field_out_sums(long nn) { return (nn + 255) / 256; }
 void launch_field_out(const double* psi, double* phi, void* E, int e_f64,
                       unsigned long long* zero_next, const double* b, double* partials,
-                      const MdTables& md, int nx, int ny, int nz, double dx, RfDrive rf,
-                      hipStream_t st);
+                      const MdTables& md, const WorkLists L[2], int nx, int ny, int nz, double dx,
+                      RfDrive rf, hipStream_t st);
 void launch_init_f64(const PartF64& P, int n, int ppc, int nx, int ny, int sp, uint32_t k0,
                      uint32_t k1, double vth, hipStream_t st);
 void launch_init_f32r(const PartF32R& P, int n, int ppc, int nx, int ny, int sp, uint32_t k0,
                       uint32_t k1, double vth, hipStream_t st);
-// deposit of the current positions through the tile windows (arrays freshly sorted)
-void launch_deposit_f64(const PartF64& P, double* rho, const MdTables& md, const SpeciesStep& S,
-                        const WorkLists& L, hipStream_t st);
-void launch_deposit_f32r(const PartF32R& P, long long* rho, const MdTables& md,
-                         const SpeciesStep& S, const WorkLists& L, hipStream_t st);
 // density and flux moments of one species: mom [4][nn] gets W, v W summed per
 // node (added to what it holds, in the rf-phase bin of the step if avg.step
 // is set); exactly one of P64, P32 is non-null
@@ -141,18 +130,21 @@ void launch_avg_phi(const double* phi, double* acc, long nn, const AvgBins& avg,
 void launch_avg_out(const double* acc, int b0, int b1, long stride, long total, long n_plain,
                     const unsigned long long* cnt, double wv, double* out, hipStream_t st);
 // counting sort of the slots in use into dst (dropping empty slots, padding
-// every tile to a multiple of 4); capacity bounds the slots in use
-void launch_sort_f64(const PartF64& src, const PartF64& dst, const WorkLists& L, int* hist,
-                     int* sums, long capacity, hipStream_t st);
-void launch_sort_f32r(const PartF32R& src, const PartF32R& dst, const WorkLists& L, int* hist,
-                      int* sums, long capacity, hipStream_t st);
+// every tile to a multiple of 4), and the particles in MD cubes listed anew in
+// md_list, *n_md of them; capacity bounds the slots in use
+void launch_sort(const PartF64& src, const PartF64& dst, const WorkLists& L, const MdTables& md,
+                 int nx, int ny, int32_t* md_list, int* n_md, int* hist, int* sums, long capacity,
+                 hipStream_t st);
+void launch_sort(const PartF32R& src, const PartF32R& dst, const WorkLists& L, const MdTables& md,
+                 int nx, int ny, int32_t* md_list, int* n_md, int* hist, int* sums, long capacity,
+                 hipStream_t st);
 void launch_fill_int(int* a, long n, int v, hipStream_t st);
 // the step's ionisations made into particles (one block; see ionize_kernel):
 // exactly one of the FP64 and FP32R pointer pairs is non-null
 void launch_ionize(const PartF64* Pe64, const PartF64* Pi64, const PartF32R* Pe32,
                    const PartF32R* Pi32, const WorkLists& Le, const WorkLists& Li,
-                   const SpeciesStep& Se, uint32_t* next_id, long room_e, long room_i,
-                   unsigned long long* dropped, hipStream_t st);
+                   const SpeciesStep& Se, const MdTables& md, uint32_t* next_id, long room_e,
+                   long room_i, unsigned long long* dropped, hipStream_t st);
 // FP64 energy diagnostic: per-block sums (energy_blocks() of them) of |v|^2
 // over a species' live particles, and of |E|^2 times each node's share of a
 // cell volume over the mesh (E as stored: double pairs if e_f64, else float4)
@@ -160,9 +152,8 @@ int energy_blocks();
 void launch_energy(const PartF64* P64, const PartF32R* P32, const WorkLists& L, double* out,
                    hipStream_t st);
 void launch_field_energy(const void* E, int e_f64, long nxy, int nz, double* out, hipStream_t st);
-// the step counter advances and the dense MD lists of both species start
-// empty for the next step
-void launch_advance_step(uint32_t* step, int32_t* cnt0, int32_t* cnt1, hipStream_t st);
+// the step counter advances
+void launch_advance_step(uint32_t* step, hipStream_t st);
 
 // mesh
 // one grain's share of the right-hand side: interior node `node` (the index
@@ -229,8 +220,7 @@ struct RefineState {
   double tol2;
 };
 void launch_spectral_solve(const SpectralPlan& p, const SpectralArgs& a, int in, double2* work,
-                           const double* inv, const RefineState& rs, hipStream_t st,
-                           hipEvent_t first_done = nullptr, int* rc = nullptr);
+                           const double* inv, const RefineState& rs, hipStream_t st);
 void launch_final_test(const RefineState& rs, hipStream_t st);
 // tridiagonal factors of `cols` columns from sin^2 tables (pi m / nx, pi n / ny)
 void launch_factors(const double* sx2, const double* sy2, int cols, int ny, int K, double* inv,
@@ -262,14 +252,12 @@ struct RhsArgs {
 // kernels where the plane transforms fit in LDS (same phi, psi and Q; the
 // norms' partial sums are grouped differently).  With defer_final the
 // residual after the last sweep and its test are left to the caller where that
-// path applies (returns 1; launch_refine_final), else returns 0.  first_done
-// (may be null) is recorded on st after the right-hand side's kernel; -1 if
-// that record fails.
-int launch_rhs_solve_refined(const RhsArgs& a, const FftPlanHost& P, int nx, int ny, int nz,
+// path applies (returns true; launch_refine_final).
+bool launch_rhs_solve_refined(const RhsArgs& a, const FftPlanHost& P, int nx, int ny, int nz,
                              double* b, double* psi, double* r, void* work32,
                              const void* tw_x32, const void* tw_y32, const void* inv,
                              int sweeps, double tol, double* norms, int* ctl, hipStream_t st,
-                             bool defer_final, hipEvent_t first_done);
+                             bool defer_final);
 // the residual after the last of `sweeps` refinement sweeps and its stopping
 // test (norms, ctl as launch_solve_refined); psi and b unchanged since the solve
 void launch_refine_final(int nx, int ny, int nz, const double* b, const double* psi, double* r,

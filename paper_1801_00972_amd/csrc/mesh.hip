@@ -1107,25 +1107,22 @@ void launch_refine_final(int nx, int ny, int nz, const double* b, const double* 
 // formed inside the sweep's forward plane transform (the first one also forms
 // b), so the sweep runs transform, tridiagonal, inverse transform; the
 // residual after the last sweep has its own kernel (launch_refine_final; with
-// defer_final the caller launches it, and 1 is returned).  The stopping test
+// defer_final the caller launches it, and true is returned).  The stopping test
 // is the same, with the per-plane partial sums of those fused kernels.
-// first_done, when given, is recorded on st after the first kernel (the one
-// that reads rho and the grains' counts); -1 if that record fails.
-int launch_rhs_solve_refined(const RhsArgs& a, const FftPlanHost& P, int nx, int ny, int nz,
+bool launch_rhs_solve_refined(const RhsArgs& a, const FftPlanHost& P, int nx, int ny, int nz,
                              double* b, double* psi, double* r, void* work32,
                              const void* tw_x32, const void* tw_y32, const void* inv,
                              int sweeps, double tol, double* norms, int* ctl, hipStream_t st,
-                             bool defer_final, hipEvent_t first_done) {
+                             bool defer_final) {
   using C = cplx<float>;
   const long plane = (long)nx * ny;
   const int K = nz - 1;
   if (2 * sizeof(C) * (size_t)plane > kPlaneLds) {
     launch_rhs_residual(a.rho, a.scale, a.tab, a.ntab, a.counts, a.ng, a.we, a.Q, b, psi, r, nx,
                         ny, nz, norms + 2, st);
-    if (first_done && hipEventRecord(first_done, st) != hipSuccess) return -1;
     launch_solve_refined(P, nx, ny, nz, b, psi, r, work32, tw_x32, tw_y32, inv, sweeps, tol,
                          norms, ctl, st, true);
-    return 0;
+    return false;
   }
   Fft2Geom g{};
   g.nx = nx;
@@ -1142,7 +1139,6 @@ int launch_rhs_solve_refined(const RhsArgs& a, const FftPlanHost& P, int nx, int
   C* w = (C*)work32;
   hipLaunchKernelGGL((residual_fft_kernel<float, true>), dim3(K), dim3(kPlaneThreads), lds, st, g,
                      tx, ty, w, psi, b, a, norms + 2, nullptr);
-  if (first_done && hipEventRecord(first_done, st) != hipSuccess) return -1;
   hipLaunchKernelGGL(norm_reduce_kernel, dim3(1), dim3(1024), 0, st, norms + 2, K, norms, ctl,
                      tol * tol, 0, 0);
   for (int it = 1; it <= sweeps; ++it) {
@@ -1158,7 +1154,7 @@ int launch_rhs_solve_refined(const RhsArgs& a, const FftPlanHost& P, int nx, int
       launch_refine_final(nx, ny, nz, b, psi, r, sweeps, tol, norms, ctl, st);
     }
   }
-  return defer_final ? 1 : 0;
+  return defer_final;
 }
 
 // the residual after the last sweep and its stopping test (the reported

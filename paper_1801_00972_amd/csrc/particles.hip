@@ -9,6 +9,7 @@
 // collisions with the neutral reservoir (Table I) in null-collision form.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 
@@ -17,11 +18,16 @@
 
 namespace pic {
 
+// constant memory: descriptors that no kernel writes, read by scalar loads
+#define PIC_CONST __attribute__((address_space(4)))
+
+// (the push packs them in nibbles: ST_ALIVE is 0)
 enum { ST_ALIVE = 0, ST_WALL0 = 1, ST_WALL1 = 2, ST_GRAIN = 3, ST_NONE = 4, ST_BAD = 5, ST_MD = 6, ST_OUT = 7 };
 
 // electrode test of a position already wrapped in x,y; a non-finite or
 // out-of-range coordinate (which no valid input produces) removes the particle
-__device__ __forceinline__ int z_status(const double x[3], const SpeciesStep& S) {
+template <typename H>
+__device__ __forceinline__ int z_status(const double x[3], const H& S) {
   if (x[2] >= 0.0 && x[2] < (double)S.nz) {
     return (x[0] >= 0.0 && x[0] < (double)S.nx && x[1] >= 0.0 && x[1] < (double)S.ny) ? ST_ALIVE
                                                                                      : ST_BAD;
@@ -75,8 +81,8 @@ __device__ __forceinline__ void load_node(const float4* __restrict__ E, long n, 
 }
 
 // CIC gather in double precision at cell (i0,j0,k0), offsets (fx,fy,fz)
-template <typename ET>
-__device__ __forceinline__ void gather_d(const ET* __restrict__ E, const SpeciesStep& S, int i0,
+template <typename ET, typename H>
+__device__ __forceinline__ void gather_d(const ET* __restrict__ E, const H& S, int i0,
                                          int j0, int k0, double fx, double fy, double fz,
                                          double out[3]) {
   const int i1 = i0 + 1 == S.nx ? 0 : i0 + 1;
@@ -104,7 +110,8 @@ __device__ __forceinline__ void gather_d(const ET* __restrict__ E, const Species
 
 // ---------------------------------------------------------------- MD region
 // index of cell (i, j, k) in the bounding box of the MD cubes, or -1
-__device__ __forceinline__ long md_box_index(const MdTables& md, int nx, int ny, int i, int j,
+template <typename M>
+__device__ __forceinline__ long md_box_index(const M& md, int nx, int ny, int i, int j,
                                              int k) {
   if (md.n_grains == 0) return -1;
   int a = i - md.bx0;
@@ -118,7 +125,8 @@ __device__ __forceinline__ long md_box_index(const MdTables& md, int nx, int ny,
   return ((long)c * md.bsy + b) * md.bsx + a;
 }
 
-__device__ __forceinline__ uint32_t md_lookup(const MdTables& md, int nx, int ny, int i, int j,
+template <typename M>
+__device__ __forceinline__ uint32_t md_lookup(const M& md, int nx, int ny, int i, int j,
                                               int k) {
   const long bi = md_box_index(md, nx, ny, i, j, k);
   if (bi < 0) return 0u;
@@ -302,7 +310,7 @@ __device__ __forceinline__ void md_corner(const MdTables& md, int nx, int ny, ui
 // overlap the node blocks' streaming).  Blocks from nbm on: one thread per
 // node writes phi (psi, the solve's interior potential, and the electrodes'
 // lift) and E = -grad phi in the storage type, and clears the next step's
-// charge accumulator.  With b (FP32R) the block's sums of (b - A psi)^2 and b^2
+// charge accumulator (and the counts of its MD lists).  With b (FP32R) the block's sums of (b - A psi)^2 and b^2
 // over its interior nodes go to partials: the six neighbours are at hand, so
 // the residual costs one more read per node and no pass of its own.
 template <typename ET>
@@ -312,8 +320,9 @@ __global__ __launch_bounds__(256) void field_out_kernel(const double* __restrict
                                                         unsigned long long* __restrict__ zero_next,
                                                         const double* __restrict__ b,
                                                         double* __restrict__ partials,
-                                                        MdTables md, int nx, int ny, int nz,
-                                                        double dx, RfDrive rf, int nbm) {
+                                                        MdTables md, int* n_md0, int* n_md1,
+                                                        int nx, int ny, int nz, double dx,
+                                                        RfDrive rf, int nbm) {
   const double V = rf_voltage(rf);
   if ((int)blockIdx.x >= nbm) {
     __shared__ double s_r[4], s_b[4];
@@ -324,6 +333,10 @@ __global__ __launch_bounds__(256) void field_out_kernel(const double* __restrict
       const int k = n / plane, pn = n - k * plane;
       const int y = pn / nx, x = pn - y * nx;
       if (zero_next) zero_next[n] = 0ull;
+      if (zero_next && n == 0) {
+        *n_md0 = 0;
+        *n_md1 = 0;
+      }
       const int row = y * nx;
       const int xp = row + (x + 1 == nx ? 0 : x + 1), xm = row + (x == 0 ? nx - 1 : x - 1);
       const int yp = (y + 1 == ny ? 0 : y + 1) * nx + x, ym = (y == 0 ? ny - 1 : y - 1) * nx + x;
@@ -437,7 +450,8 @@ __device__ __forceinline__ void normal_pair_t(uint32_t wa, uint32_t wb, T& n0, T
 
 // sigma of table column `col` at energy E (eV): linear between the grid
 // points, the end values past them
-__device__ inline double xs_at(const SpeciesStep& S, int col, double E) {
+template <typename H>
+__device__ inline double xs_at(const H& S, int col, double E) {
   const double* x = S.xs;
   const double* t = S.xs + (long)col * S.xs_n;
   const int n = S.xs_n;
@@ -464,8 +478,8 @@ __device__ inline double xs_at(const SpeciesStep& S, int col, double E) {
 // ions: charge exchange, then isotropic elastic scattering in the CM frame of
 // ion and neutral (equal masses).  Above the bound the collision happens
 // (counted) and u1 splits the cross section.
-template <typename T>
-__device__ void collide_xs(const SpeciesStep& S, const uint4& r, const T vn[3], T v[3], bool& coll,
+template <typename T, typename H>
+__device__ void collide_xs(const H& S, const uint4& r, const T vn[3], T v[3], bool& coll,
                            bool& capv, uint32_t id, long slot) {
   const double gx = (double)v[0] - (double)vn[0], gy = (double)v[1] - (double)vn[1],
                gz = (double)v[2] - (double)vn[2];
@@ -526,8 +540,8 @@ __device__ void collide_xs(const SpeciesStep& S, const uint4& r, const T vn[3], 
   }
 }
 
-template <typename T>
-__device__ __forceinline__ void collide(const SpeciesStep& S, uint32_t id, T v[3], bool& coll,
+template <typename T, typename H>
+__device__ __forceinline__ void collide(const H& S, uint32_t id, T v[3], bool& coll,
                                         bool& capv, long slot) {
   if constexpr (sizeof(T) == 4) {
     // FP32R records: the collision in FP64 (2 % of the particles per step),
@@ -610,31 +624,31 @@ __device__ __forceinline__ void deposit_f64(double* __restrict__ rho, const Spec
 // parts, along x by q1 = (Q f24) >> 24 with f24 = floor(offset 2^24), then each
 // half along y, each quarter along z; integer atomics, so the sum is exact and
 // independent of order.
-// a * b for 0 <= a < 2^63, 0 <= b < 2^32 with a * b < 2^63: two 32x32 -> 64-bit
-// multiply-adds instead of a general 64-bit product
-__device__ __forceinline__ long long mul_q(long long a, uint32_t b) {
-  const unsigned long long ua = (unsigned long long)a;
-  const unsigned long long lo = (unsigned long long)(uint32_t)ua * b;
-  const unsigned long long hi = (unsigned long long)(uint32_t)(ua >> 32) * b;
-  return (long long)(lo + (hi << 32));
+// (a b) >> 24 for 0 <= a < 2^39, 0 <= b < 2^24, exactly: a split at bit 24, so
+// both products have 24-bit factors, which multiply at the full rate (a 32x32
+// product takes four times as long)
+__device__ __forceinline__ long long mul_shift24(long long a, uint32_t b) {
+  const uint32_t lo = (uint32_t)a & 0xffffffu, hi = (uint32_t)(a >> 24) & 0xffffffu;
+  const unsigned long long p = (unsigned long long)lo * b, q = (unsigned long long)hi * b;
+  return (long long)(q + (uint32_t)(p >> 24));
 }
 
 __device__ __forceinline__ void split8(long long Q, float ox, float oy, float oz,
                                        long long part[8]) {
   // offsets in [0, 1): f24 in [0, 2^24), the parts stay in [0, Q]
-  const uint32_t qx = (uint32_t)(ox * 16777216.0f);
-  const uint32_t qy = (uint32_t)(oy * 16777216.0f);
-  const uint32_t qz = (uint32_t)(oz * 16777216.0f);
+  const uint32_t qx = (uint32_t)(ox * 16777216.0f) & 0xffffffu;
+  const uint32_t qy = (uint32_t)(oy * 16777216.0f) & 0xffffffu;
+  const uint32_t qz = (uint32_t)(oz * 16777216.0f) & 0xffffffu;
   long long ax[2];
-  ax[1] = mul_q(Q, qx) >> 24;
+  ax[1] = mul_shift24(Q, qx);
   ax[0] = Q - ax[1];
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
-    const long long y1 = mul_q(ax[a], qy) >> 24;
+    const long long y1 = mul_shift24(ax[a], qy);
     const long long yy[2] = {ax[a] - y1, y1};
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      const long long z1 = mul_q(yy[b], qz) >> 24;
+      const long long z1 = mul_shift24(yy[b], qz);
       part[a + 2 * b] = yy[b] - z1;
       part[a + 2 * b + 4] = z1;
     }
@@ -666,7 +680,8 @@ __device__ __forceinline__ void wave_add_count(int v, unsigned long long* dst) {
 // ---------------------------------------------------------------- one particle
 // FP32R: gather from the 8 node fields ec, kick Eq. (2), drift Eq. (1) in cell +
 // offset form, periodic wrap; returns the electrode status
-__device__ __forceinline__ int push_one_f32(const SpeciesStep& S, const float ec[8][3], float o[3],
+template <typename H>
+__device__ __forceinline__ int push_one_f32(const H& S, const float ec[8][3], float o[3],
                                             float v[3], int& ci, int& cj, int& ck) {
   const float wx[2] = {1.0f - o[0], o[0]};
   const float wy[2] = {1.0f - o[1], o[1]};
@@ -679,7 +694,6 @@ __device__ __forceinline__ int push_one_f32(const SpeciesStep& S, const float ec
     v[a] += S.qm_dt_f * e;
   }
   int d[3];
-  bool ok = true;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     float f = o[a] + v[a] * S.dt_dx_f;
@@ -690,8 +704,7 @@ __device__ __forceinline__ int push_one_f32(const SpeciesStep& S, const float ec
       f = 0.0f;
       d[a] += 1;
     }
-    ok = ok && (f >= 0.0f && f < 1.0f);
-    o[a] = f;
+    o[a] = f;  // in [0, 1), or NaN
   }
   ci += d[0];
   cj += d[1];
@@ -702,13 +715,16 @@ __device__ __forceinline__ int push_one_f32(const SpeciesStep& S, const float ec
   else if (ci >= S.nx) ci -= S.nx;
   if (cj < 0) cj += S.ny;
   else if (cj >= S.ny) cj -= S.ny;
-  if (ci < 0 || ci >= S.nx) ci = ((ci % S.nx) + S.nx) % S.nx;
-  if (cj < 0 || cj >= S.ny) cj = ((cj % S.ny) + S.ny) % S.ny;
-  return !ok ? ST_BAD : (ck < 0 ? ST_WALL0 : (ck >= S.nz ? ST_WALL1 : ST_ALIVE));
+  if ((unsigned)ci >= (unsigned)S.nx || (unsigned)cj >= (unsigned)S.ny) {
+    ci = ((ci % S.nx) + S.nx) % S.nx;
+    cj = ((cj % S.ny) + S.ny) % S.ny;
+  }
+  return !(o[0] + o[1] + o[2] >= 0.0f) ? ST_BAD : (ck < 0 ? ST_WALL0 : (ck >= S.nz ? ST_WALL1 : ST_ALIVE));
 }
 
 // FP64: kick with the gathered field, drift, wrap; returns the electrode status
-__device__ __forceinline__ int push_one_f64(const SpeciesStep& S, const double Ep[3], double x[3],
+template <typename H>
+__device__ __forceinline__ int push_one_f64(const H& S, const double Ep[3], double x[3],
                                             double v[3]) {
   v[0] += S.qm_dt * Ep[0];
   v[1] += S.qm_dt * Ep[1];
@@ -717,6 +733,39 @@ __device__ __forceinline__ int push_one_f64(const SpeciesStep& S, const double E
   x[1] = wrap_coord(x[1] + v[1] * S.dt_dx, S.ny);
   x[2] += v[2] * S.dt_dx;
   return z_status(x, S);
+}
+
+// ---------------------------------------------------------------- MD lists
+// The dense MD list of the next step is formed at the end of this one.  The
+// particles of a push block whose window meets the MD cubes' bounding box are
+// looked through by the lists kernel (near_block, in slot order: the MD kernel
+// is 1.5 times slower on a list in the order of arrival).  Elsewhere only a
+// particle that has left its window can be in a cube: the kernel that moves it
+// there (push, outliers, copy back, ionisation) appends it.  The re-binning,
+// which moves the slots, lists its species anew.  A pass over the cells before
+// each push instead was on the way to it and, as it had to look through every
+// block that held a stray, read most slots (0.04 ms at 64x64x256, 32 ppc; 0.43
+// ms at 128x128x512, 16 ppc).
+template <typename M>
+__device__ __forceinline__ bool in_md(const M& md, int nx, int ny, int c) {
+  return md_lookup(md, nx, ny, cell_i(c), cell_j(c), cell_k(c)) != 0u;
+}
+__device__ __forceinline__ bool slot_alive(const PartF64& P, long p) { return P.z[p] >= 0.0; }
+__device__ __forceinline__ bool slot_alive(const PartF32R& P, long p) { return P.cell[p] >= 0; }
+__device__ __forceinline__ int slot_cell(const PartF64& P, long p) {
+  return pack_cell((int)floor(P.x[p]), (int)floor(P.y[p]), (int)floor(P.z[p]));
+}
+__device__ __forceinline__ int slot_cell(const PartF32R& P, long p) { return P.cell[p]; }
+// appends the value of each lane whose flag is set: one reservation for the wave
+__device__ __forceinline__ void wave_append(bool flag, int32_t* list, int* count, int value) {
+  const unsigned long long m = __ballot(flag);
+  if (!m) return;
+  const int lane = threadIdx.x & 63;
+  const int leader = __ffsll((long long)m) - 1;
+  int base = 0;
+  if (lane == leader) base = atomicAdd(count, __popcll(m));
+  base = __shfl(base, leader, 64);
+  if (flag) list[base + __popcll(m & ((1ull << lane) - 1ull))] = value;
 }
 
 // ---------------------------------------------------------------- tile windows
@@ -735,7 +784,8 @@ struct Tile {
 // the window of tiles t .. t + span - 1 (consecutive along x): their cells
 // plus m cells on each side, in nodes; the margin shrinks until the window
 // fits `cap` nodes
-__device__ __forceinline__ Tile make_tile(int t, const WorkLists& L, int nx, int ny, int nz,
+template <typename WL>
+__host__ __device__ __forceinline__ Tile make_tile(int t, const WL& L, int nx, int ny, int nz,
                                           int margin, int cap, int span = 1) {
   Tile w;
   w.on = false;
@@ -794,7 +844,8 @@ __device__ __forceinline__ int tile_cell(const Tile& t, int i, int j, int k, int
   if ((unsigned)lx > (unsigned)(t.tx - 2) || (unsigned)ly > (unsigned)(t.ty - 2) ||
       (unsigned)lz > (unsigned)(t.tz - 2))
     return -1;
-  return (lz * t.ty + ly) * t.tx + lx;
+  // (24-bit products: a 32-bit one takes four times as long)
+  return (int)(__umul24(__umul24((unsigned)lz, (unsigned)t.ty) + (unsigned)ly, (unsigned)t.tx)) + lx;
 }
 
 // a / b for 0 <= a < 2^24 without an integer divide (rb = 1/b)
@@ -832,9 +883,9 @@ __device__ __forceinline__ void atomic_add_acc(A* p, A v) {
 }
 
 // the 8 corner contributions of one cell into the tile (lbase >= 0) or to global
-template <typename A>
+template <typename A, typename H>
 __device__ __forceinline__ void corner_add(const Tile& T, int lbase, A* s_rho, A* __restrict__ rho,
-                                           const SpeciesStep& S, int i, int j, int k,
+                                           const H& S, int i, int j, int k,
                                            const A acc[8]) {
   if (lbase >= 0) {
 #pragma unroll
@@ -858,8 +909,8 @@ __device__ __forceinline__ void corner_add(const Tile& T, int lbase, A* s_rho, A
 }
 
 // one particle's CIC charge straight to the global mesh (particles outside their tile's window)
-__device__ __forceinline__ void deposit_global_fixed(long long* __restrict__ rho,
-                                                     const SpeciesStep& S, int i, int j, int k,
+template <typename H>
+__device__ __forceinline__ void deposit_global_fixed(long long* __restrict__ rho, const H& S, int i, int j, int k,
                                                      float ox, float oy, float oz) {
   long long part[8];
   split8(S.Qp, ox, oy, oz, part);
@@ -888,108 +939,102 @@ __device__ __forceinline__ void chunk_append(bool flag, int32_t* seg, int* s_n, 
   if (flag) seg[base + __popcll(m & ((1ull << lane) - 1ull))] = value;
 }
 
-// the same for the slots p0 .. p0 + kPPT - 1 of every lane at once: one LDS
-// reservation for the whole wave (entries lane-ordered per q); every lane of
-// the wave must take part.  (Used by the FP64 push; in the FP32R push the
-// flags' registers cost more than the atomics saved.)
-__device__ __forceinline__ void chunk_append4(const bool (&flag)[kPPT], int32_t* seg, int* s_n,
-                                              int p0) {
-  unsigned long long m[kPPT];
-  int total = 0;
-#pragma unroll
-  for (int q = 0; q < kPPT; ++q) {
-    m[q] = __ballot(flag[q]);
-    total += __popcll(m[q]);
-  }
-  if (!total) return;
-  const int lane = threadIdx.x & 63;
-  int base = 0;
-  if (lane == 0) base = atomicAdd(s_n, total);
-  base = __shfl(base, 0, 64);
-  const unsigned long long below = (1ull << lane) - 1ull;
-#pragma unroll
-  for (int q = 0; q < kPPT; ++q) {
-    if (flag[q]) seg[base + __popcll(m[q] & below)] = p0 + q;
-    base += __popcll(m[q]);
-  }
-}
-
-// the slots p0 + q of every lane whose status st[q] is `want`, appended in
-// slot order (lane by lane, q ascending within a lane) with one reservation
-// for the wave: the dense MD list then runs through the cells in order, so the
-// MD kernel's waves meet few distinct cells when they deposit; every lane of
-// the wave must take part
-__device__ __forceinline__ void append_slot_order(const int (&st)[kPPT], int want, int32_t* seg,
-                                                  int* s_n, int p0) {
-  unsigned long long m[kPPT];
-  int total = 0;
-#pragma unroll
-  for (int q = 0; q < kPPT; ++q) {
-    m[q] = __ballot(st[q] == want);
-    total += __popcll(m[q]);
-  }
-  if (!total) return;
-  const int lane = threadIdx.x & 63;
-  int base = 0;
-  if (lane == 0) base = atomicAdd(s_n, total);
-  base = __shfl(base, 0, 64);
-  const unsigned long long below = (1ull << lane) - 1ull;
-#pragma unroll
-  for (int q = 0; q < kPPT; ++q) base += __popcll(m[q] & below);
-#pragma unroll
-  for (int q = 0; q < kPPT; ++q)
-    if (st[q] == want) seg[base++] = p0 + q;
-}
-
 // block-level tallies: wave sums into LDS; thread 0 then adds them to the
 // tile's own accumulators (each tile has one writer per kernel: no atomics)
 __device__ __forceinline__ void tally_add(unsigned* s_t, int which, int v) {
   v = wave_sum(v);
   if ((threadIdx.x & 63) == 0 && v) atomicAdd(&s_t[which], (unsigned)v);
 }
-__device__ __forceinline__ void tally_store(const unsigned* s_t, unsigned long long* tally) {
+__device__ __forceinline__ void tally_store(unsigned* s_t, unsigned long long* tally) {
   if (threadIdx.x != 0) return;
+  s_t[TL_DEAD] = s_t[TL_W0] + s_t[TL_W1] + s_t[TL_BAD];
   for (int w = 0; w < TL_N; ++w)
     if (s_t[w]) tally[w] += s_t[w];
 }
 
-// The MD particles of one pass of a push block are staged in LDS and appended
-// to the dense MD list with one reservation.  Every thread calls this after a
-// barrier that follows the pass's last append.
-constexpr int kMdStage = kBlock * kPPT;
-__device__ __forceinline__ void md_flush(int32_t* s_md, int* s_nmd, int* s_mdbase,
-                                         const WorkLists& L) {
-  const int nmd = *s_nmd;
-  __syncthreads();  // every thread has read the count before it changes
-  if (nmd == 0) return;
-  if (threadIdx.x == 0) {
-    *s_mdbase = atomicAdd(&L.cnt[2], nmd);
-    *s_nmd = 0;
-  }
-  __syncthreads();
-  for (int t = threadIdx.x; t < nmd; t += kBlock) L.md[*s_mdbase + t] = s_md[t];
-  __syncthreads();  // the stage is free again
+__device__ __forceinline__ PartF32R desc_records(const PIC_CONST PushDescF32* d) {
+  return PartF32R{d->P.cell, d->P.ox, d->P.oy, d->P.oz, d->P.vx, d->P.vy, d->P.vz, d->P.id};
 }
-
+__device__ __forceinline__ PartF64 desc_records(const PIC_CONST PushDescF64* d) {
+  return PartF64{d->P.x, d->P.y, d->P.z, d->P.vx, d->P.vy, d->P.vz, d->P.id};
+}
+// whether the packed cell lies in an MD cube, for the push's inner loop: the
+// tables are read here, not kept in registers
+template <typename Desc>
+__device__ __forceinline__ bool push_in_md(const PIC_CONST Desc* d, int c) {
+  return in_md(d->md, d->S.nx, d->S.ny, c);
+}
 // one run of same-cell charge parts (magnitudes) into the window, or, outside
-// it, with the species' sign straight to the global mesh (and the block's
-// stray flag set)
+// it, with the species' sign straight to the global mesh (*s_far is set if that
+// cell lies in an MD cube)
 __device__ __forceinline__ void deposit_run(const Tile& tile, long long* s_rho,
-                                            long long* __restrict__ rho, const SpeciesStep& S,
-                                            int c, long long acc[8], int* s_stray) {
-  const int ai = cell_i(c), aj = cell_j(c), ak = cell_k(c);
-  const int lb = tile_cell(tile, ai, aj, ak, S.nx, S.ny);
-  if (lb < 0) *s_stray = 1;  // the run ends the push outside the window
-  if (lb < 0 && S.isign < 0) {
+                                            const PIC_CONST PushDescF32* d, int nx, int ny, int c,
+                                            long long acc[8], int* s_far) {
+  const int lb = tile_cell(tile, cell_i(c), cell_j(c), cell_k(c), nx, ny);
+  if (lb >= 0) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int off = (t & 1) + tile.tx * (((t >> 1) & 1) + tile.ty * (t >> 2));
+      atomicAdd((unsigned long long*)&s_rho[lb + off], (unsigned long long)acc[t]);
+    }
+    return;
+  }
+  if (push_in_md(d, c)) *s_far = 1;
+  if (d->S.isign < 0) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) acc[t] = -acc[t];
   }
-  corner_add<long long>(tile, lb, s_rho, rho, S, ai, aj, ak, acc);
+  corner_add<long long>(tile, -1, s_rho, d->rho, d->S, cell_i(c), cell_j(c), cell_k(c), acc);
+}
+// A push block away from the MD cubes moved a particle into one (rare): its
+// slots [beg, end) are looked through again, and those in a cube that did not
+// start there (as ~slot in the out list's n_out entries) listed for the next step.
+template <typename PT, typename WL, typename M>
+__device__ void list_far(const PT& P, const WL& L, const M& md, int nx, int ny, int beg,
+                         int end, int n_out) {
+  for (int p = beg + (int)threadIdx.x; p < end; p += kBlock) {
+    if (!slot_alive(P, p) || !in_md(md, nx, ny, slot_cell(P, p))) continue;
+    bool started = false;
+    for (int t = 0; t < n_out && !started; ++t) started = L.out[beg + t] == ~p;
+    if (!started) L.md_next[atomicAdd(L.n_md_next, 1)] = p;
+  }
+}
+
+// The events of a push pass that few particles have, out of the inner loop's
+// way: st packs the status of a lane's kPPT slots (from p0) in nibbles.  Counts
+// the absorbed and the bad ones, the MD particles and those outside the window,
+// lists the latter two where they are to be listed, and marks both in the mask
+// of a block near the MD cubes.  The whole wave calls it.
+template <typename WL>
+__device__ __forceinline__ void push_events(unsigned st, int p0, bool have, bool md_near,
+                                            const WL& L, int32_t* out, int* s_nout,
+                                            unsigned* s_tally) {
+  unsigned mask = 0;
+#pragma unroll
+  for (int q = 0; q < kPPT; ++q) {
+    const int e = (int)((st >> (4 * q)) & 15u);
+    if (!__any(e != ST_ALIVE && e != ST_NONE)) continue;
+    const bool md = e == ST_MD, o = e == ST_OUT;
+    const unsigned long long w0 = __ballot(e == ST_WALL0), w1 = __ballot(e == ST_WALL1),
+                             bad = __ballot(e == ST_BAD), m = __ballot(md), f = __ballot(o);
+    if ((threadIdx.x & 63) == 0) {
+      if (w0) atomicAdd(&s_tally[TL_W0], (unsigned)__popcll(w0));
+      if (w1) atomicAdd(&s_tally[TL_W1], (unsigned)__popcll(w1));
+      if (bad) atomicAdd(&s_tally[TL_BAD], (unsigned)__popcll(bad));
+      if (m) atomicAdd(&s_tally[TL_MD], (unsigned)__popcll(m));
+      if (f) atomicAdd(&s_tally[TL_FALL], (unsigned)__popcll(f));
+    }
+    const bool far_md = md && !md_near;
+    chunk_append(o || far_md, out, s_nout, far_md ? ~(p0 + q) : p0 + q);
+    mask |= (md ? 1u << q : 0u) | (o ? 16u << q : 0u);
+  }
+  if (md_near && have && mask) L.mask[p0 / kPPT] = (uint8_t)mask;
 }
 
 // whether any cell of the window lies in the bounding box of the MD cubes
 // (periodic in x, y)
-__device__ __forceinline__ bool window_meets_md(const Tile& w, const MdTables& md, int nx, int ny) {
+template <typename M>
+__host__ __device__ __forceinline__ bool window_meets_md(const Tile& w, const M& md, int nx, int ny) {
   if (md.n_grains == 0) return false;
   if (!w.on) return true;
   const int wx = w.tx - 1, wy = w.ty - 1;  // cells of the window per axis
@@ -1012,10 +1057,8 @@ __device__ __forceinline__ bool window_meets_md(const Tile& w, const MdTables& m
 // the new positions are deposited into the LDS window (per-thread sums over a
 // run of particles in one cell first), whose occupied nodes are then added to
 // rho.  Particles starting inside an MD cube are left untouched (their list
-// is formed before the push, md_scan_kernel, and the sub-cycled kernel moves
-// them meanwhile into the other record buffer); candidates are listed for the
-// collision kernel, which runs right after the push while the records it
-// wrote are still in cache.
+// is there when the step starts, and the sub-cycled kernel moves them meanwhile
+// into the other record buffer); the block collides its candidates at its end (cand_collide).
 constexpr int kWinF32 = 1331;  // window capacity (nodes): a tile with a 3-cell margin
 
 // The FP32R push streams the particle records once per step in each direction
@@ -1050,48 +1093,132 @@ __device__ __forceinline__ V nt_loadP(const T* p, long g) {
   return __builtin_nontemporal_load(reinterpret_cast<const V*>(p) + g);
 }
 
+// The collision candidates of a push block, kept in LDS with what the collision
+// needs: the block collides them after its last pass, 64 to a wave, and writes
+// the velocities back.  A kernel of its own after the push gathered id and
+// velocity of every candidate (2 % of the electrons) from memory again, half of
+// all the cache lines of those arrays: 64x64x256 75 us, 128x128x512 0.9 ms a
+// step.  Candidates beyond the stage go to the list in memory.
+template <typename V, int N>
+struct CandStage {
+  V v[3][N];
+  uint32_t id[N];
+  int slot[N];
+};
+constexpr int kCandF32 = 368;  // (39.4 KB of LDS in all: four blocks a CU)
+constexpr int kCandF64 = 320;  // (52.4 KB: three)
+
+// the candidates of a wave's slots p0 .. p0 + kPPT - 1 (bit q of cm) into the
+// stage or, past it, the list: one reservation.  The whole wave calls it.
+template <typename V, int N>
+__device__ __forceinline__ void cand_append(unsigned cm, CandStage<V, N>& cs, int32_t* list, int* s_n,
+                                            int p0, const uint32_t id[kPPT], const V v[kPPT][3]) {
+  unsigned long long m[kPPT];
+  int total = 0;
+#pragma unroll
+  for (int q = 0; q < kPPT; ++q) {
+    m[q] = __ballot((cm >> q) & 1u);
+    total += __popcll(m[q]);
+  }
+  const int lane = threadIdx.x & 63;
+  int base = 0;
+  if (lane == 0) base = atomicAdd(s_n, total);
+  base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+  for (int q = 0; q < kPPT; ++q) {
+    if ((cm >> q) & 1u) {
+      const int at = base + __popcll(m[q] & ((1ull << lane) - 1ull));
+      if (at < N) {
+        cs.v[0][at] = v[q][0];
+        cs.v[1][at] = v[q][1];
+        cs.v[2][at] = v[q][2];
+        cs.id[at] = id[q];
+        cs.slot[at] = p0 + q;
+      } else {
+        list[at - N] = p0 + q;
+      }
+    }
+    base += __popcll(m[q]);
+  }
+}
+// collides the staged candidates (after a barrier) and writes those that did
+// collide back to P
+template <typename PT, typename H, typename V, int N>
+__device__ __forceinline__ void cand_collide(const PT& P, const H& S, const CandStage<V, N>& cs,
+                                             int n, unsigned* s_tally) {
+  n = min(n, N);
+  if (((int)threadIdx.x & ~63) >= n) return;  // (wave-uniform)
+  int n_coll = 0, n_cap = 0;
+  for (int i = (int)threadIdx.x; i < n; i += kBlock) {
+    bool coll = false, capv = false;
+    V v[3] = {cs.v[0][i], cs.v[1][i], cs.v[2][i]};
+    const int p = cs.slot[i];
+    collide(S, cs.id[i], v, coll, capv, (long)p);
+    if (coll) {
+      P.vx[p] = v[0];
+      P.vy[p] = v[1];
+      P.vz[p] = v[2];
+    }
+    n_coll += coll;
+    n_cap += capv;
+  }
+  tally_add(s_tally, TL_COLL, n_coll);
+  tally_add(s_tally, TL_CAP, n_cap);
+}
+
 // LDS of one push block (FP32R)
 struct PushSmemF32 {
   float4 E[kWinF32];
   long long rho[kWinF32];
   unsigned tally[TL_N];
-  int ncoll, nout, stray;
+  int ncoll, nout, far;
+  CandStage<float, kCandF32> cand;
 };
 
 // A block takes `span` tiles that are consecutive along x (1 or 2): their
 // slots are one contiguous range and they share one window; the lists of the
 // span go to the first tile's segments, the others' counts are zero.
+struct PushHot {  // what the inner loop needs of a SpeciesStep
+  int nx, ny, nz;
+  float qm_dt_f, dt_dx_f;
+};
 template <bool kMove>
-__device__ __forceinline__ void push_tile_f32r(const PartF32R& P, const float4* __restrict__ E,
-                                               long long* __restrict__ rho, const MdTables& md,
-                                               const SpeciesStep& S, const WorkLists& L, int tidx,
-                                               int span, PushSmemF32& sm) {
-  const int beg = L.tstart[tidx], end = L.tstart[tidx + span];
+__device__ __forceinline__ void push_tile_f32r(const PIC_CONST PushDescF32* d, int tidx, int span,
+                                               PushSmemF32& sm) {
+  const int beg = d->L.tstart[tidx], end = d->L.tstart[tidx + span];
   if (kMove && threadIdx.x < span) {
-    L.coll_cnt[tidx + threadIdx.x] = 0;
-    L.out_cnt[tidx + threadIdx.x] = 0;
+    d->L.coll_cnt[tidx + threadIdx.x] = 0;
+    d->L.out_cnt[tidx + threadIdx.x] = 0;
   }
   if (beg >= end) return;
-  const Tile tile = make_tile(tidx, L, S.nx, S.ny, S.nz, S.margin, kWinF32, span);
+  const PushHot S{d->S.nx, d->S.ny, d->S.nz, d->S.qm_dt_f, d->S.dt_dx_f};
+  const Tile tile = make_tile(tidx, d->L, S.nx, S.ny, S.nz, d->S.margin, kWinF32, span);
   const int vol = tile.on ? tile.tx * tile.ty * tile.tz : 0;
   const float rtx = 1.0f / (float)max(tile.tx, 1), rtxy = 1.0f / (float)max(tile.tx * tile.ty, 1);
   for (int t = threadIdx.x; t < vol; t += kBlock) {
-    if (kMove) sm.E[t] = E[tile_node(tile, t, rtx, rtxy, S.nx, S.ny, S.nxy)];
+    if (kMove) sm.E[t] = d->E[tile_node(tile, t, rtx, rtxy, S.nx, S.ny, d->S.nxy)];
     sm.rho[t] = 0;
   }
   if (threadIdx.x < TL_N) sm.tally[threadIdx.x] = 0;
   if (threadIdx.x == 0) {
     sm.ncoll = 0;
     sm.nout = 0;
-    sm.stray = 0;
+    sm.far = 0;
   }
   // MD cubes near the window: only then does every particle need the lookup
-  const bool md_near = window_meets_md(tile, md, S.nx, S.ny);
+  const bool md_near = window_meets_md(tile, d->md, S.nx, S.ny);
+  const PartF32R P = desc_records(d);
+  int32_t* const coll = d->L.coll + beg;
+  int32_t* const out = d->L.out + beg;
+  const float vfast2 = d->S.vfast2_f;
+  const uint32_t step = kMove ? *d->S.step : 0u, key0 = d->S.key0, key1 = d->S.key1, sp = (uint32_t)d->S.sp;
+  // a candidate has word 0 < T_null (at most 2^32), that is <= T_null - 1
+  const bool cand_on = d->S.T_null != 0;
+  const uint32_t T_last = (uint32_t)(d->S.T_null - 1);
+  const long long Qp = d->S.Qp;
   __syncthreads();
-  // event counts per thread, one byte per status, added up every 32 passes
-  unsigned long long packed = 0ull;
-  int n_w0 = 0, n_w1 = 0, n_bad = 0, n_md = 0, n_out = 0, n_fast = 0;
-  for (int base = beg, pass = 0; base < end; base += kChunk, ++pass) {
+  int n_fast = 0;
+  for (int base = beg; base < end; base += kChunk) {
     // tile ranges are multiples of 4 slots: a thread's kPPT slots are all in
     // the tile or all beyond it
     const int p0 = base + kPPT * (int)threadIdx.x;
@@ -1126,67 +1253,55 @@ __device__ __forceinline__ void push_tile_f32r(const PartF32R& P, const float4* 
         id[q] = I4[q];
       }
     }
-    int st[kPPT];
-    bool cand[kPPT];
-    int cached = -1;
-    float ec[8][3];
+    // the statuses, in nibbles; live: bit q set for a particle that moved and is
+    // alive (its charge is deposited)
+    unsigned st = 0, live = 0;
 #pragma unroll
     for (int q = 0; q < kPPT; ++q) {
-      st[q] = ST_NONE;
-      cand[q] = false;
-      if (cell[q] < 0) continue;
       if (!kMove) {
-        st[q] = ST_ALIVE;
+        if (cell[q] >= 0) live |= 1u << q;
         continue;
       }
       int ci = cell_i(cell[q]), cj = cell_j(cell[q]), ck = cell_k(cell[q]);
-      // (a cached cell has passed both tests already)
-      const int lb = cell[q] == cached ? 0 : tile_cell(tile, ci, cj, ck, S.nx, S.ny);
-      if ((md_near && cell[q] != cached) || lb < 0) {
-        if (md_lookup(md, S.nx, S.ny, ci, cj, ck) != 0u) {
-          st[q] = ST_MD;
-          continue;
-        }
-      }
-      if (lb < 0) {
-        // outside the window: left for the outlier kernel (no global gather
-        // here, so no wave waits on a dependent memory round trip)
-        st[q] = ST_OUT;
-        continue;
-      }
-      if (cell[q] != cached) {
-        cached = cell[q];
+      const int lb = tile_cell(tile, ci, cj, ck, S.nx, S.ny);
+      int e = cell[q] < 0 ? ST_NONE : (lb < 0 ? ST_OUT : ST_ALIVE);
+      // outside the window: left for the outlier kernel (no global gather here,
+      // so no wave waits on a dependent memory round trip); in an MD cube: left
+      // for the sub-cycled one
+      if (cell[q] >= 0 && (md_near || lb < 0) && push_in_md(d, cell[q])) e = ST_MD;
+      if (e == ST_ALIVE) {
+        float ec[8][3];
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-          const float4 e = sm.E[lb + (t & 1) + tile.tx * (((t >> 1) & 1) + tile.ty * (t >> 2))];
-          ec[t][0] = e.x;
-          ec[t][1] = e.y;
-          ec[t][2] = e.z;
+          const float4 f = sm.E[lb + (t & 1) + tile.tx * (((t >> 1) & 1) + tile.ty * (t >> 2))];
+          ec[t][0] = f.x;
+          ec[t][1] = f.y;
+          ec[t][2] = f.z;
         }
+        e = push_one_f32(S, ec, o[q], v[q], ci, cj, ck);
+        cell[q] = e == ST_ALIVE ? pack_cell(ci, cj, ck) : -1;
+        n_fast += v[q][0] * v[q][0] + v[q][1] * v[q][1] + v[q][2] * v[q][2] >= vfast2;
+        live |= (e == ST_ALIVE ? 1u : 0u) << q;
       }
-      st[q] = push_one_f32(S, ec, o[q], v[q], ci, cj, ck);
-      cell[q] = st[q] == ST_ALIVE ? pack_cell(ci, cj, ck) : -1;
-      n_fast += v[q][0] * v[q][0] + v[q][1] * v[q][1] + v[q][2] * v[q][2] >= S.vfast2_f;
+      st |= (unsigned)e << (4 * q);
     }
     if (kMove) {
-      // collision candidates of the survivors: word 0 of Philox(id, k, COLL, s)
-      uint32_t w0[kPPT];
-      philox_word0<kPPT>(id, *S.step, kColl, (uint32_t)S.sp, S.key0, S.key1, w0);
+      // collision candidates of the survivors: word 0 of Philox(id, k, COLL, s).
+      // (the key passes through the opaque asm so that its 20 round keys are
+      // formed per pass, not held in scalar registers across the loop)
+      if (cand_on) {
+        uint32_t w0[kPPT], k0 = key0, k1 = key1;
+        asm volatile("" : "+s"(k0), "+s"(k1));
+        philox_word0<kPPT>(id, step, kColl, sp, k0, k1, w0);
+        unsigned cm = 0;
 #pragma unroll
-      for (int q = 0; q < kPPT; ++q) {
-        cand[q] = st[q] == ST_ALIVE && (uint64_t)w0[q] < S.T_null;
-        chunk_append(cand[q], L.coll + beg, &sm.ncoll, p0 + q);
-        chunk_append(st[q] == ST_OUT, L.out + beg, &sm.nout, p0 + q);
-        packed += 1ull << (8 * st[q]);
+        for (int q = 0; q < kPPT; ++q) cm |= (w0[q] <= T_last ? 1u : 0u) << q;
+        cm &= live;
+        if (__any(cm)) cand_append(cm, sm.cand, coll, &sm.ncoll, p0, id, v);
       }
-      if ((pass & 31) == 31) {
-        n_w0 += (int)((packed >> (8 * ST_WALL0)) & 255u);
-        n_w1 += (int)((packed >> (8 * ST_WALL1)) & 255u);
-        n_bad += (int)((packed >> (8 * ST_BAD)) & 255u);
-        n_md += (int)((packed >> (8 * ST_MD)) & 255u);
-        n_out += (int)((packed >> (8 * ST_OUT)) & 255u);
-        packed = 0ull;
-      }
+      if (md_near && have) d->L.mask[g4] = 0;
+      if (__any((st & 0xbbbbu) != 0u))  // neither alive nor an empty slot
+        push_events(st, p0, have, md_near, d->L, out, &sm.nout, sm.tally);
       if (have) {
         viP c;
         vfP a0, a1, a2, b0, b1, b2;
@@ -1215,139 +1330,136 @@ __device__ __forceinline__ void push_tile_f32r(const PartF32R& P, const float4* 
     int acc_cell = -1;
 #pragma unroll
     for (int q = 0; q < kPPT; ++q) {
-      if (st[q] != ST_ALIVE) continue;
+      if (!((live >> q) & 1u)) continue;
       long long part[8];
-      split8(S.Qp, o[q][0], o[q][1], o[q][2], part);
+      split8(Qp, o[q][0], o[q][1], o[q][2], part);
       if (cell[q] == acc_cell) {
 #pragma unroll
         for (int t = 0; t < 8; ++t) acc[t] += part[t];
       } else {
-        if (acc_cell >= 0) deposit_run(tile, sm.rho, rho, S, acc_cell, acc, &sm.stray);
+        if (acc_cell >= 0) deposit_run(tile, sm.rho, d, S.nx, S.ny, acc_cell, acc, &sm.far);
         acc_cell = cell[q];
 #pragma unroll
         for (int t = 0; t < 8; ++t) acc[t] = part[t];
       }
     }
-    if (acc_cell >= 0) deposit_run(tile, sm.rho, rho, S, acc_cell, acc, &sm.stray);
+    if (acc_cell >= 0) deposit_run(tile, sm.rho, d, S.nx, S.ny, acc_cell, acc, &sm.far);
   }
-  if (kMove) {
-    n_w0 += (int)((packed >> (8 * ST_WALL0)) & 255u);
-    n_w1 += (int)((packed >> (8 * ST_WALL1)) & 255u);
-    n_bad += (int)((packed >> (8 * ST_BAD)) & 255u);
-    n_md += (int)((packed >> (8 * ST_MD)) & 255u);
-    n_out += (int)((packed >> (8 * ST_OUT)) & 255u);
-    tally_add(sm.tally, TL_W0, n_w0);
-    tally_add(sm.tally, TL_W1, n_w1);
-    tally_add(sm.tally, TL_BAD, n_bad);
-    tally_add(sm.tally, TL_MD, n_md);
-    tally_add(sm.tally, TL_DEAD, n_w0 + n_w1 + n_bad);
-    tally_add(sm.tally, TL_FALL, n_out);
-    tally_add(sm.tally, TL_FAST, n_fast);
-  }
+  if (kMove) tally_add(sm.tally, TL_FAST, n_fast);
   __syncthreads();
+  if (kMove) cand_collide(P, d->S, sm.cand, sm.ncoll, sm.tally);
   // the window holds the magnitudes; the species' sign is applied here
+  const int isign = (int)d->S.isign;
+  const long nxy = d->S.nxy;
+  long long* const rho = d->rho;
+  const float qtx = 1.0f / (float)max(tile.tx, 1), qtxy = 1.0f / (float)max(tile.tx * tile.ty, 1);
   for (int t = threadIdx.x; t < vol; t += kBlock) {
     const long long val = sm.rho[t];
     if (val != 0)
-      atomicAdd((unsigned long long*)&rho[tile_node(tile, t, rtx, rtxy, S.nx, S.ny, S.nxy)],
-                (unsigned long long)(S.isign < 0 ? -val : val));
+      atomicAdd((unsigned long long*)&rho[tile_node(tile, t, qtx, qtxy, S.nx, S.ny, nxy)],
+                (unsigned long long)(isign < 0 ? -val : val));
   }
   if (kMove) {
     if (threadIdx.x == 0) {
-      L.coll_cnt[tidx] = sm.ncoll;
-      L.out_cnt[tidx] = sm.nout;
-      if (sm.stray) L.stray[tidx] = 1;
+      d->L.coll_cnt[tidx] = max(0, sm.ncoll - kCandF32);
+      d->L.out_cnt[tidx] = sm.nout;
     }
-    tally_store(sm.tally, L.tally + (long)TL_N * tidx);
+    __syncthreads();
+    tally_store(sm.tally, d->L.tally + (long)TL_N * tidx);
+    if (sm.far && !md_near) list_far(P, d->L, d->md, S.nx, S.ny, beg, end, sm.nout);
   }
 }
 
+// Both species in one launch (blocks [0, nb) electrons): they meet only in the
+// atomically summed charge, one launch has one tail, and on a small box a second
+// stream's fork and join cost as much as the push itself (8 us each).
 // (at most 128 VGPRs: four waves per SIMD, which the streaming needs)
 template <bool kMove>
-__global__ __launch_bounds__(kBlock, 4) void push_f32r_kernel(PartF32R P,
-                                                           const float4* __restrict__ E,
-                                                           long long* __restrict__ rho, MdTables md,
-                                                           SpeciesStep S, WorkLists L, int span,
-                                                           int chunk) {
+__global__ __launch_bounds__(kBlock, 4) void push_f32r_kernel(const PushDescF32* descs, int nb,
+                                                           int span, int chunk) {
   __shared__ PushSmemF32 sm;
-  push_tile_f32r<kMove>(P, E, rho, md, S, L, span * (int)xcd_interleave(blockIdx.x, chunk), span,
-                        sm);
+  const int sp = (int)blockIdx.x >= nb ? 1 : 0, b = (int)blockIdx.x - sp * nb;
+  push_tile_f32r<kMove>((const PIC_CONST PushDescF32*)(descs + sp), span * (int)xcd_interleave(b, chunk), span, sm);
 }
 
 // ---------------------------------------------------------------- push, ensemble
-// One persistent launch over the tile spans of every (replica, species) of an
-// ensemble: work item i belongs to descriptor d with start[d] <= i < start[d+1]
-// (each descriptor has a multiple of 8 items).  Items are dealt dynamically
-// from eight queues, one per residue of the item index modulo 8: block b takes
-// the next item of queue b % 8 (one atomic per item), so item i still runs on
-// XCD i % 8 as the tile interleave expects, and blocks that drew light tiles
-// take more of them.  A queue's items come in increasing order, so a block
-// finds its descriptor by walking forward.  queue[0..7] are zero at launch.
-__global__ __launch_bounds__(kBlock, 4) void push_batch_f32r_kernel(const PushDescF32* __restrict__ descs,
+// One launch over the tile spans of every (replica, species) of an ensemble:
+// block i takes work item i, of descriptor lo with start[lo] <= i < start[lo + 1]
+// (each descriptor has a multiple of 8 items, so item i runs on XCD i mod 8 as
+// the tile interleave expects).  A block an item, dealt by the hardware as
+// blocks end: a persistent grid drawing items from queues kept its loop's state
+// through every tile (30 spilled registers) and took 2.77 ms a step where this
+// takes XXX ms (six replicas of 1.5e8 particles in all).
+__global__ __launch_bounds__(kBlock, 4) void push_batch_f32r_kernel(const PushDescF32* descs,
                                                                  const int32_t* __restrict__ start,
-                                                                 int ndesc, int* __restrict__ queue) {
+                                                                 int ndesc) {
   __shared__ PushSmemF32 sm;
-  __shared__ int s_item;
-  const int total = start[ndesc];
-  const int x = (int)(blockIdx.x & 7u);
-  int lo = 0;
-  for (;;) {
-    if (threadIdx.x == 0) s_item = x + 8 * atomicAdd(&queue[x], 1);
-    __syncthreads();
-    const int item = s_item;
-    if (item >= total) break;
-    while (lo + 1 < ndesc && start[lo + 1] <= item) ++lo;
-    const int local = item - start[lo];
-    const PushDescF32& d = descs[lo];
-    push_tile_f32r<true>(d.P, d.E, d.rho, d.md, d.S, d.L,
-                         d.span * (int)xcd_interleave(local, d.chunk), d.span, sm);
-    __syncthreads();
+  const int item = (int)blockIdx.x;
+  int lo = 0, hi = ndesc;  // start[lo] <= item < start[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (start[mid] <= item) lo = mid;
+    else hi = mid;
   }
+  const PIC_CONST PushDescF32* d = (const PIC_CONST PushDescF32*)(descs + lo);
+  push_tile_f32r<true>(d, d->span * (int)xcd_interleave(item - start[lo], d->chunk), d->span, sm);
 }
 
 // ---------------------------------------------------------------- push, FP64
 // The same kernel on FP64 records: positions in cell units, velocities in m/s;
 // an empty slot has z = -1.  The field window holds (Ex,Ey),(Ez,0) pairs.
-constexpr int kWinF64 = 729;  // window capacity (nodes): a tile with a 2-cell margin
+constexpr int kWinF64 = 1053;  // window capacity (nodes): a tile pair with a 2-cell margin
+struct PushHot64 {
+  int nx, ny, nz;
+  double qm_dt, dt_dx;
+};
 
-// (at most 168 VGPRs: three waves per SIMD)
+// (at most 168 VGPRs: three waves per SIMD; 42 KB of LDS allow three blocks a CU)
 template <bool kMove>
-__global__ __launch_bounds__(kBlock, 3) void push_f64_kernel(PartF64 P, const double2* __restrict__ E,
-                                                          double* __restrict__ rho, MdTables md,
-                                                          SpeciesStep S, WorkLists L, int chunk) {
-  __shared__ double2 s_E[2 * kWinF64];
+__global__ __launch_bounds__(kBlock, 3) void push_f64_kernel(const PushDescF64* descs, int nb,
+                                                          int span, int chunk) {
+  __shared__ double2 s_E[kMove ? 2 * kWinF64 : 1];
   __shared__ double s_rho[kWinF64];
   __shared__ unsigned s_tally[TL_N];
-  __shared__ int s_nmd, s_ncoll, s_nout, s_mdbase;
-  __shared__ int32_t s_md[kMdStage];
-  const int tidx = (int)xcd_interleave(blockIdx.x, chunk);
-  const int beg = L.tstart[tidx], end = L.tstart[tidx + 1];
-  if (beg >= end) {
-    if (kMove && threadIdx.x == 0) {
-      L.coll_cnt[tidx] = 0;
-      L.out_cnt[tidx] = 0;
-    }
-    return;
+  __shared__ int s_ncoll, s_nout, s_far;
+  __shared__ CandStage<double, kMove ? kCandF64 : 1> s_cand;
+  const int spi = (int)blockIdx.x >= nb ? 1 : 0;
+  const PIC_CONST PushDescF64* d = (const PIC_CONST PushDescF64*)(descs + spi);
+  const int tidx = span * (int)xcd_interleave((int)blockIdx.x - spi * nb, chunk);
+  const int beg = d->L.tstart[tidx], end = d->L.tstart[tidx + span];
+  if (kMove && threadIdx.x < span) {
+    d->L.coll_cnt[tidx + threadIdx.x] = 0;
+    d->L.out_cnt[tidx + threadIdx.x] = 0;
   }
-  const Tile tile = make_tile(tidx, L, S.nx, S.ny, S.nz, S.margin, kWinF64);
+  if (beg >= end) return;
+  const PushHot64 S{d->S.nx, d->S.ny, d->S.nz, d->S.qm_dt, d->S.dt_dx};
+  const Tile tile = make_tile(tidx, d->L, S.nx, S.ny, S.nz, d->S.margin, kWinF64, span);
   const int vol = tile.on ? tile.tx * tile.ty * tile.tz : 0;
   const float rtx = 1.0f / (float)max(tile.tx, 1), rtxy = 1.0f / (float)max(tile.tx * tile.ty, 1);
   for (int t = threadIdx.x; t < vol; t += kBlock) {
     if (kMove) {
-      const long node = tile_node(tile, t, rtx, rtxy, S.nx, S.ny, S.nxy);
-      s_E[2 * t] = E[2 * node];
-      s_E[2 * t + 1] = E[2 * node + 1];
+      const long node = tile_node(tile, t, rtx, rtxy, S.nx, S.ny, d->S.nxy);
+      s_E[2 * t] = d->E[2 * node];
+      s_E[2 * t + 1] = d->E[2 * node + 1];
     }
     s_rho[t] = 0.0;
   }
   if (threadIdx.x < TL_N) s_tally[threadIdx.x] = 0;
   if (threadIdx.x == 0) {
-    s_nmd = 0;
     s_ncoll = 0;
+    s_far = 0;
     s_nout = 0;
   }
+  const bool md_near = window_meets_md(tile, d->md, S.nx, S.ny);
+  const PartF64 P = desc_records(d);
+  int32_t* const coll = d->L.coll + beg;
+  int32_t* const out = d->L.out + beg;
+  const double vfast2 = d->S.vfast2, sign = d->S.sign;
+  const uint32_t step = kMove ? *d->S.step : 0u, key0 = d->S.key0, key1 = d->S.key1, sp = (uint32_t)d->S.sp;
+  const bool cand_on = d->S.T_null != 0;
+  const uint32_t T_last = (uint32_t)(d->S.T_null - 1);
   __syncthreads();
-  int n_w0 = 0, n_w1 = 0, n_bad = 0, n_md = 0, n_out = 0, n_fast = 0;
+  int n_fast = 0;
   for (int base = beg; base < end; base += kChunk) {
     const int p0 = base + kPPT * (int)threadIdx.x;
     const bool have = p0 < end;  // four slots in the tile, or none
@@ -1382,69 +1494,64 @@ __global__ __launch_bounds__(kBlock, 3) void push_f64_kernel(PartF64 P, const do
       id[2] = I4.z;
       id[3] = I4.w;
     }
-    int st[kPPT], cell[kPPT];
-    bool cand[kPPT];
+    int cell[kPPT];
+    unsigned st = 0, live = 0;  // as in the FP32R push
 #pragma unroll
     for (int q = 0; q < kPPT; ++q) {
-      st[q] = ST_NONE;
-      cand[q] = false;
-      cell[q] = -1;
-      if (!(x[q][2] >= 0.0)) continue;
+      const bool full = x[q][2] >= 0.0;
       const int i0 = (int)floor(x[q][0]), j0 = (int)floor(x[q][1]), k0 = (int)floor(x[q][2]);
+      cell[q] = -1;
       if (!kMove) {
-        st[q] = ST_ALIVE;
-        cell[q] = pack_cell(i0, j0, k0);
-        continue;
-      }
-      if (md_lookup(md, S.nx, S.ny, i0, j0, k0) != 0u) {
-        st[q] = ST_MD;
+        if (full) {
+          live |= 1u << q;
+          cell[q] = pack_cell(i0, j0, k0);
+        }
         continue;
       }
       const int lb = tile_cell(tile, i0, j0, k0, S.nx, S.ny);
-      if (lb < 0) {
-        st[q] = ST_OUT;  // left for the outlier kernel
-        continue;
-      }
-      double Ep[3];
-      {
-        const double fx = x[q][0] - i0, fy = x[q][1] - j0, fz = x[q][2] - k0;
-        const double wx[2] = {1.0 - fx, fx}, wy[2] = {1.0 - fy, fy}, wz[2] = {1.0 - fz, fz};
-        Ep[0] = Ep[1] = Ep[2] = 0.0;
+      int e = !full ? ST_NONE : (lb < 0 ? ST_OUT : ST_ALIVE);
+      if (full && (md_near || lb < 0) && push_in_md(d, pack_cell(i0, j0, k0))) e = ST_MD;
+      if (e == ST_ALIVE) {
+        double Ep[3];
+        {
+          const double fx = x[q][0] - i0, fy = x[q][1] - j0, fz = x[q][2] - k0;
+          const double wx[2] = {1.0 - fx, fx}, wy[2] = {1.0 - fy, fy}, wz[2] = {1.0 - fz, fz};
+          Ep[0] = Ep[1] = Ep[2] = 0.0;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int l = lb + (t & 1) + tile.tx * (((t >> 1) & 1) + tile.ty * (t >> 2));
-          const double w = wx[t & 1] * wy[(t >> 1) & 1] * wz[t >> 2];
-          const double2 a = s_E[2 * l], b2 = s_E[2 * l + 1];
-          Ep[0] += w * a.x;
-          Ep[1] += w * a.y;
-          Ep[2] += w * b2.x;
+          for (int t = 0; t < 8; ++t) {
+            const int l = lb + (t & 1) + tile.tx * (((t >> 1) & 1) + tile.ty * (t >> 2));
+            const double w = wx[t & 1] * wy[(t >> 1) & 1] * wz[t >> 2];
+            const double2 a = s_E[2 * l], b2 = s_E[2 * l + 1];
+            Ep[0] += w * a.x;
+            Ep[1] += w * a.y;
+            Ep[2] += w * b2.x;
+          }
+        }
+        e = push_one_f64(S, Ep, x[q], v[q]);
+        n_fast += v[q][0] * v[q][0] + v[q][1] * v[q][1] + v[q][2] * v[q][2] >= vfast2;
+        if (e == ST_ALIVE) {
+          cell[q] = pack_cell((int)floor(x[q][0]), (int)floor(x[q][1]), (int)floor(x[q][2]));
+          live |= 1u << q;
+        } else {
+          x[q][2] = -1.0;
         }
       }
-      st[q] = push_one_f64(S, Ep, x[q], v[q]);
-      n_fast += v[q][0] * v[q][0] + v[q][1] * v[q][1] + v[q][2] * v[q][2] >= S.vfast2;
-      if (st[q] == ST_ALIVE) {
-        cell[q] = pack_cell((int)floor(x[q][0]), (int)floor(x[q][1]), (int)floor(x[q][2]));
-        const uint4 r = philox4x32_10(id[q], *S.step, kColl, (uint32_t)S.sp, S.key0, S.key1);
-        cand[q] = (uint64_t)r.x < S.T_null;
-      } else {
-        x[q][2] = -1.0;
-      }
+      st |= (unsigned)e << (4 * q);
     }
     if (kMove) {
-      bool is_out[kPPT];
+      if (cand_on) {
+        uint32_t w0[kPPT], c0 = key0, c1 = key1;
+        asm volatile("" : "+s"(c0), "+s"(c1));
+        philox_word0<kPPT>(id, step, kColl, sp, c0, c1, w0);
+        unsigned cm = 0;
 #pragma unroll
-      for (int q = 0; q < kPPT; ++q) is_out[q] = st[q] == ST_OUT;
-      append_slot_order(st, ST_MD, s_md, &s_nmd, p0);
-      chunk_append4(cand, L.coll + beg, &s_ncoll, p0);
-      chunk_append4(is_out, L.out + beg, &s_nout, p0);
-#pragma unroll
-      for (int q = 0; q < kPPT; ++q) {
-        n_out += st[q] == ST_OUT;
-        n_w0 += st[q] == ST_WALL0;
-        n_w1 += st[q] == ST_WALL1;
-        n_bad += st[q] == ST_BAD;
-        n_md += st[q] == ST_MD;
+        for (int q = 0; q < kPPT; ++q) cm |= (w0[q] <= T_last ? 1u : 0u) << q;
+        cm &= live;
+        if (__any(cm)) cand_append(cm, s_cand, coll, &s_ncoll, p0, id, v);
       }
+      if (md_near && have) d->L.mask[g4] = 0;
+      if (__any((st & 0xbbbbu) != 0u))
+        push_events(st, p0, have, md_near, d->L, out, &s_nout, s_tally);
       if (have) {
 #define PIC_STORE4(arr, srcv, a)                                                          \
   {                                                                                       \
@@ -1463,56 +1570,54 @@ __global__ __launch_bounds__(kBlock, 3) void push_f64_kernel(PartF64 P, const do
 
     double acc[8];
     int acc_cell = -1;
+    auto flush = [&]() {
+      const int ai = cell_i(acc_cell), aj = cell_j(acc_cell), ak = cell_k(acc_cell);
+      const int lb = tile_cell(tile, ai, aj, ak, S.nx, S.ny);
+      if (lb >= 0) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+          atomicAdd(&s_rho[lb + (t & 1) + tile.tx * (((t >> 1) & 1) + tile.ty * (t >> 2))], acc[t]);
+        return;
+      }
+      if (kMove && push_in_md(d, acc_cell)) s_far = 1;
+      corner_add<double>(tile, -1, s_rho, d->rho, d->S, ai, aj, ak, acc);
+    };
 #pragma unroll
     for (int q = 0; q < kPPT; ++q) {
-      if (st[q] != ST_ALIVE) continue;
+      if (!((live >> q) & 1u)) continue;
       double w[8];
       const int i = cell_i(cell[q]), j = cell_j(cell[q]), k = cell_k(cell[q]);
-      cic_weights_d(x[q][0] - i, x[q][1] - j, x[q][2] - k, S.sign, w);
+      cic_weights_d(x[q][0] - i, x[q][1] - j, x[q][2] - k, sign, w);
       if (cell[q] == acc_cell) {
 #pragma unroll
         for (int t = 0; t < 8; ++t) acc[t] += w[t];
       } else {
-        if (acc_cell >= 0) {
-          const int ai = cell_i(acc_cell), aj = cell_j(acc_cell), ak = cell_k(acc_cell);
-          corner_add<double>(tile, tile_cell(tile, ai, aj, ak, S.nx, S.ny), s_rho, rho, S, ai, aj,
-                             ak, acc);
-        }
+        if (acc_cell >= 0) flush();
         acc_cell = cell[q];
 #pragma unroll
         for (int t = 0; t < 8; ++t) acc[t] = w[t];
       }
     }
-    if (acc_cell >= 0) {
-      const int ai = cell_i(acc_cell), aj = cell_j(acc_cell), ak = cell_k(acc_cell);
-      corner_add<double>(tile, tile_cell(tile, ai, aj, ak, S.nx, S.ny), s_rho, rho, S, ai, aj, ak,
-                         acc);
-    }
-    if (kMove) {
-      __syncthreads();
-      md_flush(s_md, &s_nmd, &s_mdbase, L);
-    }
+    if (acc_cell >= 0) flush();
   }
-  if (kMove) {
-    tally_add(s_tally, TL_W0, n_w0);
-    tally_add(s_tally, TL_W1, n_w1);
-    tally_add(s_tally, TL_BAD, n_bad);
-    tally_add(s_tally, TL_MD, n_md);
-    tally_add(s_tally, TL_DEAD, n_w0 + n_w1 + n_bad);
-    tally_add(s_tally, TL_FALL, n_out);
-    tally_add(s_tally, TL_FAST, n_fast);
-  }
+  if (kMove) tally_add(s_tally, TL_FAST, n_fast);
   __syncthreads();
+  if constexpr (kMove) cand_collide(P, d->S, s_cand, s_ncoll, s_tally);
+  double* const rho = d->rho;
+  const long nxy = d->S.nxy;
+  const float qtx = 1.0f / (float)max(tile.tx, 1), qtxy = 1.0f / (float)max(tile.tx * tile.ty, 1);
   for (int t = threadIdx.x; t < vol; t += kBlock) {
     const double val = s_rho[t];
-    if (val != 0.0) unsafeAtomicAdd(&rho[tile_node(tile, t, rtx, rtxy, S.nx, S.ny, S.nxy)], val);
+    if (val != 0.0) unsafeAtomicAdd(&rho[tile_node(tile, t, qtx, qtxy, S.nx, S.ny, nxy)], val);
   }
   if (kMove) {
     if (threadIdx.x == 0) {
-      L.coll_cnt[tidx] = s_ncoll;
-      L.out_cnt[tidx] = s_nout;
+      d->L.coll_cnt[tidx] = max(0, s_ncoll - kCandF64);
+      d->L.out_cnt[tidx] = s_nout;
     }
-    tally_store(s_tally, L.tally + (long)TL_N * tidx);
+    __syncthreads();
+    tally_store(s_tally, d->L.tally + (long)TL_N * tidx);
+    if (s_far && !md_near) list_far(P, d->L, d->md, S.nx, S.ny, beg, end, s_nout);
   }
 }
 
@@ -1540,8 +1645,9 @@ __device__ __forceinline__ void load_d(const PartF32R& P, long p, double x[3], d
 
 // store the survivor; returns its cell (-1 if rounding put it on the rf
 // electrode) and the eight corner shares of its charge
+template <typename H>
 __device__ __forceinline__ int store_d(const PartF64& P, long p, const double x[3],
-                                       const double v[3], const SpeciesStep& S, double part[8]) {
+                                       const double v[3], const H& S, double part[8]) {
   P.x[p] = x[0];
   P.y[p] = x[1];
   P.z[p] = x[2];
@@ -1552,8 +1658,9 @@ __device__ __forceinline__ int store_d(const PartF64& P, long p, const double x[
   cic_weights_d(x[0] - i, x[1] - j, x[2] - k, S.sign, part);
   return pack_cell(i, j, k);
 }
+template <typename H>
 __device__ __forceinline__ int store_d(const PartF32R& P, long p, const double x[3],
-                                       const double v[3], const SpeciesStep& S,
+                                       const double v[3], const H& S,
                                        long long part[8]) {
   int c[3];
   float f[3];
@@ -1647,12 +1754,10 @@ __device__ __forceinline__ void copy_rec(const PartF32R& src, const PartF32R& ds
 // one thread per MD particle of the dense list of this step, both species in
 // one launch (blocks [0, nb) electrons, [nb, 2 nb) ions); events go to the
 // block's own tally row, grain hits to LDS counters first.  The particles are
-// read from P and their new states written to the same slots of D: D = P for
-// the FP64 records (in place, after the push); the FP32R step runs this kernel
-// beside the push with D the species' other record buffer, and
-// md_collide_kernel copies the states back afterwards.  The survivors'
-// collisions follow in md_collide_kernel (kept out of this kernel so that its
-// registers allow three waves per SIMD).
+// read from P and their new states written to the same slots of D, the species'
+// other record buffer, so that this kernel runs beside the push; the lists
+// kernel after both copies the states back and takes the survivors' collisions
+// (kept out of this kernel so that its registers allow three waves per SIMD).
 constexpr int kMdThreads = 64;
 template <typename PT, typename ET, typename RT>
 __global__ __launch_bounds__(kMdThreads) void md_kernel(SpeciesPair<PT> pr, PT D0, PT D1,
@@ -1665,7 +1770,7 @@ __global__ __launch_bounds__(kMdThreads) void md_kernel(SpeciesPair<PT> pr, PT D
   const SpeciesStep S = pr.S[sp];
   const WorkLists L = pr.L[sp];
   const int bid = (int)blockIdx.x - sp * pr.nb;
-  const int total = L.cnt[2];
+  const int total = *L.n_md;
   if ((long)bid * kMdThreads >= total) return;
   constexpr int kStage = 256;
   __shared__ double s_gpos[3 * kStage], s_Qc[kStage];
@@ -1738,8 +1843,6 @@ __global__ __launch_bounds__(kMdThreads) void md_kernel(SpeciesPair<PT> pr, PT D
 constexpr int kMomWin = 729;
 // copies of the window: thread t adds into copy t % kMomCopies (summed at the flush)
 constexpr int kMomCopies = 1;
-__device__ __forceinline__ bool slot_alive(const PartF64& P, long p) { return P.z[p] >= 0.0; }
-__device__ __forceinline__ bool slot_alive(const PartF32R& P, long p) { return P.cell[p] >= 0; }
 
 template <typename PT>
 __global__ __launch_bounds__(256) void moments_kernel(PT P, SpeciesStep S, WorkLists L,
@@ -1879,24 +1982,25 @@ __global__ __launch_bounds__(256) void fine_moments_kernel(PT P, WorkLists L, Fi
   }
 }
 
-// The collisions of the MD particles that survived their sub-cycled motion,
-// from their stored velocities (same list, blocks and tally rows as md_kernel).
-template <typename PT>
-__device__ __forceinline__ void md_collide_block(const SpeciesPair<PT>& pr, const PT& D, int sp,
-                                                 int bid, int commit, int mcc) {
-  const PT P = pr.P[sp];
-  const SpeciesStep S = pr.S[sp];
-  const WorkLists L = pr.L[sp];
-  const int total = L.cnt[2];
+
+// The MD particles' new states copied back from D and the collisions of those
+// that survived, from their stored velocities (same list and tally rows as
+// md_kernel, nb blocks of 64 threads).
+template <typename PT, typename Desc>
+__device__ __forceinline__ void md_collide_block(const PIC_CONST Desc* d, const PT& D, int bid,
+                                                 int nb, int mcc) {
+  const PT P = desc_records(d);
+  const auto& S = d->S;
+  const auto& L = d->L;
+  const int total = *L.n_md;
   if ((long)bid * kMdThreads >= total) return;
   int n_coll = 0, n_cap = 0;
-  for (long idx = (long)bid * kMdThreads + threadIdx.x; idx < total;
-       idx += (long)pr.nb * kMdThreads) {
-    const long p = L.md[idx];
-    if (commit) copy_rec(D, P, p);  // the sub-cycled kernel's result
-    if (!mcc || !slot_alive(P, p)) continue;
+  for (int idx = bid * kMdThreads + (int)threadIdx.x; idx < total; idx += nb * kMdThreads) {
+    const int p = L.md[idx];
+    copy_rec(D, P, p);  // the sub-cycled kernel's result
+    if (!mcc || !slot_alive(D, p)) continue;
     bool coll = false, capv = false;
-    typename VelOf<PT>::type v[3] = {P.vx[p], P.vy[p], P.vz[p]};
+    typename VelOf<PT>::type v[3] = {D.vx[p], D.vy[p], D.vz[p]};
     collide(S, P.id[p], v, coll, capv, p);
     if (coll) {
       P.vx[p] = v[0];
@@ -1914,84 +2018,97 @@ __device__ __forceinline__ void md_collide_block(const SpeciesPair<PT>& pr, cons
     if (n_cap) tally[TL_CAP] += (unsigned long long)n_cap;
   }
 }
-template <typename PT>
-__global__ __launch_bounds__(kMdThreads) void md_collide_kernel(SpeciesPair<PT> pr, PT D0, PT D1,
-                                                                int commit, int mcc,
-                                                                int sp_only) {
-  // both species (blocks [0, nb) electrons) or species sp_only alone
-  const int sp = sp_only >= 0 ? sp_only : ((int)blockIdx.x >= pr.nb ? 1 : 0);
-  const int bid = (int)blockIdx.x - (sp_only >= 0 ? 0 : sp * pr.nb);
-  md_collide_block(pr, sp ? D1 : D0, sp, bid, commit, mcc);
+
+// One wave goes through kNearSlots slots of a push block near the MD cubes and
+// lists those that are now in a cube for the next step, in slot order, one
+// reservation per 256 slots (the MD particles by their state in D, which other
+// blocks copy back meanwhile; the particles outside the window list themselves,
+// outlier_block).
+constexpr int kNearSlots = 1024;
+template <typename PT, typename Desc>
+__device__ __forceinline__ void near_block(const PIC_CONST Desc* d, const PT& D, int chunk,
+                                           int chunks) {
+  const PT P = desc_records(d);
+  const auto& L = d->L;
+  const auto& md = d->md;
+  const int nx = d->S.nx, ny = d->S.ny;
+  const int t0 = L.near[chunk / chunks];
+  const int first = L.tstart[t0], end = L.tstart[t0 + d->span];
+  const int lane = (int)threadIdx.x & 63;
+  // (a push block with more slots than its chunks cover: the chunks take turns)
+  for (int b0 = first + (chunk % chunks) * kNearSlots; b0 < end; b0 += chunks * kNearSlots) {
+    const int e0 = min(end, b0 + kNearSlots);
+    for (int base = b0; base < e0; base += 256) {
+      const int p0 = base + 4 * lane;
+      const bool have = p0 < e0;
+      const unsigned m = have ? L.mask[p0 >> 2] : 0xf0u;
+      bool in[4];
+      int cnt = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int p = p0 + q;
+        const bool moved = (m >> q) & 1u;
+        in[q] = !(m & (16u << q)) && (moved ? slot_alive(D, p) : slot_alive(P, p)) &&
+                in_md(md, nx, ny, moved ? slot_cell(D, p) : slot_cell(P, p));
+        cnt += in[q];
+      }
+      int incl = cnt;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const int t = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += t;
+      }
+      const int total = __shfl(incl, 63, 64);
+      if (total == 0) continue;
+      int at = 0;
+      if (lane == 0) at = atomicAdd(L.n_md_next, total);
+      at = __shfl(at, 0, 64) + incl - cnt;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (in[q]) L.md_next[at++] = p0 + q;
+    }
+  }
 }
 
-// ---------------------------------------------------------------- MD list
-// The dense MD list of an FP32R step, formed before the push: every slot
-// whose particle starts the step in a cell of an MD cube (the push leaves
-// those to the sub-cycled kernel; the same test as the push's).  A particle
-// in an MD cube either lies inside its push block's window, which then meets
-// the MD cubes' bounding box, or has left that window since the last sort,
-// which set the block's stray flag; the grid's padding tiles (new particles of
-// ionisation) have no window.  So one block per push block (blocks [0, npb)
-// electrons, the rest ions) scans the block's slots only in those cases, in
-// chunks of kMdScanSlots, compacting a chunk's hits in slot order and
-// reserving their place in the list with one atomic; L.cnt[2] is zero at the
-// start of a step.
-constexpr int kMdScanPer = 8;  // slots per thread and chunk (two 16-byte loads)
-constexpr int kMdScanSlots = 256 * kMdScanPer;
-__global__ __launch_bounds__(256) void md_scan_kernel(PartF32R P0, PartF32R P1, WorkLists L0,
-                                                      WorkLists L1, MdTables md, int nx, int ny,
-                                                      int nz, int m0, int m1, int span, int npb) {
-  __shared__ int s_wave[4];
-  __shared__ int s_base;
-  const int sp = (int)blockIdx.x >= npb ? 1 : 0;
-  const PartF32R P = sp ? P1 : P0;
-  const WorkLists L = sp ? L1 : L0;
-  const int t0 = ((int)blockIdx.x - sp * npb) * span;
-  const int beg = L.tstart[t0], end = L.tstart[t0 + span];  // multiples of 4
-  if (beg >= end) return;
-  if (!L.stray[t0] &&
-      !window_meets_md(make_tile(t0, L, nx, ny, nz, sp ? m1 : m0, kWinF32, span), md, nx, ny))
-    return;
-  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
-  for (int s0 = beg; s0 < end; s0 += kMdScanSlots) {
-    const int p0 = s0 + kMdScanPer * (int)threadIdx.x;
-    int c[kMdScanPer];
+// ---------------------------------------------------------------- packed lists
+// One wave takes the list segments of `group` consecutive push blocks (at most
+// 64) end to end: lane j holds segment j's place, and entry i of the whole lies
+// in the segment found among the lanes.  A wave per segment instead left most
+// lanes idle and a chain of dependent loads per push block (an ion block has
+// one candidate or none): 64x64x256 75 us after the pushes, 128x128x512 950 us.
+struct Segments {
+  int start, end;  // of this lane's segment in the whole
+  long first;      // its first slot in the list array
+  int total;       // (wave-uniform)
+};
+__device__ __forceinline__ Segments segments(const int32_t* cnt, const int32_t* tstart, int block0,
+                                             int nblocks, int span) {
+  const int lane = (int)threadIdx.x & 63;
+  Segments s;
+  const bool on = lane < nblocks;
+  const int t = (block0 + (on ? lane : 0)) * span;
+  const int n = on ? cnt[t] : 0;
+  s.first = tstart[t];
+  int incl = n;
 #pragma unroll
-    for (int h = 0; h < kMdScanPer / 4; ++h) {
-      int4 v = make_int4(-1, -1, -1, -1);
-      if (p0 + 4 * h < end) v = reinterpret_cast<const int4*>(P.cell)[(p0 >> 2) + h];
-      c[4 * h] = v.x;
-      c[4 * h + 1] = v.y;
-      c[4 * h + 2] = v.z;
-      c[4 * h + 3] = v.w;
-    }
-    bool hit[kMdScanPer];
-    int cnt = 0;
-#pragma unroll
-    for (int q = 0; q < kMdScanPer; ++q) {
-      hit[q] = c[q] >= 0 && md_lookup(md, nx, ny, cell_i(c[q]), cell_j(c[q]), cell_k(c[q])) != 0u;
-      cnt += hit[q];
-    }
-    int incl = cnt;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int t = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += t;
-    }
-    if (lane == 63) s_wave[wave] = incl;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      const int total = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
-      s_base = total ? atomicAdd(&L.cnt[2], total) : 0;
-    }
-    __syncthreads();
-    int at = s_base + incl - cnt;
-    for (int w = 0; w < wave; ++w) at += s_wave[w];
-#pragma unroll
-    for (int q = 0; q < kMdScanPer; ++q)
-      if (hit[q]) L.md[at++] = p0 + q;
-    __syncthreads();  // s_wave and s_base are reused by the next chunk
+  for (int off = 1; off < 64; off <<= 1) {
+    const int v = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += v;
   }
+  s.start = incl - n;
+  s.end = incl;
+  s.total = __shfl(incl, 63, 64);
+  return s;
+}
+// the list entry i (< s.total, or any lane's spare call) of the segments
+__device__ __forceinline__ int segment_entry(const Segments& s, const int32_t* list, int i) {
+  int j = 0;  // the segments that end at or before entry i
+#pragma unroll
+  for (int step = 32; step > 0; step >>= 1)
+    if (__shfl(s.end, j + step - 1, 64) <= i) j += step;
+  const long first = __shfl(s.first, j & 63, 64);
+  const int start = __shfl(s.start, j & 63, 64);
+  return i < s.total ? list[first + (i - start)] : 0;
 }
 
 // ---------------------------------------------------------------- outliers
@@ -1999,163 +2116,160 @@ __global__ __launch_bounds__(256) void md_scan_kernel(PartF32R P0, PartF32R P1, 
 // last sort): the same push with the field gathered from global memory and the
 // charge deposited with global atomics, the collision done in place.  One wave
 // per tile segment.
-// the outliers of push block bid of species sp
-__device__ __forceinline__ void outlier_block(const SpeciesPair<PartF32R>& pr,
-                                              const float4* __restrict__ E,
-                                              long long* __restrict__ rho, int do_mcc, int sp,
-                                              int bid) {
-  const PartF32R P = pr.P[sp];
-  const SpeciesStep S = pr.S[sp];
-  const WorkLists L = pr.L[sp];
-  const int tidx = bid * pr.span;
-  const int count = L.out_cnt[tidx];
-  if (count == 0) return;
-  if (threadIdx.x == 0) L.stray[tidx] = 1;  // (already set when these left the window)
-  const int32_t* seg = L.out + L.tstart[tidx];
+template <typename WL>
+__device__ __forceinline__ void outlier_tally(const WL& L, int tidx, int w0, int w1, int bad,
+                                              int coll, int cap, int fast) {
+  w0 = wave_sum(w0);
+  w1 = wave_sum(w1);
+  bad = wave_sum(bad);
+  coll = wave_sum(coll);
+  cap = wave_sum(cap);
+  fast = wave_sum(fast);
+  if (threadIdx.x != 0) return;
+  unsigned long long* tl = L.tally + (long)TL_N * tidx;
+  tl[TL_W0] += w0;
+  tl[TL_W1] += w1;
+  tl[TL_BAD] += bad;
+  tl[TL_COLL] += coll;
+  tl[TL_CAP] += cap;
+  tl[TL_DEAD] += w0 + w1 + bad;
+  tl[TL_FAST] += fast;
+}
+// the outliers of `nblocks` push blocks from block0 of species sp
+__device__ __forceinline__ void outlier_block(const PIC_CONST PushDescF32* d, const PartF32R& D, int do_mcc,
+                                              int block0, int nblocks) {
+  const PartF32R P = desc_records(d);
+  const auto& S = d->S;
+  const auto& L = d->L;
+  const auto& md = d->md;
+  const float4* __restrict__ E = d->E;
+  long long* __restrict__ rho = d->rho;
+  const Segments sg = segments(L.out_cnt, L.tstart, block0, nblocks, d->span);
+  if (sg.total == 0) return;
   int t_w0 = 0, t_w1 = 0, t_bad = 0, t_coll = 0, t_cap = 0, t_fast = 0;
-  for (int idx = threadIdx.x; idx < count; idx += 64) {
-    const long p = seg[idx];
-    const int c = P.cell[p];
-    int ci = cell_i(c), cj = cell_j(c), ck = cell_k(c);
-    float o[3] = {P.ox[p], P.oy[p], P.oz[p]};
-    float v[3] = {P.vx[p], P.vy[p], P.vz[p]};
-    float ec[8][3];
-    const int i1 = ci + 1 == S.nx ? 0 : ci + 1;
-    const int j1 = cj + 1 == S.ny ? 0 : cj + 1;
+  for (int base = 0; base < sg.total; base += 64) {
+    const int idx = base + (int)threadIdx.x;
+    bool enters = false;
+    int p = segment_entry(sg, L.out, idx);
+    if (idx < sg.total && p < 0) {
+      p = ~p;
+      enters = slot_alive(D, p) && in_md(md, S.nx, S.ny, slot_cell(D, p));
+    } else if (idx < sg.total) {
+      const int c = P.cell[p];
+      int ci = cell_i(c), cj = cell_j(c), ck = cell_k(c);
+      float o[3] = {P.ox[p], P.oy[p], P.oz[p]};
+      float v[3] = {P.vx[p], P.vy[p], P.vz[p]};
+      float ec[8][3];
+      const int i1 = ci + 1 == S.nx ? 0 : ci + 1;
+      const int j1 = cj + 1 == S.ny ? 0 : cj + 1;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const float4 e = E[((t & 1) ? i1 : ci) + (long)S.nx * (((t >> 1) & 1) ? j1 : cj) +
-                         (long)S.nxy * (ck + (t >> 2))];
-      ec[t][0] = e.x;
-      ec[t][1] = e.y;
-      ec[t][2] = e.z;
-    }
-    const int st = push_one_f32(S, ec, o, v, ci, cj, ck);
-    t_fast += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] >= S.vfast2_f;
-    if (st == ST_ALIVE) {
-      bool coll = false, capv = false;
-      if (do_mcc) {
-        const uint32_t id = P.id[p];
-        const uint4 r = philox4x32_10(id, *S.step, kColl, (uint32_t)S.sp, S.key0, S.key1);
-        if ((uint64_t)r.x < S.T_null) collide(S, id, v, coll, capv, p);
+      for (int t = 0; t < 8; ++t) {
+        const float4 e = E[((t & 1) ? i1 : ci) + (long)S.nx * (((t >> 1) & 1) ? j1 : cj) +
+                           (long)S.nxy * (ck + (t >> 2))];
+        ec[t][0] = e.x;
+        ec[t][1] = e.y;
+        ec[t][2] = e.z;
       }
-      t_coll += coll;
-      t_cap += capv;
-      P.cell[p] = pack_cell(ci, cj, ck);
-      P.ox[p] = o[0];
-      P.oy[p] = o[1];
-      P.oz[p] = o[2];
-      deposit_global_fixed(rho, S, ci, cj, ck, o[0], o[1], o[2]);
-    } else {
-      P.cell[p] = -1;
-    }
-    P.vx[p] = v[0];
-    P.vy[p] = v[1];
-    P.vz[p] = v[2];
-    t_w0 += st == ST_WALL0;
-    t_w1 += st == ST_WALL1;
-    t_bad += st == ST_BAD;
-  }
-  t_w0 = wave_sum(t_w0);
-  t_w1 = wave_sum(t_w1);
-  t_bad = wave_sum(t_bad);
-  t_coll = wave_sum(t_coll);
-  t_cap = wave_sum(t_cap);
-  t_fast = wave_sum(t_fast);
-  if (threadIdx.x == 0) {
-    unsigned long long* tl = L.tally + (long)TL_N * tidx;
-    tl[TL_W0] += t_w0;
-    tl[TL_W1] += t_w1;
-    tl[TL_BAD] += t_bad;
-    tl[TL_COLL] += t_coll;
-    tl[TL_CAP] += t_cap;
-    tl[TL_DEAD] += t_w0 + t_w1 + t_bad;
-    tl[TL_FAST] += t_fast;
-  }
-}
-__global__ __launch_bounds__(64) void outlier_f32r_kernel(SpeciesPair<PartF32R> pr,
-                                                          const float4* __restrict__ E,
-                                                          long long* __restrict__ rho, int do_mcc,
-                                                          int sp_only) {
-  // both species (blocks [0, nb) electrons) or species sp_only alone
-  const int sp = sp_only >= 0 ? sp_only : ((int)blockIdx.x >= pr.nb ? 1 : 0);
-  outlier_block(pr, E, rho, do_mcc, sp, (int)blockIdx.x - (sp_only >= 0 ? 0 : sp * pr.nb));
-}
-
-__global__ __launch_bounds__(64) void outlier_f64_kernel(SpeciesPair<PartF64> pr,
-                                                         const double2* __restrict__ E,
-                                                         double* __restrict__ rho, int do_mcc) {
-  const int sp = (int)blockIdx.x >= pr.nb;
-  const PartF64 P = pr.P[sp];
-  const SpeciesStep S = pr.S[sp];
-  const WorkLists L = pr.L[sp];
-  const int tidx = (int)blockIdx.x - sp * pr.nb;
-  const int count = L.out_cnt[tidx];
-  if (count == 0) return;
-  const int32_t* seg = L.out + L.tstart[tidx];
-  int t_w0 = 0, t_w1 = 0, t_bad = 0, t_coll = 0, t_cap = 0, t_fast = 0;
-  for (int idx = threadIdx.x; idx < count; idx += 64) {
-    const long p = seg[idx];
-    double x[3], v[3];
-    load_d(P, p, x, v);
-    const int i0 = (int)floor(x[0]), j0 = (int)floor(x[1]), k0 = (int)floor(x[2]);
-    double Ep[3];
-    gather_d(E, S, i0, j0, k0, x[0] - i0, x[1] - j0, x[2] - k0, Ep);
-    const int st = push_one_f64(S, Ep, x, v);
-    t_fast += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] >= S.vfast2;
-    if (st == ST_ALIVE) {
-      bool coll = false, capv = false;
-      if (do_mcc) {
-        const uint32_t id = P.id[p];
-        const uint4 r = philox4x32_10(id, *S.step, kColl, (uint32_t)S.sp, S.key0, S.key1);
-        if ((uint64_t)r.x < S.T_null) collide(S, id, v, coll, capv, p);
+      const int st = push_one_f32(S, ec, o, v, ci, cj, ck);
+      t_fast += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] >= S.vfast2_f;
+      if (st == ST_ALIVE) {
+        bool coll = false, capv = false;
+        if (do_mcc) {
+          const uint32_t id = P.id[p];
+          const uint4 r = philox4x32_10(id, *S.step, kColl, (uint32_t)S.sp, S.key0, S.key1);
+          if ((uint64_t)r.x < S.T_null) collide(S, id, v, coll, capv, p);
+        }
+        t_coll += coll;
+        t_cap += capv;
+        const int cn = pack_cell(ci, cj, ck);
+        enters = in_md(md, S.nx, S.ny, cn);
+        P.cell[p] = cn;
+        P.ox[p] = o[0];
+        P.oy[p] = o[1];
+        P.oz[p] = o[2];
+        deposit_global_fixed(rho, S, ci, cj, ck, o[0], o[1], o[2]);
+      } else {
+        P.cell[p] = -1;
       }
-      t_coll += coll;
-      t_cap += capv;
-      double part[8];
-      const int c = store_d(P, p, x, v, S, part);
-      Tile none{};
-      corner_add<double>(none, -1, nullptr, rho, S, cell_i(c), cell_j(c), cell_k(c), part);
-    } else {
-      kill(P, p);
       P.vx[p] = v[0];
       P.vy[p] = v[1];
       P.vz[p] = v[2];
+      t_w0 += st == ST_WALL0;
+      t_w1 += st == ST_WALL1;
+      t_bad += st == ST_BAD;
     }
-    t_w0 += st == ST_WALL0;
-    t_w1 += st == ST_WALL1;
-    t_bad += st == ST_BAD;
+    wave_append(enters, L.md_next, L.n_md_next, p);
   }
-  t_w0 = wave_sum(t_w0);
-  t_w1 = wave_sum(t_w1);
-  t_bad = wave_sum(t_bad);
-  t_coll = wave_sum(t_coll);
-  t_cap = wave_sum(t_cap);
-  t_fast = wave_sum(t_fast);
-  if (threadIdx.x == 0) {
-    unsigned long long* tl = L.tally + (long)TL_N * tidx;
-    tl[TL_W0] += t_w0;
-    tl[TL_W1] += t_w1;
-    tl[TL_BAD] += t_bad;
-    tl[TL_COLL] += t_coll;
-    tl[TL_CAP] += t_cap;
-    tl[TL_DEAD] += t_w0 + t_w1 + t_bad;
-    tl[TL_FAST] += t_fast;
+  outlier_tally(L, block0 * d->span, t_w0, t_w1, t_bad, t_coll, t_cap, t_fast);
+}
+__device__ __forceinline__ void outlier_block(const PIC_CONST PushDescF64* d, const PartF64& D, int do_mcc,
+                                              int block0, int nblocks) {
+  const PartF64 P = desc_records(d);
+  const auto& S = d->S;
+  const auto& L = d->L;
+  const auto& md = d->md;
+  const double2* __restrict__ E = d->E;
+  double* __restrict__ rho = d->rho;
+  const Segments sg = segments(L.out_cnt, L.tstart, block0, nblocks, d->span);
+  if (sg.total == 0) return;
+  int t_w0 = 0, t_w1 = 0, t_bad = 0, t_coll = 0, t_cap = 0, t_fast = 0;
+  for (int base = 0; base < sg.total; base += 64) {
+    const int idx = base + (int)threadIdx.x;
+    bool enters = false;
+    int p = segment_entry(sg, L.out, idx);
+    if (idx < sg.total && p < 0) {
+      p = ~p;
+      enters = slot_alive(D, p) && in_md(md, S.nx, S.ny, slot_cell(D, p));
+    } else if (idx < sg.total) {
+      double x[3], v[3];
+      load_d(P, p, x, v);
+      const int i0 = (int)floor(x[0]), j0 = (int)floor(x[1]), k0 = (int)floor(x[2]);
+      double Ep[3];
+      gather_d(E, S, i0, j0, k0, x[0] - i0, x[1] - j0, x[2] - k0, Ep);
+      const int st = push_one_f64(S, Ep, x, v);
+      t_fast += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] >= S.vfast2;
+      if (st == ST_ALIVE) {
+        bool coll = false, capv = false;
+        if (do_mcc) {
+          const uint32_t id = P.id[p];
+          const uint4 r = philox4x32_10(id, *S.step, kColl, (uint32_t)S.sp, S.key0, S.key1);
+          if ((uint64_t)r.x < S.T_null) collide(S, id, v, coll, capv, p);
+        }
+        t_coll += coll;
+        t_cap += capv;
+        double part[8];
+        const int c = store_d(P, p, x, v, S, part);
+        enters = in_md(md, S.nx, S.ny, c);
+        Tile none{};
+        corner_add<double>(none, -1, nullptr, rho, S, cell_i(c), cell_j(c), cell_k(c), part);
+      } else {
+        kill(P, p);
+        P.vx[p] = v[0];
+        P.vy[p] = v[1];
+        P.vz[p] = v[2];
+      }
+      t_w0 += st == ST_WALL0;
+      t_w1 += st == ST_WALL1;
+      t_bad += st == ST_BAD;
+    }
+    wave_append(enters, L.md_next, L.n_md_next, p);
   }
+  outlier_tally(L, block0 * d->span, t_w0, t_w1, t_bad, t_coll, t_cap, t_fast);
 }
 
 // ---------------------------------------------------------------- collisions
-// One wave per push block's segment of collision candidates (the push block
-// of `span` tiles lists them at its first tile).
-template <typename PT>
-__device__ __forceinline__ void collide_block(const PT& P, const SpeciesStep& S, const WorkLists& L,
-                                              int tidx) {
-  const int count = L.coll_cnt[tidx];
-  if (count == 0) return;
-  const int32_t* seg = L.coll + L.tstart[tidx];
+// The collision candidates that found no room in the LDS of their push block,
+// of `nblocks` push blocks from block0 (listed at the block's first tile).
+template <typename PT, typename H, typename WL>
+__device__ __forceinline__ void collide_block(const PT& P, const H& S, const WL& L, int block0,
+                                              int nblocks, int span) {
+  const Segments sg = segments(L.coll_cnt, L.tstart, block0, nblocks, span);
+  if (sg.total == 0) return;
   int n_coll = 0, n_cap = 0;
-  for (int idx = threadIdx.x; idx < count; idx += 64) {
-    const long p = seg[idx];
+  for (int base = 0; base < sg.total; base += 64) {
+    const int idx = base + (int)threadIdx.x;
+    const long p = segment_entry(sg, L.coll, idx);
+    if (idx >= sg.total) continue;
     bool coll = false, capv = false;
     typename VelOf<PT>::type v[3] = {P.vx[p], P.vy[p], P.vz[p]};
     collide(S, P.id[p], v, coll, capv, p);
@@ -2170,34 +2284,41 @@ __device__ __forceinline__ void collide_block(const PT& P, const SpeciesStep& S,
   n_coll = wave_sum(n_coll);
   n_cap = wave_sum(n_cap);
   if (threadIdx.x == 0) {
-    unsigned long long* tl = L.tally + (long)TL_N * tidx;
+    unsigned long long* tl = L.tally + (long)TL_N * (block0 * span);
     tl[TL_COLL] += (unsigned long long)n_coll;
     tl[TL_CAP] += (unsigned long long)n_cap;
   }
 }
-template <typename PT>
-__global__ __launch_bounds__(64) void collide_kernel(PT P, SpeciesStep S, WorkLists L, int span) {
-  collide_block(P, S, L, (int)blockIdx.x * span);
-}
 
-// Everything after one FP32R species' push in one launch: block b < npb takes
-// push block b's collision candidates and then its outliers (disjoint sets of
-// particles, one tally row), and the kMdListBlocks blocks after those copy the
-// MD particles' states back and collide them.
-constexpr int kMdListBlocks = 512;
-__global__ __launch_bounds__(64) void species_lists_f32r_kernel(SpeciesPair<PartF32R> pr,
-                                                                PartF32R D, const float4* E,
-                                                                long long* rho, int do_mcc, int sp,
-                                                                int npb, int md) {
-  const int b = (int)blockIdx.x;
-  if (b < npb) {
-    collide_block(pr.P[sp], pr.S[sp], pr.L[sp], b * pr.span);
-    outlier_block(pr, E, rho, do_mcc, sp, b);
-  } else if (md) {
-    SpeciesPair<PartF32R> pm = pr;
-    pm.nb = kMdListBlocks;  // the blocks' stride over the MD list (tally rows 0 .. 511)
-    md_collide_block(pm, D, sp, b - npb, 1, do_mcc);
+// Everything after the push in one launch, one wave a block: nbmd blocks a
+// species copy the MD particles' states back and collide them, `chunks` blocks
+// to each push block near the MD cubes list the next step's, and the rest take
+// the collision candidates and then the outliers of `group` push blocks each
+// (disjoint sets of particles, one tally row).
+template <typename PT, typename Desc>
+__global__ __launch_bounds__(64) void lists_kernel(const Desc* descs, PT D0, PT D1, int npb,
+                                                   int do_mcc, int nbmd, int near0, int near1,
+                                                   int group, int chunks) {
+  const PIC_CONST Desc* d = (const PIC_CONST Desc*)descs;
+  int b = (int)blockIdx.x;
+  if (b < 2 * nbmd) {
+    const int sp = b >= nbmd ? 1 : 0;
+    md_collide_block(d + sp, sp ? D1 : D0, b - sp * nbmd, nbmd, do_mcc);
+    return;
   }
+  b -= 2 * nbmd;
+  if (b < near0 + near1) {
+    const int sp = b >= near0 ? 1 : 0;
+    near_block(d + sp, sp ? D1 : D0, b - sp * near0, chunks);
+    return;
+  }
+  b -= near0 + near1;
+  const int groups = (npb + group - 1) / group;
+  const int sp = b >= groups ? 1 : 0;
+  const int block0 = (b - sp * groups) * group, n = min(group, npb - block0);
+  d += sp;
+  if (do_mcc) collide_block(desc_records(d), d->S, d->L, block0, n, d->span);
+  outlier_block(d, sp ? D1 : D0, do_mcc, block0, n);
 }
 
 // ---------------------------------------------------------------- loading
@@ -2424,6 +2545,10 @@ __device__ __forceinline__ int rec_key(const RecF32R& r, TileOrder o) {
   if (r.cell < 0) return -1;
   return tiled_key(cell_i(r.cell), cell_j(r.cell), cell_k(r.cell), o);
 }
+__device__ __forceinline__ int rec_cell(const RecF64& r) {
+  return pack_cell((int)floor(r.x), (int)floor(r.y), (int)floor(r.z));
+}
+__device__ __forceinline__ int rec_cell(const RecF32R& r) { return r.cell; }
 template <typename PT>
 struct RecOf;
 template <>
@@ -2480,13 +2605,16 @@ struct SortStage<RecF64, N> {
 
 template <typename PT>
 __global__ __launch_bounds__(256) void bin_scatter_kernel(PT src, PT dst, const int* __restrict__ cnt,
-                                                          int* __restrict__ cursor, TileOrder o) {
+                                                          int* __restrict__ cursor, TileOrder o,
+                                                          MdTables md, int nx, int ny,
+                                                          int32_t* __restrict__ md_list,
+                                                          int* __restrict__ n_md) {
   using Rec = typename RecOf<PT>::type;
   constexpr int kBins = kTable * 64;         // (table slot, cell in tile)
   constexpr int kPerThread = kBins / 256;    // bins scanned per thread
   __shared__ int s_tile[kTable], s_base[kTable];
   __shared__ int s_bin[kBins];
-  __shared__ int s_wsum[4];
+  __shared__ int s_wsum[4], s_mdbase;
   for (int i = threadIdx.x; i < kBins; i += 256) s_bin[i] = 0;
   if (threadIdx.x < kTable) s_tile[threadIdx.x] = -1;
   const int n = cnt[0];
@@ -2567,18 +2695,41 @@ __global__ __launch_bounds__(256) void bin_scatter_kernel(PT src, PT dst, const 
       s_stage.put(u, rec[r]);
       s_stage.dest[u] = s_base[slot[r]] + u;
     } else {
-      store_rec(dst, atomicAdd(&cursor[key[r] >> 6], 1), rec[r]);  // the table was full
+      const int j = atomicAdd(&cursor[key[r] >> 6], 1);  // the table was full
+      store_rec(dst, j, rec[r]);
+      if (in_md(md, nx, ny, rec_cell(rec[r]))) md_list[atomicAdd(n_md, 1)] = j;
     }
   }
   __syncthreads();
-  for (int u = threadIdx.x; u < total; u += 256) store_rec(dst, s_stage.dest[u], s_stage.get(u));
+  bool mine = false;  // any record of this thread that is in an MD cube
+  for (int u = threadIdx.x; u < total; u += 256) {
+    const Rec r = s_stage.get(u);
+    store_rec(dst, s_stage.dest[u], r);
+    if (md.n_grains > 0) mine = mine || in_md(md, nx, ny, rec_cell(r));
+  }
+  if (!__syncthreads_or(mine)) return;
+  // those listed in destination order, one reservation per 256 (most blocks have none)
+  for (int u0 = 0; u0 < total; u0 += 256) {
+    const int u = u0 + (int)threadIdx.x;
+    const bool in = u < total && in_md(md, nx, ny, rec_cell(s_stage.get(u)));
+    const unsigned long long m = __ballot(in);
+    __syncthreads();
+    if (lane == 0) s_wsum[w] = __popcll(m);
+    __syncthreads();
+    if (threadIdx.x == 0) s_mdbase = atomicAdd(n_md, s_wsum[0] + s_wsum[1] + s_wsum[2] + s_wsum[3]);
+    __syncthreads();
+    int at = s_mdbase + __popcll(m & ((1ull << lane) - 1ull));
+    for (int k = 0; k < w; ++k) at += s_wsum[k];
+    if (in) md_list[at] = s_stage.dest[u];
+  }
 }
 
 // t <= ngrid: the tile's size rounded up to a multiple of 4 (0 for the grid's
 // padding tiles and the end entry), scanned afterwards into the tile starts
 __global__ void tile_size_kernel(const int* __restrict__ tcount, int* __restrict__ tsize,
-                                 int ngrid) {
+                                 int ngrid, int* __restrict__ n_md) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t == 0) *n_md = 0;  // the scatter lists the MD particles anew
   if (t > ngrid) return;
   tsize[t] = t < ngrid ? (tcount[t] + 3) & ~3 : 0;
 }
@@ -2659,14 +2810,8 @@ __global__ void fill_int_kernel(int* a, long n, int v) {
 }
 
 // k -> k + 1 at the end of a step
-// the end of a step: the step counter advances and the dense MD lists start
-// empty for the next step
-__global__ void advance_step_kernel(uint32_t* step, int32_t* cnt0, int32_t* cnt1) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    *step += 1u;
-    cnt0[2] = 0;
-    cnt1[2] = 0;
-  }
+__global__ void advance_step_kernel(uint32_t* step) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) *step += 1u;
 }
 
 // ---------------------------------------------------------------- ionisation
@@ -2702,6 +2847,7 @@ __device__ __forceinline__ void copy_pos(const PartF32R& s, long p, const PartF3
 template <typename PT>
 __global__ __launch_bounds__(kIzThreads) void ionize_kernel(PT Pe, PT Pi, WorkLists Le,
                                                             WorkLists Li, SpeciesStep Se,
+                                                            MdTables md,
                                                             uint32_t* __restrict__ next_id,
                                                             long room_e, long room_i,
                                                             unsigned long long* dropped) {
@@ -2753,6 +2899,10 @@ __global__ __launch_bounds__(kIzThreads) void ionize_kernel(PT Pe, PT Pi, WorkLi
     Pi.vz[pi] = (V)(Se.vth_gas * n2);
     Pe.id[pe] = next_id[0] + (uint32_t)rank;
     Pi.id[pi] = next_id[1] + (uint32_t)rank;
+    if (in_md(md, Se.nx, Se.ny, slot_cell(Pe, ev.slot))) {
+      Le.md_next[atomicAdd(Le.n_md_next, 1)] = (int32_t)pe;
+      Li.md_next[atomicAdd(Li.n_md_next, 1)] = (int32_t)pi;
+    }
   }
   if (fit && (int)threadIdx.x < n4 - n) {
     kill(Pe, be + n + threadIdx.x);
@@ -2829,122 +2979,105 @@ int tile_grid(int nx, int ny, int nz, int extra) {
 }
 
 
-void launch_advance_step(uint32_t* step, int32_t* cnt0, int32_t* cnt1, hipStream_t st) {
-  hipLaunchKernelGGL(advance_step_kernel, dim3(1), dim3(64), 0, st, step, cnt0, cnt1);
+void launch_advance_step(uint32_t* step, hipStream_t st) {
+  hipLaunchKernelGGL(advance_step_kernel, dim3(1), dim3(64), 0, st, step);
 }
 
-void launch_push_f64(const PartF64& P, const double* E, double* rho, const MdTables& md,
-                     const SpeciesStep& S, const WorkLists& L, hipStream_t st) {
+void launch_push(const PushDescF64* descs, const WorkLists& L, bool move, hipStream_t st) {
   if (L.ngrid <= 0) return;
-  hipLaunchKernelGGL(push_f64_kernel<true>, dim3(L.ngrid), dim3(kBlock), 0, st, P,
-                     (const double2*)E, rho, md, S, L, push_chunk(L, 1));
+  const int span = push_span(L), nb = L.ngrid / span, chunk = push_chunk(L, span);
+  if (move)
+    hipLaunchKernelGGL(push_f64_kernel<true>, dim3(2 * nb), dim3(kBlock), 0, st, descs, nb, span, chunk);
+  else
+    hipLaunchKernelGGL(push_f64_kernel<false>, dim3(2 * nb), dim3(kBlock), 0, st, descs, nb, span, chunk);
 }
-
-void launch_push_f32r(const PartF32R& P, const float* E, long long* rho, const MdTables& md,
-                      const SpeciesStep& S, const WorkLists& L, hipStream_t st) {
+void launch_push(const PushDescF32* descs, const WorkLists& L, bool move, hipStream_t st) {
   if (L.ngrid <= 0) return;
-  const int span = push_span(L);
-  hipLaunchKernelGGL(push_f32r_kernel<true>, dim3(L.ngrid / span), dim3(kBlock), 0, st, P,
-                     (const float4*)E, rho, md, S, L, span, push_chunk(L, span));
+  const int span = push_span(L), nb = L.ngrid / span, chunk = push_chunk(L, span);
+  if (move)
+    hipLaunchKernelGGL(push_f32r_kernel<true>, dim3(2 * nb), dim3(kBlock), 0, st, descs, nb, span, chunk);
+  else
+    hipLaunchKernelGGL(push_f32r_kernel<false>, dim3(2 * nb), dim3(kBlock), 0, st, descs, nb, span, chunk);
 }
 
-void launch_push_batch_f32r(const PushDescF32* descs, const int32_t* start, int ndesc, int grid,
-                            int* queue, hipStream_t st) {
-  if (ndesc <= 0 || grid <= 0) return;
-  launch_zero_i32(queue, 8, st);
-  hipLaunchKernelGGL(push_batch_f32r_kernel, dim3(grid), dim3(kBlock), 0, st, descs, start, ndesc,
-                     queue);
+void launch_push_batch_f32r(const PushDescF32* descs, const int32_t* start, int ndesc, int items,
+                            hipStream_t st) {
+  if (ndesc <= 0 || items <= 0) return;
+  hipLaunchKernelGGL(push_batch_f32r_kernel, dim3(items), dim3(kBlock), 0, st, descs, start, ndesc);
 }
 
 constexpr int kMdBlocks = kMdTallyRows;
 
 void launch_field_out(const double* psi, double* phi, void* E, int e_f64,
                       unsigned long long* zero_next, const double* b, double* partials,
-                      const MdTables& md, int nx, int ny, int nz, double dx, RfDrive rf,
-                      hipStream_t st) {
+                      const MdTables& md, const WorkLists L[2], int nx, int ny, int nz, double dx,
+                      RfDrive rf, hipStream_t st) {
   const long nn = (long)nx * ny * (nz + 1);
   const int nbe = (int)field_out_sums(nn);
   const int nbm = md.n_grains > 0 ? nblk(8L * md.bsx * md.bsy * md.bsz, 256) : 0;
   if (e_f64)
     hipLaunchKernelGGL(field_out_kernel<double2>, dim3(nbe + nbm), dim3(256), 0, st, psi, phi,
-                       (double2*)E, zero_next, b, partials, md, nx, ny, nz, dx, rf, nbm);
+                       (double2*)E, zero_next, b, partials, md, L[0].n_md_next, L[1].n_md_next, nx, ny,
+                       nz, dx, rf, nbm);
   else
     hipLaunchKernelGGL(field_out_kernel<float4>, dim3(nbe + nbm), dim3(256), 0, st, psi, phi,
-                       (float4*)E, zero_next, b, partials, md, nx, ny, nz, dx, rf, nbm);
+                       (float4*)E, zero_next, b, partials, md, L[0].n_md_next, L[1].n_md_next, nx, ny,
+                       nz, dx, rf, nbm);
 }
 
-void launch_collide_f64(const PartF64& P, const SpeciesStep& S, const WorkLists& L,
-                        hipStream_t st) {
-  if (L.ngrid > 0)
-    hipLaunchKernelGGL(collide_kernel<PartF64>, dim3(L.ngrid), dim3(64), 0, st, P, S, L, 1);
-}
-
-void launch_collide_f32r(const PartF32R& P, const SpeciesStep& S, const WorkLists& L,
-                         hipStream_t st) {
-  if (L.ngrid > 0)
-    hipLaunchKernelGGL(collide_kernel<PartF32R>, dim3(L.ngrid / push_span(L)), dim3(64), 0, st, P,
-                       S, L, push_span(L));
-}
-
-void launch_lists_f64(const PartF64 P[2], const double* E, double* rho, const MdTables& md,
-                      const SpeciesStep S[2], unsigned long long* gc, const WorkLists L[2],
-                      int do_mcc, hipStream_t st) {
-  if (L[0].ngrid <= 0) return;
-  SpeciesPair<PartF64> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, L[0].ngrid, 1};
-  hipLaunchKernelGGL(outlier_f64_kernel, dim3(2 * pr.nb), dim3(64), 0, st, pr, (const double2*)E,
-                     rho, do_mcc);
-  if (md.n_grains > 0) {
-    pr.nb = kMdBlocks;
-    hipLaunchKernelGGL((md_kernel<PartF64, double2, double>), dim3(2 * kMdBlocks), dim3(kMdThreads),
-                       0, st, pr, P[0], P[1], (const double2*)E, rho, md, gc);
-    if (do_mcc)
-      hipLaunchKernelGGL(md_collide_kernel<PartF64>, dim3(2 * kMdBlocks), dim3(kMdThreads), 0, st,
-                         pr, P[0], P[1], 0, 1, -1);
-  }
-}
-
-void launch_md_scan_f32r(const PartF32R P[2], const WorkLists L[2], const MdTables& md,
-                         const SpeciesStep S[2], int nx, int ny, int nz, hipStream_t st) {
+template <typename PT, typename ET, typename RT>
+static void md_move_impl(const PT P[2], const PT D[2], const void* E, void* rho, const MdTables& md,
+                         const SpeciesStep S[2], unsigned long long* gc, const WorkLists L[2],
+                         int span, hipStream_t st) {
   if (md.n_grains == 0 || L[0].ngrid <= 0) return;
-  const int span = push_span(L[0]), npb = L[0].ngrid / span;
-  hipLaunchKernelGGL(md_scan_kernel, dim3(2 * npb), dim3(256), 0, st, P[0], P[1], L[0], L[1], md,
-                     nx, ny, nz, S[0].margin, S[1].margin, span, npb);
+  SpeciesPair<PT> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, kMdBlocks, span};
+  hipLaunchKernelGGL((md_kernel<PT, ET, RT>), dim3(2 * kMdBlocks), dim3(kMdThreads), 0, st, pr,
+                     D[0], D[1], (const ET*)E, (RT*)rho, md, gc);
+}
+void launch_md_move(const PartF64 P[2], const PartF64 D[2], const void* E, void* rho,
+                    const MdTables& md, const SpeciesStep S[2], unsigned long long* gc,
+                    const WorkLists L[2], hipStream_t st) {
+  md_move_impl<PartF64, double2, double>(P, D, E, rho, md, S, gc, L, push_span(L[0]), st);
+}
+void launch_md_move(const PartF32R P[2], const PartF32R D[2], const void* E, void* rho,
+                    const MdTables& md, const SpeciesStep S[2], unsigned long long* gc,
+                    const WorkLists L[2], hipStream_t st) {
+  md_move_impl<PartF32R, float4, long long>(P, D, E, rho, md, S, gc, L, push_span(L[0]), st);
 }
 
-void launch_md_move_f32r(const PartF32R P[2], const PartF32R D[2], const float* E,
-                         long long* rho, const MdTables& md, const SpeciesStep S[2],
-                         unsigned long long* gc, const WorkLists L[2], hipStream_t st) {
-  if (md.n_grains == 0 || L[0].ngrid <= 0) return;
-  SpeciesPair<PartF32R> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, kMdBlocks, push_span(L[0])};
-  hipLaunchKernelGGL((md_kernel<PartF32R, float4, long long>), dim3(2 * kMdBlocks),
-                     dim3(kMdThreads), 0, st, pr, D[0], D[1], (const float4*)E, rho, md, gc);
+std::vector<int32_t> near_blocks(const WorkLists& L, const MdTables& md, int nx, int ny, int nz,
+                                 int margin, bool f64) {
+  std::vector<int32_t> v;
+  const int span = push_span(L);
+  for (int t = 0; md.n_grains > 0 && t < L.ngrid; t += span)
+    if (window_meets_md(make_tile(t, L, nx, ny, nz, margin, f64 ? kWinF64 : kWinF32, span), md, nx, ny))
+      v.push_back(t);
+  return v;
 }
 
-void launch_species_lists_f32r(const PartF32R P[2], const PartF32R D[2], const float* E,
-                               long long* rho, const MdTables& md, const SpeciesStep S[2],
-                               const WorkLists L[2], int do_mcc, int sp, hipStream_t st) {
+constexpr int kMdListBlocks = 512;  // per species (tally rows 0 .. 511 of the MD rows)
+template <typename PT, typename Desc>
+static void lists_impl(const Desc* descs, const PT D[2], bool grains, const WorkLists L[2],
+                       int do_mcc, hipStream_t st) {
   if (L[0].ngrid <= 0) return;
-  const int span = push_span(L[0]), npb = L[0].ngrid / span;
-  SpeciesPair<PartF32R> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, npb, span};
-  const int md_on = md.n_grains > 0 ? 1 : 0;
-  hipLaunchKernelGGL(species_lists_f32r_kernel, dim3(npb + md_on * kMdListBlocks), dim3(64), 0,
-                     st, pr, D[sp], (const float4*)E, rho, do_mcc, sp, npb, md_on);
+  const int npb = L[0].ngrid / push_span(L[0]), nbmd = grains ? kMdListBlocks : 0;
+  // waves per near push block: its slots if the particles were spread evenly
+  const long slots = L[0].slots / std::max(1, npb);
+  const int chunks = (int)std::min<long>(64, std::max<long>(1, (slots + kNearSlots - 1) / kNearSlots));
+  // push blocks per wave: about 4,096 waves a species (more than the chip holds
+  // at once), so a wave has some entries to pack
+  const int group = std::min(64, std::max(1, npb / 4096)), groups = (npb + group - 1) / group;
+  const int n0 = L[0].n_near * chunks, n1 = L[1].n_near * chunks;
+  hipLaunchKernelGGL((lists_kernel<PT, Desc>), dim3(2 * nbmd + n0 + n1 + 2 * groups), dim3(64), 0, st,
+                     descs, D[0], D[1], npb, do_mcc, nbmd, n0, n1, group, chunks);
 }
-
-void launch_lists_f32r(const PartF32R P[2], const PartF32R D[2], const float* E, long long* rho,
-                       const MdTables& md, const SpeciesStep S[2], const WorkLists L[2],
-                       int do_mcc, int sp_only, hipStream_t st) {
-  if (L[0].ngrid <= 0) return;
-  const int span = push_span(L[0]);
-  const int ns = sp_only >= 0 ? 1 : 2;
-  SpeciesPair<PartF32R> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, L[0].ngrid / span, span};
-  hipLaunchKernelGGL(outlier_f32r_kernel, dim3(ns * pr.nb), dim3(64), 0, st, pr, (const float4*)E,
-                     rho, do_mcc, sp_only);
-  if (md.n_grains > 0) {
-    pr.nb = kMdBlocks;
-    hipLaunchKernelGGL(md_collide_kernel<PartF32R>, dim3(ns * kMdBlocks), dim3(kMdThreads), 0, st,
-                       pr, D[0], D[1], 1, do_mcc, sp_only);
-  }
+void launch_lists(const PushDescF64* descs, const PartF64 D[2], bool grains, const WorkLists L[2],
+                  int do_mcc, hipStream_t st) {
+  lists_impl(descs, D, grains, L, do_mcc, st);
+}
+void launch_lists(const PushDescF32* descs, const PartF32R D[2], bool grains, const WorkLists L[2],
+                  int do_mcc, hipStream_t st) {
+  lists_impl(descs, D, grains, L, do_mcc, st);
 }
 
 void launch_init_f64(const PartF64& P, int n, int ppc, int nx, int ny, int sp, uint32_t k0,
@@ -2959,21 +3092,6 @@ void launch_init_f32r(const PartF32R& P, int n, int ppc, int nx, int ny, int sp,
   if (n <= 0) return;
   hipLaunchKernelGGL(init_f32r_kernel, dim3(nblk(n, 256)), dim3(256), 0, st, P, n, ppc, nx, ny, sp,
                      k0, k1, vth);
-}
-
-void launch_deposit_f64(const PartF64& P, double* rho, const MdTables& md, const SpeciesStep& S,
-                        const WorkLists& L, hipStream_t st) {
-  if (L.ngrid <= 0) return;
-  hipLaunchKernelGGL(push_f64_kernel<false>, dim3(L.ngrid), dim3(kBlock), 0, st, P, nullptr, rho,
-                     md, S, L, push_chunk(L, 1));
-}
-
-void launch_deposit_f32r(const PartF32R& P, long long* rho, const MdTables& md,
-                         const SpeciesStep& S, const WorkLists& L, hipStream_t st) {
-  if (L.ngrid <= 0) return;
-  const int span = push_span(L);
-  hipLaunchKernelGGL(push_f32r_kernel<false>, dim3(L.ngrid / span), dim3(kBlock), 0, st, P,
-                     nullptr, rho, md, S, L, span, push_chunk(L, span));
 }
 
 void launch_moments(const PartF64* P64, const PartF32R* P32, const SpeciesStep& S,
@@ -3003,14 +3121,14 @@ void launch_fine_moments(const PartF64* P64, const PartF32R* P32, const WorkList
 
 void launch_ionize(const PartF64* Pe64, const PartF64* Pi64, const PartF32R* Pe32,
                    const PartF32R* Pi32, const WorkLists& Le, const WorkLists& Li,
-                   const SpeciesStep& Se, uint32_t* next_id, long room_e, long room_i,
-                   unsigned long long* dropped, hipStream_t st) {
+                   const SpeciesStep& Se, const MdTables& md, uint32_t* next_id, long room_e,
+                   long room_i, unsigned long long* dropped, hipStream_t st) {
   if (Pe64)
     hipLaunchKernelGGL(ionize_kernel<PartF64>, dim3(1), dim3(kIzThreads), 0, st, *Pe64, *Pi64, Le,
-                       Li, Se, next_id, room_e, room_i, dropped);
+                       Li, Se, md, next_id, room_e, room_i, dropped);
   else
     hipLaunchKernelGGL(ionize_kernel<PartF32R>, dim3(1), dim3(kIzThreads), 0, st, *Pe32, *Pi32, Le,
-                       Li, Se, next_id, room_e, room_i, dropped);
+                       Li, Se, md, next_id, room_e, room_i, dropped);
 }
 
 int energy_blocks() { return kEnergyBlocks; }
@@ -3042,8 +3160,9 @@ void launch_fill_int(int* a, long n, int v, hipStream_t st) {
 long sort_keys(int ngrid) { return 2L * ngrid + 1; }
 
 template <typename PT>
-static void sort_impl(const PT& src, const PT& dst, const WorkLists& L, int* hist, int* sums,
-                      long capacity, hipStream_t st) {
+static void sort_impl(const PT& src, const PT& dst, const WorkLists& L, const MdTables& md, int nx,
+                      int ny, int32_t* md_list, int* n_md, int* hist, int* sums, long capacity,
+                      hipStream_t st) {
   const TileOrder o{L.ntx, L.nty};
   const int ng = L.ngrid;
   int* tcount = hist;            // [ngrid + 1]
@@ -3052,7 +3171,8 @@ static void sort_impl(const PT& src, const PT& dst, const WorkLists& L, int* his
   hipLaunchKernelGGL(bin_count_kernel<PT>, dim3(nblk(capacity, kSortSlots)), dim3(256), 0, st, src,
                      L.cnt, tcount, o);
   const int n = ng + 1;
-  hipLaunchKernelGGL(tile_size_kernel, dim3(nblk(n, 256)), dim3(256), 0, st, tcount, L.tstart, ng);
+  hipLaunchKernelGGL(tile_size_kernel, dim3(nblk(n, 256)), dim3(256), 0, st, tcount, L.tstart, ng,
+                     n_md);
   const int nb = nblk(n, kScanBlock);
   hipLaunchKernelGGL(scan_block_sums, dim3(nb), dim3(kScanBlock), 0, st, L.tstart, n, sums);
   hipLaunchKernelGGL(scan_sums_serial, dim3(1), dim3(kScanBlock), 0, st, sums, nb, L.cnt + 4);
@@ -3061,21 +3181,19 @@ static void sort_impl(const PT& src, const PT& dst, const WorkLists& L, int* his
                      cursor, dst, ng);
   hipLaunchKernelGGL(bin_scatter_kernel<PT>, dim3(nblk(capacity, 256 * scatter_rounds<PT>())),
                      dim3(256), 0, st,
-                     src, dst, L.cnt, cursor, o);
+                     src, dst, L.cnt, cursor, o, md, nx, ny, md_list, n_md);
   hipLaunchKernelGGL(sort_finish_kernel, dim3(1), dim3(64), 0, st, L.cnt, L.tstart, ng);
 }
 
-void launch_sort_f64(const PartF64& src, const PartF64& dst, const WorkLists& L, int* hist,
-                     int* sums, long capacity, hipStream_t st) {
-  if (capacity <= 0) return;
-  sort_impl(src, dst, L, hist, sums, capacity, st);
+void launch_sort(const PartF64& src, const PartF64& dst, const WorkLists& L, const MdTables& md,
+                 int nx, int ny, int32_t* md_list, int* n_md, int* hist, int* sums, long capacity,
+                 hipStream_t st) {
+  if (capacity > 0) sort_impl(src, dst, L, md, nx, ny, md_list, n_md, hist, sums, capacity, st);
 }
-
-void launch_sort_f32r(const PartF32R& src, const PartF32R& dst, const WorkLists& L, int* hist,
-                      int* sums, long capacity, hipStream_t st) {
-  if (capacity <= 0) return;
-  sort_impl(src, dst, L, hist, sums, capacity, st);
-  launch_zero_i32(L.stray, L.ngrid, st);  // every particle is in its own tile again
+void launch_sort(const PartF32R& src, const PartF32R& dst, const WorkLists& L, const MdTables& md,
+                 int nx, int ny, int32_t* md_list, int* n_md, int* hist, int* sums, long capacity,
+                 hipStream_t st) {
+  if (capacity > 0) sort_impl(src, dst, L, md, nx, ny, md_list, n_md, hist, sums, capacity, st);
 }
 
 }  // namespace pic

@@ -66,6 +66,7 @@ struct Replica {
   int ntiles = 0, ngrid = 0;
   int* d_cnt = nullptr;  // [species][8]: see WorkLists
   WorkLists lists[2]{};
+  int32_t* md_list[2][2]{};  // [species][rho phase]: the dense MD lists (see lists_of)
   // mesh
   void* rho[2]{};      // accumulators: double (units w e) or int64 (2^-32 e)
   int rho_cur = 0;
@@ -131,6 +132,9 @@ struct Replica {
   uint32_t step = 0;       // host mirror of *d_step
   uint32_t* d_step = nullptr;
   int margin[2]{2, 1};     // LDS window margin of the push per species (cells)
+  // the push's descriptors: two species for each of the 8 buffer phases
+  PushDescF64* push64 = nullptr;
+  PushDescF32* push32 = nullptr;
   DevMem mem;
 };
 
@@ -151,14 +155,9 @@ struct pic_ctx {
   int since_sort[2]{};
   // captured steps, by phase (see step_all)
   hipStream_t capture_stream = nullptr;
-  // a second stream for the ions' push and collisions in a one-replica step
-  // (fork and join events around them on the step's stream)
-  hipStream_t species_stream = nullptr;
-  hipEvent_t species_fork = nullptr, species_join = nullptr;
-  // FP32R MD particles beside the field solve and the push (one replica)
+  // the MD particles beside the push (one replica)
   hipStream_t md_stream = nullptr;
   hipEvent_t md_fork = nullptr, md_join = nullptr;
-  hipEvent_t md_scanned = nullptr, md_fields = nullptr;
   // replicas stepped one by one are spread over worker streams (default
   // priority), forked from and joined back into the caller's stream
   std::vector<hipStream_t> workers;
@@ -176,7 +175,7 @@ struct pic_ctx {
   int ndesc = 0;
   PushDescF32* d_desc = nullptr;
   int32_t* d_start = nullptr;
-  int* d_queue = nullptr;  // the persistent push's 8 work queues
+  int batch_items = 0;     // push blocks in all
   int n_cu = 256;
   // device of the context, and whether the fixed scratch array of
   // pic_fields_static has its address resolved there
@@ -196,20 +195,14 @@ struct pic_ctx {
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
     drop_graphs();
     if (capture_stream) (void)hipStreamDestroy(capture_stream);
-    if (species_stream) (void)hipStreamDestroy(species_stream);
-    if (species_fork) (void)hipEventDestroy(species_fork);
-    if (species_join) (void)hipEventDestroy(species_join);
     if (md_stream) (void)hipStreamDestroy(md_stream);
     if (md_fork) (void)hipEventDestroy(md_fork);
     if (md_join) (void)hipEventDestroy(md_join);
-    if (md_scanned) (void)hipEventDestroy(md_scanned);
-    if (md_fields) (void)hipEventDestroy(md_fields);
     for (hipStream_t w : workers) (void)hipStreamDestroy(w);
     if (fork_ev) (void)hipEventDestroy(fork_ev);
     for (hipEvent_t e : join_ev) (void)hipEventDestroy(e);
     if (d_desc) (void)hipFree(d_desc);
     if (d_start) (void)hipFree(d_start);
-    if (d_queue) (void)hipFree(d_queue);
   }
 };
 
@@ -703,18 +696,18 @@ int alloc_particles(pic_ctx* ctx, Replica& R) {
     L.nty = (R.ny + 3) / 4;
     L.ntz = (R.nz + 3) / 4;
     L.ngrid = R.ngrid;
-    TRY(dalloc(ctx, R, &L.md, R.cap[sp]));
+    for (int ph = 0; ph < 2; ++ph) TRY(dalloc(ctx, R, &R.md_list[sp][ph], R.cap[sp]));
     TRY(dalloc(ctx, R, &L.coll, R.cap[sp]));
     TRY(dalloc(ctx, R, &L.out, R.cap[sp]));
+    TRY(dalloc(ctx, R, &L.mask, R.cap[sp] / 4));
+    L.slots = (int)R.cap[sp];
     TRY(dalloc(ctx, R, &L.coll_cnt, R.ngrid));
     TRY(dalloc(ctx, R, &L.out_cnt, R.ngrid));
     TRY(dalloc(ctx, R, &L.tstart, R.ngrid + 1));
     TRY(dalloc(ctx, R, &L.tally, TL_N * (R.ngrid + kMdTallyRows)));
-    TRY(dalloc(ctx, R, &L.stray, R.ngrid));
     L.cnt = R.d_cnt + 8 * sp;
     HIPCHK(ctx, hipMemsetAsync(L.tally, 0, 8 * TL_N * (R.ngrid + kMdTallyRows), ctx->stream));
     HIPCHK(ctx, hipMemsetAsync(L.tstart, 0, 4 * (R.ngrid + 1), ctx->stream));
-    HIPCHK(ctx, hipMemsetAsync(L.stray, 0, 4 * R.ngrid, ctx->stream));
   }
   return PIC_OK;
 }
@@ -736,20 +729,97 @@ void prof_pair(pic_ctx* ctx, int cls, hipEvent_t a, hipEvent_t b) {
   if (a && b) ctx->ev_pairs[cls].push_back({a, b});
 }
 
+// the work lists of a species in a step that starts in rho phase `ph`: list ph
+// holds the particles that start it in an MD cube, the other one is appended
+WorkLists lists_at(const Replica& R, int sp, int ph) {
+  WorkLists L = R.lists[sp];
+  L.md = R.md_list[sp][ph];
+  L.md_next = R.md_list[sp][1 - ph];
+  L.n_md = L.cnt + 2 + ph;
+  L.n_md_next = L.cnt + 2 + (1 - ph);
+  return L;
+}
+WorkLists lists_of(const Replica& R, int sp) { return lists_at(R, sp, R.rho_cur); }
+
+// lists the push blocks near the MD cubes for the species' window margins
+int setup_near(pic_ctx* ctx, Replica& R) {
+  for (int sp = 0; sp < 2; ++sp) {
+    WorkLists& L = R.lists[sp];
+    const std::vector<int32_t> v =
+        near_blocks(L, R.md, R.nx, R.ny, R.nz, R.margin[sp], R.prec == PIC_FP64);
+    int32_t* d = const_cast<int32_t*>(L.near);
+    if (!d) TRY(dalloc(ctx, R, &d, R.ngrid));
+    L.near = d;
+    L.n_near = (int)v.size();
+    if (!v.empty()) HIPCHK(ctx, hipMemcpy(d, v.data(), v.size() * 4, hipMemcpyHostToDevice));
+  }
+  return PIC_OK;
+}
+
+// the species' current and other record buffers of a replica
+void buffers(const Replica& R, PartF64 P[2], PartF64 D[2]) {
+  for (int sp = 0; sp < 2; ++sp) {
+    P[sp] = R.p64[sp][R.cur[sp]];
+    D[sp] = R.p64[sp][1 - R.cur[sp]];
+  }
+}
+void buffers(const Replica& R, PartF32R P[2], PartF32R D[2]) {
+  for (int sp = 0; sp < 2; ++sp) {
+    P[sp] = R.p32[sp][R.cur[sp]];
+    D[sp] = R.p32[sp][1 - R.cur[sp]];
+  }
+}
+
+// Buffer phase of a replica: which particle buffer each species uses and
+// which rho buffer holds rho_k.  A step is fully described by the phase and
+// the species sorted at its end (bit sp of `sorts`).
+int phase_of(const Replica& R) { return R.cur[0] | (R.cur[1] << 1) | (R.rho_cur << 2); }
+
+PartF64 records(const PartF64*, const Replica& R, int sp, int buf) { return R.p64[sp][buf]; }
+PartF32R records(const PartF32R*, const Replica& R, int sp, int buf) { return R.p32[sp][buf]; }
+
+// the push of species sp from buffer phase ph: into the rho buffer that ph does not hold
+template <typename PT, typename ET, typename RT>
+PushDesc<PT, ET, RT> push_desc(const Replica& R, int sp, int ph) {
+  PushDesc<PT, ET, RT> d{};
+  d.P = records((const PT*)nullptr, R, sp, (ph >> sp) & 1);
+  d.E = (const ET*)R.E;
+  d.rho = (RT*)R.rho[1 - ((ph >> 2) & 1)];
+  d.md = R.md;
+  d.S = species_step(R, sp);
+  d.L = lists_at(R, sp, (ph >> 2) & 1);
+  d.span = push_span(R.lists[sp]);
+  d.chunk = push_chunk(R.lists[sp], d.span);
+  return d;
+}
+template <typename PT, typename ET, typename RT>
+int build_push_form(pic_ctx* ctx, Replica& R, PushDesc<PT, ET, RT>** out) {
+  std::vector<PushDesc<PT, ET, RT>> h;
+  for (int ph = 0; ph < 8; ++ph)
+    for (int sp = 0; sp < 2; ++sp) h.push_back(push_desc<PT, ET, RT>(R, sp, ph));
+  if (!*out) TRY(dalloc(ctx, R, out, h.size()));
+  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  HIPCHK(ctx, hipMemcpy(*out, h.data(), h.size() * sizeof(h[0]), hipMemcpyHostToDevice));
+  return PIC_OK;
+}
+// (re)builds the push's descriptors of a replica (after loading, and when the
+// window margins change)
+int build_push(pic_ctx* ctx, Replica& R) {
+  if (R.prec == PIC_FP64) return build_push_form<PartF64, double2, double>(ctx, R, &R.push64);
+  return build_push_form<PartF32R, float4, long long>(ctx, R, &R.push32);
+}
+const PushDescF64* descs_of(const PartF64*, const Replica& R) { return R.push64 + 2 * phase_of(R); }
+const PushDescF32* descs_of(const PartF32R*, const Replica& R) { return R.push32 + 2 * phase_of(R); }
+// the push from buffer phase ph
+void push(const Replica& R, int ph, bool move, hipStream_t st) {
+  if (R.prec == PIC_FP64) launch_push(R.push64 + 2 * ph, R.lists[0], move, st);
+  else launch_push(R.push32 + 2 * ph, R.lists[0], move, st);
+}
+
 // rho_cur <- deposit of the current particles (used after loading or set_state)
 int deposit_current(pic_ctx* ctx, Replica& R) {
-  hipStream_t st = ctx->stream;
-  if (R.prec == PIC_FP64) {
-    launch_zero_f64((double*)R.rho[R.rho_cur], R.nn, st);
-    for (int sp = 0; sp < 2; ++sp)
-      launch_deposit_f64(R.p64[sp][R.cur[sp]], (double*)R.rho[R.rho_cur], R.md,
-                         species_step(R, sp), R.lists[sp], st);
-  } else {
-    launch_zero_i64((long long*)R.rho[R.rho_cur], R.nn, st);
-    for (int sp = 0; sp < 2; ++sp)
-      launch_deposit_f32r(R.p32[sp][R.cur[sp]], (long long*)R.rho[R.rho_cur], R.md,
-                          species_step(R, sp), R.lists[sp], st);
-  }
+  launch_zero_i64((long long*)R.rho[R.rho_cur], R.nn, ctx->stream);  // 8-byte words, 0 = 0.0
+  push(R, phase_of(R) ^ 4, false, ctx->stream);
   CHECK_LAUNCH(ctx);
   return PIC_OK;
 }
@@ -764,11 +834,8 @@ RefineState refine_state(const Replica& R) {
 // step's deposit of rho_{k+1}
 // final_pending (FP32R): when given, the residual after the last refinement
 // sweep and its test may be left to the caller (*final_pending tells), who
-// launches them with launch_refine_final on another stream.  first_done
-// (FP32R, may be null): recorded on the stream after the right-hand side's
-// kernel, so that other work can start beside the rest of the solve.
-int solve_fields(pic_ctx* ctx, Replica& R, bool zero_next = false,
-                 bool* final_pending = nullptr, hipEvent_t first_done = nullptr) {
+// launches them with launch_refine_final on another stream.
+int solve_fields(pic_ctx* ctx, Replica& R, bool zero_next = false, bool* final_pending = nullptr) {
   hipStream_t st = ctx->stream;
   const pic_config& c = R.cfg;
   const RfDrive rf{c.V_dc, c.V_rf, c.f_rf, c.dt, R.d_step};
@@ -800,25 +867,22 @@ int solve_fields(pic_ctx* ctx, Replica& R, bool zero_next = false,
     a.Q = R.d_Q;
     a.psi = R.psi;
     a.b = R.b;
-    int rc = 0;
     launch_spectral_solve(R.plan, a, f64 ? kRhsRho64 : kRhsFixed, R.work, R.inv,
-                          f64 ? RefineState{} : refine_state(R), st, first_done, &rc);
-    if (rc != 0) return fail(ctx, PIC_EDEVICE, "event record in the field solve failed");
+                          f64 ? RefineState{} : refine_state(R), st);
     if (final_pending) *final_pending = false;
     R.final_pending = !f64;
   } else {
     const double scale = -c.dx * c.dx / kEps0 * (kCharge / 4294967296.0 / vol);
     const RhsArgs ra{(const long long*)R.rho[R.rho_cur], scale, R.d_gtab, R.n_gtab, R.d_gc,
                      c.n_grains, R.we, R.d_Q};
-    const int deferred = launch_rhs_solve_refined(
+    const bool deferred = launch_rhs_solve_refined(
         ra, R.fft, R.nx, R.ny, R.nz, R.b, R.psi, R.r, R.work32, R.tw_x32, R.tw_y32, R.inv_full,
-        c.max_refine, c.refine_tol, R.norms, R.refine_ctl, st, final_pending != nullptr,
-        first_done);
-    if (deferred < 0) return fail(ctx, PIC_EDEVICE, "event record in the field solve failed");
-    if (final_pending) *final_pending = deferred != 0;
+        c.max_refine, c.refine_tol, R.norms, R.refine_ctl, st, final_pending != nullptr);
+    if (final_pending) *final_pending = deferred;
   }
   const bool sums = R.prec != PIC_FP64 && !R.sweeps32;
-  launch_field_out(R.psi, R.phi, R.E, R.prec == PIC_FP64, next, sums ? R.b : nullptr, R.norms + 2, R.md,
+  const WorkLists L[2] = {lists_of(R, 0), lists_of(R, 1)};
+  launch_field_out(R.psi, R.phi, R.E, R.prec == PIC_FP64, next, sums ? R.b : nullptr, R.norms + 2, R.md, L,
                    R.nx, R.ny, R.nz, c.dx, rf, st);
   CHECK_LAUNCH(ctx);
   return PIC_OK;
@@ -836,15 +900,18 @@ int flush_final(pic_ctx* ctx, Replica& R) {
 }
 
 // counting sort of one species into its other buffer (drops empty slots,
-// restores the tile order), launched on ctx->stream; the caller flips cur
-int enqueue_sort(pic_ctx* ctx, Replica& R, int sp) {
-  const int c = R.cur[sp], o = 1 - c;
+// restores the tile order), launched on ctx->stream; the caller flips cur.  The
+// MD list rebuilt is the next step's (at the end of a step) or, with `now`, the
+// one of a step from the present state.
+int enqueue_sort(pic_ctx* ctx, Replica& R, int sp, bool now = false) {
+  const int c = R.cur[sp], o = 1 - c, ph = now ? R.rho_cur : 1 - R.rho_cur;
+  const WorkLists L = lists_at(R, sp, ph);
   if (R.prec == PIC_FP64)
-    launch_sort_f64(R.p64[sp][c], R.p64[sp][o], R.lists[sp], R.d_hist, R.d_sums, R.cap[sp],
-                    ctx->stream);
+    launch_sort(R.p64[sp][c], R.p64[sp][o], L, R.md, R.nx, R.ny, L.md, L.n_md, R.d_hist, R.d_sums,
+                R.cap[sp], ctx->stream);
   else
-    launch_sort_f32r(R.p32[sp][c], R.p32[sp][o], R.lists[sp], R.d_hist, R.d_sums, R.cap[sp],
-                     ctx->stream);
+    launch_sort(R.p32[sp][c], R.p32[sp][o], L, R.md, R.nx, R.ny, L.md, L.n_md, R.d_hist, R.d_sums,
+                R.cap[sp], ctx->stream);
   CHECK_LAUNCH(ctx);
   return PIC_OK;
 }
@@ -852,7 +919,7 @@ int enqueue_sort(pic_ctx* ctx, Replica& R, int sp) {
 // sorts both species now (loading, pic_set_state)
 int resort(pic_ctx* ctx, Replica& R) {
   for (int sp = 0; sp < 2; ++sp) {
-    TRY(enqueue_sort(ctx, R, sp));
+    TRY(enqueue_sort(ctx, R, sp, true));
     R.cur[sp] = 1 - R.cur[sp];
   }
   return PIC_OK;
@@ -867,11 +934,6 @@ int read_tallies(pic_ctx* ctx, Replica& R, int sp, unsigned long long out[TL_N])
     for (int w = 0; w < TL_N; ++w) out[w] += h[(size_t)TL_N * c + w];
   return PIC_OK;
 }
-
-// Buffer phase of a replica: which particle buffer each species uses and
-// which rho buffer holds rho_k.  A step is fully described by the phase and
-// the species sorted at its end (bit sp of `sorts`).
-int phase_of(const Replica& R) { return R.cur[0] | (R.cur[1] << 1) | (R.rho_cur << 2); }
 
 AvgBins avg_bins_of(const pic_ctx* ctx, const Replica& R) {
   return AvgBins{R.d_step, R.cfg.f_rf, R.cfg.dt, ctx->avg_bins, 9 * R.nn};
@@ -958,40 +1020,11 @@ int enqueue_sample(pic_ctx* ctx, Replica& R) {
 // the next re-binning (each tile padded to a multiple of 4) still fits
 long iz_room(const Replica& R) { return R.cap[0] - 4L * R.ngrid; }
 
-// The two species' push and collision kernels depend on each other only
-// through the atomically summed charge: in a one-replica context (and not
-// while kernels are timed one by one) the ions' go to a second stream,
-// forked after the field solve and joined before the list kernels, so that
-// one species' latency-bound kernels and launch tails overlap the other's
-// streaming.  *forked tells whether the ions' kernels go to ctx->species_stream.
-int species_fork(pic_ctx* ctx, bool* forked) {
-  *forked = ctx->reps.size() == 1 && !ctx->prof;
-  if (!*forked) return PIC_OK;
-  if (!ctx->species_stream) {
-    HIPCHK(ctx, hipStreamCreateWithFlags(&ctx->species_stream, hipStreamNonBlocking));
-    HIPCHK(ctx, hipEventCreateWithFlags(&ctx->species_fork, hipEventDisableTiming));
-    HIPCHK(ctx, hipEventCreateWithFlags(&ctx->species_join, hipEventDisableTiming));
-  }
-  HIPCHK(ctx, hipEventRecord(ctx->species_fork, ctx->stream));
-  HIPCHK(ctx, hipStreamWaitEvent(ctx->species_stream, ctx->species_fork, 0));
-  return PIC_OK;
-}
-int species_join(pic_ctx* ctx, bool forked) {
-  if (!forked) return PIC_OK;
-  HIPCHK(ctx, hipEventRecord(ctx->species_join, ctx->species_stream));
-  HIPCHK(ctx, hipStreamWaitEvent(ctx->stream, ctx->species_join, 0));
-  return PIC_OK;
-}
-
-// The FP32R MD particles of a one-replica step on a stream of their own
-// (md_streams makes the stream and its events): md_fork, recorded after the
-// field solve's first kernel, starts the scan of their list beside the rest of
-// the solve from the cells the previous step left (the pushes, which rewrite
-// the cells in place, wait for the scan: md_scanned); their sub-cycled motion
-// follows once the fields (and any Coulomb pass) are in place (md_fields) and
-// runs beside the pushes; md_done marks the end of that work, which each
-// species' stream waits for before its lists kernels copy the states back.
-// *forked tells whether ctx->md_stream is used.
+// The MD particles of a one-replica step on a stream of their own (md_streams
+// makes the stream and its events): md_fork, once the fields (and any Coulomb
+// pass) are in place, starts their sub-cycled motion beside the push; md_join
+// marks the end of that work, which the lists kernel, which copies the states
+// back, waits for.  *forked tells whether ctx->md_stream is used.
 int md_streams(pic_ctx* ctx, bool* forked) {
   *forked = ctx->reps.size() == 1 && !ctx->prof;
   if (!*forked) return PIC_OK;
@@ -999,55 +1032,64 @@ int md_streams(pic_ctx* ctx, bool* forked) {
     HIPCHK(ctx, hipStreamCreateWithFlags(&ctx->md_stream, hipStreamNonBlocking));
     HIPCHK(ctx, hipEventCreateWithFlags(&ctx->md_fork, hipEventDisableTiming));
     HIPCHK(ctx, hipEventCreateWithFlags(&ctx->md_join, hipEventDisableTiming));
-    HIPCHK(ctx, hipEventCreateWithFlags(&ctx->md_scanned, hipEventDisableTiming));
-    HIPCHK(ctx, hipEventCreateWithFlags(&ctx->md_fields, hipEventDisableTiming));
   }
-  return PIC_OK;
-}
-int md_done(pic_ctx* ctx, bool forked) {
-  if (!forked) return PIC_OK;
-  HIPCHK(ctx, hipEventRecord(ctx->md_join, ctx->md_stream));
-  return PIC_OK;
-}
-int md_wait(pic_ctx* ctx, bool forked, hipStream_t s) {
-  if (!forked) return PIC_OK;
-  HIPCHK(ctx, hipStreamWaitEvent(s, ctx->md_join, 0));
   return PIC_OK;
 }
 
-// the species' current and other record buffers of an FP32R replica
-static void f32_buffers(const Replica& R, PartF32R P[2], PartF32R D[2]) {
-  for (int sp = 0; sp < 2; ++sp) {
-    P[sp] = R.p32[sp][R.cur[sp]];
-    D[sp] = R.p32[sp][1 - R.cur[sp]];
+void ionize(Replica& R, const PartF64 P[2], const WorkLists L[2], const SpeciesStep& Se,
+            hipStream_t st) {
+  launch_ionize(&P[0], &P[1], nullptr, nullptr, L[0], L[1], Se, R.md, R.d_next_id, iz_room(R),
+                iz_room(R), R.d_iz_drop, st);
+}
+void ionize(Replica& R, const PartF32R P[2], const WorkLists L[2], const SpeciesStep& Se,
+            hipStream_t st) {
+  launch_ionize(nullptr, nullptr, &P[0], &P[1], L[0], L[1], Se, R.md, R.d_next_id, iz_room(R),
+                iz_room(R), R.d_iz_drop, st);
+}
+
+// the particles' part of a step in the form of the records PT
+template <typename PT>
+int enqueue_particles(pic_ctx* ctx, Replica& R, bool fin) {
+  hipStream_t st = ctx->stream;
+  void* rho = R.rho[1 - R.rho_cur];
+  const SpeciesStep S[2] = {species_step(R, 0), species_step(R, 1)};
+  const WorkLists L[2] = {lists_of(R, 0), lists_of(R, 1)};
+  PT P[2], D[2];
+  buffers(R, P, D);
+  bool mdf = false;
+  TRY(md_streams(ctx, &mdf));
+  hipStream_t ms = st;
+  if (mdf) {
+    ms = ctx->md_stream;
+    HIPCHK(ctx, hipEventRecord(ctx->md_fork, st));
+    HIPCHK(ctx, hipStreamWaitEvent(ms, ctx->md_fork, 0));
   }
+  // the FP32 sweeps' last residual and test: nothing in the step reads them
+  if (fin)
+    launch_refine_final(R.nx, R.ny, R.nz, R.b, R.psi, R.r, R.cfg.max_refine, R.cfg.refine_tol,
+                        R.norms, R.refine_ctl, ms);
+  hipEvent_t m0 = prof_event(ctx);
+  launch_md_move(P, D, R.E, rho, R.md, S, R.d_gc, L, ms);
+  if (mdf) HIPCHK(ctx, hipEventRecord(ctx->md_join, ms));
+  hipEvent_t a = prof_event(ctx);
+  prof_pair(ctx, PIC_PROF_LISTS, m0, a);
+  push(R, phase_of(R), true, st);
+  hipEvent_t b = prof_event(ctx);
+  prof_pair(ctx, PIC_PROF_PUSH, a, b);
+  if (mdf) HIPCHK(ctx, hipStreamWaitEvent(st, ctx->md_join, 0));
+  launch_lists(descs_of(D, R), D, R.cfg.n_grains > 0, L, 1, st);
+  if (R.ionize) ionize(R, P, L, S[0], st);
+  prof_pair(ctx, PIC_PROF_LISTS, b, prof_event(ctx));
+  return PIC_OK;
 }
 
 // launches one step of a replica on ctx->stream from the host state at the
 // start of the step (buffer phases); advance_host then moves the host mirrors
 int enqueue_step(pic_ctx* ctx, Replica& R, int sorts, int sample) {
   hipStream_t st = ctx->stream;
-  // FP32R: the MD list scan must read the particles' cells as the previous
-  // step left them (the pushes rewrite them in place).  With the MD stream it
-  // runs first, beside the field solve, and the pushes wait for it; otherwise
-  // it runs in line before them.
-  bool mdf = false;
-  if (R.prec != PIC_FP64) TRY(md_streams(ctx, &mdf));
   hipEvent_t f0 = prof_event(ctx);
-  // with the MD stream, the refinement's last residual and test go there too
-  // (nothing in the step reads them), off the path to the pushes.  The scan
-  // starts once the solve's first kernel is done (md_fork): beside the large
-  // plane-transform blocks of that kernel its blocks slowed it by half.
   bool fin = false;
-  TRY(solve_fields(ctx, R, true, mdf ? &fin : nullptr, mdf ? ctx->md_fork : nullptr));
-  if (mdf) {
-    PartF32R P[2], D[2];
-    f32_buffers(R, P, D);
-    const SpeciesStep S[2] = {species_step(R, 0), species_step(R, 1)};
-    HIPCHK(ctx, hipStreamWaitEvent(ctx->md_stream, ctx->md_fork, 0));
-    launch_md_scan_f32r(P, R.lists, R.md, S, R.nx, R.ny, R.nz, ctx->md_stream);
-    HIPCHK(ctx, hipEventRecord(ctx->md_scanned, ctx->md_stream));
-  }
+  TRY(solve_fields(ctx, R, true, ctx->reps.size() == 1 && !ctx->prof ? &fin : nullptr));
   if (sample) TRY(enqueue_sample(ctx, R));
   prof_pair(ctx, PIC_PROF_FIELD, f0, prof_event(ctx));
   if (coulomb_due(R)) {
@@ -1055,76 +1097,9 @@ int enqueue_step(pic_ctx* ctx, Replica& R, int sorts, int sample) {
     TRY(enqueue_coulomb(ctx, R));
     prof_pair(ctx, PIC_PROF_COULOMB, c0, prof_event(ctx));
   }
-  const int rnx = 1 - R.rho_cur;
-  const int do_mcc = 1;
-  const SpeciesStep S[2] = {species_step(R, 0), species_step(R, 1)};
-  bool forked = false;
-  if (R.prec == PIC_FP64) {
-    const PartF64 P[2] = {R.p64[0][R.cur[0]], R.p64[1][R.cur[1]]};
-    TRY(species_fork(ctx, &forked));
-    for (int sp = 0; sp < 2; ++sp) {
-      hipStream_t ss = forked && sp == 1 ? ctx->species_stream : st;
-      hipEvent_t a = prof_event(ctx);
-      launch_push_f64(P[sp], (const double*)R.E, (double*)R.rho[rnx], R.md, S[sp], R.lists[sp], ss);
-      hipEvent_t b = prof_event(ctx);
-      launch_collide_f64(P[sp], S[sp], R.lists[sp], ss);
-      prof_pair(ctx, PIC_PROF_PUSH, a, b);
-      prof_pair(ctx, PIC_PROF_LISTS, b, prof_event(ctx));
-    }
-    TRY(species_join(ctx, forked));
-    hipEvent_t b = prof_event(ctx);
-    launch_lists_f64(P, (const double*)R.E, (double*)R.rho[rnx], R.md, S, R.d_gc, R.lists, do_mcc,
-                     st);
-    if (R.ionize)
-      launch_ionize(&P[0], &P[1], nullptr, nullptr, R.lists[0], R.lists[1], S[0], R.d_next_id,
-                    iz_room(R), iz_room(R), R.d_iz_drop, st);
-    prof_pair(ctx, PIC_PROF_LISTS, b, prof_event(ctx));
-  } else {
-    PartF32R P[2], D[2];
-    f32_buffers(R, P, D);
-    {
-      hipStream_t ms = mdf ? ctx->md_stream : st;
-      if (mdf) {
-        // the MD kernel needs the fields (and any Coulomb pass); the pushes
-        // need the scan done
-        HIPCHK(ctx, hipEventRecord(ctx->md_fields, st));
-        HIPCHK(ctx, hipStreamWaitEvent(ms, ctx->md_fields, 0));
-        HIPCHK(ctx, hipStreamWaitEvent(st, ctx->md_scanned, 0));
-      }
-      if (fin)
-        launch_refine_final(R.nx, R.ny, R.nz, R.b, R.psi, R.r, R.cfg.max_refine,
-                            R.cfg.refine_tol, R.norms, R.refine_ctl, ms);
-      hipEvent_t m0 = prof_event(ctx);
-      if (!mdf) launch_md_scan_f32r(P, R.lists, R.md, S, R.nx, R.ny, R.nz, ms);
-      launch_md_move_f32r(P, D, (const float*)R.E, (long long*)R.rho[rnx], R.md, S, R.d_gc,
-                          R.lists, ms);
-      TRY(md_done(ctx, mdf));
-      prof_pair(ctx, PIC_PROF_LISTS, m0, prof_event(ctx));
-    }
-    TRY(species_fork(ctx, &forked));
-    for (int sp = 0; sp < 2; ++sp) {
-      hipStream_t ss = forked && sp == 1 ? ctx->species_stream : st;
-      hipEvent_t a = prof_event(ctx);
-      launch_push_f32r(P[sp], (const float*)R.E, (long long*)R.rho[rnx], R.md, S[sp], R.lists[sp],
-                       ss);
-      hipEvent_t b = prof_event(ctx);
-      // this species' collisions, outliers, and MD particles' states back
-      // (once the MD kernel is done) in one launch, while the other species
-      // may still stream
-      TRY(md_wait(ctx, mdf, ss));
-      launch_species_lists_f32r(P, D, (const float*)R.E, (long long*)R.rho[rnx], R.md, S, R.lists,
-                                do_mcc, sp, ss);
-      prof_pair(ctx, PIC_PROF_PUSH, a, b);
-      prof_pair(ctx, PIC_PROF_LISTS, b, prof_event(ctx));
-    }
-    TRY(species_join(ctx, forked));
-    hipEvent_t b = prof_event(ctx);
-    if (R.ionize)
-      launch_ionize(nullptr, nullptr, &P[0], &P[1], R.lists[0], R.lists[1], S[0], R.d_next_id,
-                    iz_room(R), iz_room(R), R.d_iz_drop, st);
-    prof_pair(ctx, PIC_PROF_LISTS, b, prof_event(ctx));
-  }
-  launch_advance_step(R.d_step, R.lists[0].cnt, R.lists[1].cnt, st);
+  if (R.prec == PIC_FP64) TRY(enqueue_particles<PartF64>(ctx, R, fin));
+  else TRY(enqueue_particles<PartF32R>(ctx, R, fin));
+  launch_advance_step(R.d_step, st);
   CHECK_LAUNCH(ctx);
   if (sorts) {
     hipEvent_t s0 = prof_event(ctx);
@@ -1192,14 +1167,6 @@ int enqueue_batch(pic_ctx* ctx, int sorts, int sample) {
   const Replica& R0 = *ctx->reps[0];
   hipEvent_t f0 = prof_event(ctx);
   TRY(for_replicas(ctx, [&](Replica& R) -> int {
-    // the MD list scan reads the cells as the previous step left them: on the
-    // replica's worker stream, joined before the push launch
-    {
-      PartF32R P[2], D[2];
-      f32_buffers(R, P, D);
-      const SpeciesStep S[2] = {species_step(R, 0), species_step(R, 1)};
-      launch_md_scan_f32r(P, R.lists, R.md, S, R.nx, R.ny, R.nz, ctx->stream);
-    }
     TRY(solve_fields(ctx, R, true));
     if (sample) TRY(enqueue_sample(ctx, R));
     if (coulomb_due(R)) TRY(enqueue_coulomb(ctx, R));
@@ -1214,32 +1181,28 @@ int enqueue_batch(pic_ctx* ctx, int sorts, int sample) {
       ctx,
       [&](Replica& R) -> int {
         PartF32R P[2], D[2];
-        f32_buffers(R, P, D);
+        buffers(R, P, D);
         const SpeciesStep S[2] = {species_step(R, 0), species_step(R, 1)};
-        launch_md_move_f32r(P, D, (const float*)R.E, (long long*)R.rho[1 - R.rho_cur], R.md, S,
-                            R.d_gc, R.lists, ctx->stream);
+        const WorkLists L[2] = {lists_of(R, 0), lists_of(R, 1)};
+        launch_md_move(P, D, R.E, R.rho[1 - R.rho_cur], R.md, S, R.d_gc, L, ctx->stream);
         return PIC_OK;
       },
       false));
   hipEvent_t a = prof_event(ctx);
   launch_push_batch_f32r(ctx->d_desc + (size_t)phase_of(R0) * ctx->ndesc, ctx->d_start, ctx->ndesc,
-                         ctx->tune.batch_blocks, ctx->d_queue, st);
+                         ctx->batch_items, st);
   CHECK_LAUNCH(ctx);
   hipEvent_t b = prof_event(ctx);
   TRY(join_replicas(ctx));
   TRY(for_replicas(ctx, [&](Replica& R) -> int {
     hipStream_t ws = ctx->stream;
-    const int rnx = 1 - R.rho_cur;
     PartF32R P[2], D[2];
-    f32_buffers(R, P, D);
+    buffers(R, P, D);
     const SpeciesStep S[2] = {species_step(R, 0), species_step(R, 1)};
-    for (int sp = 0; sp < 2; ++sp) launch_collide_f32r(P[sp], S[sp], R.lists[sp], ws);
-    launch_lists_f32r(P, D, (const float*)R.E, (long long*)R.rho[rnx], R.md, S, R.lists, 1, -1,
-                      ws);
-    if (R.ionize)
-      launch_ionize(nullptr, nullptr, &P[0], &P[1], R.lists[0], R.lists[1], S[0], R.d_next_id,
-                    iz_room(R), iz_room(R), R.d_iz_drop, ws);
-    launch_advance_step(R.d_step, R.lists[0].cnt, R.lists[1].cnt, ws);
+    const WorkLists L[2] = {lists_of(R, 0), lists_of(R, 1)};
+    launch_lists(descs_of(D, R), D, R.cfg.n_grains > 0, L, 1, ws);
+    if (R.ionize) ionize(R, P, L, S[0], ws);
+    launch_advance_step(R.d_step, ws);
     return PIC_OK;
   }));
   CHECK_LAUNCH(ctx);
@@ -1285,15 +1248,8 @@ int build_batch(pic_ctx* ctx) {
     for (int r = 0; r < (int)ctx->reps.size(); ++r) {
       const Replica& R = *ctx->reps[r];
       for (int sp = 0; sp < 2; ++sp) {
-        PushDescF32& d = h[(size_t)ph * nd + 2 * r + sp];
-        d.P = R.p32[sp][(ph >> sp) & 1];
-        d.E = (const float4*)R.E;
-        d.rho = (long long*)R.rho[1 - ((ph >> 2) & 1)];
-        d.md = R.md;
-        d.S = species_step(R, sp);
-        d.L = R.lists[sp];
-        d.span = push_span(R.lists[sp]);
-        d.chunk = push_chunk(R.lists[sp], d.span);
+        const PushDescF32 d = push_desc<PartF32R, float4, long long>(R, sp, ph);
+        h[(size_t)ph * nd + 2 * r + sp] = d;
         if (ph == 0) {
           const long total = (long)start[2 * r + sp] + R.ngrid / d.span;
           if (total > 0x7fffffffL) return PIC_OK;  // beyond the int32 item index
@@ -1304,7 +1260,6 @@ int build_batch(pic_ctx* ctx) {
   if (!ctx->d_desc) {
     HIPCHK(ctx, hipMalloc(&ctx->d_desc, h.size() * sizeof(PushDescF32)));
     HIPCHK(ctx, hipMalloc(&ctx->d_start, start.size() * sizeof(int32_t)));
-    HIPCHK(ctx, hipMalloc(&ctx->d_queue, 8 * sizeof(int)));
   }
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   HIPCHK(ctx, hipMemcpy(ctx->d_desc, h.data(), h.size() * sizeof(PushDescF32),
@@ -1312,6 +1267,7 @@ int build_batch(pic_ctx* ctx) {
   HIPCHK(ctx, hipMemcpy(ctx->d_start, start.data(), start.size() * sizeof(int32_t),
                         hipMemcpyHostToDevice));
   ctx->ndesc = nd;
+  ctx->batch_items = start[nd];
   ctx->batchable = true;
   return PIC_OK;
 }
@@ -1474,10 +1430,10 @@ int apply_tuning(pic_ctx* ctx, const pic_tuning& t) {
   for (auto& R : ctx->reps) {
     R->margin[0] = t.tile_margin;
     R->margin[1] = t.ion_tile_margin;
-    // the stray flags refer to the old windows: every push block counts as
-    // stray until the next sort (the MD list's scan then covers all slots)
-    if (margin_changed && R->prec != PIC_FP64)
-      for (int sp = 0; sp < 2; ++sp) launch_fill_int(R->lists[sp].stray, R->ngrid, 1, ctx->stream);
+    if (margin_changed) {
+      TRY(setup_near(ctx, *R));
+      TRY(build_push(ctx, *R));
+    }
   }
   if (margin_changed && ctx->batchable) TRY(build_batch(ctx));
   ctx->drop_graphs();
@@ -1686,6 +1642,7 @@ int init_replica(pic_ctx* ctx, Replica& R, const pic_config& cin) {
     ctx->coulomb = true;
   }
   TRY(setup_md(ctx, R));
+  TRY(setup_near(ctx, R));
   TRY(unit_fields(ctx, R));
   launch_zero_f64(R.psi, R.n_int, st);  // the first FP32R solve starts from psi = 0
 
@@ -1706,6 +1663,7 @@ int init_replica(pic_ctx* ctx, Replica& R, const pic_config& cin) {
   R.rho_cur = 0;
   R.step = 0;
   R.n_base[0] = R.n_base[1] = R.n_load;
+  TRY(build_push(ctx, R));
   TRY(resort(ctx, R));
   TRY(deposit_current(ctx, R));
   HIPCHK(ctx, hipStreamSynchronize(st));

@@ -57,18 +57,25 @@ struct RfDrive {
 // grid of tiles is padded to a multiple of 16 (twice the XCD count) with empty tiles.
 // coll and out are segmented the same way: tile t's entries start at tstart[t].
 struct WorkLists {
-  int32_t* md;        // dense list: slots of particles that start the step in an MD cube
+  int32_t* md;        // dense list: slots of particles that start this step in an MD cube
+  int32_t* md_next;   // the same for the next step, appended during this one
+  int* n_md;          // entries in md
+  int* n_md_next;     // entries in md_next
   int32_t* coll;      // slots of collision candidates (tile segments)
-  int32_t* out;       // slots of particles outside their tile's LDS window (tile segments)
+  int32_t* out;       // slots of particles outside their tile's LDS window (tile segments); as
+                      // ~slot, the MD particles of a push block away from the MD cubes
+  uint8_t* mask;      // [slots / 4] of the push blocks near the MD cubes, per four slots: bit q
+                      // an MD particle, bit 4 + q a particle outside the window
+  const int32_t* near;  // the push blocks whose window meets the MD cubes' bounding box
+  int n_near;           // (their first tiles)
   int32_t* coll_cnt;  // [ngrid] entries in coll
   int32_t* out_cnt;   // [ngrid] entries in out
   int32_t* tstart;    // [ngrid + 1] first slot of each tile (set by the sort)
   unsigned long long* tally;  // [ngrid + MD blocks][TL_N] accumulated event counts (see
                               // TallyKind); one row per tile, then one per MD block
-  int32_t* cnt;       // [0] slots in use, [2] entries in md, [4] scan total of the sort
-  int32_t* stray;     // [ngrid] per push block (at its first tile), FP32R: nonzero once a
-                      // particle of the block's slots has ended a push outside the block's
-                      // window since the last sort (cleared by the sort)
+  int32_t* cnt;       // [0] slots in use, [2], [3] entries of the two MD lists, [4] scan
+                      // total of the sort
+  int slots;          // slots of the arrays
   int ntx, nty, ntz;  // tiles along x, y, z
   int ngrid;          // tiles rounded up to a multiple of 8
 };
@@ -176,19 +183,25 @@ struct FineBox {
   long mx, my, fn;
 };
 
-// one (replica, species) of a batched push launch
-struct PushDescF32 {
-  PartF32R P;
-  const float4* E;
-  long long* rho;
+// one species of one replica for the push, in device memory: a push block keeps
+// in registers what its inner loop needs and reads the rest where it is needed
+// (passed as kernel arguments, everything was loaded up front and the scalar
+// registers spilled into vector lanes, which the inner loop then read back)
+template <typename PT, typename ET, typename RT>
+struct PushDesc {
+  PT P;
+  const ET* E;
+  RT* rho;
   MdTables md;
   SpeciesStep S;
   WorkLists L;
   int span;   // tiles per push block (push_span)
   int chunk;  // z-layer chunk of the XCD interleaving (push_chunk)
 };
+using PushDescF32 = PushDesc<PartF32R, float4, long long>;
+using PushDescF64 = PushDesc<PartF64, double2, double>;
 
-// tiles per FP32R push block: pairs along x where the rows of tiles split into
+// tiles per push block: pairs along x where the rows of tiles split into
 // pairs (the tile grid, a multiple of 16, then still gives a multiple of 8
 // blocks); the kernels that read the push's lists use the same span
 __host__ __device__ inline int push_span(const WorkLists& L) { return L.ntx % 2 == 0 ? 2 : 1; }

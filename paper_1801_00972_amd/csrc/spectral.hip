@@ -669,8 +669,7 @@ void launch_factors(const double* sx2, const double* sy2, int cols, int ny, int 
 }
 
 void launch_spectral_solve(const SpectralPlan& p, const SpectralArgs& a, int in, double2* work, const double* inv,
-                           const RefineState& rs, hipStream_t st, hipEvent_t first_done, int* rc) {
-  if (rc) *rc = 0;
+                           const RefineState& rs, hipStream_t st) {
   const dim3 rows((unsigned)(p.K * p.chunks)), thr(row_threads(p));
   const size_t lds = row_lds(p);
   if (in == kRhsUnit)
@@ -679,7 +678,6 @@ void launch_spectral_solve(const SpectralPlan& p, const SpectralArgs& a, int in,
     hipLaunchKernelGGL(rows_fwd_kernel<kRhsRho64>, rows, thr, lds, st, p, a, work);
   else
     hipLaunchKernelGGL(rows_fwd_kernel<kRhsFixed>, rows, thr, lds, st, p, a, work);
-  if (first_done && hipEventRecord(first_done, st) != hipSuccess && rc) *rc = -1;
   const size_t col_lds = sizeof(double2) * ((size_t)p.fy.N + 2 * (size_t)p.cols * p.fy.N);
   if (!p.full)
     hipLaunchKernelGGL(cols_kernel<true>, dim3((unsigned)(p.K * p.col_chunks)), dim3(256), col_lds, st, p, a.tw_y,
