@@ -583,6 +583,7 @@ int setup_roots(pic_ctx* ctx, Replica& R, int N, T** out) {
 int setup_solver(pic_ctx* ctx, Replica& R) {
   if (!spectral_plan(R.nx, R.ny, R.nz, &R.plan))
     return fail(ctx, PIC_EINVAL, "FFT length not supported");
+  if (spectral_setup() != 0) return fail(ctx, PIC_EDEVICE, "kernel attributes could not be set");
   const int K = R.nz - 1;
   const long modes = (long)R.plan.hx * R.ny;
   TRY(dalloc(ctx, R, &R.work, (size_t)K * modes));
@@ -1896,7 +1897,6 @@ int pic_init(const pic_config* cfgs, int n_replicas, void* hip_stream, pic_ctx**
   std::unique_ptr<pic_ctx> ctx(new (std::nothrow) pic_ctx());
   if (!ctx) return fail(nullptr, PIC_ENOMEM, "host allocation failed");
   ctx->stream = (hipStream_t)hip_stream;
-  if (spectral_setup() != 0) return fail(nullptr, PIC_EDEVICE, "kernel attributes could not be set");
   for (int r = 0; r < n_replicas; ++r) {
     std::unique_ptr<Replica> R(new (std::nothrow) Replica());
     if (!R) return fail(nullptr, PIC_ENOMEM, "host allocation failed");
