@@ -134,13 +134,6 @@ __device__ __forceinline__ uint32_t md_lookup(const M& md, int nx, int ny, int i
   return (cl & 255u) ? cl : 0u;  // a cell of the box outside every cube has no grains
 }
 
-// per-grain data the sub-stepping reads every sub-step (staged in LDS)
-struct GrainView {
-  const double* gpos;   // [g][3] cell units
-  const double* Q;      // [g] grain charge frozen for the step, times qscale:
-  double qscale;        // Q qscale = Q / (4 pi eps0 dx^2)
-};
-
 // 1 / sqrt(a), a > 0: the hardware estimate refined by two Newton steps
 // y <- y (3 - a y^2) / 2 (each squares the relative error)
 __device__ __forceinline__ double rsqrt_refined(double a) {
@@ -148,18 +141,6 @@ __device__ __forceinline__ double rsqrt_refined(double a) {
   y = y * (1.5 - 0.5 * a * y * y);
   y = y * (1.5 - 0.5 * a * y * y);
   return y;
-}
-
-// separation x - x_g (cell units), minimum image across the periodic x,y
-__device__ __forceinline__ void grain_sep(const GrainView& G, const SpeciesStep& S, int g,
-                                          const double x[3], double r[3]) {
-  r[0] = x[0] - G.gpos[3 * g + 0];
-  r[1] = x[1] - G.gpos[3 * g + 1];
-  r[2] = x[2] - G.gpos[3 * g + 2];
-  if (r[0] > 0.5 * S.nx) r[0] -= S.nx;
-  else if (r[0] < -0.5 * S.nx) r[0] += S.nx;
-  if (r[1] > 0.5 * S.ny) r[1] -= S.ny;
-  else if (r[1] < -0.5 * S.ny) r[1] += S.ny;
 }
 
 __device__ __forceinline__ double wrap_coord(double X, int n) {
@@ -170,108 +151,177 @@ __device__ __forceinline__ double wrap_coord(double X, int n) {
   return X;
 }
 
-constexpr int kMdCache = 8;  // grains of the current cell kept in registers
+// grain data the sub-stepping reads every sub-step (staged in LDS): positions
+// in the frame of the MD box (x and y shifted by its origin, in [0, n)), and
+// Q / (4 pi eps0 dx^2)
+// (raw: more grains than the stage holds; as they are in memory, shifted and
+// scaled where they are read)
+struct GrainView {
+  const double* pos;  // [g][3]
+  const double* Qc;   // [g]
+  bool raw;
+};
+
+// the sum over the four lanes of a quad, in every lane (the two exchanges add
+// the same pairs in each lane: equal bits)
+__device__ __forceinline__ double quad_sum(double v) {
+#define PIC_QUAD(ctrl)                                                                  \
+  {                                                                                     \
+    union {                                                                             \
+      double d;                                                                         \
+      int i[2];                                                                         \
+    } a, b;                                                                             \
+    a.d = v;                                                                            \
+    b.i[0] = __builtin_amdgcn_mov_dpp(a.i[0], ctrl, 0xf, 0xf, true);                    \
+    b.i[1] = __builtin_amdgcn_mov_dpp(a.i[1], ctrl, 0xf, 0xf, true);                    \
+    v += b.d;                                                                           \
+  }
+  PIC_QUAD(0xB1)  // lanes 1 0 3 2
+  PIC_QUAD(0x4E)  // lanes 2 3 0 1
+#undef PIC_QUAD
+  return v;
+}
+__device__ __forceinline__ int quad_min(int v) {
+  v = min(v, __builtin_amdgcn_mov_dpp(v, 0xB1, 0xf, 0xf, true));
+  return min(v, __builtin_amdgcn_mov_dpp(v, 0x4E, 0xf, 0xf, true));
+}
 
 // Sub-cycled PPPM motion near grains, Eq. (5)-(6): md_sub sub-steps of
 // h = dt/md_sub with E = E_mesh - sum_g Q_g U_g + sum_g Q_g r / (4 pi eps0 r^3)
 // over the grains whose cube holds the current cell; hit when |r| <= a (the
-// lowest grain index of the cell's list wins).  The first two terms are
-// gathered from the cell's corrected node fields (built once per step by
-// md_field_kernel).  A particle crosses a cell boundary in only a few of its
-// sub-steps, so the cell's node fields and grain list are kept until the cell
-// changes.
-template <typename ET>
-__device__ int md_move(const ET* __restrict__ E, const MdTables& md, const GrainView& G,
-                       const SpeciesStep& S, double x[3], double v[3], int& hit) {
-  int e_cell = -1;
-  double ec[8][3];
+// first grain of the cell's list wins).  The first two terms are gathered from
+// the cell's corrected node fields (built once per step by field_out_kernel),
+// which are kept, with the cell's grains, until the cell changes.  x is in the
+// MD box's frame (x and y minus its origin, in [0, n)): a cell's index in the
+// box follows from the floor alone, and a separation inside the box needs no
+// minimum image unless the box spans the period.
+// kLanes = 4: the four lanes of a quad move one particle together, two corners
+// of the cell and every fourth grain each; all its state is the same in each.  A
+// sub-step is a serial chain, so a short list is bound by its length: 16x16x32
+// cells, 5,500 particles, 62 to 72 us with one lane a particle, 35 us with four.  A
+// long list (above kMdQuad particles) fills the chip with one lane each.
+template <int kLanes, typename ET>
+__device__ __forceinline__ int md_move(const ET* __restrict__ E, const MdTables& md,
+                                       const GrainView& G, const SpeciesStep& S, double a2_cells,
+                                       bool image, double x[3], double v[3], int& hit) {
+  constexpr int kC = 8 / kLanes;            // corners of this lane
+  constexpr int kG = kMdInline / kLanes;    // inline grains of this lane
+  const int l = kLanes == 1 ? 0 : (int)threadIdx.x & (kLanes - 1);
+  int ei = -1, ej = -1, ek = -1;
+  double ec[kC][3];
   uint32_t cl = 0u;
   int cnt = 0;
-  int gl[kMdCache];
-  auto load_cell = [&](int cell, int i0, int j0, int k0) {
-    if (cell == e_cell) return;
-    e_cell = cell;
-    const long bi = md_box_index(md, S.nx, S.ny, i0, j0, k0);
-    cl = bi >= 0 ? md.cell_list[bi] : 0u;
-    cnt = (int)(cl & 255u);
-    if (cnt > 0) {
-      const double* src = md.ecorr + bi * 24;
+  int gl[kG];
+  double Ep[3];
+  int first;  // list position of the first grain that holds the particle
+  auto grain = [&](int t, int g, bool test) {
+    double g0 = G.pos[3 * g], g1 = G.pos[3 * g + 1], Qc = G.Qc[g];
+    if (G.raw) {
+      g0 -= md.bx0;
+      g1 -= md.by0;
+      if (g0 < 0.0) g0 += S.nx;
+      if (g1 < 0.0) g1 += S.ny;
+      Qc *= S.coul_c;
+    }
+    double r0 = x[0] - g0, r1 = x[1] - g1;
+    const double r2 = x[2] - G.pos[3 * g + 2];
+    if (image) {
+      r0 = r0 > 0.5 * S.nx ? r0 - S.nx : (r0 < -0.5 * S.nx ? r0 + S.nx : r0);
+      r1 = r1 > 0.5 * S.ny ? r1 - S.ny : (r1 < -0.5 * S.ny ? r1 + S.ny : r1);
+    }
+    const double rr = r0 * r0 + r1 * r1 + r2 * r2;
+    if (test && rr <= a2_cells) first = min(first, t);
+    if (Qc == 0.0) return;
+    const double rs = rsqrt_refined(rr);
+    const double inv = Qc * rs * rs * rs;
+    Ep[0] += r0 * inv;
+    Ep[1] += r1 * inv;
+    Ep[2] += r2 * inv;
+  };
+  // position x_s, s = 0 .. md_sub: after a drift (s > 0) the hit test and,
+  // before the next kick, the field, from one walk over the cell's grains
+  for (int sub = 0;; ++sub) {
+    const double f0 = floor(x[0]), f1 = floor(x[1]), f2 = floor(x[2]);
+    const int i = (int)f0, j = (int)f1, k = (int)f2;
+    if (i != ei || j != ej || k != ek) {
+      ei = i;
+      ej = j;
+      ek = k;
+      const int c = k - md.bz0;
+      if ((unsigned)i < (unsigned)md.bsx && (unsigned)j < (unsigned)md.bsy &&
+          (unsigned)c < (unsigned)md.bsz) {
+        // (independent loads: one memory round trip)
+        const long bi = ((long)c * md.bsy + j) * md.bsx + i;
+        cl = md.cell_list[bi];
+        const double* src = md.ecorr + bi * 24 + 3 * kC * l;
 #pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        ec[c][0] = src[3 * c];
-        ec[c][1] = src[3 * c + 1];
-        ec[c][2] = src[3 * c + 2];
+        for (int t = 0; t < kC; ++t) {
+          ec[t][0] = src[3 * t];
+          ec[t][1] = src[3 * t + 1];
+          ec[t][2] = src[3 * t + 2];
+        }
+#pragma unroll
+        for (int u = 0; u < kG; ++u) gl[u] = md.cell_first[bi * kMdInline + l + kLanes * u];
+        cnt = (int)(cl & 255u);
+      } else {
+        cnt = 0;
+        int i0 = i + md.bx0, j0 = j + md.by0;
+        if (i0 >= S.nx) i0 -= S.nx;
+        if (j0 >= S.ny) j0 -= S.ny;
+        const int i1 = i0 + 1 == S.nx ? 0 : i0 + 1, j1 = j0 + 1 == S.ny ? 0 : j0 + 1;
+#pragma unroll
+        for (int t = 0; t < kC; ++t) {
+          const int tt = kC * l + t;
+          load_node(E, ((tt & 1) ? i1 : i0) + (long)S.nx * (((tt >> 1) & 1) ? j1 : j0) +
+                           (long)S.nxy * (k + (tt >> 2)),
+                    ec[t][0], ec[t][1], ec[t][2]);
+        }
+#pragma unroll
+        for (int u = 0; u < kG; ++u) gl[u] = 0;
+      }
+    }
+    const double fx = x[0] - f0, fy = x[1] - f1, fz = x[2] - f2;
+    Ep[0] = Ep[1] = Ep[2] = 0.0;
+    if constexpr (kLanes == 1) {
+      const double wx[2] = {1.0 - fx, fx}, wy[2] = {1.0 - fy, fy}, wz[2] = {1.0 - fz, fz};
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const double w = wx[t & 1] * wy[(t >> 1) & 1] * wz[t >> 2];
+        Ep[0] += w * ec[t][0];
+        Ep[1] += w * ec[t][1];
+        Ep[2] += w * ec[t][2];
       }
     } else {
-      const int i1 = i0 + 1 == S.nx ? 0 : i0 + 1;
-      const int j1 = j0 + 1 == S.ny ? 0 : j0 + 1;
+      const double wyz = ((l & 1) ? fy : 1.0 - fy) * ((l & 2) ? fz : 1.0 - fz);
+      const double w0 = (1.0 - fx) * wyz, w1 = fx * wyz;
 #pragma unroll
-      for (int c = 0; c < 8; ++c)
-        load_node(E, ((c & 1) ? i1 : i0) + (long)S.nx * (((c >> 1) & 1) ? j1 : j0) +
-                         (long)S.nxy * (k0 + (c >> 2)),
-                  ec[c][0], ec[c][1], ec[c][2]);
+      for (int a = 0; a < 3; ++a) Ep[a] = w0 * ec[0][a] + w1 * ec[1][a];
     }
+    first = 256;
 #pragma unroll
-    for (int u = 0; u < kMdCache; ++u) gl[u] = u < cnt ? md.grain_idx[(cl >> 8) + u] : 0;
-  };
-  auto grain_at = [&](int t) -> int {
-    int g = 0;
-#pragma unroll
-    for (int u = 0; u < kMdCache; ++u)
-      if (u == t) g = gl[u];
-    return t < kMdCache ? g : md.grain_idx[(cl >> 8) + t];
-  };
-  // the field at x: the mesh part from the cell's corrected node fields,
-  // then the grains' Coulomb fields (their mesh parts are in the corrected
-  // nodes): Q r / (4 pi eps0 |r|^3) with r in cells and Q qscale = Q / (4 pi eps0 dx^2)
-  auto mesh_field = [&](double Ep[3]) {
-    const int i0 = (int)floor(x[0]), j0 = (int)floor(x[1]), k0 = (int)floor(x[2]);
-    const double fx = x[0] - i0, fy = x[1] - j0, fz = x[2] - k0;
-    load_cell(pack_cell(i0, j0, k0), i0, j0, k0);
-    const double wx[2] = {1.0 - fx, fx}, wy[2] = {1.0 - fy, fy}, wz[2] = {1.0 - fz, fz};
-    Ep[0] = Ep[1] = Ep[2] = 0.0;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const double wt = wx[c & 1] * wy[(c >> 1) & 1] * wz[c >> 2];
-      Ep[0] += wt * ec[c][0];
-      Ep[1] += wt * ec[c][1];
-      Ep[2] += wt * ec[c][2];
-    }
-  };
-  auto grain_field = [&](int g, const double r[3], double Ep[3]) {
-    const double Qc = G.Q[g] * G.qscale;
-    if (Qc == 0.0) return;
-    const double r2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-    const double rs = rsqrt_refined(r2);
-    const double inv = Qc * rs * rs * rs;
-    Ep[0] += r[0] * inv;
-    Ep[1] += r[1] * inv;
-    Ep[2] += r[2] * inv;
-  };
-  // position x_s, s = 0 .. md_sub: after a drift (s > 0) the hit test, in list
-  // order (the first grain that holds the particle wins), and, before the
-  // next kick, the field, from one walk over the cell's grains
-  double Ep[3];
-  for (int sub = 0;; ++sub) {
-    mesh_field(Ep);
-    for (int t = 0; t < cnt; ++t) {
-      const int g = grain_at(t);
-      double r[3];
-      grain_sep(G, S, g, x, r);
-      const double d0 = r[0] * S.dx, d1 = r[1] * S.dx, d2 = r[2] * S.dx;
-      if (sub > 0 && d0 * d0 + d1 * d1 + d2 * d2 <= md.a2) {
-        hit = g;
-        return ST_GRAIN;
-      }
-      grain_field(g, r, Ep);
+    for (int u = 0; u < kG; ++u)
+      if (l + kLanes * u < cnt) grain(l + kLanes * u, gl[u], sub > 0);
+    if (cnt > kMdInline)
+      for (int t = kMdInline + l; t < cnt; t += kLanes) grain(t, md.grain_idx[(cl >> 8) + t], sub > 0);
+    if constexpr (kLanes > 1) first = quad_min(first);
+    if (first < 256) {
+      hit = md.grain_idx[(cl >> 8) + first];
+      return ST_GRAIN;
     }
     if (sub == S.md_sub) break;
-    v[0] += S.qm_h * Ep[0];
-    v[1] += S.qm_h * Ep[1];
-    v[2] += S.qm_h * Ep[2];
-    x[0] = wrap_coord(x[0] + v[0] * S.h_dx, S.nx);
-    x[1] = wrap_coord(x[1] + v[1] * S.h_dx, S.ny);
-    x[2] += v[2] * S.h_dx;
+    if constexpr (kLanes > 1) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) Ep[a] = quad_sum(Ep[a]);
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      v[a] += S.qm_h * Ep[a];
+      x[a] += v[a] * S.h_dx;
+    }
+    if (!(x[0] >= 0.0 && x[0] < (double)S.nx && x[1] >= 0.0 && x[1] < (double)S.ny)) {
+      x[0] = wrap_coord(x[0], S.nx);
+      x[1] = wrap_coord(x[1], S.ny);
+    }
     const int zs = z_status(x, S);
     if (zs != ST_ALIVE) return zs;
   }
@@ -304,7 +354,7 @@ __device__ __forceinline__ void md_corner(const MdTables& md, int nx, int ny, ui
 }
 
 // The fields of a step in one launch.  Blocks [0, nbm): one thread per (MD box
-// cell in a cube, corner) forms the corrected node field; E at the node is
+// cell, corner) forms the corrected node field; E at the node is
 // formed from psi and rounded to the storage type first, so it is what a read
 // of E returns (these blocks come first: their dependent table loads then
 // overlap the node blocks' streaming).  Blocks from nbm on: one thread per
@@ -393,7 +443,6 @@ __global__ __launch_bounds__(256) void field_out_kernel(const double* __restrict
   const long bi = gid >> 3;
   const int t = (int)(gid & 7);
   const uint32_t cl = md.cell_list[bi];
-  if ((cl & 255u) == 0u) return;
   const int a = (int)(bi % md.bsx), bb = (int)((bi / md.bsx) % md.bsy);
   const int c = (int)(bi / ((long)md.bsx * md.bsy));
   const int i0 = (md.bx0 + a) % nx, j0 = (md.by0 + bb) % ny, k0 = md.bz0 + c;
@@ -1389,7 +1438,7 @@ __global__ __launch_bounds__(kBlock, 4) void push_f32r_kernel(const PushDescF32*
 // the tile interleave expects).  A block an item, dealt by the hardware as
 // blocks end: a persistent grid drawing items from queues kept its loop's state
 // through every tile (30 spilled registers) and took 2.77 ms a step where this
-// takes XXX ms (six replicas of 1.5e8 particles in all).
+// takes 2.32 ms (six replicas of 1.5e8 particles in all).
 __global__ __launch_bounds__(kBlock, 4) void push_batch_f32r_kernel(const PushDescF32* descs,
                                                                  const int32_t* __restrict__ start,
                                                                  int ndesc) {
@@ -1701,54 +1750,72 @@ __device__ __forceinline__ T wave_sum_t(T v) {
 
 // The charges of a wave's MD particles to the global mesh.  The particles of
 // a cell of the dense list tend to sit in neighbouring lanes and hit the same
-// eight nodes, which all MD blocks share, so per distinct cell the wave first
-// sums the corner shares and one lane adds them (for the fixed-point charge
-// the sums are exact and the mesh does not depend on the grouping).  After
-// kDepGroups distinct cells the remaining lanes add their own shares.
+// eight nodes, which all MD blocks share, so the wave first sums the corner
+// shares of each of its first kDepGroups distinct cells in LDS (for the
+// fixed-point charge the sums are exact and the mesh does not depend on the
+// grouping); the remaining lanes add their own shares.
 constexpr int kDepGroups = 16;
 template <typename A>
-__device__ __forceinline__ void deposit_wave(A* __restrict__ rho, const SpeciesStep& S, int cell,
-                                             const A part[8]) {
+__device__ __forceinline__ void deposit_wave(A (*s_sum)[8], int* s_cell, A* __restrict__ rho,
+                                             const SpeciesStep& S, int cell, const A part[8]) {
   const int lane = threadIdx.x & 63;
   unsigned long long pending = __ballot(cell >= 0);
-  Tile none{};
-  for (int it = 0; it < kDepGroups && pending; ++it) {
-    const int leader = __ffsll((long long)pending) - 1;
-    const int key = __shfl(cell, leader, 64);
-    const bool mine = cell == key;
-    const unsigned long long m = __ballot(mine);
-    pending &= ~m;
-    A sum[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) sum[t] = wave_sum_t<A>(mine ? part[t] : (A)0);
-    if (lane == leader)
-      corner_add<A>(none, -1, nullptr, rho, S, cell_i(key), cell_j(key), cell_k(key), sum);
+  int mine = -1, n = 0;
+  for (; n < kDepGroups && pending; ++n) {
+    const int key = __shfl(cell, __ffsll((long long)pending) - 1, 64);
+    if (cell == key) mine = n;
+    if (lane == 0) s_cell[n] = key;
+    pending &= ~__ballot(cell == key);
   }
-  if ((pending >> lane) & 1ull)
+  for (int t = lane; t < 8 * n; t += 64) (&s_sum[0][0])[t] = (A)0;
+  __syncthreads();  // (one wave a block)
+  if (mine >= 0) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      if constexpr (std::is_same<A, long long>::value)
+        atomicAdd((unsigned long long*)&s_sum[mine][t], (unsigned long long)part[t]);
+      else
+        atomicAdd(&s_sum[mine][t], part[t]);
+    }
+  }
+  __syncthreads();
+  for (int e = lane; e < 8 * n; e += 64) {
+    const int c = s_cell[e >> 3], t = e & 7;
+    int i = cell_i(c) + (t & 1), j = cell_j(c) + ((t >> 1) & 1);
+    if (i == S.nx) i = 0;
+    if (j == S.ny) j = 0;
+    atomic_add_acc(&rho[i + (long)S.nx * j + (long)S.nxy * (cell_k(c) + (t >> 2))], (&s_sum[0][0])[e]);
+  }
+  Tile none{};
+  if (cell >= 0 && mine < 0)
     corner_add<A>(none, -1, nullptr, rho, S, cell_i(cell), cell_j(cell), cell_k(cell), part);
+  __syncthreads();  // the sums are free again
 }
 
 __device__ __forceinline__ void kill(const PartF64& P, long p) { P.z[p] = -1.0; }
 __device__ __forceinline__ void kill(const PartF32R& P, long p) { P.cell[p] = -1; }
 // slot p of src into slot p of dst (an empty src slot empties dst's)
 __device__ __forceinline__ void copy_rec(const PartF64& src, const PartF64& dst, long p) {
-  dst.x[p] = src.x[p];
-  dst.y[p] = src.y[p];
-  dst.z[p] = src.z[p];
-  dst.vx[p] = src.vx[p];
-  dst.vy[p] = src.vy[p];
-  dst.vz[p] = src.vz[p];
+  const double a = src.x[p], b = src.y[p], c = src.z[p], f = src.vx[p], g = src.vy[p], h = src.vz[p];
+  dst.x[p] = a;
+  dst.y[p] = b;
+  dst.z[p] = c;
+  dst.vx[p] = f;
+  dst.vy[p] = g;
+  dst.vz[p] = h;
 }
 __device__ __forceinline__ void copy_rec(const PartF32R& src, const PartF32R& dst, long p) {
+  // (every load before the first store: one memory round trip)
   const int c = src.cell[p];
+  const float a = src.ox[p], b = src.oy[p], e = src.oz[p], f = src.vx[p], g = src.vy[p], h = src.vz[p];
   dst.cell[p] = c;
   if (c < 0) return;
-  dst.ox[p] = src.ox[p];
-  dst.oy[p] = src.oy[p];
-  dst.oz[p] = src.oz[p];
-  dst.vx[p] = src.vx[p];
-  dst.vy[p] = src.vy[p];
-  dst.vz[p] = src.vz[p];
+  dst.ox[p] = a;
+  dst.oy[p] = b;
+  dst.oz[p] = e;
+  dst.vx[p] = f;
+  dst.vy[p] = g;
+  dst.vz[p] = h;
 }
 
 // one thread per MD particle of the dense list of this step, both species in
@@ -1759,6 +1826,9 @@ __device__ __forceinline__ void copy_rec(const PartF32R& src, const PartF32R& ds
 // kernel after both copies the states back and takes the survivors' collisions
 // (kept out of this kernel so that its registers allow three waves per SIMD).
 constexpr int kMdThreads = 64;
+// lists up to this length move four lanes a particle (about the particles that
+// one lane each would leave the chip's 1,024 SIMDs a wave or less)
+constexpr int kMdQuad = 49152;
 template <typename PT, typename ET, typename RT>
 __global__ __launch_bounds__(kMdThreads) void md_kernel(SpeciesPair<PT> pr, PT D0, PT D1,
                                                         const ET* __restrict__ E,
@@ -1771,45 +1841,68 @@ __global__ __launch_bounds__(kMdThreads) void md_kernel(SpeciesPair<PT> pr, PT D
   const WorkLists L = pr.L[sp];
   const int bid = (int)blockIdx.x - sp * pr.nb;
   const int total = *L.n_md;
-  if ((long)bid * kMdThreads >= total) return;
+  if ((long)bid * (total <= kMdQuad ? kMdThreads / 4 : kMdThreads) >= total) return;
   constexpr int kStage = 256;
   __shared__ double s_gpos[3 * kStage], s_Qc[kStage];
   __shared__ unsigned s_hits[kStage];
+  __shared__ RT s_sum[kDepGroups][8];
+  __shared__ int s_cell[kDepGroups];
+  const bool staged = md.n_grains <= kStage;
   for (int t = threadIdx.x; t < min(md.n_grains, kStage); t += blockDim.x) {
-    s_Qc[t] = md.Q[t] * S.coul_c;
     s_hits[t] = 0u;
-    for (int a = 0; a < 3; ++a) s_gpos[3 * t + a] = md.gpos[3 * t + a];
+    if (staged) {
+      s_Qc[t] = md.Q[t] * S.coul_c;
+      double gx = md.gpos[3 * t] - md.bx0, gy = md.gpos[3 * t + 1] - md.by0;
+      s_gpos[3 * t] = gx < 0.0 ? gx + S.nx : gx;
+      s_gpos[3 * t + 1] = gy < 0.0 ? gy + S.ny : gy;
+      s_gpos[3 * t + 2] = md.gpos[3 * t + 2];
+    }
   }
   __syncthreads();
-  const GrainView G = md.n_grains <= kStage ? GrainView{s_gpos, s_Qc, 1.0}
-                                            : GrainView{md.gpos, md.Q, S.coul_c};
+  const GrainView G = staged ? GrainView{s_gpos, s_Qc, false} : GrainView{md.gpos, md.Q, true};
+  const double a2_cells = md.a2 / (S.dx * S.dx);
+  const bool image = md.bsx == S.nx || md.bsy == S.ny;
   int n_w0 = 0, n_w1 = 0, n_bad = 0, n_dead = 0;
-  for (long base = (long)bid * kMdThreads; base < total; base += (long)pr.nb * kMdThreads) {
-    const long idx = base + threadIdx.x;
+  auto move = [&](auto lanes, long idx, int sub_lane) {
     int st = ST_NONE, cell = -1;
     RT part[8];
     if (idx < total) {
       const long p = L.md[idx];
       double x[3], v[3];
       load_d(P, p, x, v);
+      x[0] -= md.bx0;
+      x[1] -= md.by0;
+      if (x[0] < 0.0) x[0] = wrap_coord(x[0], S.nx);
+      if (x[1] < 0.0) x[1] = wrap_coord(x[1], S.ny);
       int hit = -1;
-      st = md_move(E, md, G, S, x, v, hit);
-      if (st == ST_GRAIN) {
-        if (hit < kStage) atomicAdd(&s_hits[hit], 1u);
-        else atomicAdd(&grain_count[2 * hit + S.sp], 1ull);
-      }
-      if (st == ST_ALIVE) {
+      st = md_move<decltype(lanes)::value>(E, md, G, S, a2_cells, image, x, v, hit);
+      if (sub_lane != 0) {
+        st = ST_NONE;  // (the quad's first lane settles the particle)
+      } else if (st == ST_ALIVE) {
+        x[0] = wrap_coord(x[0] + md.bx0, S.nx);
+        x[1] = wrap_coord(x[1] + md.by0, S.ny);
         cell = store_d(D, p, x, v, S, part);
         if (cell < 0) st = ST_WALL1;
       } else {
+        if (st == ST_GRAIN) {
+          if (hit < kStage) atomicAdd(&s_hits[hit], 1u);
+          else atomicAdd(&grain_count[2 * hit + S.sp], 1ull);
+        }
         kill(D, p);
       }
     }
-    deposit_wave<RT>(rho, S, cell, part);
+    deposit_wave<RT>(s_sum, s_cell, rho, S, cell, part);
     n_w0 += st == ST_WALL0;
     n_w1 += st == ST_WALL1;
     n_bad += st == ST_BAD;
     n_dead += st == ST_WALL0 || st == ST_WALL1 || st == ST_BAD || st == ST_GRAIN;
+  };
+  if (total <= kMdQuad) {
+    for (long base = (long)bid * (kMdThreads / 4); base < total; base += (long)pr.nb * (kMdThreads / 4))
+      move(std::integral_constant<int, 4>{}, base + (threadIdx.x >> 2), (int)threadIdx.x & 3);
+  } else {
+    for (long base = (long)bid * kMdThreads; base < total; base += (long)pr.nb * kMdThreads)
+      move(std::integral_constant<int, 1>{}, base + threadIdx.x, 0);
   }
   int c4[4] = {n_w0, n_w1, n_bad, n_dead};
 #pragma unroll
@@ -3030,8 +3123,13 @@ static void md_move_impl(const PT P[2], const PT D[2], const void* E, void* rho,
                          const SpeciesStep S[2], unsigned long long* gc, const WorkLists L[2],
                          int span, hipStream_t st) {
   if (md.n_grains == 0 || L[0].ngrid <= 0) return;
-  SpeciesPair<PT> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, kMdBlocks, span};
-  hipLaunchKernelGGL((md_kernel<PT, ET, RT>), dim3(2 * kMdBlocks), dim3(kMdThreads), 0, st, pr,
+  // blocks for the particles that the loading density puts into the cubes (the
+  // kernel strides over what there is)
+  const long guess = (long)(md.n_cells * (L[0].slots / ((double)S[0].nx * S[0].ny * S[0].nz)));
+  const long per = guess <= kMdQuad ? kMdThreads / 4 : kMdThreads;
+  const int nb = (int)std::min<long>(kMdBlocks, std::max<long>(64, guess / per * 5 / 4));
+  SpeciesPair<PT> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, nb, span};
+  hipLaunchKernelGGL((md_kernel<PT, ET, RT>), dim3(2 * nb), dim3(kMdThreads), 0, st, pr,
                      D[0], D[1], (const ET*)E, (RT*)rho, md, gc);
 }
 void launch_md_move(const PartF64 P[2], const PartF64 D[2], const void* E, void* rho,

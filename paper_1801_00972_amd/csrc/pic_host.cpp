@@ -506,7 +506,7 @@ int setup_md(pic_ctx* ctx, Replica& R) {
   md.bz0 = zmin;
   md.bsz = zmax - zmin + 1;
   std::vector<uint32_t> cell_list((size_t)md.bsx * md.bsy * md.bsz, 0u);
-  std::vector<int32_t> idx;
+  std::vector<int32_t> idx, inl(cell_list.size() * kMdInline, 0);
   for (int z = 0; z < md.bsz; ++z)
     for (int y = 0; y < md.bsy; ++y)
       for (int x = 0; x < md.bsx; ++x) {
@@ -520,16 +520,23 @@ int setup_md(pic_ctx* ctx, Replica& R) {
         const size_t cnt = idx.size() - start;
         if (cnt > 255) return fail(ctx, PIC_ECONFIG, "more than 255 grains share an MD cell");
         if (start >= (1u << 24)) return fail(ctx, PIC_ECONFIG, "MD tables too large");
-        cell_list[((size_t)z * md.bsy + y) * md.bsx + x] = (uint32_t)(start << 8) | (uint32_t)cnt;
+        const size_t bi = ((size_t)z * md.bsy + y) * md.bsx + x;
+        cell_list[bi] = (uint32_t)(start << 8) | (uint32_t)cnt;
+        for (size_t u = 0; u < std::min<size_t>(cnt, kMdInline); ++u)
+          inl[bi * kMdInline + u] = idx[start + u];
+        md.n_cells += cnt > 0;
       }
   uint32_t* d_cl;
-  int32_t* d_idx;
+  int32_t *d_idx, *d_first;
   double* d_gpos;
   int32_t* d_gcell;
   double* d_U;
   const long cube = (long)md.side * md.side * md.side;
   TRY(dalloc(ctx, R, &d_cl, cell_list.size()));
   TRY(dalloc(ctx, R, &d_idx, std::max<size_t>(idx.size(), 1)));
+  TRY(dalloc(ctx, R, &d_first, inl.size()));
+  HIPCHK(ctx, hipMemcpy(d_first, inl.data(), inl.size() * 4, hipMemcpyHostToDevice));
+  md.cell_first = d_first;
   TRY(dalloc(ctx, R, &d_gpos, 3 * ng));
   TRY(dalloc(ctx, R, &d_gcell, 3 * ng));
   TRY(dalloc(ctx, R, &d_U, (size_t)ng * 3 * cube));

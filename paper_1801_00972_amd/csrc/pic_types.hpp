@@ -88,6 +88,7 @@ enum TallyKind {
 };
 
 // near-grain (MD) tables of one replica
+constexpr int kMdInline = 8;  // grains of a cell listed beside its field
 struct MdTables {
   int n_grains;
   int cutoff;
@@ -96,14 +97,16 @@ struct MdTables {
   int bsx, bsy, bsz;
   const uint32_t* cell_list;  // [bsz][bsy][bsx]: (start << 8) | count
   const int32_t* grain_idx;   // grain indices referenced by cell_list
+  const int32_t* cell_first;  // [bsz][bsy][bsx][kMdInline] the first of each cell's grains
   const double* gpos;         // [g][3] cell units
   const int32_t* gcell;       // [g][3] floor of gpos
   const double* Q;            // [g] grain charge (C) frozen at the start of the step
   const double* U;            // [g][3][side^3] unit-charge mesh field on the cube
   double* ecorr;              // [bsz][bsy][bsx][8][3] per box cell, rebuilt every step:
                               // E_k - sum_g Q_g U_g on the cell's 8 nodes (V/m), the sum
-                              // over the grains whose cube holds the cell
+                              // over the grains whose cube holds the cell (E_k if none)
   double a2;                  // grain radius^2 (m^2)
+  int n_cells;                // cells in cubes
 };
 
 // everything the particle kernels need for one species of one replica
