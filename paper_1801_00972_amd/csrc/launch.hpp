@@ -78,6 +78,7 @@ void launch_init_f32r(const PartF32R& P, int n, int ppc, int nx, int ny, int sp,
 // density and flux moments of one species: mom [4][nn] gets W, v W summed per
 // node (added to what it holds, in the rf-phase bin of the step if avg.step
 // is set); exactly one of P64, P32 is non-null
+int moments_setup();  // the kernels' LDS sizes; 0 or an error
 void launch_moments(const PartF64* P64, const PartF32R* P32, const SpeciesStep& S,
                     const WorkLists& L, double* mom, long nn, const AvgBins& avg,
                     hipStream_t st);

@@ -830,22 +830,16 @@ struct Tile {
   bool wraps;      // the window crosses the periodic seam in x or y
 };
 
-// the window of tiles t .. t + span - 1 (consecutive along x): their cells
+// the window of `span` tiles from (ti, tj, tk) (consecutive along x): their cells
 // plus m cells on each side, in nodes; the margin shrinks until the window
 // fits `cap` nodes
-template <typename WL>
-__host__ __device__ __forceinline__ Tile make_tile(int t, const WL& L, int nx, int ny, int nz,
-                                          int margin, int cap, int span = 1) {
+__host__ __device__ __forceinline__ Tile tile_window(int ti, int tj, int tk, int nx, int ny, int nz,
+                                                     int margin, int cap, int span) {
   Tile w;
   w.on = false;
   w.wraps = false;
   w.x0 = w.y0 = w.k0 = 0;
   w.tx = w.ty = w.tz = 0;
-  // a padding tile of the grid (its slots, if any, hold particles made by
-  // ionisation since the last re-binning): no window, every particle takes
-  // the global-memory paths
-  if (t >= L.ntx * L.nty * L.ntz) return w;
-  const int ti = t % L.ntx, tj = (t / L.ntx) % L.nty, tk = t / (L.ntx * L.nty);
   const int i0 = 4 * ti, ni = min(4 * span, nx - i0), j0 = 4 * tj, nj = min(4, ny - j0);
   const int k0 = 4 * tk, nk = min(4, nz - k0);
   for (int m = margin; m >= 0; --m) {
@@ -876,6 +870,21 @@ __host__ __device__ __forceinline__ Tile make_tile(int t, const WL& L, int nx, i
   return w;
 }
 
+// the window of tiles t .. t + span - 1
+template <typename WL>
+__host__ __device__ __forceinline__ Tile make_tile(int t, const WL& L, int nx, int ny, int nz,
+                                          int margin, int cap, int span = 1) {
+  Tile w;
+  w.on = false;
+  w.wraps = false;
+  w.x0 = w.y0 = w.k0 = 0;
+  w.tx = w.ty = w.tz = 0;
+  // a padding tile of the grid (its slots, if any, hold particles made by
+  // ionisation since the last re-binning): no window, every particle takes
+  // the global-memory paths
+  if (t >= L.ntx * L.nty * L.ntz) return w;
+  return tile_window(t % L.ntx, (t / L.ntx) % L.nty, t / (L.ntx * L.nty), nx, ny, nz, margin, cap, span);
+}
 // tile-local index of the cell's lower corner node, or -1 if the cell's 8
 // nodes are not all in the tile
 __device__ __forceinline__ int tile_cell(const Tile& t, int i, int j, int k, int nx, int ny) {
@@ -1924,96 +1933,227 @@ __global__ __launch_bounds__(kMdThreads) void md_kernel(SpeciesPair<PT> pr, PT D
 // and fluxes of Sec. IV): per node the sums over the particles of W and of
 // v W, where W is the particle's CIC weight for the node, the same
 // assignment as the charge deposit of Sec. III.  The host scales them by
-// w / dx^3.  v is the stored half-step velocity v_{k-1/2}.  One block per
-// tile: the tile's (4+1)^3 nodes accumulate in LDS and are then added to the
-// mesh; particles that left the tile since the last re-binning add to the
-// mesh directly.  mom is [4][nn]: W, v_x W, v_y W, v_z W.  For the time
-// averages (avg.step non-null) the sums go to the rf-phase bin of the
-// current step, avg.stride doubles further per bin.
-// the moment window: the tile's nodes plus the species' drift margin (as the
-// push stages them; at most 2 cells here), so particles that drifted out of
-// their tile since the last re-binning still add in LDS
-constexpr int kMomWin = 729;
-// copies of the window: thread t adds into copy t % kMomCopies (summed at the flush)
-constexpr int kMomCopies = 1;
+// w / dx^3.  v is the stored half-step velocity v_{k-1/2}.  mom is [4][nn]:
+// W, v_x W, v_y W, v_z W.  For the time averages (avg.step non-null) the sums
+// go to the rf-phase bin of the current step, avg.stride doubles further per
+// bin.
+//
+// One block per tile.  Per cell the sums are a 4 x n by n x 8 product, (1, v)
+// of its n particles by their weights, and go through the FP64 matrix units
+// (the 4x4x4 form on four cells at a time, two instructions for the eight
+// corners), so a cell's particles have to lie side by side: a chunk of the
+// tile's slots is read once, coalesced, and counted, ranked and stored by cell in
+// LDS (the particles have drifted since the last re-binning).  The four cells of a
+// wave take as many rounds as the fullest, so the tile's own cells, all about
+// as full, come first and the drift margin's after them.  The cells' sums meet
+// in a window of the tile's nodes plus the margin (at most 2 cells) and reach
+// the mesh once; a particle outside the window adds to the mesh directly.
+// One thread a run of slots with 32 sums in registers was bound by its LDS
+// atomics: 32 a run, and a run ends wherever a particle has drifted.  Now the
+// vector instructions issue about half of the time and barriers take the rest.
+// 64x64x256 cells, 32 per cell, mean of the species: FP32R 733 us -> 445 (0.94 GB),
+// FP64 1326 -> 558 (1.6 GB); 128x128x512, 16 per cell, FP32R 2,850 -> 2,240 (3.8 GB).
+constexpr int kMomWin = 729;  // most nodes of a window
+// slots of a chunk, with LDS for two blocks a CU at the largest window: a tile of
+// 32 per cell in FP32R, half of one in FP64; and, for a tile of 16 in FP32R, half
+// of that, of which a margin of one cell leaves room for four blocks of 256
+// threads (128x128x512 cells, 16 per cell: 1.55 ms against 2.15 in 512) and one
+// of two cells room for two, of 512 threads (2.9 ms against 3.5 in 256)
+constexpr int kMomCapFull = 2160, kMomCapHalf = 1080;
+__host__ __device__ constexpr size_t mom_lds(int nodes, int cap, size_t v) {
+  return nodes * 32 + cap * 6 * v + (64 + nodes + 1) * 8;
+}
+// a slot's cell (i, j, k), offsets in the cell and velocity; false if it is free
+__device__ __forceinline__ bool mom_load(const PartF32R& P, long p, int c[3], float r[6]) {
+  const int cell = P.cell[p];
+  r[0] = P.ox[p];
+  r[1] = P.oy[p];
+  r[2] = P.oz[p];
+  r[3] = P.vx[p];
+  r[4] = P.vy[p];
+  r[5] = P.vz[p];
+  c[0] = cell_i(cell);
+  c[1] = cell_j(cell);
+  c[2] = cell_k(cell);
+  return cell >= 0;
+}
+__device__ __forceinline__ bool mom_load(const PartF64& P, long p, int c[3], double r[6]) {
+  double x[3];
+  load_d(P, p, x, r + 3);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const double f = floor(x[a]);
+    c[a] = (int)f;
+    r[a] = x[a] - f;
+  }
+  return x[2] >= 0.0;
+}
 
-template <typename PT>
-__global__ __launch_bounds__(256) void moments_kernel(PT P, SpeciesStep S, WorkLists L,
-                                                      double* __restrict__ mom, long nn,
-                                                      AvgBins avg) {
-  const int t = blockIdx.x;
-  if (avg.step) mom += avg.stride * phase_bin(*avg.step, avg.f_rf, avg.dt, avg.nbins);
-  const long a = L.tstart[t], b = L.tstart[t + 1];
+// inclusive sums over the wave
+__device__ __forceinline__ int wave_prefix(int v) {
+  const int lane = (int)threadIdx.x & 63;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(v, d, 64);
+    if (lane >= d) v += o;
+  }
+  return v;
+}
+
+// grid (tiles along x, along y, along z and the grid's padding), mom_lds() bytes of LDS
+template <typename PT, int kT, int kCap>
+__global__ __launch_bounds__(kT, 4) void moments_kernel(PT P, SpeciesStep S, WorkLists L,
+                                                                 double* __restrict__ mom, long nn,
+                                                                 AvgBins avg, int nodes) {
+  using V = typename VelOf<PT>::type;
+  constexpr int kPer = (kCap + kT - 1) / kT, kWaves = kT / 64;
+  constexpr int kIds = (64 + kMomWin + kT - 1) / kT;  // ids a thread of the scan, at most
+  extern __shared__ double s_dyn[];
+  double* s_m = s_dyn;                           // [4][nodes]
+  V* s_r = (V*)(s_m + 4 * nodes);                // [6][kCap] offsets and velocities, by cell
+  const int ids = 64 + nodes;                    // cell ids: the tile's own, then by window node
+  int* s_start = (int*)(s_r + 6 * kCap);         // [ids] particles per cell id, then first entry
+  uint32_t* s_list = (uint32_t*)(s_start + ids + 1);  // the occupied cells: first entry << 16 | node
+  __shared__ int s_wave[kWaves];
+  const int tid = (int)threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ti = blockIdx.x, tj = blockIdx.y, tk = blockIdx.z;
+  const int t = (tk * L.nty + tj) * L.ntx + ti;
+  if (t >= L.ngrid) return;
+  const int a = L.tstart[t], b = L.tstart[t + 1];
   if (a == b) return;
-  __shared__ double s_m[kMomCopies][4][kMomWin];
-  const Tile T = make_tile(t, L, S.nx, S.ny, S.nz, S.margin, kMomWin);
-  for (int u = threadIdx.x; u < kMomCopies * 4 * kMomWin; u += blockDim.x) (&s_m[0][0][0])[u] = 0.0;
-  __syncthreads();
-  const int cp = (int)threadIdx.x % kMomCopies;
-  // each thread walks a contiguous run of slots: the slots of a tile are grouped
-  // by cell, so consecutive particles of one cell are summed in registers and
-  // reach the LDS window once per run
-  const long per = (b - a + blockDim.x - 1) / blockDim.x;
-  const long p0 = a + (long)threadIdx.x * per, p1 = p0 + per < b ? p0 + per : b;
-  int run_lb = -1;
-  double acc[4][8];
-  for (long p = p0; p < p1; ++p) {
-    if (!slot_alive(P, p)) continue;
-    double x[3], v[3], w[8];
-    load_d(P, p, x, v);
-    const int i = (int)floor(x[0]), j = (int)floor(x[1]), k = (int)floor(x[2]);
-    cic_weights_d(x[0] - i, x[1] - j, x[2] - k, 1.0, w);
-    const int lb = tile_cell(T, i, j, k, S.nx, S.ny);
-    if (lb < 0) {
-      // outside the window: straight to the mesh
-      double val[8];
-      corner_add<double>(T, -1, s_m[cp][0], mom, S, i, j, k, w);
+  if (avg.step) mom += avg.stride * phase_bin(*avg.step, avg.f_rf, avg.dt, avg.nbins);
+  Tile T{};
+  if (tk < L.ntz) T = tile_window(ti, tj, tk, S.nx, S.ny, S.nz, S.margin, nodes, 1);
+  // the tile's own cells in window cells
+  const int wx = 4 * ti - T.x0, wy = 4 * tj - T.y0, wz = 4 * tk - T.k0;
+  for (int u = tid; u < 4 * nodes; u += kT) s_m[u] = 0.0;
+  const int chunks = (b - a + kCap - 1) / kCap, per = (b - a + chunks - 1) / chunks;
+  for (int p0 = a; p0 < b; p0 += per) {
+    const int n = min(per, b - p0);
+    for (int u = tid; u < ids; u += kT) s_start[u] = 0;
+    __syncthreads();
+    V r[kPer][6];
+    int id[kPer], rank[kPer], far = 0;
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
-#pragma unroll
-        for (int c = 0; c < 8; ++c) val[c] = v[q] * w[c];
-        corner_add<double>(T, -1, s_m[cp][q + 1], mom + (q + 1) * nn, S, i, j, k, val);
+    for (int m = 0; m < kPer; ++m) {
+      const int u = tid + m * kT;
+      id[m] = -1;
+      rank[m] = 0;
+      if (u >= n) continue;
+      int c[3];
+      if (!mom_load(P, p0 + u, c, r[m])) continue;
+      const int lb = tile_cell(T, c[0], c[1], c[2], S.nx, S.ny);
+      if (lb < 0) {
+        far |= 1 << m;
+        continue;
       }
-      continue;
+      const int li = c[0] - 4 * ti, lj = c[1] - 4 * tj, lk = c[2] - 4 * tk;
+      id[m] = ((li | lj | lk) & ~3) == 0 ? (lk * 4 + lj) * 4 + li : 64 + lb;
+      rank[m] = atomicAdd(&s_start[id[m]], 1);
     }
-    if (lb != run_lb) {
-      if (run_lb >= 0) {
+    // outside the window: straight to the mesh
+    for (; far; far &= far - 1) {
+      int c[3];
+      V q[6];
+      mom_load(P, p0 + tid + (__ffs(far) - 1) * kT, c, q);
+      double w[8], val[8];
+      cic_weights_d(q[0], q[1], q[2], 1.0, w);
+      corner_add<double>(T, -1, nullptr, mom, S, c[0], c[1], c[2], w);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) corner_add<double>(T, run_lb, s_m[cp][q], mom, S, 0, 0, 0, acc[q]);
-      }
-      run_lb = lb;
+      for (int d = 0; d < 3; ++d) {
 #pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        acc[0][c] = w[c];
-        acc[1][c] = v[0] * w[c];
-        acc[2][c] = v[1] * w[c];
-        acc[3][c] = v[2] * w[c];
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        acc[0][c] += w[c];
-        acc[1][c] += v[0] * w[c];
-        acc[2][c] += v[1] * w[c];
-        acc[3][c] += v[2] * w[c];
+        for (int e = 0; e < 8; ++e) val[e] = (double)q[3 + d] * w[e];
+        corner_add<double>(T, -1, nullptr, mom + (d + 1) * nn, S, c[0], c[1], c[2], val);
       }
     }
-  }
-  if (run_lb >= 0) {
+    __syncthreads();
+    // first entries and the list of occupied cells: one scan of both counts
+    int cnt[kIds], own = 0, sum = 0;
+    if (64 * kIds * wave < ids) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) corner_add<double>(T, run_lb, s_m[cp][q], mom, S, 0, 0, 0, acc[q]);
+      for (int i = 0; i < kIds; ++i) {
+        cnt[i] = kIds * tid + i < ids ? s_start[kIds * tid + i] : 0;
+        own += cnt[i] + (cnt[i] ? 1 << 16 : 0);
+      }
+      sum = wave_prefix(own);
+    }
+    if (lane == 63) s_wave[wave] = sum;
+    __syncthreads();
+    int before = sum - own, all = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      if (w < wave) before += s_wave[w];
+      all += s_wave[w];
+    }
+    const int ncell = all >> 16;
+    if (64 * kIds * wave < ids) {
+#pragma unroll
+      for (int i = 0; i < kIds; ++i) {
+        const int c = kIds * tid + i;
+        if (c < ids) s_start[c] = before & 0xffff;
+        if (cnt[i]) {
+          const int node = c >= 64 ? c - 64 : ((wz + (c >> 4)) * T.ty + wy + ((c >> 2) & 3)) * T.tx + wx + (c & 3);
+          s_list[before >> 16] = (uint32_t)before << 16 | (uint32_t)node;
+          before += cnt[i] + (1 << 16);
+        }
+      }
+    }
+    if (tid == 0) s_list[ncell] = (uint32_t)all << 16;
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < kPer; ++m) {
+      if (id[m] < 0) continue;
+      const int e = s_start[id[m]] + rank[m];
+#pragma unroll
+      for (int q = 0; q < 6; ++q) s_r[q * kCap + e] = r[m][q];
+    }
+    __syncthreads();
+    // lane = j + 4 cell + 16 k: operand A (quantity j, particle k), operand B (particle
+    // k, corner j), result (quantity k, corner j)
+    const int j = lane & 3, cell = (lane >> 2) & 3, k = lane >> 4;
+    const double ax = j & 1 ? 0.0 : 1.0, bx = j & 1 ? 1.0 : -1.0;
+    const double ay = j & 2 ? 0.0 : 1.0, by = j & 2 ? 1.0 : -1.0;
+    const V* vel = s_r + (j ? 2 + j : 3) * kCap;
+    double* out = s_m + k * nodes + (j & 1) + T.tx * (j >> 1);
+    for (int g = 4 * wave; g < ncell; g += 4 * kWaves) {
+      const int at = min(g + cell, ncell - 1);
+      const bool have = g + cell < ncell;
+      const uint32_t c = s_list[at];
+      const int s = (int)(c >> 16), e = have ? (int)(s_list[at + 1] >> 16) : s;
+      // the matrix instructions take all lanes: as many rounds as the fullest cell
+      // of the four needs.  The count is a scalar (with the loop left on a ballot
+      // the compiler copied a result without the wait states it needs)
+      int most = e - s;
+      most = max(most, __builtin_amdgcn_update_dpp(0, most, 0x124, 0xf, 0xf, false));  // row_ror:4
+      most = max(most, __builtin_amdgcn_update_dpp(0, most, 0x128, 0xf, 0xf, false));  // row_ror:8
+      most = __builtin_amdgcn_readfirstlane(most);
+      double lo = 0.0, hi = 0.0;
+      for (int u = 0; u < most; u += 4) {
+        const bool in = s + u + k < e;
+        const int p = in ? s + u + k : s;
+        const double fx = s_r[p], fy = s_r[kCap + p], fz = s_r[2 * kCap + p];
+        const V v = vel[p];
+        const double A = in ? (j ? (double)v : 1.0) : 0.0;
+        const double w = (ax + bx * fx) * (ay + by * fy);
+        lo = __builtin_amdgcn_mfma_f64_4x4x4f64(A, w * (1.0 - fz), lo, 0, 0, 0);
+        hi = __builtin_amdgcn_mfma_f64_4x4x4f64(A, w * fz, hi, 0, 0, 0);
+      }
+      if (have) {
+        atomicAdd(&out[c & 0xffff], lo);
+        atomicAdd(&out[(c & 0xffff) + T.tx * T.ty], hi);
+      }
+    }
+    __syncthreads();
   }
-  __syncthreads();
   if (!T.on) return;
   const int nt = T.tx * T.ty * T.tz;
   const float rtx = 1.0f / (float)T.tx, rtxy = 1.0f / (float)(T.tx * T.ty);
-  for (int u = threadIdx.x; u < nt; u += blockDim.x) {
+  for (int u = tid; u < nt; u += kT) {
     const long node = tile_node(T, u, rtx, rtxy, S.nx, S.ny, S.nxy);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      double sum = 0.0;
-#pragma unroll
-      for (int c = 0; c < kMomCopies; ++c) sum += s_m[c][q][u];
+      const double sum = s_m[q * nodes + u];
       if (sum != 0.0) unsafeAtomicAdd(&mom[q * nn + node], sum);
     }
   }
@@ -3192,16 +3332,41 @@ void launch_init_f32r(const PartF32R& P, int n, int ppc, int nx, int ny, int sp,
                      k0, k1, vth);
 }
 
+template <int kT, int kCap, typename PT>
+static void moments_launch(const PT& P, const SpeciesStep& S, const WorkLists& L, double* mom,
+                           long nn, const AvgBins& avg, int nodes, hipStream_t st) {
+  const long layer = (long)L.ntx * L.nty, pad = L.ngrid - layer * L.ntz;
+  const dim3 grid(L.ntx, L.nty, L.ntz + (unsigned)((pad + layer - 1) / layer));
+  using V = typename VelOf<PT>::type;
+  hipLaunchKernelGGL((moments_kernel<PT, kT, kCap>), grid, dim3(kT),
+                     mom_lds(nodes, kCap, sizeof(V)), st, P, S, L, mom, nn, avg, nodes);
+}
+
+int moments_setup() {
+  const void* k[] = {(const void*)moments_kernel<PartF64, 512, kMomCapHalf>,
+                     (const void*)moments_kernel<PartF32R, 512, kMomCapFull>,
+                     (const void*)moments_kernel<PartF32R, 512, kMomCapHalf>,
+                     (const void*)moments_kernel<PartF32R, 256, kMomCapHalf>};
+  const int most = (int)mom_lds(kMomWin, kMomCapFull, sizeof(float));
+  for (const void* f : k)
+    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess) return -1;
+  return 0;
+}
+
 void launch_moments(const PartF64* P64, const PartF32R* P32, const SpeciesStep& S,
                     const WorkLists& L, double* mom, long nn, const AvgBins& avg,
                     hipStream_t st) {
   if (L.ngrid <= 0) return;
+  // the largest window: 4 cells and the margin on both sides along each axis
+  const int m = std::min(S.margin, 2), edge = 5 + 2 * m, nodes = edge * edge * edge;
   if (P64)
-    hipLaunchKernelGGL(moments_kernel<PartF64>, dim3(L.ngrid), dim3(256), 0, st, *P64, S, L, mom,
-                       nn, avg);
+    moments_launch<512, kMomCapHalf>(*P64, S, L, mom, nn, avg, nodes, st);
+  else if (L.slots / L.ngrid > kMomCapHalf * 3 / 2)  // (slots with their headroom)
+    moments_launch<512, kMomCapFull>(*P32, S, L, mom, nn, avg, nodes, st);
+  else if (m > 1)
+    moments_launch<512, kMomCapHalf>(*P32, S, L, mom, nn, avg, nodes, st);
   else
-    hipLaunchKernelGGL(moments_kernel<PartF32R>, dim3(L.ngrid), dim3(256), 0, st, *P32, S, L, mom,
-                       nn, avg);
+    moments_launch<256, kMomCapHalf>(*P32, S, L, mom, nn, avg, nodes, st);
 }
 
 void launch_fine_moments(const PartF64* P64, const PartF32R* P32, const WorkLists& L,

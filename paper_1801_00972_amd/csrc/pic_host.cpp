@@ -590,7 +590,7 @@ int setup_roots(pic_ctx* ctx, Replica& R, int N, T** out) {
 int setup_solver(pic_ctx* ctx, Replica& R) {
   if (!spectral_plan(R.nx, R.ny, R.nz, &R.plan))
     return fail(ctx, PIC_EINVAL, "FFT length not supported");
-  if (spectral_setup() != 0) return fail(ctx, PIC_EDEVICE, "kernel attributes could not be set");
+  if (spectral_setup() != 0 || moments_setup() != 0) return fail(ctx, PIC_EDEVICE, "kernel attributes could not be set");
   const int K = R.nz - 1;
   const long modes = (long)R.plan.hx * R.ny;
   TRY(dalloc(ctx, R, &R.work, (size_t)K * modes));
