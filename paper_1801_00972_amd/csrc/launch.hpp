@@ -49,6 +49,15 @@ void launch_md_move(const PartF64 P[2], const PartF64 D[2], const void* E, void*
 void launch_md_move(const PartF32R P[2], const PartF32R D[2], const void* E, void* rho,
                     const MdTables& md, const SpeciesStep S[2], unsigned long long* gc,
                     const WorkLists L[2], hipStream_t st);
+// whether a step's push blocks and MD blocks are few enough for one launch, and
+// that launch: launch_push with move and launch_md_move
+bool push_md_fits(const MdTables& md, const SpeciesStep& S, const WorkLists& L);
+void launch_push_md(const PushDescF64* descs, const PartF64 P[2], const PartF64 D[2], const void* E,
+                    void* rho, const MdTables& md, const SpeciesStep S[2], unsigned long long* gc,
+                    const WorkLists L[2], hipStream_t st);
+void launch_push_md(const PushDescF32* descs, const PartF32R P[2], const PartF32R D[2],
+                    const void* E, void* rho, const MdTables& md, const SpeciesStep S[2],
+                    unsigned long long* gc, const WorkLists L[2], hipStream_t st);
 // the push blocks (first tiles) whose window of `margin` cells meets the MD
 // cubes' bounding box
 std::vector<int32_t> near_blocks(const WorkLists& L, const MdTables& md, int nx, int ny, int nz,
@@ -153,8 +162,6 @@ int energy_blocks();
 void launch_energy(const PartF64* P64, const PartF32R* P32, const WorkLists& L, double* out,
                    hipStream_t st);
 void launch_field_energy(const void* E, int e_f64, long nxy, int nz, double* out, hipStream_t st);
-// the step counter advances
-void launch_advance_step(uint32_t* step, hipStream_t st);
 
 // mesh
 // one grain's share of the right-hand side: interior node `node` (the index

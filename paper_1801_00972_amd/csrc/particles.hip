@@ -154,11 +154,13 @@ __device__ __forceinline__ double wrap_coord(double X, int n) {
 // grain data the sub-stepping reads every sub-step (staged in LDS): positions
 // in the frame of the MD box (x and y shifted by its origin, in [0, n)), and
 // Q / (4 pi eps0 dx^2)
-// (raw: more grains than the stage holds; as they are in memory, shifted and
-// scaled where they are read)
+// in LDS (raw: more grains than the stage holds; read from the tables, shifted
+// and scaled where they are used).  LDS pointers, not generic ones: a generic
+// load waits for global memory too
+typedef const __attribute__((address_space(3))) double* LdsDoubles;
 struct GrainView {
-  const double* pos;  // [g][3]
-  const double* Qc;   // [g]
+  LdsDoubles pos;  // [g][3]
+  LdsDoubles Qc;   // [g]
   bool raw;
 };
 
@@ -215,16 +217,22 @@ __device__ __forceinline__ int md_move(const ET* __restrict__ E, const MdTables&
   double Ep[3];
   int first;  // list position of the first grain that holds the particle
   auto grain = [&](int t, int g, bool test) {
-    double g0 = G.pos[3 * g], g1 = G.pos[3 * g + 1], Qc = G.Qc[g];
+    double g0, g1, g2, Qc;
     if (G.raw) {
-      g0 -= md.bx0;
-      g1 -= md.by0;
+      g0 = md.gpos[3 * g] - md.bx0;
+      g1 = md.gpos[3 * g + 1] - md.by0;
+      g2 = md.gpos[3 * g + 2];
       if (g0 < 0.0) g0 += S.nx;
       if (g1 < 0.0) g1 += S.ny;
-      Qc *= S.coul_c;
+      Qc = md.Q[g] * S.coul_c;
+    } else {
+      g0 = G.pos[3 * g];
+      g1 = G.pos[3 * g + 1];
+      g2 = G.pos[3 * g + 2];
+      Qc = G.Qc[g];
     }
     double r0 = x[0] - g0, r1 = x[1] - g1;
-    const double r2 = x[2] - G.pos[3 * g + 2];
+    const double r2 = x[2] - g2;
     if (image) {
       r0 = r0 > 0.5 * S.nx ? r0 - S.nx : (r0 < -0.5 * S.nx ? r0 + S.nx : r0);
       r1 = r1 > 0.5 * S.ny ? r1 - S.ny : (r1 < -0.5 * S.ny ? r1 + S.ny : r1);
@@ -374,6 +382,7 @@ __global__ __launch_bounds__(256) void field_out_kernel(const double* __restrict
                                                         int nx, int ny, int nz, double dx,
                                                         RfDrive rf, int nbm) {
   const double V = rf_voltage(rf);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *rf.next = *rf.step + 1u;
   if ((int)blockIdx.x >= nbm) {
     __shared__ double s_r[4], s_b[4];
     const int plane = nx * ny;
@@ -1225,7 +1234,10 @@ __device__ __forceinline__ void cand_collide(const PT& P, const H& S, const Cand
 }
 
 // LDS of one push block (FP32R)
-struct PushSmemF32 {
+template <typename PT, bool kMove>
+struct PushSmem;
+template <bool kMove>
+struct PushSmem<PartF32R, kMove> {
   float4 E[kWinF32];
   long long rho[kWinF32];
   unsigned tally[TL_N];
@@ -1241,8 +1253,8 @@ struct PushHot {  // what the inner loop needs of a SpeciesStep
   float qm_dt_f, dt_dx_f;
 };
 template <bool kMove>
-__device__ __forceinline__ void push_tile_f32r(const PIC_CONST PushDescF32* d, int tidx, int span,
-                                               PushSmemF32& sm) {
+__device__ __forceinline__ void push_tile(const PIC_CONST PushDescF32* d, int tidx, int span,
+                                          PushSmem<PartF32R, kMove>& sm) {
   const int beg = d->L.tstart[tidx], end = d->L.tstart[tidx + span];
   if (kMove && threadIdx.x < span) {
     d->L.coll_cnt[tidx + threadIdx.x] = 0;
@@ -1435,9 +1447,9 @@ __device__ __forceinline__ void push_tile_f32r(const PIC_CONST PushDescF32* d, i
 template <bool kMove>
 __global__ __launch_bounds__(kBlock, 4) void push_f32r_kernel(const PushDescF32* descs, int nb,
                                                            int span, int chunk) {
-  __shared__ PushSmemF32 sm;
+  __shared__ PushSmem<PartF32R, kMove> sm;
   const int sp = (int)blockIdx.x >= nb ? 1 : 0, b = (int)blockIdx.x - sp * nb;
-  push_tile_f32r<kMove>((const PIC_CONST PushDescF32*)(descs + sp), span * (int)xcd_interleave(b, chunk), span, sm);
+  push_tile<kMove>((const PIC_CONST PushDescF32*)(descs + sp), span * (int)xcd_interleave(b, chunk), span, sm);
 }
 
 // ---------------------------------------------------------------- push, ensemble
@@ -1451,7 +1463,7 @@ __global__ __launch_bounds__(kBlock, 4) void push_f32r_kernel(const PushDescF32*
 __global__ __launch_bounds__(kBlock, 4) void push_batch_f32r_kernel(const PushDescF32* descs,
                                                                  const int32_t* __restrict__ start,
                                                                  int ndesc) {
-  __shared__ PushSmemF32 sm;
+  __shared__ PushSmem<PartF32R, true> sm;
   const int item = (int)blockIdx.x;
   int lo = 0, hi = ndesc;  // start[lo] <= item < start[hi]
   while (hi - lo > 1) {
@@ -1460,7 +1472,7 @@ __global__ __launch_bounds__(kBlock, 4) void push_batch_f32r_kernel(const PushDe
     else hi = mid;
   }
   const PIC_CONST PushDescF32* d = (const PIC_CONST PushDescF32*)(descs + lo);
-  push_tile_f32r<true>(d, d->span * (int)xcd_interleave(item - start[lo], d->chunk), d->span, sm);
+  push_tile<true>(d, d->span * (int)xcd_interleave(item - start[lo], d->chunk), d->span, sm);
 }
 
 // ---------------------------------------------------------------- push, FP64
@@ -1472,18 +1484,17 @@ struct PushHot64 {
   double qm_dt, dt_dx;
 };
 
-// (at most 168 VGPRs: three waves per SIMD; 42 KB of LDS allow three blocks a CU)
 template <bool kMove>
-__global__ __launch_bounds__(kBlock, 3) void push_f64_kernel(const PushDescF64* descs, int nb,
-                                                          int span, int chunk) {
-  __shared__ double2 s_E[kMove ? 2 * kWinF64 : 1];
-  __shared__ double s_rho[kWinF64];
-  __shared__ unsigned s_tally[TL_N];
-  __shared__ int s_ncoll, s_nout, s_far;
-  __shared__ CandStage<double, kMove ? kCandF64 : 1> s_cand;
-  const int spi = (int)blockIdx.x >= nb ? 1 : 0;
-  const PIC_CONST PushDescF64* d = (const PIC_CONST PushDescF64*)(descs + spi);
-  const int tidx = span * (int)xcd_interleave((int)blockIdx.x - spi * nb, chunk);
+struct PushSmem<PartF64, kMove> {
+  double2 E[kMove ? 2 * kWinF64 : 1];
+  double rho[kWinF64];
+  unsigned tally[TL_N];
+  int ncoll, nout, far;
+  CandStage<double, kMove ? kCandF64 : 1> cand;
+};
+template <bool kMove>
+__device__ __forceinline__ void push_tile(const PIC_CONST PushDescF64* d, int tidx, int span,
+                                          PushSmem<PartF64, kMove>& sm) {
   const int beg = d->L.tstart[tidx], end = d->L.tstart[tidx + span];
   if (kMove && threadIdx.x < span) {
     d->L.coll_cnt[tidx + threadIdx.x] = 0;
@@ -1497,16 +1508,16 @@ __global__ __launch_bounds__(kBlock, 3) void push_f64_kernel(const PushDescF64* 
   for (int t = threadIdx.x; t < vol; t += kBlock) {
     if (kMove) {
       const long node = tile_node(tile, t, rtx, rtxy, S.nx, S.ny, d->S.nxy);
-      s_E[2 * t] = d->E[2 * node];
-      s_E[2 * t + 1] = d->E[2 * node + 1];
+      sm.E[2 * t] = d->E[2 * node];
+      sm.E[2 * t + 1] = d->E[2 * node + 1];
     }
-    s_rho[t] = 0.0;
+    sm.rho[t] = 0.0;
   }
-  if (threadIdx.x < TL_N) s_tally[threadIdx.x] = 0;
+  if (threadIdx.x < TL_N) sm.tally[threadIdx.x] = 0;
   if (threadIdx.x == 0) {
-    s_ncoll = 0;
-    s_far = 0;
-    s_nout = 0;
+    sm.ncoll = 0;
+    sm.far = 0;
+    sm.nout = 0;
   }
   const bool md_near = window_meets_md(tile, d->md, S.nx, S.ny);
   const PartF64 P = desc_records(d);
@@ -1579,7 +1590,7 @@ __global__ __launch_bounds__(kBlock, 3) void push_f64_kernel(const PushDescF64* 
           for (int t = 0; t < 8; ++t) {
             const int l = lb + (t & 1) + tile.tx * (((t >> 1) & 1) + tile.ty * (t >> 2));
             const double w = wx[t & 1] * wy[(t >> 1) & 1] * wz[t >> 2];
-            const double2 a = s_E[2 * l], b2 = s_E[2 * l + 1];
+            const double2 a = sm.E[2 * l], b2 = sm.E[2 * l + 1];
             Ep[0] += w * a.x;
             Ep[1] += w * a.y;
             Ep[2] += w * b2.x;
@@ -1605,11 +1616,11 @@ __global__ __launch_bounds__(kBlock, 3) void push_f64_kernel(const PushDescF64* 
 #pragma unroll
         for (int q = 0; q < kPPT; ++q) cm |= (w0[q] <= T_last ? 1u : 0u) << q;
         cm &= live;
-        if (__any(cm)) cand_append(cm, s_cand, coll, &s_ncoll, p0, id, v);
+        if (__any(cm)) cand_append(cm, sm.cand, coll, &sm.ncoll, p0, id, v);
       }
       if (md_near && have) d->L.mask[g4] = 0;
       if (__any((st & 0xbbbbu) != 0u))
-        push_events(st, p0, have, md_near, d->L, out, &s_nout, s_tally);
+        push_events(st, p0, have, md_near, d->L, out, &sm.nout, sm.tally);
       if (have) {
 #define PIC_STORE4(arr, srcv, a)                                                          \
   {                                                                                       \
@@ -1634,11 +1645,11 @@ __global__ __launch_bounds__(kBlock, 3) void push_f64_kernel(const PushDescF64* 
       if (lb >= 0) {
 #pragma unroll
         for (int t = 0; t < 8; ++t)
-          atomicAdd(&s_rho[lb + (t & 1) + tile.tx * (((t >> 1) & 1) + tile.ty * (t >> 2))], acc[t]);
+          atomicAdd(&sm.rho[lb + (t & 1) + tile.tx * (((t >> 1) & 1) + tile.ty * (t >> 2))], acc[t]);
         return;
       }
-      if (kMove && push_in_md(d, acc_cell)) s_far = 1;
-      corner_add<double>(tile, -1, s_rho, d->rho, d->S, ai, aj, ak, acc);
+      if (kMove && push_in_md(d, acc_cell)) sm.far = 1;
+      corner_add<double>(tile, -1, sm.rho, d->rho, d->S, ai, aj, ak, acc);
     };
 #pragma unroll
     for (int q = 0; q < kPPT; ++q) {
@@ -1658,25 +1669,33 @@ __global__ __launch_bounds__(kBlock, 3) void push_f64_kernel(const PushDescF64* 
     }
     if (acc_cell >= 0) flush();
   }
-  if (kMove) tally_add(s_tally, TL_FAST, n_fast);
+  if (kMove) tally_add(sm.tally, TL_FAST, n_fast);
   __syncthreads();
-  if constexpr (kMove) cand_collide(P, d->S, s_cand, s_ncoll, s_tally);
+  if constexpr (kMove) cand_collide(P, d->S, sm.cand, sm.ncoll, sm.tally);
   double* const rho = d->rho;
   const long nxy = d->S.nxy;
   const float qtx = 1.0f / (float)max(tile.tx, 1), qtxy = 1.0f / (float)max(tile.tx * tile.ty, 1);
   for (int t = threadIdx.x; t < vol; t += kBlock) {
-    const double val = s_rho[t];
+    const double val = sm.rho[t];
     if (val != 0.0) unsafeAtomicAdd(&rho[tile_node(tile, t, qtx, qtxy, S.nx, S.ny, nxy)], val);
   }
   if (kMove) {
     if (threadIdx.x == 0) {
-      d->L.coll_cnt[tidx] = max(0, s_ncoll - kCandF64);
-      d->L.out_cnt[tidx] = s_nout;
+      d->L.coll_cnt[tidx] = max(0, sm.ncoll - kCandF64);
+      d->L.out_cnt[tidx] = sm.nout;
     }
     __syncthreads();
-    tally_store(s_tally, d->L.tally + (long)TL_N * tidx);
-    if (s_far && !md_near) list_far(P, d->L, d->md, S.nx, S.ny, beg, end, s_nout);
+    tally_store(sm.tally, d->L.tally + (long)TL_N * tidx);
+    if (sm.far && !md_near) list_far(P, d->L, d->md, S.nx, S.ny, beg, end, sm.nout);
   }
+}
+// (at most 168 VGPRs: three waves per SIMD; 52 KB of LDS allow three blocks a CU)
+template <bool kMove>
+__global__ __launch_bounds__(kBlock, 3) void push_f64_kernel(const PushDescF64* descs, int nb,
+                                                          int span, int chunk) {
+  __shared__ PushSmem<PartF64, kMove> sm;
+  const int sp = (int)blockIdx.x >= nb ? 1 : 0, b = (int)blockIdx.x - sp * nb;
+  push_tile<kMove>((const PIC_CONST PushDescF64*)(descs + sp), span * (int)xcd_interleave(b, chunk), span, sm);
 }
 
 // ---------------------------------------------------------------- MD particles
@@ -1764,6 +1783,12 @@ __device__ __forceinline__ T wave_sum_t(T v) {
 // fixed-point charge the sums are exact and the mesh does not depend on the
 // grouping); the remaining lanes add their own shares.
 constexpr int kDepGroups = 16;
+// what the wave's lanes wrote to LDS is seen by all of them
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 template <typename A>
 __device__ __forceinline__ void deposit_wave(A (*s_sum)[8], int* s_cell, A* __restrict__ rho,
                                              const SpeciesStep& S, int cell, const A part[8]) {
@@ -1777,7 +1802,7 @@ __device__ __forceinline__ void deposit_wave(A (*s_sum)[8], int* s_cell, A* __re
     pending &= ~__ballot(cell == key);
   }
   for (int t = lane; t < 8 * n; t += 64) (&s_sum[0][0])[t] = (A)0;
-  __syncthreads();  // (one wave a block)
+  wave_sync();
   if (mine >= 0) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
@@ -1787,7 +1812,7 @@ __device__ __forceinline__ void deposit_wave(A (*s_sum)[8], int* s_cell, A* __re
         atomicAdd(&s_sum[mine][t], part[t]);
     }
   }
-  __syncthreads();
+  wave_sync();
   for (int e = lane; e < 8 * n; e += 64) {
     const int c = s_cell[e >> 3], t = e & 7;
     int i = cell_i(c) + (t & 1), j = cell_j(c) + ((t >> 1) & 1);
@@ -1798,7 +1823,7 @@ __device__ __forceinline__ void deposit_wave(A (*s_sum)[8], int* s_cell, A* __re
   Tile none{};
   if (cell >= 0 && mine < 0)
     corner_add<A>(none, -1, nullptr, rho, S, cell_i(cell), cell_j(cell), cell_k(cell), part);
-  __syncthreads();  // the sums are free again
+  wave_sync();  // the sums are free again
 }
 
 __device__ __forceinline__ void kill(const PartF64& P, long p) { P.z[p] = -1.0; }
@@ -1827,48 +1852,57 @@ __device__ __forceinline__ void copy_rec(const PartF32R& src, const PartF32R& ds
   dst.vz[p] = h;
 }
 
-// one thread per MD particle of the dense list of this step, both species in
-// one launch (blocks [0, nb) electrons, [nb, 2 nb) ions); events go to the
-// block's own tally row, grain hits to LDS counters first.  The particles are
-// read from P and their new states written to the same slots of D, the species'
-// other record buffer, so that this kernel runs beside the push; the lists
-// kernel after both copies the states back and takes the survivors' collisions
-// (kept out of this kernel so that its registers allow three waves per SIMD).
+// The MD particles of the dense list of this step, a wave a group of them, in
+// blocks of kWaves waves: blocks [0, pr.nb) the electrons', [pr.nb, 2 pr.nb) the
+// ions'; events go to the wave's own tally row, grain hits to LDS counters
+// first.  The particles are read from P and their new states written to the same
+// slots of D, the species' other record buffer, so that this runs beside the
+// push; the lists kernel after both copies the states back and takes the
+// survivors' collisions (here they cost more registers: 113 us became 147 in the
+// 64x64x256 box).
 constexpr int kMdThreads = 64;
 // lists up to this length move four lanes a particle (about the particles that
 // one lane each would leave the chip's 1,024 SIMDs a wave or less)
 constexpr int kMdQuad = 49152;
-template <typename PT, typename ET, typename RT>
-__global__ __launch_bounds__(kMdThreads) void md_kernel(SpeciesPair<PT> pr, PT D0, PT D1,
-                                                        const ET* __restrict__ E,
-                                                        RT* __restrict__ rho, MdTables md,
-                                                        unsigned long long* __restrict__ grain_count) {
-  const int sp = (int)blockIdx.x >= pr.nb;
+constexpr int kMdStage = 256;  // grains staged in LDS
+template <typename RT, int kWaves>
+struct MdSmem {
+  RT sum[kWaves][kDepGroups][8];
+  double gpos[3 * kMdStage], Qc[kMdStage];
+  unsigned hits[kMdStage];
+  int cell[kWaves][kDepGroups];
+};
+template <int kWaves, typename PT, typename ET, typename RT>
+__device__ __forceinline__ void md_block(const SpeciesPair<PT>& pr, const PT& D0, const PT& D1,
+                                         const ET* __restrict__ E, RT* __restrict__ rho,
+                                         const MdTables& md,
+                                         unsigned long long* __restrict__ grain_count, int block,
+                                         MdSmem<RT, kWaves>& sm) {
+  const int sp = block >= pr.nb;
   const PT P = pr.P[sp];
   const PT D = sp ? D1 : D0;
   const SpeciesStep S = pr.S[sp];
   const WorkLists L = pr.L[sp];
-  const int bid = (int)blockIdx.x - sp * pr.nb;
   const int total = *L.n_md;
-  if ((long)bid * (total <= kMdQuad ? kMdThreads / 4 : kMdThreads) >= total) return;
-  constexpr int kStage = 256;
-  __shared__ double s_gpos[3 * kStage], s_Qc[kStage];
-  __shared__ unsigned s_hits[kStage];
-  __shared__ RT s_sum[kDepGroups][8];
-  __shared__ int s_cell[kDepGroups];
-  const bool staged = md.n_grains <= kStage;
-  for (int t = threadIdx.x; t < min(md.n_grains, kStage); t += blockDim.x) {
-    s_hits[t] = 0u;
+  const int per = total <= kMdQuad ? 16 : 64;  // particles a wave takes at a time
+  const int b0 = (block - sp * pr.nb) * kWaves;
+  if ((long)b0 * per >= total) return;
+  const int lane = (int)threadIdx.x & 63;
+  const int wave = kWaves == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int bid = b0 + wave, nw = pr.nb * kWaves;
+  const bool staged = md.n_grains <= kMdStage;
+  for (int t = threadIdx.x; t < min(md.n_grains, kMdStage); t += 64 * kWaves) {
+    sm.hits[t] = 0u;
     if (staged) {
-      s_Qc[t] = md.Q[t] * S.coul_c;
+      sm.Qc[t] = md.Q[t] * S.coul_c;
       double gx = md.gpos[3 * t] - md.bx0, gy = md.gpos[3 * t + 1] - md.by0;
-      s_gpos[3 * t] = gx < 0.0 ? gx + S.nx : gx;
-      s_gpos[3 * t + 1] = gy < 0.0 ? gy + S.ny : gy;
-      s_gpos[3 * t + 2] = md.gpos[3 * t + 2];
+      sm.gpos[3 * t] = gx < 0.0 ? gx + S.nx : gx;
+      sm.gpos[3 * t + 1] = gy < 0.0 ? gy + S.ny : gy;
+      sm.gpos[3 * t + 2] = md.gpos[3 * t + 2];
     }
   }
   __syncthreads();
-  const GrainView G = staged ? GrainView{s_gpos, s_Qc, false} : GrainView{md.gpos, md.Q, true};
+  const GrainView G{(LdsDoubles)sm.gpos, (LdsDoubles)sm.Qc, !staged};
   const double a2_cells = md.a2 / (S.dx * S.dx);
   const bool image = md.bsx == S.nx || md.bsy == S.ny;
   int n_w0 = 0, n_w1 = 0, n_bad = 0, n_dead = 0;
@@ -1894,29 +1928,29 @@ __global__ __launch_bounds__(kMdThreads) void md_kernel(SpeciesPair<PT> pr, PT D
         if (cell < 0) st = ST_WALL1;
       } else {
         if (st == ST_GRAIN) {
-          if (hit < kStage) atomicAdd(&s_hits[hit], 1u);
+          if (hit < kMdStage) atomicAdd(&sm.hits[hit], 1u);
           else atomicAdd(&grain_count[2 * hit + S.sp], 1ull);
         }
         kill(D, p);
       }
     }
-    deposit_wave<RT>(s_sum, s_cell, rho, S, cell, part);
+    deposit_wave<RT>(sm.sum[wave], sm.cell[wave], rho, S, cell, part);
     n_w0 += st == ST_WALL0;
     n_w1 += st == ST_WALL1;
     n_bad += st == ST_BAD;
     n_dead += st == ST_WALL0 || st == ST_WALL1 || st == ST_BAD || st == ST_GRAIN;
   };
   if (total <= kMdQuad) {
-    for (long base = (long)bid * (kMdThreads / 4); base < total; base += (long)pr.nb * (kMdThreads / 4))
-      move(std::integral_constant<int, 4>{}, base + (threadIdx.x >> 2), (int)threadIdx.x & 3);
+    for (long base = (long)bid * 16; base < total; base += (long)nw * 16)
+      move(std::integral_constant<int, 4>{}, base + (lane >> 2), lane & 3);
   } else {
-    for (long base = (long)bid * kMdThreads; base < total; base += (long)pr.nb * kMdThreads)
-      move(std::integral_constant<int, 1>{}, base + threadIdx.x, 0);
+    for (long base = (long)bid * 64; base < total; base += (long)nw * 64)
+      move(std::integral_constant<int, 1>{}, base + lane, 0);
   }
   int c4[4] = {n_w0, n_w1, n_bad, n_dead};
 #pragma unroll
   for (int k = 0; k < 4; ++k) c4[k] = wave_sum(c4[k]);
-  if (threadIdx.x == 0) {  // this block's own tally row (no atomics)
+  if (lane == 0) {  // this wave's own tally row (no atomics)
     unsigned long long* tally = L.tally + (long)TL_N * (L.ngrid + bid);
     const int kinds[4] = {TL_W0, TL_W1, TL_BAD, TL_DEAD};
 #pragma unroll
@@ -1924,8 +1958,41 @@ __global__ __launch_bounds__(kMdThreads) void md_kernel(SpeciesPair<PT> pr, PT D
       if (c4[k]) tally[kinds[k]] += (unsigned long long)c4[k];
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < min(md.n_grains, kStage); t += blockDim.x)
-    if (s_hits[t]) atomicAdd(&grain_count[2 * t + S.sp], (unsigned long long)s_hits[t]);
+  for (int t = threadIdx.x; t < min(md.n_grains, kMdStage); t += 64 * kWaves)
+    if (sm.hits[t]) atomicAdd(&grain_count[2 * t + S.sp], (unsigned long long)sm.hits[t]);
+}
+template <typename PT, typename ET, typename RT>
+__global__ __launch_bounds__(kMdThreads) void md_kernel(SpeciesPair<PT> pr, PT D0, PT D1,
+                                                        const ET* __restrict__ E,
+                                                        RT* __restrict__ rho, MdTables md,
+                                                        unsigned long long* __restrict__ grain_count) {
+  __shared__ MdSmem<RT, 1> sm;
+  md_block<1>(pr, D0, D1, E, rho, md, grain_count, (int)blockIdx.x, sm);
+}
+
+// The push and the MD particles' motion in one launch, the MD blocks (four waves
+// each) first, for a box whose blocks are all resident at once: a second stream
+// for the MD kernel costs a fork and a join, about 5 us each (16x16x32 cells: from
+// the fields to the lists 44 us with two launches, 34 us so).  A larger box keeps two:
+// the MD motion's registers (two waves per SIMD) would be the push's too.
+template <typename PT, typename Desc, typename ET, typename RT>
+__global__ __launch_bounds__(kBlock, 2) void push_md_kernel(const Desc* descs, int nb, int span,
+                                                         int chunk, SpeciesPair<PT> pr, PT D0,
+                                                         PT D1, const ET* __restrict__ E,
+                                                         RT* __restrict__ rho, MdTables md,
+                                                         unsigned long long* __restrict__ grain_count) {
+  __shared__ union {
+    PushSmem<PT, true> push;
+    MdSmem<RT, kBlock / 64> md;
+  } sm;
+  const int block = (int)blockIdx.x - 2 * pr.nb;
+  if (block < 0) {
+    md_block<kBlock / 64>(pr, D0, D1, E, rho, md, grain_count, (int)blockIdx.x, sm.md);
+    return;
+  }
+  const int sp = block >= nb ? 1 : 0;
+  push_tile<true>((const PIC_CONST Desc*)(descs + sp), span * (int)xcd_interleave(block - sp * nb, chunk), span,
+                  sm.push);
 }
 
 // ---------------------------------------------------------------- moments
@@ -2252,12 +2319,14 @@ __device__ __forceinline__ void md_collide_block(const PIC_CONST Desc* d, const 
   }
 }
 
-// One wave goes through kNearSlots slots of a push block near the MD cubes and
-// lists those that are now in a cube for the next step, in slot order, one
-// reservation per 256 slots (the MD particles by their state in D, which other
-// blocks copy back meanwhile; the particles outside the window list themselves,
-// outlier_block).
-constexpr int kNearSlots = 1024;
+// One wave takes kNearSlots slots of a push block near the MD cubes and lists
+// those that are now in a cube for the next step, in slot order, with one
+// reservation (the MD particles by their state in D, which other blocks copy
+// back meanwhile; the particles outside the window list themselves,
+// outlier_block).  Four slots a lane: the loads, the tables and the reservation
+// depend on each other, and a wave that went through 1,024 slots in turn took
+// four times that chain (16x16x32 cells: lists kernel 23 us, 7.4 us so).
+constexpr int kNearSlots = 256;
 template <typename PT, typename Desc>
 __device__ __forceinline__ void near_block(const PIC_CONST Desc* d, const PT& D, int chunk,
                                            int chunks) {
@@ -2269,37 +2338,33 @@ __device__ __forceinline__ void near_block(const PIC_CONST Desc* d, const PT& D,
   const int first = L.tstart[t0], end = L.tstart[t0 + d->span];
   const int lane = (int)threadIdx.x & 63;
   // (a push block with more slots than its chunks cover: the chunks take turns)
-  for (int b0 = first + (chunk % chunks) * kNearSlots; b0 < end; b0 += chunks * kNearSlots) {
-    const int e0 = min(end, b0 + kNearSlots);
-    for (int base = b0; base < e0; base += 256) {
-      const int p0 = base + 4 * lane;
-      const bool have = p0 < e0;
-      const unsigned m = have ? L.mask[p0 >> 2] : 0xf0u;
-      bool in[4];
-      int cnt = 0;
+  for (int base = first + (chunk % chunks) * kNearSlots; base < end; base += chunks * kNearSlots) {
+    const int p0 = base + 4 * lane;
+    const unsigned m = p0 < end ? L.mask[p0 >> 2] : 0xf0u;
+    bool in[4];
+    int cnt = 0;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int p = p0 + q;
-        const bool moved = (m >> q) & 1u;
-        in[q] = !(m & (16u << q)) && (moved ? slot_alive(D, p) : slot_alive(P, p)) &&
-                in_md(md, nx, ny, moved ? slot_cell(D, p) : slot_cell(P, p));
-        cnt += in[q];
-      }
-      int incl = cnt;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const int t = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += t;
-      }
-      const int total = __shfl(incl, 63, 64);
-      if (total == 0) continue;
-      int at = 0;
-      if (lane == 0) at = atomicAdd(L.n_md_next, total);
-      at = __shfl(at, 0, 64) + incl - cnt;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (in[q]) L.md_next[at++] = p0 + q;
+    for (int q = 0; q < 4; ++q) {
+      const int p = p0 + q;
+      const bool moved = (m >> q) & 1u;
+      in[q] = !(m & (16u << q)) && (moved ? slot_alive(D, p) : slot_alive(P, p)) &&
+              in_md(md, nx, ny, moved ? slot_cell(D, p) : slot_cell(P, p));
+      cnt += in[q];
     }
+    int incl = cnt;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int t = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += t;
+    }
+    const int total = __shfl(incl, 63, 64);
+    if (total == 0) continue;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(L.n_md_next, total);
+    at = __shfl(at, 0, 64) + incl - cnt;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (in[q]) L.md_next[at++] = p0 + q;
   }
 }
 
@@ -3043,9 +3108,6 @@ __global__ void fill_int_kernel(int* a, long n, int v) {
 }
 
 // k -> k + 1 at the end of a step
-__global__ void advance_step_kernel(uint32_t* step) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *step += 1u;
-}
 
 // ---------------------------------------------------------------- ionisation
 // The ionisations of the step, after every particle has moved and collided
@@ -3211,11 +3273,6 @@ int tile_grid(int nx, int ny, int nz, int extra) {
   return (((nx + 3) / 4) * ((ny + 3) / 4) * ((nz + 3) / 4) + extra + 15) / 16 * 16;
 }
 
-
-void launch_advance_step(uint32_t* step, hipStream_t st) {
-  hipLaunchKernelGGL(advance_step_kernel, dim3(1), dim3(64), 0, st, step);
-}
-
 void launch_push(const PushDescF64* descs, const WorkLists& L, bool move, hipStream_t st) {
   if (L.ngrid <= 0) return;
   const int span = push_span(L), nb = L.ngrid / span, chunk = push_chunk(L, span);
@@ -3258,29 +3315,62 @@ void launch_field_out(const double* psi, double* phi, void* E, int e_f64,
                        nz, dx, rf, nbm);
 }
 
+// waves for the particles that the loading density puts into the cubes, per
+// species (the kernel strides over what there is)
+static long md_particles(const MdTables& md, const SpeciesStep& S, const WorkLists& L) {
+  return (long)(md.n_cells * (L.slots / ((double)S.nx * S.ny * S.nz)));
+}
+static int md_waves(const MdTables& md, const SpeciesStep& S, const WorkLists& L) {
+  const long guess = md_particles(md, S, L), per = guess <= kMdQuad ? 16 : 64;
+  return (int)std::min<long>(kMdBlocks, std::max<long>(64, guess / per * 5 / 4));
+}
 template <typename PT, typename ET, typename RT>
 static void md_move_impl(const PT P[2], const PT D[2], const void* E, void* rho, const MdTables& md,
                          const SpeciesStep S[2], unsigned long long* gc, const WorkLists L[2],
-                         int span, hipStream_t st) {
+                         hipStream_t st) {
   if (md.n_grains == 0 || L[0].ngrid <= 0) return;
-  // blocks for the particles that the loading density puts into the cubes (the
-  // kernel strides over what there is)
-  const long guess = (long)(md.n_cells * (L[0].slots / ((double)S[0].nx * S[0].ny * S[0].nz)));
-  const long per = guess <= kMdQuad ? kMdThreads / 4 : kMdThreads;
-  const int nb = (int)std::min<long>(kMdBlocks, std::max<long>(64, guess / per * 5 / 4));
-  SpeciesPair<PT> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, nb, span};
+  const int nb = md_waves(md, S[0], L[0]);
+  SpeciesPair<PT> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, nb, push_span(L[0])};
   hipLaunchKernelGGL((md_kernel<PT, ET, RT>), dim3(2 * nb), dim3(kMdThreads), 0, st, pr,
                      D[0], D[1], (const ET*)E, (RT*)rho, md, gc);
 }
 void launch_md_move(const PartF64 P[2], const PartF64 D[2], const void* E, void* rho,
                     const MdTables& md, const SpeciesStep S[2], unsigned long long* gc,
                     const WorkLists L[2], hipStream_t st) {
-  md_move_impl<PartF64, double2, double>(P, D, E, rho, md, S, gc, L, push_span(L[0]), st);
+  md_move_impl<PartF64, double2, double>(P, D, E, rho, md, S, gc, L, st);
 }
 void launch_md_move(const PartF32R P[2], const PartF32R D[2], const void* E, void* rho,
                     const MdTables& md, const SpeciesStep S[2], unsigned long long* gc,
                     const WorkLists L[2], hipStream_t st) {
-  md_move_impl<PartF32R, float4, long long>(P, D, E, rho, md, S, gc, L, push_span(L[0]), st);
+  md_move_impl<PartF32R, float4, long long>(P, D, E, rho, md, S, gc, L, st);
+}
+
+// two blocks a CU
+constexpr int kResident = 512;
+bool push_md_fits(const MdTables& md, const SpeciesStep& S, const WorkLists& L) {
+  return md.n_grains > 0 && L.ngrid > 0 && md_particles(md, S, L) <= kMdQuad &&
+         2 * (L.ngrid / push_span(L) + (md_waves(md, S, L) + 3) / 4) <= kResident;
+}
+template <typename PT, typename Desc, typename ET, typename RT>
+static void push_md_impl(const Desc* descs, const PT P[2], const PT D[2], const void* E, void* rho,
+                         const MdTables& md, const SpeciesStep S[2], unsigned long long* gc,
+                         const WorkLists L[2], hipStream_t st) {
+  const int span = push_span(L[0]), nb = L[0].ngrid / span;
+  const int nm = (md_waves(md, S[0], L[0]) + 3) / 4;
+  SpeciesPair<PT> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, nm, span};
+  hipLaunchKernelGGL((push_md_kernel<PT, Desc, ET, RT>), dim3(2 * (nm + nb)), dim3(kBlock), 0, st,
+                     descs, nb, span, push_chunk(L[0], span), pr, D[0], D[1], (const ET*)E, (RT*)rho,
+                     md, gc);
+}
+void launch_push_md(const PushDescF64* descs, const PartF64 P[2], const PartF64 D[2], const void* E,
+                    void* rho, const MdTables& md, const SpeciesStep S[2], unsigned long long* gc,
+                    const WorkLists L[2], hipStream_t st) {
+  push_md_impl<PartF64, PushDescF64, double2, double>(descs, P, D, E, rho, md, S, gc, L, st);
+}
+void launch_push_md(const PushDescF32* descs, const PartF32R P[2], const PartF32R D[2],
+                    const void* E, void* rho, const MdTables& md, const SpeciesStep S[2],
+                    unsigned long long* gc, const WorkLists L[2], hipStream_t st) {
+  push_md_impl<PartF32R, PushDescF32, float4, long long>(descs, P, D, E, rho, md, S, gc, L, st);
 }
 
 std::vector<int32_t> near_blocks(const WorkLists& L, const MdTables& md, int nx, int ny, int nz,

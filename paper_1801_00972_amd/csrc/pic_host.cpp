@@ -129,8 +129,10 @@ struct Replica {
   // sort
   int* d_hist = nullptr;
   int* d_sums = nullptr;
-  uint32_t step = 0;       // host mirror of *d_step
-  uint32_t* d_step = nullptr;
+  uint32_t step = 0;       // host mirror of the step counter
+  uint32_t* d_step = nullptr;  // [2] the counter, in the slot of the charge buffer rho_cur; the
+                               // step's field stage writes the next one into the other
+  uint32_t* step_slot() const { return d_step + rho_cur; }
   int margin[2]{2, 1};     // LDS window margin of the push per species (cells)
   // the push's descriptors: two species for each of the 8 buffer phases
   PushDescF64* push64 = nullptr;
@@ -663,7 +665,7 @@ SpeciesStep species_step(const Replica& R, int sp) {
   }
   S.key0 = (uint32_t)(c.seed & 0xffffffffu);
   S.key1 = (uint32_t)(c.seed >> 32);
-  S.step = R.d_step;
+  S.step = R.step_slot();
   S.Qp = R.Qp;
   S.sign = sp == 0 ? -1.0 : 1.0;
   S.isign = sp == 0 ? -1 : 1;
@@ -696,8 +698,8 @@ int alloc_particles(pic_ctx* ctx, Replica& R) {
       }
     }
   TRY(dalloc(ctx, R, &R.d_cnt, 16));
-  TRY(dalloc(ctx, R, &R.d_step, 1));
-  HIPCHK(ctx, hipMemsetAsync(R.d_step, 0, 4, ctx->stream));
+  TRY(dalloc(ctx, R, &R.d_step, 2));
+  HIPCHK(ctx, hipMemsetAsync(R.d_step, 0, 8, ctx->stream));
   for (int sp = 0; sp < 2; ++sp) {
     WorkLists& L = R.lists[sp];
     L.ntx = (R.nx + 3) / 4;
@@ -795,6 +797,7 @@ PushDesc<PT, ET, RT> push_desc(const Replica& R, int sp, int ph) {
   d.rho = (RT*)R.rho[1 - ((ph >> 2) & 1)];
   d.md = R.md;
   d.S = species_step(R, sp);
+  d.S.step = R.d_step + ((ph >> 2) & 1);
   d.L = lists_at(R, sp, (ph >> 2) & 1);
   d.span = push_span(R.lists[sp]);
   d.chunk = push_chunk(R.lists[sp], d.span);
@@ -846,7 +849,7 @@ RefineState refine_state(const Replica& R) {
 int solve_fields(pic_ctx* ctx, Replica& R, bool zero_next = false, bool* final_pending = nullptr) {
   hipStream_t st = ctx->stream;
   const pic_config& c = R.cfg;
-  const RfDrive rf{c.V_dc, c.V_rf, c.f_rf, c.dt, R.d_step};
+  const RfDrive rf{c.V_dc, c.V_rf, c.f_rf, c.dt, R.step_slot(), R.d_step + (1 - R.rho_cur)};
   const double vol = c.dx * c.dx * c.dx;
   unsigned long long* next =
       zero_next ? (unsigned long long*)R.rho[1 - R.rho_cur] : nullptr;  // 8-byte words, 0 = 0.0
@@ -944,7 +947,7 @@ int read_tallies(pic_ctx* ctx, Replica& R, int sp, unsigned long long out[TL_N])
 }
 
 AvgBins avg_bins_of(const pic_ctx* ctx, const Replica& R) {
-  return AvgBins{R.d_step, R.cfg.f_rf, R.cfg.dt, ctx->avg_bins, 9 * R.nn};
+  return AvgBins{R.step_slot(), R.cfg.f_rf, R.cfg.dt, ctx->avg_bins, 9 * R.nn};
 }
 
 // fine-grid moments of both species added to mom [2][4][fn] (in the
@@ -974,7 +977,7 @@ int enqueue_coulomb(pic_ctx* ctx, Replica& R) {
   C.ncell = 64 * R.ngrid;
   C.key0 = (uint32_t)(c.seed & 0xffffffffu);
   C.key1 = (uint32_t)(c.seed >> 32);
-  C.step = R.d_step;
+  C.step = R.step_slot();
   C.w_vol = R.w / (c.dx * c.dx * c.dx);
   const double m[2] = {kMassE, kMassAr}, q[2] = {-kCharge, kCharge};
   const double dtc = (double)c.coulomb_interval * c.dt;
@@ -1015,7 +1018,7 @@ int enqueue_sample(pic_ctx* ctx, Replica& R) {
   }
   if (R.fine_avg_on) {
     // per bin: the potential, then W and v W per species (9 fine-node arrays)
-    const AvgBins fb{R.d_step, R.cfg.f_rf, R.cfg.dt, ctx->avg_bins, 9 * R.fine.fn};
+    const AvgBins fb{R.step_slot(), R.cfg.f_rf, R.cfg.dt, ctx->avg_bins, 9 * R.fine.fn};
     launch_fine_phi(R.phi, R.md, R.Uphi, R.fine, R.nx, R.ny, R.nz, R.cfg.dx, R.cfg.grain_radius,
                     R.fine_avg, fb, ctx->stream);
     TRY(enqueue_fine(ctx, R, R.fine_avg + R.fine.fn, fb));
@@ -1064,8 +1067,9 @@ int enqueue_particles(pic_ctx* ctx, Replica& R, bool fin) {
   const WorkLists L[2] = {lists_of(R, 0), lists_of(R, 1)};
   PT P[2], D[2];
   buffers(R, P, D);
+  const bool one = !ctx->prof && push_md_fits(R.md, S[0], L[0]);  // (timed: kernel by kernel)
   bool mdf = false;
-  TRY(md_streams(ctx, &mdf));
+  if (!one) TRY(md_streams(ctx, &mdf));
   hipStream_t ms = st;
   if (mdf) {
     ms = ctx->md_stream;
@@ -1076,14 +1080,27 @@ int enqueue_particles(pic_ctx* ctx, Replica& R, bool fin) {
   if (fin)
     launch_refine_final(R.nx, R.ny, R.nz, R.b, R.psi, R.r, R.cfg.max_refine, R.cfg.refine_tol,
                         R.norms, R.refine_ctl, ms);
-  hipEvent_t m0 = prof_event(ctx);
-  launch_md_move(P, D, R.E, rho, R.md, S, R.d_gc, L, ms);
-  if (mdf) HIPCHK(ctx, hipEventRecord(ctx->md_join, ms));
+  // Two launches side by side: the first enqueued gets the chip's waves first.  A long
+  // push goes first and hides the MD motion (64x64x256 cells, FP32R: 9.67 ms for 8
+  // steps against 10.21); one of about 8 million slots or less ends with it, and the
+  // MD kernel's chains go first (36x30x77 cells, 7 per cell: 2.24 ms for 16 steps
+  // against 2.27).
+  const bool push_first = one || L[0].slots + L[1].slots > 8 << 20;
+  auto md_part = [&]() -> int {
+    hipEvent_t a = prof_event(ctx);
+    launch_md_move(P, D, R.E, rho, R.md, S, R.d_gc, L, ms);
+    if (mdf) HIPCHK(ctx, hipEventRecord(ctx->md_join, ms));
+    prof_pair(ctx, PIC_PROF_LISTS, a, prof_event(ctx));
+    return PIC_OK;
+  };
+  if (!push_first) TRY(md_part());
   hipEvent_t a = prof_event(ctx);
-  prof_pair(ctx, PIC_PROF_LISTS, m0, a);
-  push(R, phase_of(R), true, st);
+  if (one) launch_push_md(descs_of(D, R), P, D, R.E, rho, R.md, S, R.d_gc, L, st);
+  else push(R, phase_of(R), true, st);
   hipEvent_t b = prof_event(ctx);
   prof_pair(ctx, PIC_PROF_PUSH, a, b);
+  if (push_first && !one) TRY(md_part());
+  b = prof_event(ctx);
   if (mdf) HIPCHK(ctx, hipStreamWaitEvent(st, ctx->md_join, 0));
   launch_lists(descs_of(D, R), D, R.cfg.n_grains > 0, L, 1, st);
   if (R.ionize) ionize(R, P, L, S[0], st);
@@ -1094,7 +1111,6 @@ int enqueue_particles(pic_ctx* ctx, Replica& R, bool fin) {
 // launches one step of a replica on ctx->stream from the host state at the
 // start of the step (buffer phases); advance_host then moves the host mirrors
 int enqueue_step(pic_ctx* ctx, Replica& R, int sorts, int sample) {
-  hipStream_t st = ctx->stream;
   hipEvent_t f0 = prof_event(ctx);
   bool fin = false;
   TRY(solve_fields(ctx, R, true, ctx->reps.size() == 1 && !ctx->prof ? &fin : nullptr));
@@ -1107,7 +1123,6 @@ int enqueue_step(pic_ctx* ctx, Replica& R, int sorts, int sample) {
   }
   if (R.prec == PIC_FP64) TRY(enqueue_particles<PartF64>(ctx, R, fin));
   else TRY(enqueue_particles<PartF32R>(ctx, R, fin));
-  launch_advance_step(R.d_step, st);
   CHECK_LAUNCH(ctx);
   if (sorts) {
     hipEvent_t s0 = prof_event(ctx);
@@ -1210,7 +1225,6 @@ int enqueue_batch(pic_ctx* ctx, int sorts, int sample) {
     const WorkLists L[2] = {lists_of(R, 0), lists_of(R, 1)};
     launch_lists(descs_of(D, R), D, R.cfg.n_grains > 0, L, 1, ws);
     if (R.ionize) ionize(R, P, L, S[0], ws);
-    launch_advance_step(R.d_step, ws);
     return PIC_OK;
   }));
   CHECK_LAUNCH(ctx);
@@ -2354,7 +2368,7 @@ int pic_set_state(pic_ctx* ctx, int replica, const pic_state_view* v) {
     HIPCHK(ctx, hipMemcpy(R->d_gc, gc.data(), 16 * ng, hipMemcpyHostToDevice));
   }
   R->step = v->step;
-  HIPCHK(ctx, hipMemcpy(R->d_step, &v->step, 4, hipMemcpyHostToDevice));
+  HIPCHK(ctx, hipMemcpy(R->step_slot(), &v->step, 4, hipMemcpyHostToDevice));
   if (R->ionize) {
     // ionisations continue with the ids after the largest given
     uint32_t nid[2] = {0u, 0u};

@@ -48,6 +48,7 @@ struct PartF32R {
 struct RfDrive {
   double V_dc, V_rf, f_rf, dt;
   const uint32_t* step;
+  uint32_t* next;  // the next step's counter
 };
 
 // per-species work lists and counters of one step (device)
