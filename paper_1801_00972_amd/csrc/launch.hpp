@@ -91,12 +91,13 @@ int moments_setup();  // the kernels' LDS sizes; 0 or an error
 void launch_moments(const PartF64* P64, const PartF32R* P32, const SpeciesStep& S,
                     const WorkLists& L, double* mom, long nn, const AvgBins& avg,
                     hipStream_t st);
-// fine-grid moments of one species: mom [4][fb.fn] gets W, v W of the
+// fine-grid moments of both species: mom [2][4][fb.fn] gets W, v W of the
 // particles inside the box summed per fine node (added as in launch_moments);
 // capacity bounds the slots in use
-void launch_fine_moments(const PartF64* P64, const PartF32R* P32, const WorkLists& L,
-                         const FineBox& fb, double* mom, const AvgBins& avg, long capacity,
-                         hipStream_t st);
+void launch_fine_moments(const PartF64 P[2], const WorkLists L[2], const FineBox& fb, double* mom,
+                         const AvgBins& avg, long capacity, hipStream_t st);
+void launch_fine_moments(const PartF32R P[2], const WorkLists L[2], const FineBox& fb, double* mom,
+                         const AvgBins& avg, long capacity, hipStream_t st);
 // Coulomb collisions (coulomb.hip).  Work buffers of a replica: per species
 // the per-cell counts turned into range starts [ncell + 1], fill cursors
 // [ncell], each tile's own particles per cell [ncell] (the counting kernel's
@@ -135,10 +136,10 @@ void launch_coulomb(const PartF64* P64, const PartF32R* P32, const WorkLists L[2
 // sample counted in cnt[bin]
 void launch_avg_phi(const double* phi, double* acc, long nn, const AvgBins& avg,
                     unsigned long long* cnt, hipStream_t st);
-// out[u] = (sum over bins b0..b1-1 of acc[b stride + u]) / (samples in those
-// bins), times wv for u >= n_plain (the moments), for u < total
-void launch_avg_out(const double* acc, int b0, int b1, long stride, long total, long n_plain,
-                    const unsigned long long* cnt, double wv, double* out, hipStream_t st);
+// the averages over bins b0..b1-1 of the nine sums per bin acc [bin][9][len]: phi,
+// densities [species][len] and fluxes [species][3][len] (times wv), each if not null
+void launch_avg_out(const double* acc, int b0, int b1, long len, const unsigned long long* cnt,
+                    double wv, double* phi, double* n_out, double* flux_out, hipStream_t st);
 // counting sort of the slots in use into dst (dropping empty slots, padding
 // every tile to a multiple of 4), and the particles in MD cubes listed anew in
 // md_list, *n_md of them; capacity bounds the slots in use
@@ -280,11 +281,15 @@ void launch_fine_phi(const double* phi, const MdTables& md, const double* Uphi, 
                      int nx, int ny, int nz, double dx, double radius, double* out,
                      const AvgBins& avg, hipStream_t st);
 void launch_e_out(const double* E64, const float* E32, double* out, long nn, hipStream_t st);
-void launch_rho_total(const double* acc64, const long long* accfx, double* tot64, long long* totfx,
-                      const unsigned long long* counts, const double* gpos, int ng, int nx, int ny,
-                      long nn, long long Qp, hipStream_t st);
-void launch_scale(const double* in, const long long* infx, double conv, double* out, long nn,
-                  hipStream_t st);
+// the total charge density: conv * (plasma + grains), or that sum in fixed point (outfx)
+void launch_rho_out(const double* acc64, const long long* accfx, const GrainShare* tab, int n_tab,
+                    const unsigned long long* counts, double conv, double* out, long long* outfx,
+                    long plane, long nn, hipStream_t st);
+// moments [species][4][nn] times conv into the densities [species][nn] and the
+// fluxes [species][3][nn] (either may be null)
+void launch_moments_out(const double* mom, long nn, double conv, double* n_out, double* flux_out,
+                        hipStream_t st);
+void launch_scale(double conv, double* a, long n, hipStream_t st);
 void launch_zero_f64(double* a, long n, hipStream_t st);
 void launch_zero_i64(long long* a, long n, hipStream_t st);
 void launch_zero_i32(int* a, long n, hipStream_t st);

@@ -543,47 +543,6 @@ __global__ void thomas_kernel(cplx<T>* __restrict__ d, const TC* __restrict__ in
 }
 
 // ---------------------------------------------------------------- grains
-// CIC nodes and weights of a grain (its position is at least one cell inside)
-__device__ __forceinline__ void grain_nodes(const double* gpos, int g, int nx, int ny, long n[8],
-                                            double w[8], float off[3], int cell[3]) {
-  const double X = gpos[3 * g], Y = gpos[3 * g + 1], Z = gpos[3 * g + 2];
-  const int i0 = (int)floor(X), j0 = (int)floor(Y), k0 = (int)floor(Z);
-  const double fx = X - i0, fy = Y - j0, fz = Z - k0;
-  const int i1 = i0 + 1 == nx ? 0 : i0 + 1, j1 = j0 + 1 == ny ? 0 : j0 + 1;
-  const int ii[2] = {i0, i1}, jj[2] = {j0, j1};
-  for (int t = 0; t < 8; ++t) {
-    const int a = t & 1, b = (t >> 1) & 1, c = t >> 2;
-    n[t] = ii[a] + (long)nx * (jj[b] + (long)ny * (k0 + c));
-    w[t] = (a ? fx : 1.0 - fx) * (b ? fy : 1.0 - fy) * (c ? fz : 1.0 - fz);
-  }
-  off[0] = (float)fx;
-  off[1] = (float)fy;
-  off[2] = (float)fz;
-  cell[0] = i0;
-  cell[1] = j0;
-  cell[2] = k0;
-}
-
-// the same exact split of the macro charge as the particle deposit (FP32R)
-__device__ __forceinline__ void grain_split(long long Q, double fx, double fy, double fz,
-                                            long long part[8]) {
-  const long long qx = (long long)floor(fx * 16777216.0);
-  const long long qy = (long long)floor(fy * 16777216.0);
-  const long long qz = (long long)floor(fz * 16777216.0);
-  long long ax[2];
-  ax[1] = (Q * qx) >> 24;
-  ax[0] = Q - ax[1];
-  for (int a = 0; a < 2; ++a) {
-    const long long y1 = (ax[a] * qy) >> 24;
-    const long long yy[2] = {ax[a] - y1, y1};
-    for (int b = 0; b < 2; ++b) {
-      const long long z1 = (yy[b] * qz) >> 24;
-      part[a + 2 * b] = yy[b] - z1;
-      part[a + 2 * b + 4] = z1;
-    }
-  }
-}
-
 // the field and the potential of grain g's unit-charge solve (psi, both
 // electrodes at 0) on its cube: U[g][3][side^3] and Uphi[g][side^3]
 __global__ void extract_cube_kernel(const double* __restrict__ psi, const int* gcell, int g, int c,
@@ -785,46 +744,59 @@ __global__ void e_out_kernel(const double2* __restrict__ E2, const float4* __res
   }
 }
 
-// total rho: plasma accumulator plus grains.  FP64 form: out = conv * (acc + net W);
-// FP32R: fixed = acc + net * part (exact), out = conv * fixed.
-__global__ void rho_out_kernel(const double* __restrict__ acc64, const long long* __restrict__ accfx,
-                               double conv, double* __restrict__ out, long long* __restrict__ outfx,
-                               long nn) {
-  const long n = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= nn) return;
-  if (acc64) {
-    out[n] = acc64[n];
-  } else {
-    outfx[n] = accfx[n];
+// Total rho: plasma accumulator plus the grains' shares (table sorted by node, then
+// grain), 1,024 nodes a block.  out = conv * (rho + net w), FP64 form, or conv *
+// (rho + net part), where the sum is exact; outfx that sum itself.  One pass to where
+// the caller wants it; a copy, one thread that walked the grains (13 us for six),
+// the scaling and a copy out were four.
+constexpr int kRhoNodes = 1024;
+__global__ __launch_bounds__(256) void rho_out_kernel(const double* __restrict__ acc64,
+                                                      const long long* __restrict__ accfx,
+                                                      const GrainShare* __restrict__ tab, int n_tab,
+                                                      const unsigned long long* __restrict__ counts,
+                                                      double conv, double* __restrict__ out,
+                                                      long long* __restrict__ outfx, long plane,
+                                                      long nn) {
+  __shared__ int s_at[kRhoNodes];  // first share of the node + 1
+  const long n0 = (long)blockIdx.x * kRhoNodes;
+  for (int u = threadIdx.x; u < kRhoNodes; u += 256) s_at[u] = 0;
+  __syncthreads();
+  for (int e = threadIdx.x; e < n_tab; e += 256) {
+    const long u = tab[e].node + plane - n0;  // (the table leaves out the plane z = 0)
+    if (u >= 0 && u < kRhoNodes && (e == 0 || tab[e - 1].node != tab[e].node)) s_at[u] = e + 1;
+  }
+  __syncthreads();
+  for (int u = threadIdx.x; u < kRhoNodes && n0 + u < nn; u += 256) {
+    const long n = n0 + u;
+    double d = acc64 ? acc64[n] : 0.0;
+    long long f = acc64 ? 0 : accfx[n];
+    if (s_at[u])
+      for (int e = s_at[u] - 1; e < n_tab && tab[e].node + plane == n; ++e) {
+        const int g = tab[e].g;
+        const long long net = (long long)counts[2 * g + 1] - (long long)counts[2 * g];
+        d += (double)net * tab[e].w;
+        f += net * tab[e].part;
+      }
+    if (outfx) outfx[n] = f;
+    else out[n] = conv * (acc64 ? d : (double)f);
   }
 }
 
-__global__ void rho_grains_kernel(const unsigned long long* __restrict__ counts, const double* gpos,
-                                  int ng, int nx, int ny, double* __restrict__ acc,
-                                  long long* __restrict__ fx, long long Qp) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  for (int g = 0; g < ng; ++g) {
-    const long long net = (long long)counts[2 * g + 1] - (long long)counts[2 * g + 0];
-    long n[8];
-    double w[8];
-    float off[3];
-    int cell[3];
-    grain_nodes(gpos, g, nx, ny, n, w, off, cell);
-    long long part[8];
-    const double X = gpos[3 * g], Y = gpos[3 * g + 1], Z = gpos[3 * g + 2];
-    grain_split(Qp, X - floor(X), Y - floor(Y), Z - floor(Z), part);
-    for (int t = 0; t < 8; ++t) {
-      if (acc) acc[n[t]] += (double)net * w[t];
-      if (fx) fx[n[t]] += net * part[t];
-    }
-  }
+// moments [species][4][nn] (W, then v W) times conv to where the caller wants
+// the densities [species][nn] and the fluxes [species][3][nn] (either may be null)
+__global__ void moments_out_kernel(const double* __restrict__ mom, long nn, double conv,
+                                   double* __restrict__ n_out, double* __restrict__ flux_out) {
+  const long n = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  const int sp = (int)blockIdx.y >> 2, q = (int)blockIdx.y & 3;
+  double* out = q == 0 ? n_out : flux_out;
+  if (n >= nn || !out) return;
+  out += q == 0 ? sp * nn : (3 * sp + q - 1) * nn;
+  out[n] = conv * mom[(4 * sp + q) * nn + n];
 }
 
-__global__ void scale_kernel(const double* __restrict__ in, const long long* __restrict__ infx,
-                             double conv, double* __restrict__ out, long nn) {
-  const long n = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= nn) return;
-  out[n] = conv * (in ? in[n] : (double)infx[n]);
+__global__ void scale_kernel(double conv, double* __restrict__ a, long n) {
+  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) a[i] = conv * a[i];
 }
 
 // time averages: phi_k into the rf-phase bin of step k, one sample counted
@@ -836,19 +808,27 @@ __global__ void avg_phi_kernel(const double* __restrict__ phi, double* __restric
   if (n < nn) acc[avg.stride * b + n] += phi[n];
 }
 
-// the averages over bins b0..b1-1: phi (u < n_plain) and the moments (times wv)
-__global__ void avg_out_kernel(const double* __restrict__ acc, int b0, int b1, long stride,
-                               long total, long n_plain, const unsigned long long* __restrict__ cnt,
-                               double wv, double* __restrict__ out) {
+// the averages over bins b0..b1-1 of the nine sums acc [bin][9][len] to where the
+// caller wants them (null: not asked for): phi [len], the densities [species][len]
+// and fluxes [species][3][len] times wv
+__global__ void avg_out_kernel(const double* __restrict__ acc, int b0, int b1, long len,
+                               const unsigned long long* __restrict__ cnt, double wv,
+                               double* __restrict__ phi, double* __restrict__ n_out,
+                               double* __restrict__ flux_out) {
+  const int w = (int)blockIdx.y - 1, sp = w >> 2, q = w & 3;  // w < 0: phi
+  double* out = w < 0 ? phi : (q == 0 ? n_out : flux_out);
   const long u = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= total) return;
+  if (u >= len || !out) return;
+  if (w >= 0) out += q == 0 ? sp * len : (3 * sp + q - 1) * len;
+  acc += (w + 1) * len + u;
   double s = 0.0;
   unsigned long long c = 0;
+#pragma unroll 4
   for (int b = b0; b < b1; ++b) {
-    s += acc[stride * b + u];
+    s += acc[9 * len * b];
     c += cnt[b];
   }
-  out[u] = c ? s / (double)c * (u < n_plain ? 1.0 : wv) : 0.0;
+  out[u] = c ? s / (double)c * (w < 0 ? 1.0 : wv) : 0.0;
 }
 
 // The potential on the nodes of the fine grid: the mesh potential with the
@@ -1184,19 +1164,20 @@ void launch_e_out(const double* E64, const float* E32, double* out, long nn, hip
                      (const float4*)E32, out, nn);
 }
 
-void launch_rho_total(const double* acc64, const long long* accfx, double* tot64,
-                      long long* totfx, const unsigned long long* counts, const double* gpos,
-                      int ng, int nx, int ny, long nn, long long Qp, hipStream_t st) {
-  hipLaunchKernelGGL(rho_out_kernel, dim3(nb256(nn)), dim3(256), 0, st, acc64, accfx, 0.0, tot64,
-                     totfx, nn);
-  if (ng > 0)
-    hipLaunchKernelGGL(rho_grains_kernel, dim3(1), dim3(64), 0, st, counts, gpos, ng, nx, ny,
-                       acc64 ? tot64 : nullptr, acc64 ? nullptr : totfx, Qp);
+void launch_rho_out(const double* acc64, const long long* accfx, const GrainShare* tab, int n_tab,
+                    const unsigned long long* counts, double conv, double* out, long long* outfx,
+                    long plane, long nn, hipStream_t st) {
+  hipLaunchKernelGGL(rho_out_kernel, dim3((unsigned)((nn + kRhoNodes - 1) / kRhoNodes)), dim3(256), 0, st,
+                     acc64, accfx, tab, n_tab, counts, conv, out, outfx, plane, nn);
 }
 
-void launch_scale(const double* in, const long long* infx, double conv, double* out, long nn,
-                  hipStream_t st) {
-  hipLaunchKernelGGL(scale_kernel, dim3(nb256(nn)), dim3(256), 0, st, in, infx, conv, out, nn);
+void launch_moments_out(const double* mom, long nn, double conv, double* n_out, double* flux_out,
+                        hipStream_t st) {
+  hipLaunchKernelGGL(moments_out_kernel, dim3(nb256(nn), 8), dim3(256), 0, st, mom, nn, conv, n_out, flux_out);
+}
+
+void launch_scale(double conv, double* a, long n, hipStream_t st) {
+  hipLaunchKernelGGL(scale_kernel, dim3(nb256(n)), dim3(256), 0, st, conv, a, n);
 }
 
 void launch_avg_phi(const double* phi, double* acc, long nn, const AvgBins& avg,
@@ -1204,11 +1185,11 @@ void launch_avg_phi(const double* phi, double* acc, long nn, const AvgBins& avg,
   hipLaunchKernelGGL(avg_phi_kernel, dim3(nb256(nn)), dim3(256), 0, st, phi, acc, nn, avg, cnt);
 }
 
-void launch_avg_out(const double* acc, int b0, int b1, long stride, long total, long n_plain,
-                    const unsigned long long* cnt, double wv, double* out, hipStream_t st) {
-  if (total <= 0) return;
-  hipLaunchKernelGGL(avg_out_kernel, dim3(nb256(total)), dim3(256), 0, st, acc, b0, b1, stride,
-                     total, n_plain, cnt, wv, out);
+void launch_avg_out(const double* acc, int b0, int b1, long len, const unsigned long long* cnt,
+                    double wv, double* phi, double* n_out, double* flux_out, hipStream_t st) {
+  if (len <= 0) return;
+  hipLaunchKernelGGL(avg_out_kernel, dim3(nb256(len), 9), dim3(256), 0, st, acc, b0, b1, len, cnt, wv, phi,
+                     n_out, flux_out);
 }
 
 void launch_fine_phi(const double* phi, const MdTables& md, const double* Uphi, const FineBox& fb,

@@ -2246,12 +2246,16 @@ __device__ __forceinline__ bool fine_near(const PartF32R& P, long p, const FineB
   return c >= 0 && fine_cell_near(fb, cell_i(c), cell_j(c), cell_k(c));
 }
 
+// Both species in one launch (blockIdx.y): each alone waits mostly for its reads.
 template <typename PT>
-__global__ __launch_bounds__(256) void fine_moments_kernel(PT P, WorkLists L, FineBox fb,
+__global__ __launch_bounds__(256) void fine_moments_kernel(PT P0, PT P1, const int32_t* end0,
+                                                           const int32_t* end1, FineBox fb,
                                                            double* __restrict__ mom,
                                                            AvgBins avg) {
+  const PT P = blockIdx.y ? P1 : P0;
+  const long total = blockIdx.y ? *end1 : *end0;
   if (avg.step) mom += avg.stride * phase_bin(*avg.step, avg.f_rf, avg.dt, avg.nbins);
-  const long total = L.tstart[L.ngrid];
+  mom += 4 * fb.fn * blockIdx.y;
   for (long p = (long)blockIdx.x * blockDim.x + threadIdx.x; p < total;
        p += (long)gridDim.x * blockDim.x) {
     if (!fine_near(P, p, fb)) continue;
@@ -3459,17 +3463,21 @@ void launch_moments(const PartF64* P64, const PartF32R* P32, const SpeciesStep& 
     moments_launch<256, kMomCapHalf>(*P32, S, L, mom, nn, avg, nodes, st);
 }
 
-void launch_fine_moments(const PartF64* P64, const PartF32R* P32, const WorkLists& L,
-                         const FineBox& fb, double* mom, const AvgBins& avg, long capacity,
-                         hipStream_t st) {
+template <typename PT>
+static void fine_moments_impl(const PT P[2], const WorkLists L[2], const FineBox& fb, double* mom,
+                              const AvgBins& avg, long capacity, hipStream_t st) {
   const int blocks = (int)std::min<long>(nblk(capacity, 256), 4096);
   if (blocks <= 0) return;
-  if (P64)
-    hipLaunchKernelGGL(fine_moments_kernel<PartF64>, dim3(blocks), dim3(256), 0, st, *P64, L, fb,
-                       mom, avg);
-  else
-    hipLaunchKernelGGL(fine_moments_kernel<PartF32R>, dim3(blocks), dim3(256), 0, st, *P32, L, fb,
-                       mom, avg);
+  hipLaunchKernelGGL(fine_moments_kernel<PT>, dim3(blocks, 2), dim3(256), 0, st, P[0], P[1],
+                     L[0].tstart + L[0].ngrid, L[1].tstart + L[1].ngrid, fb, mom, avg);
+}
+void launch_fine_moments(const PartF64 P[2], const WorkLists L[2], const FineBox& fb, double* mom,
+                         const AvgBins& avg, long capacity, hipStream_t st) {
+  fine_moments_impl(P, L, fb, mom, avg, capacity, st);
+}
+void launch_fine_moments(const PartF32R P[2], const WorkLists L[2], const FineBox& fb, double* mom,
+                         const AvgBins& avg, long capacity, hipStream_t st) {
+  fine_moments_impl(P, L, fb, mom, avg, capacity, st);
 }
 
 void launch_ionize(const PartF64* Pe64, const PartF64* Pi64, const PartF32R* Pe32,

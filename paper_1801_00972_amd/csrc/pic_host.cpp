@@ -953,14 +953,15 @@ AvgBins avg_bins_of(const pic_ctx* ctx, const Replica& R) {
 // fine-grid moments of both species added to mom [2][4][fn] (in the
 // rf-phase bin of the step when avg.step is set)
 int enqueue_fine(pic_ctx* ctx, Replica& R, double* mom, const AvgBins& avg) {
-  for (int sp = 0; sp < 2; ++sp) {
-    double* m = mom + 4 * R.fine.fn * sp;
-    if (R.prec == PIC_FP64)
-      launch_fine_moments(&R.p64[sp][R.cur[sp]], nullptr, R.lists[sp], R.fine, m, avg, R.cap[sp],
-                          ctx->stream);
-    else
-      launch_fine_moments(nullptr, &R.p32[sp][R.cur[sp]], R.lists[sp], R.fine, m, avg, R.cap[sp],
-                          ctx->stream);
+  const long cap = std::max(R.cap[0], R.cap[1]);
+  if (R.prec == PIC_FP64) {
+    PartF64 P[2], D[2];
+    buffers(R, P, D);
+    launch_fine_moments(P, R.lists, R.fine, mom, avg, cap, ctx->stream);
+  } else {
+    PartF32R P[2], D[2];
+    buffers(R, P, D);
+    launch_fine_moments(P, R.lists, R.fine, mom, avg, cap, ctx->stream);
   }
   CHECK_LAUNCH(ctx);
   return PIC_OK;
@@ -1705,6 +1706,20 @@ struct FieldStage {
   size_t cap;
 };
 
+// whether a kernel may write doubles to p, which the caller says is on the device: in
+// this device's own memory and aligned.  A copy (which takes any address a
+// copy reaches) does the rest.
+bool kernel_writes(const void* p) {
+  if ((uintptr_t)p % sizeof(double) != 0) return false;
+  hipPointerAttribute_t at{};
+  int dev = 0;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();  // (memory the runtime does not know)
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == dev;
+}
+
 int fields_impl(pic_ctx* ctx, Replica* R, unsigned what, void* const* out, int out_on_device,
                 const FieldStage* sc) {
   if (!out || (what & ~511u)) return fail(ctx, PIC_EINVAL, "bad selection or out");
@@ -1737,95 +1752,95 @@ int fields_impl(pic_ctx* ctx, Replica* R, unsigned what, void* const* out, int o
   }
   const hipMemcpyKind kind = out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
   const double vol = R->cfg.dx * R->cfg.dx * R->cfg.dx;
-  // densities and fluxes of one species into mom [4][nn] (W, then v W), scaled
+  // Without the caller's scratch, the last kernel of a quantity writes it where the
+  // caller wants it (dst where a copy has to follow: null)
+  auto direct = [&](void* dst) -> double* {
+    return dst && out_on_device && !sc && kernel_writes(dst) ? (double*)dst : nullptr;
+  };
+  auto given = [&](unsigned bit) -> void* {  // the caller's buffer of a quantity, if asked for
+    if (!(what & bit)) return nullptr;
+    int slot = 0;
+    for (unsigned b = 1; b < bit; b <<= 1) slot += (what & b) != 0;
+    return out[slot];
+  };
+  // sums of W and v W of one species into mom [4][nn]
   auto moments_of = [&](int sp, double* mom) {
-    launch_zero_f64(mom, 4 * nn, st);
     const SpeciesStep S = species_step(*R, sp);
     if (R->prec == PIC_FP64)
       launch_moments(&R->p64[sp][R->cur[sp]], nullptr, S, R->lists[sp], mom, nn, AvgBins{}, st);
     else
       launch_moments(nullptr, &R->p32[sp][R->cur[sp]], S, R->lists[sp], mom, nn, AvgBins{}, st);
-    launch_scale(mom, nullptr, R->w / vol, mom, 4 * nn, st);
   };
-  if ((what & (PIC_N | PIC_FLUX)) && !sc) {
-    if (!R->mom) TRY(dalloc(ctx, *R, &R->mom, 8 * nn));
-    for (int sp = 0; sp < 2; ++sp) moments_of(sp, R->mom + 4 * nn * sp);
+  // the moments mom [2][4][len] of both species, times conv, to the caller
+  auto hand_out = [&](double* mom, long len, double conv, void* n, void* flux) -> int {
+    double *dn = direct(n), *df = direct(flux);
+    if (dn || df) launch_moments_out(mom, len, conv, dn, df, st);
+    if ((n && !dn) || (flux && !df)) launch_scale(conv, mom, 8 * len, st);
+    for (int sp = 0; sp < 2; ++sp) {
+      if (n && !dn)
+        HIPCHK(ctx, hipMemcpyAsync((char*)n + sp * len * 8, mom + 4 * sp * len, len * 8, kind, st));
+      if (flux && !df)
+        HIPCHK(ctx, hipMemcpyAsync((char*)flux + 3 * sp * len * 8, mom + (4 * sp + 1) * len,
+                                   3 * len * 8, kind, st));
+    }
     CHECK_LAUNCH(ctx);
-  }
+    return PIC_OK;
+  };
   const long fn = R->fine.fn;
+  if (what & (PIC_N | PIC_FLUX)) {
+    if (!sc) {
+      if (!R->mom) TRY(dalloc(ctx, *R, &R->mom, 8 * nn));
+      launch_zero_f64(R->mom, 8 * nn, st);
+      for (int sp = 0; sp < 2; ++sp) moments_of(sp, R->mom + 4 * nn * sp);
+      TRY(hand_out(R->mom, nn, R->w / vol, given(PIC_N), given(PIC_FLUX)));
+    } else {
+      // one species at a time through the scratch
+      char *n = (char*)given(PIC_N), *flux = (char*)given(PIC_FLUX);
+      for (int sp = 0; sp < 2; ++sp) {
+        launch_zero_f64(sc->base, 4 * nn, st);
+        moments_of(sp, sc->base);
+        launch_scale(R->w / vol, sc->base, 4 * nn, st);
+        if (n) HIPCHK(ctx, hipMemcpyAsync(n + sp * nn * 8, sc->base, nn * 8, kind, st));
+        if (flux)
+          HIPCHK(ctx, hipMemcpyAsync(flux + 3 * sp * nn * 8, sc->base + nn, 3 * nn * 8, kind, st));
+      }
+      CHECK_LAUNCH(ctx);
+    }
+  }
   if (what & (PIC_FINE_N | PIC_FINE_FLUX)) {
     if (!R->fine_mom) TRY(dalloc(ctx, *R, &R->fine_mom, 8 * fn));
     launch_zero_f64(R->fine_mom, 8 * fn, st);
     TRY(enqueue_fine(ctx, *R, R->fine_mom, AvgBins{}));
     const double hdx = R->fine.h * R->cfg.dx;
-    launch_scale(R->fine_mom, nullptr, R->w / (hdx * hdx * hdx), R->fine_mom, 8 * fn, st);
-    CHECK_LAUNCH(ctx);
+    TRY(hand_out(R->fine_mom, fn, R->w / (hdx * hdx * hdx), given(PIC_FINE_N), given(PIC_FINE_FLUX)));
   }
-  if (what & PIC_FINE_PHI) {
-    if (!R->fine_phi) TRY(dalloc(ctx, *R, &R->fine_phi, fn));
+  if (void* dst = given(PIC_FINE_PHI)) {
+    double* d = direct(dst);
+    if (!d && !R->fine_phi) TRY(dalloc(ctx, *R, &R->fine_phi, fn));
     launch_fine_phi(R->phi, R->md, R->Uphi, R->fine, R->nx, R->ny, R->nz, R->cfg.dx,
-                    R->cfg.grain_radius, R->fine_phi, AvgBins{}, st);
+                    R->cfg.grain_radius, d ? d : R->fine_phi, AvgBins{}, st);
+    if (!d) HIPCHK(ctx, hipMemcpyAsync(dst, R->fine_phi, fn * 8, kind, st));
     CHECK_LAUNCH(ctx);
   }
-  int slot = 0, slot_n = -1, slot_flux = -1;
-  for (unsigned bit = 1; bit <= PIC_FINE_PHI; bit <<= 1) {
-    if (!(what & bit)) continue;
-    if (bit == PIC_N) slot_n = slot;
-    if (bit == PIC_FLUX) slot_flux = slot;
-    ++slot;
+  if (void* dst = given(PIC_PHI)) HIPCHK(ctx, hipMemcpyAsync(dst, R->phi, nn * 8, kind, st));
+  if (void* dst = given(PIC_E)) {
+    double* d = direct(dst);
+    launch_e_out(R->prec == PIC_FP64 ? (const double*)R->E : nullptr,
+                 R->prec == PIC_FP64 ? nullptr : (const float*)R->E, d ? d : eout, nn, st);
+    if (!d) HIPCHK(ctx, hipMemcpyAsync(dst, eout, 3 * nn * 8, kind, st));
+    CHECK_LAUNCH(ctx);
   }
-  slot = 0;
-  for (unsigned bit = 1; bit <= PIC_FINE_PHI; bit <<= 1) {
-    if (!(what & bit)) continue;
-    void* dst = out[slot++];
-    if (bit == PIC_FINE_PHI) {
-      HIPCHK(ctx, hipMemcpyAsync(dst, R->fine_phi, fn * 8, kind, st));
-    } else if (bit == PIC_FINE_N || bit == PIC_FINE_FLUX) {
-      const long len = bit == PIC_FINE_FLUX ? 3 * fn : fn;
-      for (int sp = 0; sp < 2; ++sp)
-        HIPCHK(ctx, hipMemcpyAsync((char*)dst + sp * len * 8,
-                                   R->fine_mom + (4 * sp + (bit == PIC_FINE_FLUX ? 1 : 0)) * fn,
-                                   len * 8, kind, st));
-    } else if (bit == PIC_PHI) {
-      HIPCHK(ctx, hipMemcpyAsync(dst, R->phi, nn * 8, kind, st));
-    } else if ((bit == PIC_N || bit == PIC_FLUX) && sc) {
-      // one species at a time through the scratch, both quantities at once
-      if (bit == PIC_FLUX && slot_n >= 0) continue;  // already handed out with N
-      for (int sp = 0; sp < 2; ++sp) {
-        moments_of(sp, sc->base);
-        if (slot_n >= 0)
-          HIPCHK(ctx, hipMemcpyAsync((char*)out[slot_n] + sp * nn * 8, sc->base, nn * 8, kind,
-                                     st));
-        if (slot_flux >= 0)
-          HIPCHK(ctx, hipMemcpyAsync((char*)out[slot_flux] + 3 * sp * nn * 8, sc->base + nn,
-                                     3 * nn * 8, kind, st));
-      }
-    } else if (bit == PIC_N) {
-      for (int sp = 0; sp < 2; ++sp)
-        HIPCHK(ctx, hipMemcpyAsync((char*)dst + sp * nn * 8, R->mom + 4 * nn * sp, nn * 8, kind, st));
-    } else if (bit == PIC_FLUX) {
-      for (int sp = 0; sp < 2; ++sp)
-        HIPCHK(ctx, hipMemcpyAsync((char*)dst + 3 * sp * nn * 8, R->mom + (4 * sp + 1) * nn,
-                                   3 * nn * 8, kind, st));
-    } else if (bit == PIC_E) {
-      launch_e_out(R->prec == PIC_FP64 ? (const double*)R->E : nullptr,
-                   R->prec == PIC_FP64 ? nullptr : (const float*)R->E, eout, nn, st);
-      HIPCHK(ctx, hipMemcpyAsync(dst, eout, 3 * nn * 8, kind, st));
-    } else {
-      if (R->prec == PIC_FP64) {
-        launch_rho_total((const double*)R->rho[R->rho_cur], nullptr, tot64, nullptr, R->d_gc,
-                         R->md.gpos, R->cfg.n_grains, R->nx, R->ny, nn, R->Qp, st);
-        launch_scale(tot64, nullptr, R->we / vol, tot64, nn, st);
-      } else {
-        launch_rho_total(nullptr, (const long long*)R->rho[R->rho_cur], nullptr, totfx,
-                         R->d_gc, R->md.gpos, R->cfg.n_grains, R->nx, R->ny, nn, R->Qp, st);
-        launch_scale(nullptr, totfx, kCharge / 4294967296.0 / vol, tot64, nn, st);
-      }
-      if (bit == PIC_RHO)
-        HIPCHK(ctx, hipMemcpyAsync(dst, tot64, nn * 8, kind, st));
-      else
-        HIPCHK(ctx, hipMemcpyAsync(dst, totfx, nn * 8, kind, st));
-    }
+  for (unsigned bit : {(unsigned)PIC_RHO, (unsigned)PIC_RHO_FIXED}) {
+    void* dst = given(bit);
+    if (!dst) continue;
+    const bool f64 = R->prec == PIC_FP64, fixed = bit == PIC_RHO_FIXED;
+    void* d = direct(dst);
+    if (!d) d = fixed ? (void*)totfx : (void*)tot64;
+    launch_rho_out(f64 ? (const double*)R->rho[R->rho_cur] : nullptr,
+                   f64 ? nullptr : (const long long*)R->rho[R->rho_cur], R->d_gtab, R->n_gtab,
+                   R->d_gc, f64 ? R->we / vol : kCharge / 4294967296.0 / vol,
+                   fixed ? nullptr : (double*)d, fixed ? (long long*)d : nullptr, R->nxy, nn, st);
+    if (d != dst) HIPCHK(ctx, hipMemcpyAsync(dst, d, nn * 8, kind, st));
     CHECK_LAUNCH(ctx);
   }
   if (!out_on_device) HIPCHK(ctx, hipStreamSynchronize(st));
@@ -2109,42 +2124,39 @@ int pic_average_read(pic_ctx* ctx, int replica, int bin, unsigned what, void* co
   hipStream_t st = ctx->stream;
   const long nn = R->nn;
   const int b0 = bin < 0 ? 0 : bin, b1 = bin < 0 ? ctx->avg_bins : bin + 1;
-  if (!R->avg_out) TRY(dalloc(ctx, *R, &R->avg_out, 9 * nn));
-  const double vol = R->cfg.dx * R->cfg.dx * R->cfg.dx;
-  launch_avg_out(R->avg, b0, b1, 9 * nn, 9 * nn, nn, R->d_avg_cnt, R->w / vol, R->avg_out, st);
-  const long fn = R->fine.fn;
-  if (what & fine_bits) {
-    if (!R->fine_out) TRY(dalloc(ctx, *R, &R->fine_out, 9 * fn));
-    const double hdx = R->fine.h * R->cfg.dx;
-    launch_avg_out(R->fine_avg, b0, b1, 9 * fn, 9 * fn, fn, R->d_avg_cnt, R->w / (hdx * hdx * hdx),
-                   R->fine_out, st);
+  void* given[6] = {};  // the caller's buffers in the order of the bits
+  const unsigned bits[6] = {PIC_PHI, PIC_N, PIC_FLUX, PIC_FINE_PHI, PIC_FINE_N, PIC_FINE_FLUX};
+  {
+    int slot = 0;
+    for (unsigned bit : {PIC_PHI, PIC_N, PIC_FLUX, PIC_FINE_N, PIC_FINE_FLUX, PIC_FINE_PHI}) {
+      if (!(what & bit)) continue;
+      void* dst = out[slot++];
+      if (!dst) return fail(ctx, PIC_EINVAL, "NULL output buffer");
+      given[std::find(bits, bits + 6, bit) - bits] = dst;
+    }
   }
-  CHECK_LAUNCH(ctx);
   const hipMemcpyKind kind = out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-  int slot = 0;
-  for (unsigned bit : {PIC_PHI, PIC_N, PIC_FLUX, PIC_FINE_N, PIC_FINE_FLUX, PIC_FINE_PHI}) {
-    if (!(what & bit)) continue;
-    char* dst = (char*)out[slot++];
-    if (!dst) return fail(ctx, PIC_EINVAL, "NULL output buffer");
-    if (bit == PIC_FINE_PHI) {
-      HIPCHK(ctx, hipMemcpyAsync(dst, R->fine_out, fn * 8, kind, st));
-      continue;
+  // phi, densities and fluxes of one grid: straight to the caller, or staged and copied
+  auto hand_out = [&](const double* acc, long len, double wv, void* const* dst, double** stage) -> int {
+    if (!dst[0] && !dst[1] && !dst[2]) return PIC_OK;
+    const long first[3] = {0, len, 3 * len}, size[3] = {len, 2 * len, 6 * len};
+    double* to[3];
+    for (int k = 0; k < 3; ++k) {
+      to[k] = dst[k] && out_on_device && kernel_writes(dst[k]) ? (double*)dst[k] : nullptr;
+      if (to[k] || !dst[k]) continue;
+      if (!*stage) TRY(dalloc(ctx, *R, stage, 9 * len));
+      to[k] = *stage + first[k];
     }
-    if (bit == PIC_FINE_N || bit == PIC_FINE_FLUX) {
-      const long len = bit == PIC_FINE_FLUX ? 3 * fn : fn;
-      for (int sp = 0; sp < 2; ++sp)
-        HIPCHK(ctx, hipMemcpyAsync(dst + sp * len * 8,
-                                   R->fine_out + fn + (4 * sp + (bit == PIC_FINE_FLUX ? 1 : 0)) * fn,
-                                   len * 8, kind, st));
-      continue;
-    }
-    for (int sp = 0; sp < (bit == PIC_PHI ? 1 : 2); ++sp) {
-      const double* src = bit == PIC_PHI ? R->avg_out
-                          : R->avg_out + (1 + 4 * sp + (bit == PIC_FLUX ? 1 : 0)) * nn;
-      const long len = bit == PIC_FLUX ? 3 * nn : nn;
-      HIPCHK(ctx, hipMemcpyAsync(dst + sp * len * 8, src, len * 8, kind, st));
-    }
-  }
+    launch_avg_out(acc, b0, b1, len, R->d_avg_cnt, wv, to[0], to[1], to[2], st);
+    for (int k = 0; k < 3; ++k)
+      if (dst[k] && to[k] != dst[k])
+        HIPCHK(ctx, hipMemcpyAsync(dst[k], to[k], size[k] * 8, kind, st));
+    CHECK_LAUNCH(ctx);
+    return PIC_OK;
+  };
+  const double vol = R->cfg.dx * R->cfg.dx * R->cfg.dx, hdx = R->fine.h * R->cfg.dx;
+  TRY(hand_out(R->avg, nn, R->w / vol, given, &R->avg_out));
+  TRY(hand_out(R->fine_avg, R->fine.fn, R->w / (hdx * hdx * hdx), given + 3, &R->fine_out));
   if (samples) {
     std::vector<unsigned long long> c(ctx->avg_bins);
     HIPCHK(ctx, hipMemcpyAsync(c.data(), R->d_avg_cnt, c.size() * 8, hipMemcpyDeviceToHost, st));
