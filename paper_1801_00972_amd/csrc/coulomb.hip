@@ -14,13 +14,14 @@
 //     (each a contiguous range of the key / slot arrays): it stages a group's
 //     keys in LDS (the next group's keys and slots already load meanwhile),
 //     ranks each particle inside its cell by key and puts the id (the key's
-//     low word) and the velocity in that order, then 32 lanes per
-//     cell run the like items (e-e and Ar+-Ar+ pairs, an odd count's triplet
-//     as one item), a barrier, and the unlike pairs (one lane per particle of
-//     the less numerous species, its partners in order), and the velocities
-//     go back once; the arithmetic is in the velocities' precision (FP64 or
-//     FP32); a group with a cell above 64 particles of a species runs its
-//     cells in turn through global memory with the whole block.
+//     low word) and the velocity in that order, lists the group's collisions,
+//     makes all their draws, then turns the like pairs (e-e and Ar+-Ar+, an
+//     odd count's triplet as one item), a barrier, and the unlike pairs (one
+//     lane per particle of a cell's less numerous species, its partners in
+//     order), and the velocities go back once; the arithmetic is in the
+//     velocities' precision (FP64 or FP32); a group with a cell above 64
+//     particles of a species runs its cells in turn through global memory with
+//     the whole block.
 // Counting and scattering go a block per tile of the particle bins: an LDS
 // histogram and one global atomic per cell, one more per particle that has
 // left its tile since the last binning.
@@ -279,17 +280,24 @@ __device__ __forceinline__ float coul_sqrt(float x) { return __builtin_amdgcn_sq
 __device__ __forceinline__ double coul_rcp(double x) { return 1.0 / x; }
 __device__ __forceinline__ float coul_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
+// One collision's draws as they are kept between the phases of a group: FP32 the
+// normal deviate and the azimuth's cosine and sine, FP64 the Philox words (its
+// three doubles would leave LDS for two blocks a CU)
+template <typename R> struct CoulKept;
+template <> struct CoulKept<float> {
+  static constexpr bool raw = false;
+};
+template <> struct CoulKept<double> {
+  static constexpr bool raw = true;
+};
+// the relative velocity of va, vb turned by the angle of delta about itself
 template <typename R>
-__device__ void coul_collide(const CoulombConst& C, uint32_t k, uint32_t word, R cv, R fa, R fb,
-                             R* va, R* vb, uint32_t id) {
+__device__ __forceinline__ void coul_turn(R cv, R fa, R fb, R* va, R* vb, R normal, R cp, R sp) {
   const R u0 = va[0] - vb[0], u1 = va[1] - vb[1], u2 = va[2] - vb[2];
   const R um2 = u0 * u0 + u1 * u1 + u2 * u2;
   if (!(um2 > (R)0)) return;
   const R um = coul_sqrt(um2);
-  const uint4 r = philox4x32_10(id, k, kCPair, word, C.key0, C.key1);
-  const R delta = coul_sqrt(cv * coul_rcp(um2 * um)) * CoulDraw<R>::normal(r.x, r.y);
-  R sp, cp;
-  CoulDraw<R>::azimuth(r.z, &sp, &cp);
+  const R delta = coul_sqrt(cv * coul_rcp(um2 * um)) * normal;
   const R inv = coul_rcp((R)1 + delta * delta);
   const R sn = (R)2 * delta * inv;
   const R omc = (R)2 * delta * delta * inv;
@@ -311,47 +319,14 @@ __device__ void coul_collide(const CoulombConst& C, uint32_t k, uint32_t word, R
     vb[a] -= fb * du[a];
   }
 }
-
-// The pairing rule on velocities held in a cell's arrays (LDS), in key order:
-// like items of both species (pairs, an odd count's triplet as one item) over
-// the cell's W lanes, a barrier, then the unlike pairs (lane r takes particle r
-// of the less numerous species b and its partners j = r, r + N_b, ... of a).
-// V(s, q) is the velocity of the q-th particle of species s in key order,
-// ID(s, q) its id; LANE is the lane's index among the cell's W lanes.
-#define COUL_PAIRS(V, ID, LANE, W)                                                            \
-  {                                                                                         \
-    /* like items of both species in one list: species 0's, then 1's; an */                \
-    /* odd count's triplet is its species' first item */                                   \
-    int items[2];                                                                           \
-    _Pragma("unroll") for (int s = 0; s < 2; ++s)                                            \
-      items[s] = n[s] < 2 ? 0 : ((n[s] & 1) ? 1 + (n[s] - 3) / 2 : n[s] / 2);                 \
-    for (int it = (LANE); it < items[0] + items[1]; it += (W)) {                            \
-      const int s = it < items[0] ? 0 : 1;                                                  \
-      const int i = it - (s ? items[0] : 0);                                                \
-      const int N = n[s];                                                                   \
-      const R cv = (R)(C.c_var[s] * (double)N * C.w_vol);                                   \
-      const R f = (R)C.frac[s][s];                                                          \
-      if ((N & 1) && i == 0) {                                                              \
-        coul_collide<R>(C, k, (uint32_t)s, (R)0.5 * cv, f, f, V(s, 0), V(s, 1), ID(s, 0));  \
-        coul_collide<R>(C, k, (uint32_t)s, (R)0.5 * cv, f, f, V(s, 1), V(s, 2), ID(s, 1));  \
-        coul_collide<R>(C, k, (uint32_t)s, (R)0.5 * cv, f, f, V(s, 2), V(s, 0), ID(s, 2));  \
-      } else {                                                                              \
-        const int q = (N & 1) ? 3 + 2 * (i - 1) : 2 * i;                                     \
-        coul_collide<R>(C, k, (uint32_t)s, cv, f, f, V(s, q), V(s, q + 1), ID(s, q));       \
-      }                                                                                     \
-    }                                                                                       \
-    __syncthreads();                                                                        \
-    if (n[0] > 0 && n[1] > 0) {                                                             \
-      const int sa = n[0] >= n[1] ? 0 : 1, sb = 1 - sa;                                     \
-      const int Na = n[sa], Nb = n[sb];                                                     \
-      const R cv = (R)(C.c_var[2] * (double)Nb * C.w_vol);                                  \
-      for (int r = (LANE); r < Nb; r += (W))                                                \
-        for (int j = r; j < Na; j += Nb)                                                    \
-          coul_collide<R>(C, k, 2u + (uint32_t)sa, cv, (R)C.frac[2][sa], (R)C.frac[2][sb],  \
-                          V(sa, j), V(sb, r), ID(sa, j));                                   \
-    }                                                                                       \
-    __syncthreads();                                                                        \
-  }
+template <typename R>
+__device__ void coul_collide(const CoulombConst& C, uint32_t k, uint32_t word, R cv, R fa, R fb,
+                             R* va, R* vb, uint32_t id) {
+  const uint4 r = philox4x32_10(id, k, kCPair, word, C.key0, C.key1);
+  R sp, cp;
+  CoulDraw<R>::azimuth(r.z, &sp, &cp);
+  coul_turn<R>(cv, fa, fb, va, vb, CoulDraw<R>::normal(r.x, r.y), cp, sp);
+}
 
 // cells whose species each hold at most kCellCap particles go through LDS
 constexpr int kCellCap = 64;
@@ -360,12 +335,25 @@ constexpr int kGroup = kPairThreads / 32;  // consecutive cells staged together
 constexpr int kGroupCap = 512;     // staged particles of a species per group
 constexpr int kStagePer = kGroupCap / kPairThreads;  // staged particles per thread and species
 constexpr int kRunGroups = 16;     // groups of one block: two tiles of 64 cells
+constexpr int kPairsMax = kGroupCap;                     // pairs of both species, at most
+constexpr int kTripMax = 2 * kGroup;                    // triplets: one a cell and species
+constexpr int kDraws = kPairsMax + 3 * kTripMax + kGroupCap;  // + one a particle of the majority
 template <typename R>
 struct GroupStage {
-  unsigned long long key[2][kGroupCap];
+  union {
+    // until the ranks are known: a row a cell, filled up to a multiple of four with
+    // the largest key, so that a rank is a count over four keys at a time
+    unsigned long long key[2][kGroup][kCellCap];
+    uint32_t draw[3][kDraws];              // then the draws: pairs, triplets, unlike
+  };
   int slot[2][kGroupCap];  // in key order inside each cell
   uint32_t id[2][kGroupCap];
   R v[2][kGroupCap][3];
+  // what collides, as species << 15 | place: the first of each pair, of each
+  // triplet, and each particle of a cell's majority and minority species
+  unsigned short pair[kPairsMax], trip[kTripMax], major[kGroupCap], minor[kGroupCap];
+  int pairs[2][kGroup], trips[2][kGroup], maj[kGroup], min[kGroup];  // a cell's first in each
+  int n_pair, n_trip, n_major, n_minor;
   int start[2][kRunGroups * kGroup + 1];  // the block's cells' starts in the key / slot arrays
 };
 
@@ -455,16 +443,26 @@ __device__ void cell_global(const PT P[2], const CoulombBufs& B, const CoulombCo
 // are gathered and written by one block, through one XCD's L2).  The run's
 // cell starts are staged once.  For each group the block stages the keys in
 // LDS (a key's low word is the particle's id), ranks each particle inside its
-// cell by key, puts slot, id and velocity at the ranked place, runs the pairing
-// rule with 32 lanes per cell and writes the velocities back.  The next
-// group's keys and slots are loaded into registers while the current group is
-// worked on, and the FP32 velocities are gathered before the ranking, so the
-// loads overlap the arithmetic instead of waiting in turn.  A group with a
-// cell above kCellCap particles of a species, or with more than kGroupCap of a
-// species, runs its cells one by one through global memory with the whole
-// block.
+// cell by key and puts slot, id and velocity at the ranked place; from its rank a
+// particle also knows which collision it starts and enters it in the group's
+// lists.  The collisions' draws (Philox and the functions of its words) depend on
+// no velocity: they are made for the whole group in one go, 256 at a time.  Then
+// the like pairs and triplets, a barrier, and the unlike pairs (a thread takes a
+// particle of the cell's less numerous species and its partners in order)
+// only turn velocities, and the velocities go back.  The next group's keys
+// and slots are loaded into registers while the current group is worked on, and the
+// FP32 velocities are gathered before the ranking, so the loads overlap the
+// arithmetic instead of waiting in turn.  A group with a cell above kCellCap
+// particles of a species, or with more than kGroupCap of a species, runs its cells
+// one by one through global memory with the whole block.
+// Bound by its vector instructions (Philox above all).  With 32 lanes to a cell
+// and the draws made where they are used, a wave went through six or seven rounds
+// of them a group (a triplet's three in turn, the pairs, the second partners),
+// most with few lanes, and a rank was a loop over single keys of its cell: 64x64x256
+// cells at 32 per cell, FP32R, 1.83 ms a pass, 1.4 so, of which four waves a SIMD in
+// place of three are 0.3; a step with a pass at 8 per cell in FP64 4.0 -> 3.2 ms.
 template <typename PT>
-__global__ __launch_bounds__(kPairThreads) void coul_pair_kernel(PT Pe, PT Pi, CoulombBufs B,
+__global__ __launch_bounds__(kPairThreads, sizeof(typename CoulReal<PT>::T) == 4 ? 4 : 3) void coul_pair_kernel(PT Pe, PT Pi, CoulombBufs B,
                                                                  CoulombConst C) {
   using R = typename CoulReal<PT>::T;
   // FP32 velocities are gathered in registers before the ranking; the FP64
@@ -515,11 +513,22 @@ __global__ __launch_bounds__(kPairThreads) void coul_pair_kernel(PT Pe, PT Pi, C
       N[s] = st_at(s, j0 + kGroup) - b[s];
       n[s] = st_at(s, j0 + cl + 1) - st_at(s, j0 + cl);
     }
+    // the cells' first places in the group, in scalar registers
+    int at[2][kGroup + 1];
     bool fits = N[0] <= kGroupCap && N[1] <= kGroupCap;
 #pragma unroll
-    for (int j = 0; j < kGroup; ++j)
-      fits = fits && st_at(0, j0 + j + 1) - st_at(0, j0 + j) <= kCellCap &&
-             st_at(1, j0 + j + 1) - st_at(1, j0 + j) <= kCellCap;
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int j = 0; j <= kGroup; ++j) {
+        at[s][j] = __builtin_amdgcn_readfirstlane(st_at(s, j0 + j) - b[s]);
+        if (j > 0) fits = fits && at[s][j] - at[s][j - 1] <= kCellCap;
+      }
+    auto cell_of = [&](int s, int p) {  // the cell that holds place p
+      int j = 0;
+#pragma unroll
+      for (int t = 1; t < kGroup; ++t) j += at[s][t] <= p;
+      return j;
+    };
     if (hl == 0) {
 #pragma unroll
       for (int s = 0; s < 2; ++s)
@@ -542,15 +551,55 @@ __global__ __launch_bounds__(kPairThreads) void coul_pair_kernel(PT Pe, PT Pi, C
       __syncthreads();
       continue;
     }
+    // where each cell's pairs, triplets and unlike collisions begin in the lists
+    if (tid < 64) {
+      const int s = (tid >> 3) & 1, j = tid & 7;  // (lanes 16 and up repeat)
+      const int m = st_at(s, j0 + j + 1) - st_at(s, j0 + j);
+      const int o = __shfl_xor(m, 8);  // the other species
+      const int np = m < 2 ? 0 : ((m & 1) ? (m - 3) / 2 : m / 2), nt = m >= 3 && (m & 1);
+      const bool both = m > 0 && o > 0;
+      // (counts of at most 512 and 16: two to a word)
+      int like = np | nt << 16, unlike = s == 0 && both ? max(m, o) | min(m, o) << 16 : 0;
+      const int like0 = like, unlike0 = unlike;
+#pragma unroll
+      for (int d = 1; d < 16; d <<= 1) {
+        const int a = __shfl_up(like, d, 16), b = __shfl_up(unlike, d, 16);
+        if ((tid & 15) >= d) {
+          like += a;
+          unlike += b;
+        }
+      }
+      if (tid < 16) {
+        sm.pairs[s][j] = (like - like0) & 0xffff;
+        sm.trips[s][j] = (like - like0) >> 16;
+        if (s == 0) {
+          sm.maj[j] = (unlike - unlike0) & 0xffff;
+          sm.min[j] = (unlike - unlike0) >> 16;
+        }
+      }
+      if (tid == 15) {
+        sm.n_pair = like & 0xffff;
+        sm.n_trip = like >> 16;
+        sm.n_major = unlike & 0xffff;
+        sm.n_minor = unlike >> 16;
+      }
+    }
     R vv[2][kStagePer][3];
+    int cj[2][kStagePer], lo[2][kStagePer], hi[2][kStagePer];  // a particle's cell, its range
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
       for (int u = 0; u < kStagePer; ++u) {
         const int i = tid + u * kPairThreads;
         if (i < N[s]) {
-          sm.key[s][i] = kk[s][u];
           if (kEarlyV) load_v(P[s], sl[s][u], vv[s][u]);
+          const int j = cell_of(s, i);
+          cj[s][u] = j;
+          lo[s][u] = st_at(s, j0 + j) - b[s];
+          hi[s][u] = st_at(s, j0 + j + 1) - b[s];
+          sm.key[s][j][i - lo[s][u]] = kk[s][u];
+          if (i + 1 == hi[s][u])
+            for (int t = i + 1 - lo[s][u]; t & 3; ++t) sm.key[s][j][t] = ~0ull;
         }
       }
     __syncthreads();
@@ -561,14 +610,30 @@ __global__ __launch_bounds__(kPairThreads) void coul_pair_kernel(PT Pe, PT Pi, C
       for (int u = 0; u < kStagePer; ++u) {
         const int i = tid + u * kPairThreads;
         if (i >= N[s]) continue;
-        int j = 0;
-        while (j + 1 < kGroup && st_at(s, j0 + j + 1) - b[s] <= i) ++j;
-        const int lo = st_at(s, j0 + j) - b[s], hi = st_at(s, j0 + j + 1) - b[s];
+        const int j = cj[s][u], m = hi[s][u] - lo[s][u];
         const unsigned long long kq = kk[s][u];
-        int rank = lo;
-        for (int t = lo; t < hi; ++t) rank += sm.key[s][t] < kq;
+        int q = 0;  // its rank in the cell
+        for (int t = 0; t < m; t += 4) {
+          const unsigned long long* r = &sm.key[s][j][t];
+          q += (int)(r[0] < kq) + (int)(r[1] < kq) + (int)(r[2] < kq) + (int)(r[3] < kq);
+        }
+        const int rank = lo[s][u] + q;
         sm.slot[s][rank] = sl[s][u];
         sm.id[s][rank] = (uint32_t)kq;
+        {
+          // the collisions that this particle starts, from its rank q in the cell
+          const unsigned short me = (unsigned short)(s << 15 | rank);
+          const int o = st_at(1 - s, j0 + j + 1) - st_at(1 - s, j0 + j);
+          const int first = m & 1 ? 3 : 0;  // (an odd count's first three are its triplet)
+          if (m >= 2) {
+            if (first && q == 0) sm.trip[sm.trips[s][j]] = me;
+            else if (q >= first && !((q - first) & 1)) sm.pair[sm.pairs[s][j] + ((q - first) >> 1)] = me;
+          }
+          if (o > 0) {
+            if (m > o || (m == o && s == 0)) sm.major[sm.maj[j] + q] = me;
+            else sm.minor[sm.min[j] + q] = (unsigned short)(s << 15 | j << 9 | q);
+          }
+        }
         if (kEarlyV) {
 #pragma unroll
           for (int a = 0; a < 3; ++a) sm.v[s][rank][a] = vv[s][u][a];
@@ -577,12 +642,70 @@ __global__ __launch_bounds__(kPairThreads) void coul_pair_kernel(PT Pe, PT Pi, C
         }
       }
     __syncthreads();
-    const int o0 = st_at(0, j0 + cl) - b[0], o1 = st_at(1, j0 + cl) - b[1];
-#define GRP_V(s, q) (sm.v[s][((s) ? o1 : o0) + (q)])
-#define GRP_ID(s, q) (sm.id[s][((s) ? o1 : o0) + (q)])
-    COUL_PAIRS(GRP_V, GRP_ID, hl, 32)
-#undef GRP_V
-#undef GRP_ID
+    // the draws of every collision of the group
+    const int n_pair = sm.n_pair, n_trip = sm.n_trip, n_minor = sm.n_minor;
+    const int d_trip = n_pair, d_unlike = n_pair + 3 * n_trip, n_draw = d_unlike + sm.n_major;
+    for (int d = tid; d < n_draw; d += kPairThreads) {
+      int w = d < d_trip ? sm.pair[d] : d >= d_unlike ? sm.major[d - d_unlike] : -1;
+      if (w < 0) {
+        const int t = (d - d_trip) / 3;
+        w = sm.trip[t] + (d - d_trip - 3 * t);
+      }
+      const int s = w >> 15;
+      const uint4 r = philox4x32_10(sm.id[s][w & 0x7fff], k, kCPair, (uint32_t)(d >= d_unlike ? 2 + s : s),
+                                    C.key0, C.key1);
+      if constexpr (CoulKept<R>::raw) {
+        sm.draw[0][d] = r.x;
+        sm.draw[1][d] = r.y;
+        sm.draw[2][d] = r.z;
+      } else {
+        R si, co;
+        CoulDraw<R>::azimuth(r.z, &si, &co);
+        sm.draw[0][d] = __float_as_uint(CoulDraw<R>::normal(r.x, r.y));
+        sm.draw[1][d] = __float_as_uint(co);
+        sm.draw[2][d] = __float_as_uint(si);
+      }
+    }
+    __syncthreads();
+    auto turn = [&](int d, R cv, R fa, R fb, R* va, R* vb) {
+      const uint32_t x = sm.draw[0][d], y = sm.draw[1][d], z = sm.draw[2][d];
+      if constexpr (CoulKept<R>::raw) {
+        R si, co;
+        CoulDraw<R>::azimuth(z, &si, &co);
+        coul_turn<R>(cv, fa, fb, va, vb, CoulDraw<R>::normal(x, y), co, si);
+      } else {
+        coul_turn<R>(cv, fa, fb, va, vb, __uint_as_float(x), __uint_as_float(y), __uint_as_float(z));
+      }
+    };
+    for (int it = tid; it < n_pair + n_trip; it += kPairThreads) {
+      const bool trip = it >= n_pair;
+      const int w = trip ? sm.trip[it - n_pair] : sm.pair[it], s = w >> 15, p = w & 0x7fff;
+      const int j = s ? cell_of(1, p) : cell_of(0, p);
+      const R cv = (R)(C.c_var[s] * (double)(st_at(s, j0 + j + 1) - st_at(s, j0 + j)) * C.w_vol);
+      const R f = (R)C.frac[s][s];
+      if (!trip) {
+        turn(it, cv, f, f, sm.v[s][p], sm.v[s][p + 1]);
+      } else {
+        const int d = d_trip + 3 * (it - n_pair);
+        turn(d, (R)0.5 * cv, f, f, sm.v[s][p], sm.v[s][p + 1]);
+        turn(d + 1, (R)0.5 * cv, f, f, sm.v[s][p + 1], sm.v[s][p + 2]);
+        turn(d + 2, (R)0.5 * cv, f, f, sm.v[s][p + 2], sm.v[s][p]);
+      }
+    }
+    __syncthreads();
+    for (int it = tid; it < n_minor; it += kPairThreads) {
+      const int w = sm.minor[it], sb = w >> 15, sa = 1 - sb, j = (w >> 9) & 7, r = w & 0x1ff;
+      const int ob = st_at(sb, j0 + j) - b[sb], oa = st_at(sa, j0 + j) - b[sa];
+      const int Nb = st_at(sb, j0 + j + 1) - b[sb] - ob, Na = st_at(sa, j0 + j + 1) - b[sa] - oa;
+      const R cv = (R)(C.c_var[2] * (double)Nb * C.w_vol);
+      const R fa = (R)C.frac[2][sa], fb = (R)C.frac[2][sb];
+      R vb[3] = {sm.v[sb][ob + r][0], sm.v[sb][ob + r][1], sm.v[sb][ob + r][2]};
+      const int d = d_unlike + sm.maj[j];
+      for (int q = r; q < Na; q += Nb) turn(d + q, cv, fa, fb, sm.v[sa][oa + q], vb);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) sm.v[sb][ob + r][a] = vb[a];
+    }
+    __syncthreads();
 #pragma unroll
     for (int s = 0; s < 2; ++s)
       for (int i = tid; i < N[s]; i += kPairThreads) store_v(P[s], sm.slot[s][i], sm.v[s][i]);
