@@ -200,7 +200,8 @@ __device__ __forceinline__ int quad_min(int v) {
 // kLanes = 4: the four lanes of a quad move one particle together, two corners
 // of the cell and every fourth grain each; all its state is the same in each.  A
 // sub-step is a serial chain, so a short list is bound by its length: 16x16x32
-// cells, 5,500 particles, 62 to 72 us with one lane a particle, 35 us with four.  A
+// cells, 5,500 particles, 62 to 72 us with one lane a particle, 35 us with four, 28 us
+// with each lane's grains kept in registers and one test for the box's faces.  A
 // long list (above kMdQuad particles) fills the chip with one lane each.
 template <int kLanes, typename ET>
 __device__ __forceinline__ int md_move(const ET* __restrict__ E, const MdTables& md,
@@ -214,10 +215,12 @@ __device__ __forceinline__ int md_move(const ET* __restrict__ E, const MdTables&
   uint32_t cl = 0u;
   int cnt = 0;
   int gl[kG];
+  // a quad's lanes keep their grains (box frame) and charges until the cell changes
+  constexpr bool kKeep = kLanes == 4;
+  double gk[kKeep ? kG : 1][4];
   double Ep[3];
   int first;  // list position of the first grain that holds the particle
-  auto grain = [&](int t, int g, bool test) {
-    double g0, g1, g2, Qc;
+  auto read_grain = [&](int g, double& g0, double& g1, double& g2, double& Qc) {
     if (G.raw) {
       g0 = md.gpos[3 * g] - md.bx0;
       g1 = md.gpos[3 * g + 1] - md.by0;
@@ -231,6 +234,8 @@ __device__ __forceinline__ int md_move(const ET* __restrict__ E, const MdTables&
       g2 = G.pos[3 * g + 2];
       Qc = G.Qc[g];
     }
+  };
+  auto pull = [&](int t, double g0, double g1, double g2, double Qc, bool test) {
     double r0 = x[0] - g0, r1 = x[1] - g1;
     const double r2 = x[2] - g2;
     if (image) {
@@ -245,6 +250,11 @@ __device__ __forceinline__ int md_move(const ET* __restrict__ E, const MdTables&
     Ep[0] += r0 * inv;
     Ep[1] += r1 * inv;
     Ep[2] += r2 * inv;
+  };
+  auto grain = [&](int t, int g, bool test) {
+    double g0, g1, g2, Qc;
+    read_grain(g, g0, g1, g2, Qc);
+    pull(t, g0, g1, g2, Qc, test);
   };
   // position x_s, s = 0 .. md_sub: after a drift (s > 0) the hit test and,
   // before the next kick, the field, from one walk over the cell's grains
@@ -271,6 +281,11 @@ __device__ __forceinline__ int md_move(const ET* __restrict__ E, const MdTables&
 #pragma unroll
         for (int u = 0; u < kG; ++u) gl[u] = md.cell_first[bi * kMdInline + l + kLanes * u];
         cnt = (int)(cl & 255u);
+        if constexpr (kKeep) {
+#pragma unroll
+          for (int u = 0; u < kG; ++u)
+            if (l + kLanes * u < cnt) read_grain(gl[u], gk[u][0], gk[u][1], gk[u][2], gk[u][3]);
+        }
       } else {
         cnt = 0;
         int i0 = i + md.bx0, j0 = j + md.by0;
@@ -307,8 +322,11 @@ __device__ __forceinline__ int md_move(const ET* __restrict__ E, const MdTables&
     }
     first = 256;
 #pragma unroll
-    for (int u = 0; u < kG; ++u)
-      if (l + kLanes * u < cnt) grain(l + kLanes * u, gl[u], sub > 0);
+    for (int u = 0; u < kG; ++u) {
+      if (l + kLanes * u >= cnt) continue;
+      if constexpr (kKeep) pull(l + kLanes * u, gk[u][0], gk[u][1], gk[u][2], gk[u][3], sub > 0);
+      else grain(l + kLanes * u, gl[u], sub > 0);
+    }
     if (cnt > kMdInline)
       for (int t = kMdInline + l; t < cnt; t += kLanes) grain(t, md.grain_idx[(cl >> 8) + t], sub > 0);
     if constexpr (kLanes > 1) first = quad_min(first);
@@ -326,12 +344,14 @@ __device__ __forceinline__ int md_move(const ET* __restrict__ E, const MdTables&
       v[a] += S.qm_h * Ep[a];
       x[a] += v[a] * S.h_dx;
     }
-    if (!(x[0] >= 0.0 && x[0] < (double)S.nx && x[1] >= 0.0 && x[1] < (double)S.ny)) {
+    // (one test for the usual case, inside the box)
+    if (!(x[0] >= 0.0 && x[0] < (double)S.nx && x[1] >= 0.0 && x[1] < (double)S.ny && x[2] > 0.0 &&
+          x[2] < (double)S.nz)) {
       x[0] = wrap_coord(x[0], S.nx);
       x[1] = wrap_coord(x[1], S.ny);
+      const int zs = z_status(x, S);
+      if (zs != ST_ALIVE) return zs;
     }
-    const int zs = z_status(x, S);
-    if (zs != ST_ALIVE) return zs;
   }
   return ST_ALIVE;
 }
@@ -1973,7 +1993,8 @@ __global__ __launch_bounds__(kMdThreads) void md_kernel(SpeciesPair<PT> pr, PT D
 // The push and the MD particles' motion in one launch, the MD blocks (four waves
 // each) first, for a box whose blocks are all resident at once: a second stream
 // for the MD kernel costs a fork and a join, about 5 us each (16x16x32 cells: from
-// the fields to the lists 44 us with two launches, 34 us so).  A larger box keeps two:
+// the fields to the lists 44 us with two launches, 34 us so, before the chain of
+// md_move was shortened to 28).  A larger box keeps two:
 // the MD motion's registers (two waves per SIMD) would be the push's too.
 template <typename PT, typename Desc, typename ET, typename RT>
 __global__ __launch_bounds__(kBlock, 2) void push_md_kernel(const Desc* descs, int nb, int span,
