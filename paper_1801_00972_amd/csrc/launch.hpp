@@ -74,8 +74,15 @@ void launch_lists(const PushDescF32* descs, const PartF32R D[2], bool grains, co
 // float4), the MD cells' corrected node fields, zero_next (nn 8-byte words,
 // may be null) cleared for the next deposit, with it the counts of the lists
 // L[].md_next, and, with b, the sums of the
-// squared residual b - A psi and of b^2 per block of field_out_sums(nn) blocks.
-inline long field_out_sums(long nn) { return (nn + 255) / 256; }
+// squared residual b - A psi and of b^2 per block of field_out_sums() blocks.
+inline int field_out_planes(int plane, int nz) {
+  const long one = (plane + 255) / 256 * (long)(nz + 1);  // blocks of one plane
+  return (int)(one < 4096 ? 1 : one >= 16384 ? 8 : one / 2048);
+}
+inline long field_out_sums(int plane, int nz) {
+  const int u = field_out_planes(plane, nz);
+  return (plane + 255) / 256 * (long)((nz + u) / u);
+}
 void launch_field_out(const double* psi, double* phi, void* E, int e_f64,
                       unsigned long long* zero_next, const double* b, double* partials,
                       const MdTables& md, const WorkLists L[2], int nx, int ny, int nz, double dx,

@@ -385,12 +385,17 @@ __device__ __forceinline__ void md_corner(const MdTables& md, int nx, int ny, ui
 // cell, corner) forms the corrected node field; E at the node is
 // formed from psi and rounded to the storage type first, so it is what a read
 // of E returns (these blocks come first: their dependent table loads then
-// overlap the node blocks' streaming).  Blocks from nbm on: one thread per
-// node writes phi (psi, the solve's interior potential, and the electrodes'
-// lift) and E = -grad phi in the storage type, and clears the next step's
-// charge accumulator (and the counts of its MD lists).  With b (FP32R) the block's sums of (b - A psi)^2 and b^2
-// over its interior nodes go to partials: the six neighbours are at hand, so
-// the residual costs one more read per node and no pass of its own.
+// overlap the node blocks' streaming).  Blocks from nbm on: a thread takes one
+// column of nodes through `planes` planes and writes phi (psi, the solve's interior
+// potential, and the electrodes' lift) and E = -grad phi in the storage type, and
+// clears the next step's charge accumulator (and the counts of its MD lists).
+// With b (FP32R) the block's sums of (b - A psi)^2 and b^2 over its interior nodes
+// go to partials: the six neighbours are at hand, so the residual costs one more
+// read per node and no pass of its own.  Along the column the neighbours above
+// and below and the lift's division are kept, and a large mesh leaves an eighth of
+// the partial sums for the next solve to add up: 128x128x512 cells 167 -> 148 us here
+// and 92 -> 42 in the solve, 64x64x256 18.5 -> 14.8 us; below 4,096 blocks of one
+// plane each the chip has no work to spare, and a block takes one.
 template <typename ET>
 __global__ __launch_bounds__(256) void field_out_kernel(const double* __restrict__ psi,
                                                         double* __restrict__ phi,
@@ -400,52 +405,59 @@ __global__ __launch_bounds__(256) void field_out_kernel(const double* __restrict
                                                         double* __restrict__ partials,
                                                         MdTables md, int* n_md0, int* n_md1,
                                                         int nx, int ny, int nz, double dx,
-                                                        RfDrive rf, int nbm) {
+                                                        RfDrive rf, int nbm, int planes) {
   const double V = rf_voltage(rf);
   if (blockIdx.x == 0 && threadIdx.x == 0) *rf.next = *rf.step + 1u;
   if ((int)blockIdx.x >= nbm) {
     __shared__ double s_r[4], s_b[4];
-    const int plane = nx * ny;
-    const int n = ((int)blockIdx.x - nbm) * (int)blockDim.x + (int)threadIdx.x;
+    const int plane = nx * ny, per = (plane + 255) / 256;
+    const int blk = (int)blockIdx.x - nbm, k0 = blk / per * planes;
+    const int pn = (blk - blk / per * per) * 256 + (int)threadIdx.x;
     double rr = 0.0, bb = 0.0;
-    if (n < plane * (nz + 1)) {
-      const int k = n / plane, pn = n - k * plane;
-      const int y = pn / nx, x = pn - y * nx;
-      if (zero_next) zero_next[n] = 0ull;
-      if (zero_next && n == 0) {
+    if (pn < plane) {
+      if (zero_next && k0 == 0 && pn == 0) {
         *n_md0 = 0;
         *n_md1 = 0;
       }
-      const int row = y * nx;
+      const int y = pn / nx, x = pn - y * nx, row = y * nx;
       const int xp = row + (x + 1 == nx ? 0 : x + 1), xm = row + (x == 0 ? nx - 1 : x - 1);
       const int yp = (y + 1 == ny ? 0 : y + 1) * nx + x, ym = (y == 0 ? ny - 1 : y - 1) * nx + x;
-      const bool in = k > 0 && k < nz;
-      const double* p0 = psi + (long)(k - 1) * plane;
-      const double qc = in ? p0[pn] : 0.0;
-      const double qxp = in ? p0[xp] : 0.0, qxm = in ? p0[xm] : 0.0;
-      const double qyp = in ? p0[yp] : 0.0, qym = in ? p0[ym] : 0.0;
-      const double qzp = k + 1 < nz ? p0[plane + pn] : 0.0, qzm = k > 1 ? p0[pn - plane] : 0.0;
-      // the lifted potential at height q: psi + V q / nz, 0 and V on the electrodes
-      auto lift = [&](double q, int h) { return h == 0 ? 0.0 : (h == nz ? V : q + V * (double)h / (double)nz); };
-      const double c = lift(qc, k);
-      phi[n] = c;
-      const double ex = -(lift(qxp, k) - lift(qxm, k)) / (2.0 * dx);
-      const double ey = -(lift(qyp, k) - lift(qym, k)) / (2.0 * dx);
-      double ez;
-      if (k == 0) ez = -(lift(qzp, 1) - c) / dx;
-      else if (k == nz) ez = -(c - lift(qzm, nz - 1)) / dx;
-      else ez = -(lift(qzp, k + 1) - lift(qzm, k - 1)) / (2.0 * dx);
-      if constexpr (std::is_same<ET, double2>::value) {
-        E[2 * (long)n] = make_double2(ex, ey);
-        E[2 * (long)n + 1] = make_double2(ez, 0.0);
-      } else {
-        E[n] = make_float4((float)ex, (float)ey, (float)ez, 0.0f);
-      }
-      if (b && in) {
-        const double bi = b[n - plane];
-        const double r = bi - (qxp + qxm + qyp + qym + qzp + qzm - 6.0 * qc);
-        rr = r * r;
-        bb = bi * bi;
+      // psi at height h (interior: 1 .. nz - 1), the lift of its plane, and the lifted
+      // potential: 0 and V on the electrodes
+      auto psi_at = [&](int h, int i) { return h > 0 && h < nz ? psi[(long)(h - 1) * plane + i] : 0.0; };
+      auto lift_of = [&](int h) { return V * (double)h / (double)nz; };
+      auto lifted = [&](double q, double l, int h) { return h == 0 ? 0.0 : (h == nz ? V : q + l); };
+      double l = lift_of(k0), qm = psi_at(k0 - 1, pn), q = psi_at(k0, pn);
+      double cm = lifted(qm, lift_of(k0 - 1), k0 - 1), c = lifted(q, l, k0);
+      const int k1 = min(k0 + planes, nz + 1);
+      for (int k = k0; k < k1; ++k) {
+        const long n = (long)k * plane + pn;
+        const bool in = k > 0 && k < nz;
+        const double qp = psi_at(k + 1, pn), ln = lift_of(k + 1), cp = lifted(qp, ln, k + 1);
+        const double qxp = psi_at(k, xp), qxm = psi_at(k, xm), qyp = psi_at(k, yp), qym = psi_at(k, ym);
+        if (zero_next) zero_next[n] = 0ull;
+        phi[n] = c;
+        const double ex = -(lifted(qxp, l, k) - lifted(qxm, l, k)) / (2.0 * dx);
+        const double ey = -(lifted(qyp, l, k) - lifted(qym, l, k)) / (2.0 * dx);
+        const double up = k == nz ? c : cp, dn = k == 0 ? c : cm;
+        const double ez = -(up - dn) / (in ? 2.0 * dx : dx);
+        if constexpr (std::is_same<ET, double2>::value) {
+          E[2 * n] = make_double2(ex, ey);
+          E[2 * n + 1] = make_double2(ez, 0.0);
+        } else {
+          E[n] = make_float4((float)ex, (float)ey, (float)ez, 0.0f);
+        }
+        if (b && in) {
+          const double bi = b[n - plane];
+          const double r = bi - (qxp + qxm + qyp + qym + qp + qm - 6.0 * q);
+          rr += r * r;
+          bb += bi * bi;
+        }
+        qm = q;
+        q = qp;
+        cm = c;
+        c = cp;
+        l = ln;
       }
     }
     if (!b) return;
@@ -460,9 +472,8 @@ __global__ __launch_bounds__(256) void field_out_kernel(const double* __restrict
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-      const long blk = (long)blockIdx.x - nbm;
-      partials[2 * blk] = s_r[0] + s_r[1] + s_r[2] + s_r[3];
-      partials[2 * blk + 1] = s_b[0] + s_b[1] + s_b[2] + s_b[3];
+      partials[2 * (long)blk] = s_r[0] + s_r[1] + s_r[2] + s_r[3];
+      partials[2 * (long)blk + 1] = s_b[0] + s_b[1] + s_b[2] + s_b[3];
     }
     return;
   }
@@ -3327,17 +3338,16 @@ void launch_field_out(const double* psi, double* phi, void* E, int e_f64,
                       unsigned long long* zero_next, const double* b, double* partials,
                       const MdTables& md, const WorkLists L[2], int nx, int ny, int nz, double dx,
                       RfDrive rf, hipStream_t st) {
-  const long nn = (long)nx * ny * (nz + 1);
-  const int nbe = (int)field_out_sums(nn);
+  const int planes = field_out_planes(nx * ny, nz), nbe = (int)field_out_sums(nx * ny, nz);
   const int nbm = md.n_grains > 0 ? nblk(8L * md.bsx * md.bsy * md.bsz, 256) : 0;
   if (e_f64)
     hipLaunchKernelGGL(field_out_kernel<double2>, dim3(nbe + nbm), dim3(256), 0, st, psi, phi,
                        (double2*)E, zero_next, b, partials, md, L[0].n_md_next, L[1].n_md_next, nx, ny,
-                       nz, dx, rf, nbm);
+                       nz, dx, rf, nbm, planes);
   else
     hipLaunchKernelGGL(field_out_kernel<float4>, dim3(nbe + nbm), dim3(256), 0, st, psi, phi,
                        (float4*)E, zero_next, b, partials, md, L[0].n_md_next, L[1].n_md_next, nx, ny,
-                       nz, dx, rf, nbm);
+                       nz, dx, rf, nbm, planes);
 }
 
 // waves for the particles that the loading density puts into the cubes, per

@@ -836,7 +836,7 @@ int deposit_current(pic_ctx* ctx, Replica& R) {
 }
 
 RefineState refine_state(const Replica& R) {
-  return RefineState{R.norms + 2, (int)field_out_sums(R.nn), R.norms, R.refine_ctl,
+  return RefineState{R.norms + 2, (int)field_out_sums((int)R.nxy, R.nz), R.norms, R.refine_ctl,
                      R.cfg.refine_tol * R.cfg.refine_tol};
 }
 
@@ -1640,7 +1640,7 @@ int init_replica(pic_ctx* ctx, Replica& R, const pic_config& cin) {
   TRY(dalloc(ctx, R, &R.psi, R.n_int));
   TRY(dalloc(ctx, R, &R.phi, R.nn));
   // two sums and a partial pair per residual block (blocks of 256 nodes per plane)
-  TRY(dalloc(ctx, R, &R.norms, 2 + 2 * std::max(((R.nxy + 255) / 256) * (R.nz - 1), field_out_sums(R.nn))));
+  TRY(dalloc(ctx, R, &R.norms, 2 + 2 * std::max(((R.nxy + 255) / 256) * (R.nz - 1), field_out_sums((int)R.nxy, R.nz))));
   TRY(dalloc(ctx, R, &R.d_gc, 2 * std::max(c.n_grains, 1)));
   const long nkey = sort_keys(R.ngrid);
   TRY(dalloc(ctx, R, &R.d_hist, nkey));
