@@ -204,10 +204,10 @@ def run_form(wls, steps, warmup, sort_interval=8, autotune=True, label=None, ave
         md_particle_steps=md1 - md0,
         collisions=coll1 - coll0,
     )
-    res["push_form"] = ("one persistent launch for every replica and species"
+    res["push_form"] = ("one launch for every replica and species"
                         if tuning.get("batch_push") else
-                        "one launch per replica and species" if len(wls) > 1 else
-                        "one launch per species")
+                        "one launch per replica, both species" if len(wls) > 1 else
+                        "one launch of both species")
     if persistent and len(wls) > 1 and not tuning.get("batch_push"):
         # the persistent one-launch push, timed on the same live run
         sim.set_tuning(batch_push=1)

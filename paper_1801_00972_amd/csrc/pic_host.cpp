@@ -1185,7 +1185,7 @@ int for_replicas(pic_ctx* ctx, Fn fn, bool join = true) {
 }
 
 // one step of every replica of an FP32R context with the push of all
-// replicas and species in one persistent launch (replicas in the same phase)
+// replicas and species in one launch (replicas in the same phase)
 int enqueue_batch(pic_ctx* ctx, int sorts, int sample) {
   hipStream_t st = ctx->stream;
   const Replica& R0 = *ctx->reps[0];
