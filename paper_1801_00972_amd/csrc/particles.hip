@@ -2238,6 +2238,8 @@ __global__ __launch_bounds__(kT, 4) void moments_kernel(PT P, SpeciesStep S, Wor
         lo = __builtin_amdgcn_mfma_f64_4x4x4f64(A, w * (1.0 - fz), lo, 0, 0, 0);
         hi = __builtin_amdgcn_mfma_f64_4x4x4f64(A, w * fz, hi, 0, 0, 0);
       }
+      // (the last results' wait states, whatever the compiler places next)
+      asm volatile("s_nop 7\n\ts_nop 3" : "+v"(lo), "+v"(hi));
       if (have) {
         atomicAdd(&out[c & 0xffff], lo);
         atomicAdd(&out[(c & 0xffff) + T.tx * T.ty], hi);
