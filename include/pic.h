@@ -273,7 +273,8 @@ int pic_grain_positions(pic_ctx* ctx, int replica, double* pos);
  * Sec. III) at x_k, and v_p the stored half-step velocity v_{k-1/2}.  They
  * are computed on request (summed in FP64 with atomics, so the last bits
  * depend on the order of additions) and are not part of pic_step.
- * Errors: PIC_EINVAL (bad replica, NULL buffer, RHO_FIXED without FP32R,
+ * Errors: PIC_EINVAL (bad replica, NULL buffer, a device buffer whose
+ * allocation ends before the quantity does, RHO_FIXED without FP32R,
  * unknown bits), PIC_ESTATE (FINE bits without a fine grid).
  */
 int pic_fields(pic_ctx* ctx, int replica, unsigned what, void* const* out, int out_on_device);

@@ -1706,18 +1706,26 @@ struct FieldStage {
   size_t cap;
 };
 
-// whether a kernel may write doubles to p, which the caller says is on the device: in
-// this device's own memory and aligned.  A copy (which takes any address a
-// copy reaches) does the rest.
-bool kernel_writes(const void* p) {
-  if ((uintptr_t)p % sizeof(double) != 0) return false;
+// What the caller says is a device buffer for `count` 8-byte values: one that a kernel
+// may write (aligned, this device's own memory), one that takes a copy (any address a
+// copy reaches), or one that ends too early, which no kernel may be handed.  Asked
+// before a call's first launch, so that clearing the error of an unknown address hides
+// none of a launch.
+enum { kOutCopy, kOutKernel, kOutShort };
+int out_kind(const void* p, long count) {
   hipPointerAttribute_t at{};
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
   int dev = 0;
-  if (hipPointerGetAttributes(&at, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
-    (void)hipGetLastError();  // (memory the runtime does not know)
-    return false;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
+      at.type != hipMemoryTypeDevice ||
+      hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+    (void)hipGetLastError();  // (memory the runtime does not know, or no device memory)
+    return kOutCopy;
   }
-  return at.type == hipMemoryTypeDevice && at.device == dev;
+  const size_t off = (size_t)((const char*)p - (const char*)base);
+  if (off > size || (size - off) / 8 < (size_t)count) return kOutShort;
+  return (uintptr_t)p % 8 == 0 && at.device == dev ? kOutKernel : kOutCopy;
 }
 
 int fields_impl(pic_ctx* ctx, Replica* R, unsigned what, void* const* out, int out_on_device,
@@ -1727,14 +1735,28 @@ int fields_impl(pic_ctx* ctx, Replica* R, unsigned what, void* const* out, int o
     return fail(ctx, PIC_EINVAL, "PIC_RHO_FIXED needs the FP32R form");
   if ((what & (PIC_FINE_N | PIC_FINE_FLUX | PIC_FINE_PHI)) && !R->fine_on)
     return fail(ctx, PIC_ESTATE, "no fine grid: call pic_set_fine_grid");
+  const long nn = R->nn, fn = R->fine.fn;
+  // the caller's buffers, by bit, and those that the last kernel of their quantity
+  // writes itself (null where a copy has to follow; with the caller's scratch all are)
+  void* bufs[9] = {};
+  double* in_place[9] = {};
+  auto given = [&](unsigned bit) { return bufs[__builtin_ctz(bit)]; };
+  auto direct = [&](unsigned bit) { return in_place[__builtin_ctz(bit)]; };
   {
     int slot = 0;
-    for (unsigned bit = 1; bit <= PIC_FINE_PHI; bit <<= 1)
-      if ((what & bit) && !out[slot++]) return fail(ctx, PIC_EINVAL, "NULL output buffer");
+    for (int b = 0; b < 9; ++b)
+      if ((what & (1u << b)) && !(bufs[b] = out[slot++]))
+        return fail(ctx, PIC_EINVAL, "NULL output buffer");
+    const long len[9] = {nn, 3 * nn, nn, nn, 2 * nn, 6 * nn, 2 * fn, 6 * fn, fn};
+    for (int b = 0; b < 9; ++b) {
+      if (!bufs[b] || !out_on_device || sc) continue;
+      const int kind = out_kind(bufs[b], len[b]);
+      if (kind == kOutShort) return fail(ctx, PIC_EINVAL, "output buffer too short");
+      if (kind == kOutKernel) in_place[b] = (double*)bufs[b];
+    }
   }
   hipStream_t st = ctx->stream;
   TRY(solve_fields(ctx, *R));
-  const long nn = R->nn;
   double* tot64 = nullptr;
   long long* totfx = nullptr;
   double* eout = nullptr;
@@ -1752,17 +1774,6 @@ int fields_impl(pic_ctx* ctx, Replica* R, unsigned what, void* const* out, int o
   }
   const hipMemcpyKind kind = out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
   const double vol = R->cfg.dx * R->cfg.dx * R->cfg.dx;
-  // Without the caller's scratch, the last kernel of a quantity writes it where the
-  // caller wants it (dst where a copy has to follow: null)
-  auto direct = [&](void* dst) -> double* {
-    return dst && out_on_device && !sc && kernel_writes(dst) ? (double*)dst : nullptr;
-  };
-  auto given = [&](unsigned bit) -> void* {  // the caller's buffer of a quantity, if asked for
-    if (!(what & bit)) return nullptr;
-    int slot = 0;
-    for (unsigned b = 1; b < bit; b <<= 1) slot += (what & b) != 0;
-    return out[slot];
-  };
   // sums of W and v W of one species into mom [4][nn]
   auto moments_of = [&](int sp, double* mom) {
     const SpeciesStep S = species_step(*R, sp);
@@ -1772,8 +1783,9 @@ int fields_impl(pic_ctx* ctx, Replica* R, unsigned what, void* const* out, int o
       launch_moments(nullptr, &R->p32[sp][R->cur[sp]], S, R->lists[sp], mom, nn, AvgBins{}, st);
   };
   // the moments mom [2][4][len] of both species, times conv, to the caller
-  auto hand_out = [&](double* mom, long len, double conv, void* n, void* flux) -> int {
-    double *dn = direct(n), *df = direct(flux);
+  auto hand_out = [&](double* mom, long len, double conv, unsigned n_bit, unsigned flux_bit) -> int {
+    void *n = given(n_bit), *flux = given(flux_bit);
+    double *dn = direct(n_bit), *df = direct(flux_bit);
     if (dn || df) launch_moments_out(mom, len, conv, dn, df, st);
     if ((n && !dn) || (flux && !df)) launch_scale(conv, mom, 8 * len, st);
     for (int sp = 0; sp < 2; ++sp) {
@@ -1786,13 +1798,12 @@ int fields_impl(pic_ctx* ctx, Replica* R, unsigned what, void* const* out, int o
     CHECK_LAUNCH(ctx);
     return PIC_OK;
   };
-  const long fn = R->fine.fn;
   if (what & (PIC_N | PIC_FLUX)) {
     if (!sc) {
       if (!R->mom) TRY(dalloc(ctx, *R, &R->mom, 8 * nn));
       launch_zero_f64(R->mom, 8 * nn, st);
       for (int sp = 0; sp < 2; ++sp) moments_of(sp, R->mom + 4 * nn * sp);
-      TRY(hand_out(R->mom, nn, R->w / vol, given(PIC_N), given(PIC_FLUX)));
+      TRY(hand_out(R->mom, nn, R->w / vol, PIC_N, PIC_FLUX));
     } else {
       // one species at a time through the scratch
       char *n = (char*)given(PIC_N), *flux = (char*)given(PIC_FLUX);
@@ -1812,10 +1823,10 @@ int fields_impl(pic_ctx* ctx, Replica* R, unsigned what, void* const* out, int o
     launch_zero_f64(R->fine_mom, 8 * fn, st);
     TRY(enqueue_fine(ctx, *R, R->fine_mom, AvgBins{}));
     const double hdx = R->fine.h * R->cfg.dx;
-    TRY(hand_out(R->fine_mom, fn, R->w / (hdx * hdx * hdx), given(PIC_FINE_N), given(PIC_FINE_FLUX)));
+    TRY(hand_out(R->fine_mom, fn, R->w / (hdx * hdx * hdx), PIC_FINE_N, PIC_FINE_FLUX));
   }
   if (void* dst = given(PIC_FINE_PHI)) {
-    double* d = direct(dst);
+    double* d = direct(PIC_FINE_PHI);
     if (!d && !R->fine_phi) TRY(dalloc(ctx, *R, &R->fine_phi, fn));
     launch_fine_phi(R->phi, R->md, R->Uphi, R->fine, R->nx, R->ny, R->nz, R->cfg.dx,
                     R->cfg.grain_radius, d ? d : R->fine_phi, AvgBins{}, st);
@@ -1824,7 +1835,7 @@ int fields_impl(pic_ctx* ctx, Replica* R, unsigned what, void* const* out, int o
   }
   if (void* dst = given(PIC_PHI)) HIPCHK(ctx, hipMemcpyAsync(dst, R->phi, nn * 8, kind, st));
   if (void* dst = given(PIC_E)) {
-    double* d = direct(dst);
+    double* d = direct(PIC_E);
     launch_e_out(R->prec == PIC_FP64 ? (const double*)R->E : nullptr,
                  R->prec == PIC_FP64 ? nullptr : (const float*)R->E, d ? d : eout, nn, st);
     if (!d) HIPCHK(ctx, hipMemcpyAsync(dst, eout, 3 * nn * 8, kind, st));
@@ -1834,7 +1845,7 @@ int fields_impl(pic_ctx* ctx, Replica* R, unsigned what, void* const* out, int o
     void* dst = given(bit);
     if (!dst) continue;
     const bool f64 = R->prec == PIC_FP64, fixed = bit == PIC_RHO_FIXED;
-    void* d = direct(dst);
+    void* d = direct(bit);
     if (!d) d = fixed ? (void*)totfx : (void*)tot64;
     launch_rho_out(f64 ? (const double*)R->rho[R->rho_cur] : nullptr,
                    f64 ? nullptr : (const long long*)R->rho[R->rho_cur], R->d_gtab, R->n_gtab,
@@ -2135,14 +2146,23 @@ int pic_average_read(pic_ctx* ctx, int replica, int bin, unsigned what, void* co
       given[std::find(bits, bits + 6, bit) - bits] = dst;
     }
   }
+  const long fn = R->fine.fn, count[6] = {nn, 2 * nn, 6 * nn, fn, 2 * fn, 6 * fn};
+  double* in_place[6] = {};  // those that the kernel writes itself
+  for (int k = 0; k < 6; ++k) {
+    if (!given[k] || !out_on_device) continue;
+    const int kind = out_kind(given[k], count[k]);
+    if (kind == kOutShort) return fail(ctx, PIC_EINVAL, "output buffer too short");
+    if (kind == kOutKernel) in_place[k] = (double*)given[k];
+  }
   const hipMemcpyKind kind = out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
   // phi, densities and fluxes of one grid: straight to the caller, or staged and copied
-  auto hand_out = [&](const double* acc, long len, double wv, void* const* dst, double** stage) -> int {
+  auto hand_out = [&](const double* acc, long len, double wv, int at, double** stage) -> int {
+    void* const* dst = given + at;
     if (!dst[0] && !dst[1] && !dst[2]) return PIC_OK;
     const long first[3] = {0, len, 3 * len}, size[3] = {len, 2 * len, 6 * len};
     double* to[3];
     for (int k = 0; k < 3; ++k) {
-      to[k] = dst[k] && out_on_device && kernel_writes(dst[k]) ? (double*)dst[k] : nullptr;
+      to[k] = in_place[at + k];
       if (to[k] || !dst[k]) continue;
       if (!*stage) TRY(dalloc(ctx, *R, stage, 9 * len));
       to[k] = *stage + first[k];
@@ -2155,8 +2175,8 @@ int pic_average_read(pic_ctx* ctx, int replica, int bin, unsigned what, void* co
     return PIC_OK;
   };
   const double vol = R->cfg.dx * R->cfg.dx * R->cfg.dx, hdx = R->fine.h * R->cfg.dx;
-  TRY(hand_out(R->avg, nn, R->w / vol, given, &R->avg_out));
-  TRY(hand_out(R->fine_avg, R->fine.fn, R->w / (hdx * hdx * hdx), given + 3, &R->fine_out));
+  TRY(hand_out(R->avg, nn, R->w / vol, 0, &R->avg_out));
+  TRY(hand_out(R->fine_avg, fn, R->w / (hdx * hdx * hdx), 3, &R->fine_out));
   if (samples) {
     std::vector<unsigned long long> c(ctx->avg_bins);
     HIPCHK(ctx, hipMemcpyAsync(c.data(), R->d_avg_cnt, c.size() * 8, hipMemcpyDeviceToHost, st));
