@@ -58,6 +58,14 @@ void launch_push_md(const PushDescF64* descs, const PartF64 P[2], const PartF64 
 void launch_push_md(const PushDescF32* descs, const PartF32R P[2], const PartF32R D[2],
                     const void* E, void* rho, const MdTables& md, const SpeciesStep S[2],
                     unsigned long long* gc, const WorkLists L[2], hipStream_t st);
+// Push and MD motion as two launches side by side: the first enqueued gets the
+// chip's waves first.  A long push goes first and hides the MD motion (64x64x256
+// cells, FP32R: 9.67 ms for 8 steps against 10.21); one of about 8 million slots or
+// less ends with it, and the MD kernel's chains go first (36x30x77 cells, 7 per
+// cell: 2.24 ms for 16 steps against 2.27).  (Two species of up to 2^31 - 1 slots each.)
+inline bool push_goes_first(const WorkLists L[2]) {
+  return (long)L[0].slots + (long)L[1].slots > 8L << 20;
+}
 // the push blocks (first tiles) whose window of `margin` cells meets the MD
 // cubes' bounding box
 std::vector<int32_t> near_blocks(const WorkLists& L, const MdTables& md, int nx, int ny, int nz,

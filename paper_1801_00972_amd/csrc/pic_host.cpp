@@ -1081,12 +1081,7 @@ int enqueue_particles(pic_ctx* ctx, Replica& R, bool fin) {
   if (fin)
     launch_refine_final(R.nx, R.ny, R.nz, R.b, R.psi, R.r, R.cfg.max_refine, R.cfg.refine_tol,
                         R.norms, R.refine_ctl, ms);
-  // Two launches side by side: the first enqueued gets the chip's waves first.  A long
-  // push goes first and hides the MD motion (64x64x256 cells, FP32R: 9.67 ms for 8
-  // steps against 10.21); one of about 8 million slots or less ends with it, and the
-  // MD kernel's chains go first (36x30x77 cells, 7 per cell: 2.24 ms for 16 steps
-  // against 2.27).
-  const bool push_first = one || L[0].slots + L[1].slots > 8 << 20;
+  const bool push_first = one || push_goes_first(L);
   auto md_part = [&]() -> int {
     hipEvent_t a = prof_event(ctx);
     launch_md_move(P, D, R.E, rho, R.md, S, R.d_gc, L, ms);

@@ -1,0 +1,32 @@
+"""CPU checks of the host's launch rules at the edges of their ranges: a C++
+program compiled against the library's headers and linked with it prints what
+each rule says.  No device call is made."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_1801_00972_amd")
+
+
+def _run(tmp_path, body):
+    src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
+    src.write_text('#include <cstdio>\n#include "launch.hpp"\nusing namespace pic;\nint main() {\n' + body + "\n}\n")
+    if not os.path.exists(os.path.join(PKG, "libpic.so")):
+        from paper_1801_00972_amd import build
+        build.build()
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-fsanitize=undefined", "-I/opt/rocm/include",
+                    "-I", os.path.join(PKG, "csrc"), str(src), "-o", str(exe),
+                    os.path.join(PKG, "libpic.so"), "-Wl,-rpath," + PKG, "-L/opt/rocm/lib", "-lamdhip64",
+                    "-Wl,-rpath,/opt/rocm/lib"], check=True)
+    res = subprocess.run([str(exe)], capture_output=True, text=True, check=True)
+    assert "runtime error" not in res.stderr, res.stderr
+    return [int(x) for x in res.stdout.split()]
+
+
+@pytest.mark.parametrize("slots,first", [((4 << 20, 4 << 20), 0), ((4 << 20, (4 << 20) + 4), 1),
+                                         ((1 << 30, 1 << 30), 1), ((2 ** 31 - 4, 2 ** 31 - 4), 1), ((0, 1024), 0)])
+def test_long_pushes_go_first(tmp_path, slots, first):
+    assert _run(tmp_path, "WorkLists L[2]{}; L[0].slots = %d; L[1].slots = %d;\n"
+                          'std::printf("%%d\\n", (int)push_goes_first(L));' % slots) == [first]
