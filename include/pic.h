@@ -434,8 +434,10 @@ int pic_derived(pic_ctx* ctx, int replica, double out[7]);
  *                      after loading); initially pic_config.sort_interval of
  *                      replica 0
  *   ion_sort_interval  the same for the ions; initially 64
- *   tile_margin        the electrons' window margin in cells (0..3; particles
- *                      beyond it take the global-memory path); initially 2
+ *   tile_margin        the electrons' window margin in cells (0..3, fewer where
+ *                      the window would exceed 1331 nodes, 1053 in FP64;
+ *                      particles beyond it take the global-memory path);
+ *                      initially 2
  *   ion_tile_margin    the same for the ions; initially 1
  *   batch_push         1: the pushes of every replica and species run as one
  *                      launch (all replicas FP32R only); initially 1 for an FP32R
@@ -465,9 +467,9 @@ int pic_set_tuning(pic_ctx* ctx, const pic_tuning* t);
 /*
  * pic_autotune -- choose the settings by measurement on live steps: starting
  * from the current settings, a coordinate search over sort_interval in
- * {4, 6, 8, 12, 16}, then tile_margin in {1, 2, 3}, then (FP32R contexts)
- * batch_push off or on with batch_blocks of 2, 3, 4 or 6 per compute unit,
- * then use_graphs on or off (the ion settings are kept).  Each trial takes 2
+ * {4, 6, 8, 12, 16}, then tile_margin in {1, 2, 3} (without one whose windows
+ * are all another's), then (FP32R contexts) batch_push off or on, then
+ * use_graphs on or off (the ion settings are kept).  Each trial takes 2
  * untimed steps, then trial_steps steps, each bracketed by HIP events after
  * any graph capture (a multiple of 48 gives every interval the same share of
  * re-binnings).  As the plasma evolves during the search, each candidate is

@@ -70,6 +70,8 @@ inline bool push_goes_first(const WorkLists L[2]) {
 // cubes' bounding box
 std::vector<int32_t> near_blocks(const WorkLists& L, const MdTables& md, int nx, int ny, int nz,
                                  int margin, bool f64);
+// whether two window margins give every push block the same window
+bool same_windows(const WorkLists& L, int nx, int ny, int nz, int m0, int m1, bool f64);
 // everything after the push (descs as in launch_push): the collision candidates
 // it had no room for, the outliers, the MD particles' states back from D with
 // their collisions, and the next step's MD lists

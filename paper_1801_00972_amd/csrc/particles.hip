@@ -3420,6 +3420,15 @@ std::vector<int32_t> near_blocks(const WorkLists& L, const MdTables& md, int nx,
   return v;
 }
 
+bool same_windows(const WorkLists& L, int nx, int ny, int nz, int m0, int m1, bool f64) {
+  const int span = push_span(L), cap = f64 ? kWinF64 : kWinF32;
+  for (int t = 0; t < L.ngrid; t += span) {
+    const Tile a = make_tile(t, L, nx, ny, nz, m0, cap, span), b = make_tile(t, L, nx, ny, nz, m1, cap, span);
+    if (a.x0 != b.x0 || a.y0 != b.y0 || a.k0 != b.k0 || a.tx != b.tx || a.ty != b.ty || a.tz != b.tz) return false;
+  }
+  return true;
+}
+
 constexpr int kMdListBlocks = 512;  // per species (tally rows 0 .. 511 of the MD rows)
 template <typename PT, typename Desc>
 static void lists_impl(const Desc* descs, const PT D[2], bool grains, const WorkLists L[2],

@@ -1424,6 +1424,14 @@ int step_all(pic_ctx* ctx) {
   return PIC_OK;
 }
 
+// whether two margins of the electrons' windows make the same push (a window that
+// exceeds its capacity shrinks: in FP64 a tile pair's three cells are two)
+bool same_push(const pic_ctx* ctx, int m0, int m1) {
+  for (auto& R : ctx->reps)
+    if (!same_windows(R->lists[0], R->nx, R->ny, R->nz, m0, m1, R->prec == PIC_FP64)) return false;
+  return true;
+}
+
 int check_tuning(const pic_ctx* ctx, const pic_tuning& t, std::string& why) {
   if (t.sort_interval < 0 || t.sort_interval > 1000000) why = "sort_interval out of range";
   else if (t.ion_sort_interval < 0 || t.ion_sort_interval > 1000000)
@@ -2736,20 +2744,15 @@ int pic_autotune(pic_ctx* ctx, int trial_steps, pic_tuning* tried, double* ms_pe
       }
     } else if (axis == 1) {
       for (int m : {1, 2, 3}) {
+        if (m > 1 && same_push(ctx, m, m - 1)) continue;
         pic_tuning t = best;
         t.tile_margin = m;
         cands.push_back(t);
       }
     } else if (axis == 2 && ctx->batchable) {
       pic_tuning t = best;
-      t.batch_push = 0;
+      t.batch_push = 1 - best.batch_push;
       cands.push_back(t);
-      for (int k : {2, 3, 4, 6}) {
-        t = best;
-        t.batch_push = 1;
-        t.batch_blocks = (k * ctx->n_cu + 7) / 8 * 8;
-        cands.push_back(t);
-      }
     } else if (axis == 3) {
       pic_tuning t = best;
       t.use_graphs = 1 - best.use_graphs;
@@ -2760,6 +2763,7 @@ int pic_autotune(pic_ctx* ctx, int trial_steps, pic_tuning* tried, double* ms_pe
     // after it, which cancels a drift that is linear in time
     for (const pic_tuning& t : cands) {
       if (std::memcmp(&t, &best, sizeof(t)) == 0) continue;
+      if (axis == 1 && same_push(ctx, t.tile_margin, best.tile_margin)) continue;
       double ms = 0.0, again = 0.0;
       rc = measure(t, &ms);
       if (rc == PIC_OK) rc = measure(best, &again);

@@ -30,3 +30,19 @@ def _run(tmp_path, body):
 def test_long_pushes_go_first(tmp_path, slots, first):
     assert _run(tmp_path, "WorkLists L[2]{}; L[0].slots = %d; L[1].slots = %d;\n"
                           'std::printf("%%d\\n", (int)push_goes_first(L));' % slots) == [first]
+
+
+@pytest.mark.parametrize("box,f64,same", [
+    ((64, 64, 64), 1, [0, 0, 1]),   # tile pairs in FP64: three cells shrink to two everywhere
+    ((36, 32, 64), 1, [0, 0, 0]),   # single tiles: three cells fit at the electrodes
+    ((8, 8, 64), 1, [0, 0, 0]),     # a pair's window spans the period: three cells fit
+    ((64, 64, 64), 0, [0, 0, 0]),   # (FP32R pairs: 15 x 11 x 8 nodes at the electrodes)
+    ((2, 2, 2), 0, [1, 1, 1]),      # the whole box in any window
+])
+def test_margins_of_the_same_windows(tmp_path, box, f64, same):
+    nx, ny, nz = box
+    body = "WorkLists L{}; L.ntx = %d; L.nty = %d; L.ntz = %d; L.ngrid = tile_grid(%d, %d, %d, 0);\n" % (
+        (nx + 3) // 4, (ny + 3) // 4, (nz + 3) // 4, nx, ny, nz)
+    body += 'for (int m = 0; m < 3; ++m) std::printf("%%d\\n", (int)same_windows(L, %d, %d, %d, m, m + 1, %d));' % (
+        nx, ny, nz, f64)
+    assert _run(tmp_path, body) == same
