@@ -2338,6 +2338,8 @@ int pic_set_state(pic_ctx* ctx, int replica, const pic_state_view* v) {
                       x[2] < R->nz && std::isfinite(u[0]) && std::isfinite(u[1]) &&
                       std::isfinite(u[2]);
       if (!ok) return fail(ctx, PIC_ENUMERIC, "particle outside the box or not finite");
+      if (R->prec == PIC_FP32R && (int)x[2] == R->nz - 1 && (float)(x[2] - (R->nz - 1)) >= 1.0f)
+        return fail(ctx, PIC_ENUMERIC, "particle rounds onto z = L_z");
     }
   }
   // upload into the spare buffers; the sort below brings the particles back
@@ -2373,7 +2375,6 @@ int pic_set_state(pic_ctx* ctx, int replica, const pic_state_view* v) {
             f = 0.0f;
             ci += 1;
             if (q < 2 && ci == nq) ci = 0;
-            if (q == 2 && ci == nq) return fail(ctx, PIC_ENUMERIC, "particle rounds onto z = L_z");
           }
           c3[q] = ci;
           a[q * cnt + i] = f;
