@@ -46,3 +46,19 @@ def test_margins_of_the_same_windows(tmp_path, box, f64, same):
     body += 'for (int m = 0; m < 3; ++m) std::printf("%%d\\n", (int)same_windows(L, %d, %d, %d, m, m + 1, %d));' % (
         nx, ny, nz, f64)
     assert _run(tmp_path, body) == same
+
+
+@pytest.mark.parametrize("box,ppc,one", [((32, 32, 28), 1, 1), ((32, 32, 32), 1, 0), ((8, 8, 16), 2, 1),
+                                         ((16, 16, 16), 16, 1), ((32, 32, 32), 2, 0)])
+def test_boxes_of_one_launch(tmp_path, box, ppc, one):
+    """The boxes that the GPU tests of push and MD motion take lie on the side of the
+    one-launch limit that they name (two grains apart, cubes of 7 cells)."""
+    nx, ny, nz = box
+    cells = 2 * 343 if ny > 8 else 7 * 8 * 7 * 2  # (8 cells: the cubes of 7 overlap; a bound is enough)
+    body = "WorkLists L{}; L.ntx = %d; L.nty = %d; L.ntz = %d; L.ngrid = tile_grid(%d, %d, %d, 0);\n" % (
+        (nx + 3) // 4, (ny + 3) // 4, (nz + 3) // 4, nx, ny, nz)
+    body += "L.slots = (%d + 4 * L.ngrid + 1023) / 1024 * 1024;\n" % (nx * ny * nz * ppc)
+    body += "MdTables md{}; md.n_grains = 2; md.n_cells = %d;\n" % cells
+    body += "SpeciesStep S{}; S.nx = %d; S.ny = %d; S.nz = %d;\n" % box
+    body += 'std::printf("%d\\n", (int)push_md_fits(md, S, L));'
+    assert _run(tmp_path, body) == [one]
