@@ -131,7 +131,4 @@ __device__ __forceinline__ void node_field(const double* __restrict__ src, int n
          (2.0 * dx);
 }
 
-// wrap an index that is at most one period outside [0, n)
-__device__ __forceinline__ int wrap1(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
-
 }  // namespace pic

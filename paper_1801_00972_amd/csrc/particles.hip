@@ -10,7 +10,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <climits>
 #include <type_traits>
 
 #include "device_common.hpp"
@@ -48,16 +47,11 @@ __device__ __forceinline__ int cell_j(int c) { return (c >> 10) & 1023; }
 __device__ __forceinline__ int cell_k(int c) { return c >> 20; }
 __device__ __forceinline__ int pack_cell(int i, int j, int k) { return i | (j << 10) | (k << 20); }
 
-// Blocks are dealt round-robin to the 8 XCDs; give each XCD one contiguous
-// run of tiles (a slab in z) so neighbouring tiles share that XCD's L2.  nb is
-// a multiple of 8, so this is a permutation of [0, nb).
-__device__ __forceinline__ long xcd_chunk(long b, long nb) { return (b % 8) * (nb / 8) + b / 8; }
-
-// The same dealing with the XCDs' runs cut into chunks of `chunk` items and
-// interleaved (XCD x takes chunks x, x + 8, ...): with a chunk of one z-layer
-// of tiles every XCD works on layers spread over the whole height, so the
-// particle density's variation along z (the sheaths) does not load some XCDs
-// more than others, while neighbouring tiles of a layer still share an L2.
+// Blocks are dealt round-robin to the 8 XCDs; the items go to them in chunks of
+// `chunk` consecutive ones, interleaved (XCD x takes chunks x, x + 8, ...): with
+// a chunk of one z-layer of tiles every XCD works on layers spread over the whole
+// height, so the particle density's variation along z (the sheaths) does not load
+// some XCDs more than others, while neighbouring tiles of a layer share an L2.
 // nb / 8 must be a multiple of chunk (then it is a permutation of [0, nb)).
 __device__ __forceinline__ long xcd_interleave(long b, long chunk) {
   const long x = b % 8, i = b / 8;
@@ -691,24 +685,8 @@ __device__ __forceinline__ void collide(const H& S, uint32_t id, T v[3], bool& c
 }
 
 // ---------------------------------------------------------------- deposit
-// FP64 form: rho accumulates sign * W in units of the macro charge w e.
-__device__ __forceinline__ void deposit_f64(double* __restrict__ rho, const SpeciesStep& S,
-                                            double X, double Y, double Z) {
-  const int i0 = (int)floor(X), j0 = (int)floor(Y), k0 = (int)floor(Z);
-  const double fx = X - i0, fy = Y - j0, fz = Z - k0;
-  const int i1 = i0 + 1 == S.nx ? 0 : i0 + 1;
-  const int j1 = j0 + 1 == S.ny ? 0 : j0 + 1;
-  const double s = S.sign;
-  const double wx[2] = {1.0 - fx, fx}, wy[2] = {1.0 - fy, fy}, wz[2] = {1.0 - fz, fz};
-  const int ii[2] = {i0, i1}, jj[2] = {j0, j1};
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    const int a = t & 1, b = (t >> 1) & 1, c = t >> 2;
-    const long n = ii[a] + (long)S.nx * jj[b] + (long)S.nxy * (k0 + c);
-    unsafeAtomicAdd(&rho[n], s * wx[a] * wy[b] * wz[c]);
-  }
-}
-
+// FP64 form: rho accumulates sign * W in units of the macro charge w e
+// (cic_weights_d).
 // FP32R form: the macro charge Qp (2^-32 e) split exactly into 8 non-negative
 // parts, along x by q1 = (Q f24) >> 24 with f24 = floor(offset 2^24), then each
 // half along y, each quarter along z; integer atomics, so the sum is exact and
@@ -750,22 +728,6 @@ __device__ __forceinline__ int wave_sum(int v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
-__device__ __forceinline__ int wave_min(int v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off, 64));
-  return v;
-}
-__device__ __forceinline__ int wave_max(int v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
-  return v;
-}
-
-__device__ __forceinline__ void wave_add_count(int v, unsigned long long* dst) {
-  v = wave_sum(v);
-  if ((threadIdx.x & 63) == 0 && v) atomicAdd(dst, (unsigned long long)v);
-}
-
 // ---------------------------------------------------------------- one particle
 // FP32R: gather from the 8 node fields ec, kick Eq. (2), drift Eq. (1) in cell +
 // offset form, periodic wrap; returns the electrode status
@@ -1165,23 +1127,6 @@ constexpr int kWinF32 = 1331;  // window capacity (nodes): a tile with a 3-cell 
 // and deposit windows and the lists cached instead.  (Measured: faster here;
 // slower for the FP64 records' 16-byte pairs and the re-binning's 4-byte
 // scatter, which keep the default.)
-typedef int vi4 __attribute__((ext_vector_type(4)));
-typedef float vf4 __attribute__((ext_vector_type(4)));
-typedef unsigned vu4 __attribute__((ext_vector_type(4)));
-template <typename Out, typename V, typename T>
-__device__ __forceinline__ Out nt_load4(const T* p, long g4) {
-  const V v = __builtin_nontemporal_load(reinterpret_cast<const V*>(p) + g4);
-  Out o;
-  o.x = v.x;
-  o.y = v.y;
-  o.z = v.z;
-  o.w = v.w;
-  return o;
-}
-template <typename V, typename T>
-__device__ __forceinline__ void nt_store4(T* p, long g4, V v) {
-  __builtin_nontemporal_store(v, reinterpret_cast<V*>(p) + g4);
-}
 // the kPPT consecutive values of one field at group g (FP32R push records)
 typedef int viP __attribute__((ext_vector_type(kPPT)));
 typedef float vfP __attribute__((ext_vector_type(kPPT)));
@@ -1189,6 +1134,10 @@ typedef unsigned vuP __attribute__((ext_vector_type(kPPT)));
 template <typename V, typename T>
 __device__ __forceinline__ V nt_loadP(const T* p, long g) {
   return __builtin_nontemporal_load(reinterpret_cast<const V*>(p) + g);
+}
+template <typename V, typename T>
+__device__ __forceinline__ void nt_store4(T* p, long g4, V v) {
+  __builtin_nontemporal_store(v, reinterpret_cast<V*>(p) + g4);
 }
 
 // The collision candidates of a push block, kept in LDS with what the collision
@@ -3145,8 +3094,6 @@ __global__ void fill_int_kernel(int* a, long n, int v) {
   if (i < n) a[i] = v;
 }
 
-// k -> k + 1 at the end of a step
-
 // ---------------------------------------------------------------- ionisation
 // The ionisations of the step, after every particle has moved and collided
 // and before any re-binning: in the order of the parent electrons' ids (an
@@ -3367,7 +3314,7 @@ static void md_move_impl(const PT P[2], const PT D[2], const void* E, void* rho,
                          hipStream_t st) {
   if (md.n_grains == 0 || L[0].ngrid <= 0) return;
   const int nb = md_waves(md, S[0], L[0]);
-  SpeciesPair<PT> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, nb, push_span(L[0])};
+  SpeciesPair<PT> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, nb};
   hipLaunchKernelGGL((md_kernel<PT, ET, RT>), dim3(2 * nb), dim3(kMdThreads), 0, st, pr,
                      D[0], D[1], (const ET*)E, (RT*)rho, md, gc);
 }
@@ -3394,7 +3341,7 @@ static void push_md_impl(const Desc* descs, const PT P[2], const PT D[2], const 
                          const WorkLists L[2], hipStream_t st) {
   const int span = push_span(L[0]), nb = L[0].ngrid / span;
   const int nm = (md_waves(md, S[0], L[0]) + 3) / 4;
-  SpeciesPair<PT> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, nm, span};
+  SpeciesPair<PT> pr{{P[0], P[1]}, {S[0], S[1]}, {L[0], L[1]}, nm};
   hipLaunchKernelGGL((push_md_kernel<PT, Desc, ET, RT>), dim3(2 * (nm + nb)), dim3(kBlock), 0, st,
                      descs, nb, span, push_chunk(L[0], span), pr, D[0], D[1], (const ET*)E, (RT*)rho,
                      md, gc);

@@ -155,16 +155,14 @@ struct SpeciesStep {
   long long isign;
 };
 
-// both species of one replica for the kernels that follow the push: blocks
-// [0, nb) of a launch work on species 0, [nb, 2 nb) on species 1; a tile
-// kernel's block b takes the lists of tile b * span (the push blocks' spans)
+// both species of one replica for the MD motion: blocks [0, nb) work on species
+// 0, [nb, 2 nb) on species 1
 template <typename PT>
 struct SpeciesPair {
   PT P[2];
   SpeciesStep S[2];
   WorkLists L[2];
   int nb;
-  int span;
 };
 
 // rf-phase binning of the time averages: sums of step k go to bin
