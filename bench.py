@@ -99,13 +99,13 @@ def fine_box(wl, h=0.08, cells=200):
 
 
 def run_form(wls, steps, warmup, sort_interval=8, autotune=True, label=None, average=0,
-             fine=False, keep_state=False, persistent=False):
+             fine=False, keep_state=False, one_launch=False):
     """Times one arithmetic form on one context (a list of replica workloads:
     one for the single-run forms, several for the batched ensemble).
     keep_state: also return the state after the timed windows, its fields and
     the state one more step later (for the CPU baseline's comparison).
-    persistent: for an ensemble whose tuner did not choose the persistent
-    push, also time the steps with it (batch_push = 1)."""
+    one_launch: for an ensemble whose tuner did not choose the push of every
+    replica in one launch, also time the steps with it (batch_push = 1)."""
     import torch
 
     from paper_1801_00972_amd.pic import (PIC_PROF_COULOMB, PIC_PROF_FIELD, PIC_PROF_LISTS,
@@ -208,8 +208,8 @@ def run_form(wls, steps, warmup, sort_interval=8, autotune=True, label=None, ave
                         if tuning.get("batch_push") else
                         "one launch per replica, both species" if len(wls) > 1 else
                         "one launch of both species")
-    if persistent and len(wls) > 1 and not tuning.get("batch_push"):
-        # the persistent one-launch push, timed on the same live run
+    if one_launch and len(wls) > 1 and not tuning.get("batch_push"):
+        # the push of every replica in one launch, timed on the same live run
         sim.set_tuning(batch_push=1)
         pic_profile_enable(sim.ctx, True)
         n0p = _alive(sim)
@@ -224,14 +224,14 @@ def run_form(wls, steps, warmup, sort_interval=8, autotune=True, label=None, ave
         pps = 0.5 * (n0p + n1p) * steps
         pbytes = pps * 2 * RECORD_BYTES[prec] + steps * nn * NODE_BYTES[prec]
         pach = pbytes / (pms * 1e-3) / 1e9 if pms > 0 else 0.0
-        res["persistent_launch"] = dict(
+        res["one_launch"] = dict(
             value=pps / (t5 - t4), ms_per_step=1e3 * (t5 - t4) / steps,
             note="direct launches with kernel events, batch_push = 1",
             push_ms_per_launch=pms / max(pn, 1),
             roofline=dict(bound="hbm", achieved=round(pach, 1), peak=HBM_PEAK_GBS, unit="GB/s",
                           frac=round(pach / HBM_PEAK_GBS, 4), kernel="push_batch_f32r"))
-        log(f"[bench] {label}: persistent push {res['persistent_launch']['value']:.3e} "
-            f"particle-steps/s, {res['persistent_launch']['ms_per_step']:.3f} ms/step")
+        log(f"[bench] {label}: push in one launch {res['one_launch']['value']:.3e} "
+            f"particle-steps/s, {res['one_launch']['ms_per_step']:.3f} ms/step")
     if keep_state:
         from paper_1801_00972_amd.pic import PIC_E, PIC_PHI, PIC_RHO_FIXED
         before = sim.get_state()
@@ -525,7 +525,7 @@ def main():
                                  autotune=not args.no_autotune, average=args.average,
                                  fine=args.fine and args.average > 0,
                                  keep_state=want_cpu and form == "fp32r" and form == head,
-                                 persistent=form == "batched",
+                                 one_launch=form == "batched",
                                  label=f"{form} {wls[0]['name']}" if len(wls) == 1 else
                                  f"batched ensemble of {len(wls)}")
         if form == "batched":

@@ -60,9 +60,13 @@ void launch_push_md(const PushDescF32* descs, const PartF32R P[2], const PartF32
                     unsigned long long* gc, const WorkLists L[2], hipStream_t st);
 // Push and MD motion as two launches side by side: the first enqueued gets the
 // chip's waves first.  A long push goes first and hides the MD motion (64x64x256
-// cells, FP32R: 9.67 ms for 8 steps against 10.21); one of about 8 million slots or
-// less ends with it, and the MD kernel's chains go first (36x30x77 cells, 7 per
-// cell: 2.24 ms for 16 steps against 2.27).  (Two species of up to 2^31 - 1 slots each.)
+// cells, 8 grains, FP32R: 1.046 ms a step against 1.119); where the push ends with
+// it, the MD kernel's chains go first (36x30x77 cells, 7 per cell, 3 grains, single
+// tiles a block: 2.24 ms for 16 steps against 2.27).  The line at 8 million slots
+// lies between those two and is no sharp one: boxes of tile pairs with 8 grains take
+// less push first on both sides of it (FP32R 2.0, 4.5, 7.6, 15, 32 and 64 million
+// slots: 1.6, 1.6, 1.7, 4.4, 10.9 and 6.9 %; FP64 6.9, 2.8, 2.8, 2.4, 2.4, 1.8 %).
+// (Two species of up to 2^31 - 1 slots each.)
 inline bool push_goes_first(const WorkLists L[2]) {
   return (long)L[0].slots + (long)L[1].slots > 8L << 20;
 }

@@ -145,12 +145,11 @@ __device__ __forceinline__ double wrap_coord(double X, int n) {
   return X;
 }
 
-// grain data the sub-stepping reads every sub-step (staged in LDS): positions
-// in the frame of the MD box (x and y shifted by its origin, in [0, n)), and
-// Q / (4 pi eps0 dx^2)
-// in LDS (raw: more grains than the stage holds; read from the tables, shifted
-// and scaled where they are used).  LDS pointers, not generic ones: a generic
-// load waits for global memory too
+// The grain data that every sub-step reads, staged in LDS: positions in the frame
+// of the MD box (x and y shifted by its origin, in [0, n)), and Q / (4 pi eps0
+// dx^2).  raw: there are more grains than the stage holds; they are read from the
+// tables, shifted and scaled where they are used.  The pointers are LDS pointers,
+// not generic ones: a generic load waits for global memory too.
 typedef const __attribute__((address_space(3))) double* LdsDoubles;
 struct GrainView {
   LdsDoubles pos;  // [g][3]
@@ -1680,8 +1679,8 @@ __global__ __launch_bounds__(kBlock, 3) void push_f64_kernel(const PushDescF64* 
 
 // ---------------------------------------------------------------- MD particles
 // The particles that started the step inside an MD cube: the sub-cycled PPPM
-// motion in FP64, grain and electrode absorption, the collision, the deposit.
-// One thread per entry of the dense list.
+// motion in FP64, grain and electrode absorption, the deposit (md_block); the
+// lists kernel collides them.  Four lanes or one per entry of the dense list.
 __device__ __forceinline__ void load_d(const PartF64& P, long p, double x[3], double v[3]) {
   x[0] = P.x[p];
   x[1] = P.y[p];
@@ -1997,8 +1996,9 @@ __global__ __launch_bounds__(kBlock, 2) void push_md_kernel(const Desc* descs, i
 // in a window of the tile's nodes plus the margin (at most 2 cells) and reach
 // the mesh once; a particle outside the window adds to the mesh directly.
 // One thread a run of slots with 32 sums in registers was bound by its LDS
-// atomics: 32 a run, and a run ends wherever a particle has drifted.  Now the
-// vector instructions issue about half of the time and barriers take the rest.
+// atomics: 32 a run, and a run ends wherever a particle has drifted.  Now vector
+// instructions take 44 to 52 % of the issue slots, and a wave waits 55 to 58 % of
+// its time (counters: memory, LDS and barriers are not told apart).
 // 64x64x256 cells, 32 per cell, mean of the species: FP32R 733 us -> 445 (0.94 GB),
 // FP64 1326 -> 558 (1.6 GB); 128x128x512, 16 per cell, FP32R 2,850 -> 2,240 (3.8 GB).
 constexpr int kMomWin = 729;  // most nodes of a window
@@ -2170,8 +2170,10 @@ __global__ __launch_bounds__(kT, 4) void moments_kernel(PT P, SpeciesStep S, Wor
       const uint32_t c = s_list[at];
       const int s = (int)(c >> 16), e = have ? (int)(s_list[at + 1] >> 16) : s;
       // the matrix instructions take all lanes: as many rounds as the fullest cell
-      // of the four needs.  The count is a scalar (with the loop left on a ballot
-      // the compiler copied a result without the wait states it needs)
+      // of the four needs.  The count has to stay a scalar: the sums then stay in
+      // their registers from the first round to the last (with the loop left on a
+      // ballot the compiler copied a result at the loop's head without the wait
+      // states it needs, and the sums came out wrong)
       int most = e - s;
       most = max(most, __builtin_amdgcn_update_dpp(0, most, 0x124, 0xf, 0xf, false));  // row_ror:4
       most = max(most, __builtin_amdgcn_update_dpp(0, most, 0x128, 0xf, 0xf, false));  // row_ror:8
@@ -2187,7 +2189,9 @@ __global__ __launch_bounds__(kT, 4) void moments_kernel(PT P, SpeciesStep S, Wor
         lo = __builtin_amdgcn_mfma_f64_4x4x4f64(A, w * (1.0 - fz), lo, 0, 0, 0);
         hi = __builtin_amdgcn_mfma_f64_4x4x4f64(A, w * fz, hi, 0, 0, 0);
       }
-      // (the last results' wait states, whatever the compiler places next)
+      // the last results' wait states before anything that follows this statement.
+      // It does not cover a copy placed between the last matrix instruction and
+      // here; with the scalar count there is none
       asm volatile("s_nop 7\n\ts_nop 3" : "+v"(lo), "+v"(hi));
       if (have) {
         atomicAdd(&out[c & 0xffff], lo);
@@ -2397,10 +2401,10 @@ __device__ __forceinline__ int segment_entry(const Segments& s, const int32_t* l
 }
 
 // ---------------------------------------------------------------- outliers
-// Particles that started outside their tile's window (they drifted since the
-// last sort): the same push with the field gathered from global memory and the
+// Particles that started outside their push block's window (they drifted since
+// the last sort): the same push with the field gathered from global memory and the
 // charge deposited with global atomics, the collision done in place.  One wave
-// per tile segment.
+// takes the packed segments of a group of push blocks.
 template <typename WL>
 __device__ __forceinline__ void outlier_tally(const WL& L, int tidx, int w0, int w1, int bad,
                                               int coll, int cap, int fast) {

@@ -1670,7 +1670,7 @@ int init_replica(pic_ctx* ctx, Replica& R, const pic_config& cin) {
   TRY(setup_md(ctx, R));
   TRY(setup_near(ctx, R));
   TRY(unit_fields(ctx, R));
-  launch_zero_f64(R.psi, R.n_int, st);  // the first FP32R solve starts from psi = 0
+  launch_zero_f64(R.psi, R.n_int, st);  // the first FP32 sweeps start from psi = 0
 
   // load: ppc particles per cell, Maxwellian, Philox keyed by the seed
   const uint32_t k0 = (uint32_t)(c.seed & 0xffffffffu), k1 = (uint32_t)(c.seed >> 32);
@@ -1867,8 +1867,9 @@ int fields_impl(pic_ctx* ctx, Replica* R, unsigned what, void* const* out, int o
 // configuration (the scalars below, the grain positions and the cross-section
 // tables, which a loading context must match), the step, grain and electrode
 // counts, the event-counter totals, and per species the particles as
-// pic_get_state gives them; FP32R adds the potential the next solve starts
-// from (psi), so a resumed run repeats the uninterrupted one bit for bit.
+// pic_get_state gives them; FP32R adds the solve's potential (psi), which the
+// FP32 sweeps (max_refine 1, refine_tol 0) start from, so that a resumed run
+// repeats the uninterrupted one bit for bit in either form of the solve.
 struct CkptConfig {
   int32_t nx, ny, nz, ppc, n_grains, cutoff, md_sub, precision, max_refine, coulomb_interval,
       xs_n, pad;

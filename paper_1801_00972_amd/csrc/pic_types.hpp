@@ -78,7 +78,7 @@ struct WorkLists {
                       // total of the sort
   int slots;          // slots of the arrays
   int ntx, nty, ntz;  // tiles along x, y, z
-  int ngrid;          // tiles rounded up to a multiple of 8
+  int ngrid;          // tiles rounded up to a multiple of 16
 };
 
 // per-tile event counts, accumulated since loading; TL_DEAD counts removed
@@ -205,7 +205,12 @@ using PushDescF64 = PushDesc<PartF64, double2, double>;
 
 // tiles per push block: pairs along x where the rows of tiles split into
 // pairs (the tile grid, a multiple of 16, then still gives a multiple of 8
-// blocks); the kernels that read the push's lists use the same span
+// blocks); the kernels that read the push's lists use the same span.  A pair
+// shares one window, 13 x 9 x 9 nodes with two cells of margin against 2 x 729, and
+// its slots are one contiguous range.  The parity is no measured line: a row of an
+// odd number of tiles would need a last block of another span, which the
+// descriptors do not hold, and takes single tiles (36x30x77 cells, 7 per cell:
+// blocks of 450 slots, less than half of a pass)
 __host__ __device__ inline int push_span(const WorkLists& L) { return L.ntx % 2 == 0 ? 2 : 1; }
 
 // the chunk of the push blocks' XCD interleaving for a grid of ngrid / span
