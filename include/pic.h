@@ -488,12 +488,13 @@ int pic_autotune(pic_ctx* ctx, int trial_steps, pic_tuning* tried, double* ms_pe
  * every following launch of the selected kernel class with HIP events on the
  * context's stream; pic_profile_read synchronises and returns the summed
  * elapsed time (ms) and the number of launches measured since enabling.
- *   PIC_PROF_PUSH   the streaming gather / push / electrode / candidate / deposit
+ *   PIC_PROF_PUSH   the streaming gather / push / electrode / collision / deposit
  *                   kernel (one launch of both species per step)
  *   PIC_PROF_FIELD  the whole field stage of a step (RHS, Poisson, E)
  *   PIC_PROF_SORT   the periodic cell sort of both species
- *   PIC_PROF_LISTS  the listed particles of one species: sub-cycled near-grain
- *                   motion and the collisions of the candidates
+ *   PIC_PROF_LISTS  the listed particles of both species: sub-cycled near-grain
+ *                   motion, particles outside their window, and the collisions
+ *                   that the push had no room for (two launches per step)
  *   PIC_PROF_COULOMB  one Coulomb-collision pass of a replica (steps launched
  *                   one replica at a time; in the batched step it is part of
  *                   PIC_PROF_FIELD)
