@@ -862,9 +862,9 @@ int solve_fields(pic_ctx* ctx, Replica& R, bool zero_next = false, bool* final_p
     // keeps them).  Solved from the right-hand side, not from a residual against
     // the last potential: the result then depends on the charge alone, and a
     // correction's error is that of the residual's rounding times the condition of
-    // the lowest mode
-    // (4x6x1025 cells: 3e-12 of phi, against 2e-15).  The sums of the residual
-    // it ends with are added up by the next solve, or on request (flush_final).
+    // the lowest mode (4x6x1025 cells: 3e-12 of phi, against 2e-15).  The sums of the
+    // residual it ends with are added up by the next solve, or on request
+    // (flush_final).
     const bool f64 = R.prec == PIC_FP64;
     SpectralArgs a{};
     a.tw_x = R.tw_x;
@@ -1712,10 +1712,12 @@ struct FieldStage {
 };
 
 // What the caller says is a device buffer for `count` 8-byte values: one that a kernel
-// may write (aligned, this device's own memory), one that takes a copy (any address a
-// copy reaches), or one that ends too early, which no kernel may be handed.  Asked
-// before a call's first launch, so that clearing the error of an unknown address hides
-// none of a launch.
+// may write (aligned, inside one allocation of this device), one that takes a copy (any
+// address a copy reaches), or one that ends too early, which no kernel may be handed.
+// Where other memory begins right at the end of the allocation, the buffer may be one of
+// several chunks mapped side by side: the copy, which knows them, decides.  Asked before
+// a call's first launch, so that clearing the error of an unknown address hides none of
+// a launch.
 enum { kOutCopy, kOutKernel, kOutShort };
 int out_kind(const void* p, long count) {
   hipPointerAttribute_t at{};
@@ -1729,7 +1731,13 @@ int out_kind(const void* p, long count) {
     return kOutCopy;
   }
   const size_t off = (size_t)((const char*)p - (const char*)base);
-  if (off > size || (size - off) / 8 < (size_t)count) return kOutShort;
+  if (off > size || (size - off) / 8 < (size_t)count) {
+    hipDeviceptr_t next = (char*)base + size, next_base = nullptr;
+    size_t next_size = 0;
+    if (hipMemGetAddressRange(&next_base, &next_size, next) == hipSuccess && next_base == next) return kOutCopy;
+    (void)hipGetLastError();  // (nothing there)
+    return kOutShort;
+  }
   return (uintptr_t)p % 8 == 0 && at.device == dev ? kOutKernel : kOutCopy;
 }
 
